@@ -56,46 +56,57 @@ __global__ void unpack_kernel(ActView in, uint8_t *codes, int64_t rows, int chun
 }
 
 // ------------------------------------------------------------ quantiser
-// Order-preserving map of fp32 to uint32 for atomic min/max.
-__device__ inline uint32_t f2ord(float f) {
-  const uint32_t b = __float_as_uint(f);
-  return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
-}
-__device__ inline float ord2f(uint32_t o) {
-  return __uint_as_float((o & 0x80000000u) ? (o & 0x7fffffffu) : ~o);
-}
+// Calibration: kRangeParts workgroups reduce the tensor to one (min, max)
+// pair each, NaN skipped; the quantising kernel's workgroups reduce the pairs
+// again, so nothing is initialised and no two workgroups meet on an address.
+// (One atomic pair per wave of 4096 workgroups serialised on two words: 379
+// us for 103 MB.)  An empty tensor, or one of NaN only, leaves (+inf, -inf),
+// which no tensor with a number in it does.
+constexpr int kRangeParts = 1024;
 
-__global__ void range_init_kernel(uint32_t *enc) {
-  enc[0] = 0xffffffffu;  // running min
-  enc[1] = 0u;           // running max
-}
-
-__global__ void minmax_kernel(const float *x, int64_t count, uint32_t *enc) {
-  uint32_t lo = 0xffffffffu, hi = 0u;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const float v = x[i];
-    if (v == v) {  // skip NaN
-      const uint32_t o = f2ord(v);
-      lo = min(lo, o);
-      hi = max(hi, o);
-    }
-  }
-  // wave64 reduction, then one atomic per wave (min/max are order-free)
+// Min and max over the workgroup of 256 threads, in every thread.
+__device__ inline float2 block_minmax(float lo, float hi) {
+  __shared__ float2 part[kBlock / 64];
   for (int off = 32; off > 0; off >>= 1) {
-    lo = min(lo, (uint32_t)__shfl_xor((int)lo, off));
-    hi = max(hi, (uint32_t)__shfl_xor((int)hi, off));
+    lo = fminf(lo, __shfl_xor(lo, off));
+    hi = fmaxf(hi, __shfl_xor(hi, off));
   }
-  if ((threadIdx.x & 63) == 0) {
-    atomicMin(&enc[0], lo);
-    atomicMax(&enc[1], hi);
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = make_float2(lo, hi);
+  __syncthreads();
+  for (int w = 0; w < kBlock / 64; ++w) {
+    lo = fminf(lo, part[w].x);
+    hi = fmaxf(hi, part[w].y);
   }
+  return make_float2(lo, hi);
 }
 
-__global__ void range_out_kernel(const uint32_t *enc, float *range_out) {
-  const bool empty = enc[0] == 0xffffffffu && enc[1] == 0u;
-  range_out[0] = empty ? __uint_as_float(0x7fc00000u) : ord2f(enc[0]);
-  range_out[1] = empty ? __uint_as_float(0x7fc00000u) : ord2f(enc[1]);
+// Bound by the read: four 16-byte loads in flight per thread where x allows
+// them (vec), a contiguous run of the tensor per round of the grid.
+__global__ __launch_bounds__(kBlock) void minmax_kernel(const float *x, int64_t count, int vec, float2 *parts) {
+  float lo = INFINITY, hi = -INFINITY;
+  const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x, step = (int64_t)gridDim.x * kBlock;
+  int64_t done = 0;
+  if (vec) {
+    const int64_t quads = count / 4;
+    const float4 *x4 = (const float4 *)x;
+    for (int64_t i = t; i < quads; i += 4 * step) {
+      float4 v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = x4[i + u * step < quads ? i + u * step : i];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        lo = fminf(fminf(fminf(lo, v[u].x), v[u].y), fminf(v[u].z, v[u].w));
+        hi = fmaxf(fmaxf(fmaxf(hi, v[u].x), v[u].y), fmaxf(v[u].z, v[u].w));
+      }
+    }
+    done = 4 * quads;
+  }
+  for (int64_t i = done + t; i < count; i += step) {
+    lo = fminf(lo, x[i]);
+    hi = fmaxf(hi, x[i]);
+  }
+  const float2 r = block_minmax(lo, hi);
+  if (threadIdx.x == 0) parts[blockIdx.x] = r;
 }
 
 // Eq. 2 in the documented fp32 op order, for one code.
@@ -107,36 +118,84 @@ __device__ inline int quant_one(float x, float l, float rng, float qmax) {
   return (int)rintf(t * qmax);
 }
 
-// 8-bit codes of 3-channel pixels (one 4-byte row each, the image input):
-// one thread per 4 pixels, three 16-byte loads and one 16-byte store.
-__global__ void quantize_px3_kernel(const float *x, float l, float u, const uint32_t *enc, ActView out,
-                                    int64_t quads) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= quads) return;
-  bool degenerate = false;
-  if (enc) {
-    const bool empty = enc[0] == 0xffffffffu && enc[1] == 0u;
-    l = ord2f(enc[0]);
-    u = ord2f(enc[1]);
+// Where a launch's range comes from (RangeArg), and the range itself with
+// what quant_code needs.
+struct Range {
+  float l, rng, inv, qmax, eps;
+  bool fast, degenerate;
+};
+__device__ inline Range make_range(float l, float u, float qmax) {
+  Range r;
+  r.l = l;
+  r.rng = u - l;
+  r.qmax = qmax;
+  r.inv = 1.0f / r.rng;
+  r.eps = 0.5f - qmax * 0x1p-21f;
+  r.fast = r.rng >= 0x1p-100f && r.rng <= 0x1p100f;  // the reciprocal is normal
+  r.degenerate = false;
+  return r;
+}
+// Called by every thread of a workgroup of kBlock; workgroup 0 writes range_out.
+__device__ inline Range load_range(const RangeArg &a, float qmax) {
+  float l = a.l, u = a.u;
+  bool empty = false, degenerate = false;
+  if (a.parts) {
+    float2 v = make_float2(INFINITY, -INFINITY);
+    for (int i = threadIdx.x; i < a.nparts; i += kBlock) {
+      const float2 p = a.parts[i];
+      v = make_float2(fminf(v.x, p.x), fmaxf(v.y, p.y));
+    }
+    v = block_minmax(v.x, v.y);
+    l = v.x;
+    u = v.y;
+    empty = l == INFINITY && u == -INFINITY;
     degenerate = empty || !(u > l);
   }
-  const float rng = u - l;
-  const int off = out.is_signed ? 128 : 0;
-  const float4 *src = (const float4 *)(x + 12 * t);
-  const float4 f0 = src[0], f1 = src[1], f2 = src[2];
-  const float v[12] = {f0.x, f0.y, f0.z, f0.w, f1.x, f1.y, f1.z, f1.w, f2.x, f2.y, f2.z, f2.w};
-  uint32_t w[4];
-#pragma unroll
-  for (int p = 0; p < 4; ++p) {
-    uint32_t word = 0;
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      const int q = (degenerate ? 0 : quant_one(v[3 * p + c], l, rng, 255.0f)) - off;
-      word |= ((uint32_t)q & 0xffu) << (8 * c);
-    }
-    w[p] = word;
+  if (a.range_out && blockIdx.x == 0 && threadIdx.x == 0) {
+    a.range_out[0] = empty ? __uint_as_float(0x7fc00000u) : l;
+    a.range_out[1] = empty ? __uint_as_float(0x7fc00000u) : u;
   }
-  *(uint4 *)(out.data + 16 * t) = make_uint4(w[0], w[1], w[2], w[3]);
+  Range r = make_range(l, u, qmax);
+  r.degenerate = degenerate;
+  return r;
+}
+
+// quant_one without its division where that cannot change the code: with inv
+// = RN(1 / rng), RN(d inv) is within 1.5 2^-23 of RN(d / rng) relatively, so
+// p is within 2.5 2^-23 qmax of quant_one's product and rounds to the same
+// code unless it lies within 4 2^-23 qmax of a half-integer; only those
+// values (about one in 2^21 / qmax) divide.  NaN gives 0 as in quant_one
+// (fmaxf takes the number).  Cuts the VALU work per value from about 25
+// instructions to 9.
+__device__ inline int quant_code(float x, const Range &r) {
+  const float t = fminf(fmaxf((x - r.l) * r.inv, 0.0f), 1.0f);
+  const float p = t * r.qmax, q = rintf(p);
+  if (!r.fast || fabsf(p - q) >= r.eps) return quant_one(x, r.l, r.rng, r.qmax);
+  return (int)q;
+}
+
+// 8-bit codes of 3-channel pixels (one 4-byte row each, the image input):
+// one thread per 4 pixels, three 16-byte loads and one 16-byte store.
+__global__ __launch_bounds__(kBlock) void quantize_px3_kernel(const float *x, RangeArg ra, ActView out, int64_t quads) {
+  const Range rg = load_range(ra, 255.0f);
+  const int off = out.is_signed ? 128 : 0;
+  for (int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x; t < quads; t += (int64_t)gridDim.x * kBlock) {
+    const float4 *src = (const float4 *)(x + 12 * t);
+    const float4 f0 = src[0], f1 = src[1], f2 = src[2];
+    const float v[12] = {f0.x, f0.y, f0.z, f0.w, f1.x, f1.y, f1.z, f1.w, f2.x, f2.y, f2.z, f2.w};
+    uint32_t w[4];
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+      uint32_t word = 0;
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        const int q = (rg.degenerate ? 0 : quant_code(v[3 * p + c], rg)) - off;
+        word |= ((uint32_t)q & 0xffu) << (8 * c);
+      }
+      w[p] = word;
+    }
+    *(uint4 *)(out.data + 16 * t) = make_uint4(w[0], w[1], w[2], w[3]);
+  }
 }
 
 // Signed 8-bit codes of 3-channel fp32 pixels written straight into a
@@ -147,7 +206,7 @@ constexpr int kQPadRows = 8;
 __global__ void quantize_pad_kernel(const float *x, float l, float u, int in_h, int in_w, int pad, ActView out,
                                     int rows) {
   const int r0 = (int)blockIdx.x * kQPadRows;
-  const float rng = u - l;
+  const Range rg = make_range(l, u, 255.0f);
   for (int c = threadIdx.x; c < out.w; c += blockDim.x) {
     const int ix = c - pad;
     float v[kQPadRows][3];
@@ -166,7 +225,7 @@ __global__ void quantize_pad_kernel(const float *x, float l, float u, int in_h, 
       uint32_t word = 0;
       if (in[j]) {
 #pragma unroll
-        for (int ch = 0; ch < 3; ++ch) word |= ((uint32_t)(quant_one(v[j][ch], l, rng, 255.0f) - 128) & 0xffu) << (8 * ch);
+        for (int ch = 0; ch < 3; ++ch) word |= ((uint32_t)(quant_code(v[j][ch], rg) - 128) & 0xffu) << (8 * ch);
       }
       ((uint32_t *)(out.data + ((int64_t)(r0 + j) * out.w + c) * out.pixel))[0] = word;
     }
@@ -192,12 +251,12 @@ __global__ void quantize_pad4_kernel(const float *x, float l, float u, int in_h,
     const float4 *src = (const float4 *)(x + (((int64_t)n * in_h + iy) * in_w + 4 * j) * 3);
     const float4 f0 = src[0], f1 = src[1], f2 = src[2];
     const float v[12] = {f0.x, f0.y, f0.z, f0.w, f1.x, f1.y, f1.z, f1.w, f2.x, f2.y, f2.z, f2.w};
-    const float rng = u - l;
+    const Range rg = make_range(l, u, 255.0f);
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
       uint32_t word = 0;
 #pragma unroll
-      for (int ch = 0; ch < 3; ++ch) word |= ((uint32_t)(quant_one(v[3 * p + ch], l, rng, 255.0f) - 128) & 0xffu) << (8 * ch);
+      for (int ch = 0; ch < 3; ++ch) word |= ((uint32_t)(quant_code(v[3 * p + ch], rg) - 128) & 0xffu) << (8 * ch);
       row[pad + 4 * j + p] = word;
     }
   } else if (j - quads < 2 * pad) {
@@ -206,48 +265,112 @@ __global__ void quantize_pad4_kernel(const float *x, float l, float u, int in_h,
   }
 }
 
-// One thread per packed word (b in {2, 4, 8}) or 32-code chunk (b = 3).
-__global__ void quantize_kernel(const float *x, float l, float u, const uint32_t *enc, ActView out,
-                                int64_t rows, int units) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= rows * units) return;
-  bool degenerate = false;
-  if (enc) {
-    const bool empty = enc[0] == 0xffffffffu && enc[1] == 0u;
-    l = ord2f(enc[0]);
-    u = ord2f(enc[1]);
-    degenerate = empty || !(u > l);
-  }
-  const int64_t r = t / units;
-  const int wi = (int)(t % units);
-  const float qmax = (float)((1 << out.bits) - 1);
-  const float rng = u - l;
-  const int off = out.is_signed ? (1 << (out.bits - 1)) : 0;
-  const float *src = x + r * out.cpg;
-  uint32_t *dst = (uint32_t *)row_at(out, r);
-  if (out.bits == 3) {
-    int c[32];
-    const int j0 = wi * 32;
-    const int nc = min(32, out.cpg - j0);
-    for (int j = 0; j < 32; ++j)
-      c[j] = (j < nc && !degenerate ? quant_one(src[j0 + j], l, rng, qmax) : 0) - off;
-    uint32_t words[3];
-    pack_chunk(c, nc, 3, words);
-    dst[3 * wi] = words[0];
-    dst[3 * wi + 1] = words[1];
-    dst[3 * wi + 2] = words[2];
-    return;
-  }
-  const int per = 32 / store_bits(out.bits);
-  const int j0 = wi * per;
-  const int nc = min(per, out.cpg - j0);
+// Rows of whole quads (cpg % 4 == 0, x 16-byte aligned), one quad of codes
+// per lane: a wave's loads are 1 KB runs and its stores runs of the quads'
+// bytes (SB = store_bits(bits): SB / 2 bytes a quad), with no exchange
+// between lanes.  SB = 3: a lane takes quads q and q + 4 of a 32-code chunk,
+// which fill byte q of the chunk's three words.  Bound by the memory path:
+// 25.7 M values to 2-bit codes, 64 -> 22 us in the kernel trace (a word of
+// codes per thread reads 64 bytes at a stride of 64 across the wave).
+// qpr: units per row, the quads of the row's padding (zero codes) included.
+template <int SB>
+__global__ __launch_bounds__(kBlock) void quantize_quads_kernel(const float *x, RangeArg ra, ActView out, FastDiv qpr,
+                                                                FastDiv groups, uint32_t units) {
+  const Range rg = load_range(ra, (float)((1 << out.bits) - 1));
   const uint32_t mask = (1u << out.bits) - 1u;
-  uint32_t w = 0;
-  for (int k = 0; k < nc; ++k) {
-    const int q = (degenerate ? 0 : quant_one(src[j0 + k], l, rng, qmax)) - off;
-    w |= ((uint32_t)q & mask) << (k * store_bits(out.bits));
+  const int off = out.is_signed ? (1 << (out.bits - 1)) : 0;
+  constexpr int Q = SB == 3 ? 2 : 1;  // quads per unit
+  constexpr int U = 4 / Q;            // units in flight per thread
+  const uint32_t step = gridDim.x * (uint32_t)kBlock;
+  for (uint32_t t0 = blockIdx.x * (uint32_t)kBlock + threadIdx.x; t0 < units; t0 += U * step) {
+    float4 v[U][Q];
+    uint8_t *dst[U];
+    bool in[U][Q];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint32_t t = t0 + u * step < units ? t0 + u * step : t0;  // past the end: unit t0 again
+      const uint32_t r = qpr.div(t), q = t - r * qpr.d;
+      const uint32_t p = groups.div(r), g = r - p * groups.d;
+      dst[u] = out.data + (int64_t)p * out.pixel + (int64_t)g * out.gstride +
+               (SB == 3 ? 12 * (q >> 2) + (q & 3) : q * (SB / 2));
+      const uint32_t c0 = SB == 3 ? 32 * (q >> 2) + 4 * (q & 3) : 4 * q;
+#pragma unroll
+      for (int k = 0; k < Q; ++k) {
+        in[u][k] = c0 + 16 * k < (uint32_t)out.cpg;
+        const float *src = x + (int64_t)r * out.cpg + (in[u][k] ? c0 + 16 * k : 0u);
+        v[u][k] = *(const float4 *)src;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      uint32_t c[Q][4];
+#pragma unroll
+      for (int k = 0; k < Q; ++k) {
+        const float f[4] = {v[u][k].x, v[u][k].y, v[u][k].z, v[u][k].w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          c[k][e] = in[u][k] ? ((uint32_t)((rg.degenerate ? 0 : quant_code(f[e], rg)) - off) & mask) : 0u;
+      }
+      if constexpr (SB == 3) {
+        uint32_t hi = 0;
+#pragma unroll
+        for (int k = 0; k < Q; ++k) {
+          uint32_t lo = 0;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            lo |= (c[k][e] & 3u) << (2 * e);
+            hi |= (c[k][e] >> 2) << (2 * e + k);
+          }
+          dst[u][4 * k] = (uint8_t)lo;
+        }
+        dst[u][8] = (uint8_t)hi;
+      } else {
+        uint32_t w = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) w |= c[0][e] << (SB * e);
+        if constexpr (SB == 2) *dst[u] = (uint8_t)w;
+        else if constexpr (SB == 4) *(uint16_t *)dst[u] = (uint16_t)w;
+        else *(uint32_t *)dst[u] = w;
+      }
+    }
   }
-  dst[wi] = w;
+}
+
+// Any other shape: one packed word (b in {2, 4, 6, 8}) or 32-code chunk
+// (b = 3) per thread and round of the grid.
+__global__ __launch_bounds__(kBlock) void quantize_kernel(const float *x, RangeArg ra, ActView out, int64_t rows,
+                                                          int units) {
+  const float qmax = (float)((1 << out.bits) - 1);
+  const Range rg = load_range(ra, qmax);
+  const int off = out.is_signed ? (1 << (out.bits - 1)) : 0;
+  for (int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x; t < rows * units; t += (int64_t)gridDim.x * kBlock) {
+    const int64_t r = t / units;
+    const int wi = (int)(t % units);
+    const float *src = x + r * out.cpg;
+    uint32_t *dst = (uint32_t *)row_at(out, r);
+    if (out.bits == 3) {
+      int c[32];
+      const int j0 = wi * 32;
+      const int nc = min(32, out.cpg - j0);
+      for (int j = 0; j < 32; ++j) c[j] = (j < nc && !rg.degenerate ? quant_code(src[j0 + j], rg) : 0) - off;
+      uint32_t words[3];
+      pack_chunk(c, nc, 3, words);
+      dst[3 * wi] = words[0];
+      dst[3 * wi + 1] = words[1];
+      dst[3 * wi + 2] = words[2];
+      continue;
+    }
+    const int per = 32 / store_bits(out.bits);
+    const int j0 = wi * per;
+    const int nc = min(per, out.cpg - j0);
+    const uint32_t mask = (1u << out.bits) - 1u;
+    uint32_t w = 0;
+    for (int k = 0; k < nc; ++k) {
+      const int q = (rg.degenerate ? 0 : quant_code(src[j0 + k], rg)) - off;
+      w |= ((uint32_t)q & mask) << (k * store_bits(out.bits));
+    }
+    dst[wi] = w;
+  }
 }
 
 // ------------------------------------------------------------ shuffle (Eq. 8)
@@ -758,14 +881,15 @@ hipError_t launch_unpack(const ActView &in, void *codes, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_minmax(const float *x, int64_t count, float *range, hipStream_t s) {
-  uint32_t *enc = (uint32_t *)range;
-  hipLaunchKernelGGL(range_init_kernel, dim3(1), dim3(1), 0, s, enc);
-  if (count > 0) {
-    int64_t g = (count + kBlock - 1) / kBlock;
-    if (g > 4096) g = 4096;
-    hipLaunchKernelGGL(minmax_kernel, dim3((unsigned)g), dim3(kBlock), 0, s, x, count, enc);
-  }
+size_t range_parts_bytes() { return kRangeParts * sizeof(float2); }
+
+hipError_t launch_minmax(const float *x, int64_t count, RangeArg *range, hipStream_t s) {
+  // a workgroup per 16 values a thread, no more than the scratch holds
+  const int64_t per = (int64_t)kBlock * 16;
+  range->nparts = (int)std::min<int64_t>(kRangeParts, (count + per - 1) / per);
+  if (range->nparts == 0) return hipSuccess;
+  hipLaunchKernelGGL(minmax_kernel, dim3((unsigned)range->nparts), dim3(kBlock), 0, s, x, count,
+                     ((uintptr_t)x & 15u) == 0 ? 1 : 0, (float2 *)range->parts);
   return hipGetLastError();
 }
 
@@ -776,22 +900,45 @@ bool quantize_by_pixels(const float *x, const ActView &out) {
          (((uintptr_t)x | (uintptr_t)out.data) & 15u) == 0;
 }
 
-const char *quantize_label(const float *x, const ActView &out) {
-  return quantize_by_pixels(x, out) ? "quantize_px3_kernel" : "quantize_kernel";
+// One quad of codes per lane (quantize_quads_kernel): rows of whole quads and
+// 32-bit unit indices.
+bool quantize_by_quads(const float *x, const ActView &out) {
+  const int64_t rows = (int64_t)out.n * out.h * out.w * out.groups;
+  return out.cpg % 4 == 0 && ((uintptr_t)x & 15u) == 0 && rows * out.row < ((int64_t)1 << 31);
 }
 
-hipError_t launch_quantize(const float *x, float l, float u, const float *range, const ActView &out,
-                           hipStream_t s) {
+const char *quantize_label(const float *x, const ActView &out) {
+  return quantize_by_pixels(x, out) ? "quantize_px3_kernel"
+                                    : quantize_by_quads(x, out) ? "quantize_quads_kernel" : "quantize_kernel";
+}
+
+hipError_t launch_quantize(const float *x, const RangeArg &range, const ActView &out, hipStream_t s) {
   const int64_t rows = (int64_t)out.n * out.h * out.w * out.groups;
-  const int units = out.bits == 3 ? (out.cpg + 31) / 32 : (int)(out.row / 4);
-  if (rows == 0) return hipSuccess;
+  if (rows == 0 && !range.range_out) return hipSuccess;
+  // workgroups walk the tensor: enough of them for every CU to hold its fill
+  // of waves, few enough that reducing the calibration's pairs stays cheap
+  auto grid = [](int64_t threads) {
+    return dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>(2048, (threads + kBlock - 1) / kBlock)));
+  };
   if (quantize_by_pixels(x, out)) {
-    hipLaunchKernelGGL(quantize_px3_kernel, dim3(grid_for(rows / 4)), dim3(kBlock), 0, s, x, l, u,
-                       (const uint32_t *)range, out, rows / 4);
+    hipLaunchKernelGGL(quantize_px3_kernel, grid(rows / 4), dim3(kBlock), 0, s, x, range, out, rows / 4);
     return hipGetLastError();
   }
-  hipLaunchKernelGGL(quantize_kernel, dim3(grid_for(rows * units)), dim3(kBlock), 0, s, x, l, u,
-                     (const uint32_t *)range, out, rows, units);
+  if (quantize_by_quads(x, out)) {
+    const int sb = store_bits(out.bits);
+    const int qpr = sb == 3 ? (int)(out.row / 3) : (int)(out.row / (sb / 2));
+    const int64_t units = rows * qpr;
+    const dim3 g = grid((units + 3) / 4);
+    const FastDiv fq = FastDiv::of((uint32_t)qpr), fg = FastDiv::of((uint32_t)out.groups);
+    auto k = sb == 2   ? quantize_quads_kernel<2>
+             : sb == 3 ? quantize_quads_kernel<3>
+             : sb == 4 ? quantize_quads_kernel<4>
+                       : quantize_quads_kernel<8>;
+    hipLaunchKernelGGL(k, g, dim3(kBlock), 0, s, x, range, out, fq, fg, (uint32_t)units);
+    return hipGetLastError();
+  }
+  const int units = out.bits == 3 ? (out.cpg + 31) / 32 : (int)(out.row / 4);
+  hipLaunchKernelGGL(quantize_kernel, grid(rows * units), dim3(kBlock), 0, s, x, range, out, rows, units);
   return hipGetLastError();
 }
 
@@ -817,11 +964,6 @@ hipError_t launch_quantize_pad(const float *x, float l, float u, int in_h, int i
   }
   hipLaunchKernelGGL(quantize_pad_kernel, dim3((unsigned)((rows + kQPadRows - 1) / kQPadRows)), dim3(256), 0, s, x,
                      l, u, in_h, in_w, pad, out, (int)rows);
-  return hipGetLastError();
-}
-
-hipError_t launch_range_out(const float *enc, float *range_out, hipStream_t s) {
-  hipLaunchKernelGGL(range_out_kernel, dim3(1), dim3(1), 0, s, (const uint32_t *)enc, range_out);
   return hipGetLastError();
 }
 

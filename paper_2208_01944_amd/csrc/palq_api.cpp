@@ -118,7 +118,7 @@ palq_status palq_create(int32_t device, void *hip_stream, palq_ctx **out) {
     // the no-alloc call's static buffer: its address on this device, looked
     // up once per device (a failure only disables palq_group_conv_noalloc)
     if (e == hipSuccess) noalloc_scratch_init(device);
-    if (e == hipSuccess) e = hipMalloc(&ctx->range_scratch, 2 * sizeof(float));
+    if (e == hipSuccess) e = hipMalloc(&ctx->range_scratch, range_parts_bytes());
     if (e == hipSuccess) e = hipEventCreateWithFlags(&ctx->order_event, hipEventDisableTiming);
     if (e != hipSuccess) {
       if (ctx->range_scratch) hipFree(ctx->range_scratch);
@@ -229,20 +229,9 @@ palq_status palq_quantize(palq_ctx *ctx, const float *x, float l, float u, const
     return fail(ctx, PALQ_ERR_ARG, "range_out: not 4-byte aligned");
   if (ctx->device < 0) return PALQ_OK;
   hipSetDevice(ctx->device);
-  hipError_t e = hipSuccess;
-  const ActView ov = view_of(out);
-  if (calibrate) {
-    e = launch_minmax(x, count, ctx->range_scratch, ctx->stream);
-    if (e == hipSuccess && range_out) e = launch_range_out(ctx->range_scratch, range_out, ctx->stream);
-    if (e == hipSuccess) e = launch_quantize(x, 0.f, 0.f, ctx->range_scratch, ov, ctx->stream);
-  } else {
-    if (range_out) {
-      const float lu[2] = {l, u};
-      e = hipMemcpyAsync(range_out, lu, sizeof(lu), hipMemcpyHostToDevice, ctx->stream);
-      if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);  // lu is on this stack frame
-    }
-    if (e == hipSuccess) e = launch_quantize(x, l, u, nullptr, ov, ctx->stream);
-  }
+  RangeArg range{l, u, calibrate ? (const float2 *)ctx->range_scratch : nullptr, 0, range_out};
+  hipError_t e = calibrate ? launch_minmax(x, count, &range, ctx->stream) : hipSuccess;
+  if (e == hipSuccess) e = launch_quantize(x, range, view_of(out), ctx->stream);
   return e == hipSuccess ? PALQ_OK : device_fail(ctx, e, "quantize");
 }
 

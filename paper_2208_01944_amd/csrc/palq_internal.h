@@ -68,6 +68,23 @@ __host__ __device__ inline uint8_t *row_at(const ActView &v, int64_t r) {
   return v.data + p * v.pixel + g * v.gstride;
 }
 
+// floor(n / d) for 0 <= n < 2^31 by one 32 x 32 high product: with 2^k the
+// least power of two >= d and m = ceil(2^(31 + k) / d) <= 2^32 - 1 (d >= 2),
+// n m / 2^(31 + k) exceeds n / d by less than n / 2^31 / d < 1 / d.
+struct FastDiv {
+  uint32_t d, m;
+  int32_t sh;  // k - 1; -1: d == 1
+  static FastDiv of(uint32_t d) {
+    int k = 0;
+    while (((uint64_t)1 << k) < d) ++k;
+    if (d == 1) return {1u, 0u, -1};
+    return {d, (uint32_t)((((uint64_t)1 << (31 + k)) + d - 1) / d), k - 1};
+  }
+  __host__ __device__ uint32_t div(uint32_t n) const {
+    return sh < 0 ? n : (uint32_t)(((uint64_t)n * m) >> 32) >> sh;
+  }
+};
+
 // ----------------------------------------------------------------- conv
 // Everything a conv launch needs, all device pointers.
 struct ConvArgs {
@@ -146,10 +163,19 @@ hipError_t launch_stem_pool(const ConvArgs &a, const uint8_t *wp, const int32_t 
 
 hipError_t launch_pack(const void *codes, const ActView &out, hipStream_t s);
 hipError_t launch_unpack(const ActView &in, void *codes, hipStream_t s);
-hipError_t launch_minmax(const float *x, int64_t count, float *range, hipStream_t s);
-hipError_t launch_range_out(const float *enc, float *range_out, hipStream_t s);
-hipError_t launch_quantize(const float *x, float l, float u, const float *range, const ActView &out,
-                           hipStream_t s);
+// The quantiser's range: l and u, or (parts set) the calibration's (min, max)
+// pairs in device scratch of range_parts_bytes(), filled by launch_minmax.
+// range_out (device, nullable): the range used, NaN for an empty calibration.
+struct RangeArg {
+  float l, u;
+  const float2 *parts;
+  int nparts;
+  float *range_out;
+};
+size_t range_parts_bytes();
+// Fills range->parts for x and sets range->nparts.
+hipError_t launch_minmax(const float *x, int64_t count, RangeArg *range, hipStream_t s);
+hipError_t launch_quantize(const float *x, const RangeArg &range, const ActView &out, hipStream_t s);
 hipError_t launch_shuffle(const ActView &in, int32_t steps, const ActView &out, hipStream_t s);
 hipError_t launch_channel_shuffle(const ActView &in, const ActView &out, hipStream_t s);
 const char *channel_shuffle_label(const ActView &in, const ActView &out);
@@ -193,7 +219,7 @@ struct palq_ctx {
   int device = -1;           // -1: validate only
   hipStream_t stream = nullptr;
   std::string err;
-  float *range_scratch = nullptr;  // 2 floats for calibration without range_out
+  void *range_scratch = nullptr;   // calibration pairs (range_parts_bytes)
   uint8_t *conv_scratch = nullptr; // prepacked weights + thresholds of the last conv call
   size_t conv_scratch_bytes = 0;
   int8_t *fc_scratch = nullptr;    // digit planes of the last FC call

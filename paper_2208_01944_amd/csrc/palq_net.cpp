@@ -774,7 +774,7 @@ palq_status palq_forward_image(palq_ctx *ctx, palq_net *net, const float *x, flo
   if (ctx->device < 0) return PALQ_OK;
   hipSetDevice(ctx->device);
   if (net->img_direct) return forward_dispatch(ctx, net, nullptr, logits, x, l, u);
-  const hipError_t e = launch_quantize(x, l, u, nullptr, view_of(&net->input), ctx->stream);
+  const hipError_t e = launch_quantize(x, RangeArg{l, u, nullptr, 0, nullptr}, view_of(&net->input), ctx->stream);
   if (e != hipSuccess) return net_fail(ctx, PALQ_ERR_DEVICE, std::string("quantize: ") + hipGetErrorString(e));
   return forward_dispatch(ctx, net, net->img_codes, logits, nullptr, 0.f, 0.f);
 }

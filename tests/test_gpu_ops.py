@@ -81,6 +81,58 @@ def test_quantize_matches_oracle(ctx, torch, bits, signed, layout):
     np.testing.assert_array_equal(ctx.unpack(out), O.quantize(x2, l, u, bits, signed))
 
 
+# a quad of codes per lane: one quad, quads that leave row padding, a second
+# round of the grid (more than 2048 x 256 x 4 units), an input off 16-byte
+# alignment (the word-per-thread kernel)
+@pytest.mark.parametrize("bits", [2, 3, 4, 6, 8])
+@pytest.mark.parametrize("n,hw,groups,cpg,layout,shift", [(1, 1, 1, 4, 0, 0), (2, 5, 3, 20, 1, 0), (3, 7, 2, 44, 0, 0),
+                                                          (1, 9, 1, 96, 0, 1), (9, 56, 4, 84, 1, 0)])
+def test_quantize_quads(ctx, torch, bits, n, hw, groups, cpg, layout, shift):
+    say(f"quantize quads bits={bits} n={n} hw={hw} groups={groups} cpg={cpg} layout={layout} shift={shift}")
+    g = np.random.default_rng(cpg + bits)
+    x = g.normal(0, 1.3, (n, hw, hw, groups * cpg)).astype(np.float32)
+    q = (1 << bits) - 1
+    flat = x.reshape(-1)
+    k = min(flat.size // 2, 4 * q)
+    # half-integers of Eq. 2 at l = -2, u = 2 and their fp32 neighbours: the
+    # values whose rounding the division decides
+    ties = (-2.0 + 4.0 * (g.integers(0, q, k) + 0.5) / q).astype(np.float32)
+    flat[:k] = np.where(g.integers(0, 2, k), ties, np.nextafter(ties, np.float32(9) * (g.integers(0, 2, k) * 2 - 1), dtype=np.float32))
+    flat[k + 1::53] = np.nan
+    buf = torch.zeros(x.size + 4, dtype=torch.float32, device=ctx.dev)
+    xd = buf[shift:shift + x.size]
+    xd.copy_(ctx.upload(flat))
+    out = ctx.empty_act(n, hw, hw, groups, cpg, bits, layout=layout)
+    out.buf.fill_(255)
+    rng = torch.empty(2, dtype=torch.float32, device=ctx.dev)
+    for l, u in ((-2.0, 2.0), (float("nan"), float("nan"))):
+        ctx.quantize(xd, l, u, out, rng)
+        if l != l:
+            l, u = O.calibrate_range(x)
+        np.testing.assert_array_equal(rng.cpu().numpy(), np.array([l, u], np.float32))
+        ref = ctx.pack(O.quantize(x, l, u, bits, False), groups, bits, layout=layout)
+        nb = n * hw * hw * groups * packref.row_bytes(cpg, bits)
+        np.testing.assert_array_equal(out.buf[:nb].cpu().numpy(), ref.buf[:nb].cpu().numpy())
+
+
+def test_quantize_calibration_edges(ctx, torch):
+    """Nothing but NaN, one value only, infinities, and a tensor of no images."""
+    say("quantize calibration edges")
+    nan, inf = float("nan"), float("inf")
+    out = ctx.empty_act(1, 2, 2, 1, 8, 4)
+    rng = torch.empty(2, dtype=torch.float32, device=ctx.dev)
+    for vals, want in (([nan] * 32, (nan, nan)), ([2.5] * 32, (2.5, 2.5)), ([-inf, nan] + [1.0] * 30, (-inf, 1.0)),
+                       ([inf] * 32, (inf, inf))):
+        x = np.array(vals, np.float32).reshape(1, 2, 2, 8)
+        ctx.quantize(ctx.upload(x), nan, nan, out, rng)
+        np.testing.assert_array_equal(rng.cpu().numpy(), np.array(want, np.float32))
+        if not want[1] > want[0]:
+            np.testing.assert_array_equal(ctx.unpack(out), np.zeros_like(x))
+    empty = ctx.empty_act(0, 2, 2, 1, 8, 4)
+    ctx.quantize(torch.empty(0, dtype=torch.float32, device=ctx.dev), nan, nan, empty, rng)
+    assert np.isnan(rng.cpu().numpy()).all()
+
+
 # ---------------------------------------------------------------- conv
 def run_conv(ctx, torch, case, centred=False, layout=(0, 0, 0)):
     """Runs a single_layer() case on the GPU; returns (codes, acc, ref_codes,
