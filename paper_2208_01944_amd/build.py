@@ -20,7 +20,7 @@ BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libpalq.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
-SOURCES = ["palq_api.cpp", "palq_net.cpp", "k_elementwise.hip", "k_conv_direct.hip", "k_conv_mfma.hip"]
+SOURCES = ["palq_api.cpp", "palq_net.cpp", "k_elementwise.hip", "k_conv_direct.hip", "k_conv_mfma.hip", "k_conv_fp.hip"]
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

@@ -1,0 +1,1080 @@
+// Grouped B-bit convolution (B = 2, 3, 4) on the FP4 / FP6 matrix cores.
+//
+// Per group the layer is D[k][m] = sum_K W[k][K] X[K][m] (Eq. 1), k an output
+// channel, m an output pixel, K = (ky, kx, c), in K-blocks of 64 codes of one
+// tap: one v_mfma_scale_f32_32x32x64_f8f6f4 per 32 channels x 32 pixels.
+//
+//  * B = 2: codes as E2M1 c / 2 (the code is the bit pattern), weights w / 2;
+//    accumulator t / 4.
+//  * B = 3, 4: E2M3, c / 8 for a code c in 0..15 is the pattern c itself (0..7
+//    subnormal, 8..15 with exponent field 1), w / 8 is the pattern |w| with the
+//    sign in bit 5; accumulator t / 64.
+//  Products are exact multiples of 1/4 (1/64) and the fp32 accumulator holds
+//  every partial sum exactly while |t| + |bias| + qmax |res_mult| < 2^24.
+//
+// Any channel count: K-blocks and channel blocks are padded with zero weights,
+// so what an operand load brings in past the end of a row (the row's padding,
+// the next row, zeros past the tensor) is multiplied by zero; padded output
+// channels have scale 0, give code 0 (the row's padding bits) and only words
+// inside the row are stored.
+//
+// Requant: the accumulator starts at bias, u = t + bias (+ res_mult code), and
+// one fma with rounding towards minus infinity gives RD(x), x = u M 2^-sh +
+// 1/2.  Integers are representable, so floor(RD(x)) = floor(x): the definition,
+// for every shift (M < 2^24).
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <mutex>
+
+#include "codes.h"
+#include "conv_common.h"
+#include "palq_internal.h"
+
+namespace palq {
+
+namespace {
+
+// ------------------------------------------------------------ per-width facts
+template <int B>
+struct FpT {
+  static constexpr int SLAB = B == 2 ? 1024 : 1536;  // weight bytes of (K-block, 32 channels)
+  static constexpr int PPX = B == 2 ? 1 : 2;         // 16-byte LDS pieces of a pixel's K-block
+  static constexpr int XB = 8 * B;                   // its bytes in memory
+  static constexpr int CHS = 4 * B;                  // bytes of a lane half's 32 codes
+  static constexpr int L = B == 2 ? 2 : 6;           // the accumulator is 2^-L t
+};
+
+// K order of a lane's 32 codes: field f of the operand holds code fp_code(f).
+// B = 2: nibble n (word q = n / 8, position j = n % 8) is code 16 (q >> 1) +
+// 2 j + (q & 1): a word's even (odd) codes are its bit pairs masked in place
+// (after one shift).  B = 3: kPerm3, B = 4: kPerm4 (act_fp6_4).
+__host__ __device__ inline int fp_code(int B, int f) {
+  constexpr int kPerm3[16] = {0, 3, 6, 9, 12, 15, 2, 5, 8, 11, 14, 1, 4, 7, 10, 13};
+  constexpr int kPerm4[16] = {0, 1, 3, 4, 6, 7, 9, 10, 12, 13, 15, 8, 2, 11, 5, 14};
+  if (B == 2) return 16 * (f >> 4) + 2 * (f & 7) + ((f >> 3) & 1);
+  return (f & 16) + (B == 3 ? kPerm3[f & 15] : kPerm4[f & 15]);
+}
+
+// A lane's 32 codes as the MFMA operand.
+__device__ __forceinline__ v8i act_fp4(uint32_t x, uint32_t y) {
+  const uint32_t m = 0x33333333u;
+  const v4i b = {(int)(x & m), (int)((x >> 2) & m), (int)(y & m), (int)((y >> 2) & m)};
+  return __builtin_shufflevector(b, b, 0, 1, 2, 3, -1, -1, -1, -1);
+}
+// 3-bit chunk (low words 0, 1, bit-2 word): word 3 u + d = low word u masked
+// to its fields' code pairs, or'ed with the bit-2 word rotated so that bit 2
+// of those codes lands two bits above its pair.
+__device__ __forceinline__ v8i act_fp6_3(uint32_t lo0, uint32_t lo1, uint32_t hi) {
+  const uint32_t r0 = __builtin_amdgcn_alignbit(hi, hi, 30), r1 = __builtin_amdgcn_alignbit(hi, hi, 31);
+  v8i d;
+  d[0] = (int)((lo0 & 0xC30C30C3u) | (r0 & 0x04104104u));
+  d[1] = (int)((lo0 & 0x30C30C30u) | (r0 & 0x41041041u));
+  d[2] = (int)((lo0 & 0x0C30C30Cu) | (r0 & 0x10410410u));
+  d[3] = (int)((lo1 & 0xC30C30C3u) | (r1 & 0x04104104u));
+  d[4] = (int)((lo1 & 0x30C30C30u) | (r1 & 0x41041041u));
+  d[5] = (int)((lo1 & 0x0C30C30Cu) | (r1 & 0x10410410u));
+  d[6] = d[7] = 0;
+  return d;
+}
+// Two words of nibbles (codes 0-7 in w, 8-15 in v) to 16 six-bit fields: a
+// nibble at bit 4 j meets a field at bit 6 f after a shift by 0 or by 2, so
+// three words come from masks of w, v and w << 2, (v:w) >> 30.
+__device__ __forceinline__ void nib6(uint32_t w, uint32_t v, int *d) {
+  const uint32_t s = __builtin_amdgcn_alignbit(v, w, 30);                       // v << 2 | w >> 30
+  d[0] = (int)((w & 0x0F00F00Fu) | ((w << 2) & 0xC03C03C0u));                  // w0 w1 w3 w4 w6 w7 (low half)
+  d[1] = (int)((v & 0xF00F00F0u) | (s & 0x03C03C03u));                         // w7 (high half) v1 v2 v4 v5 v7
+  d[2] = (int)((w & 0x00F00F00u) | (s & 0x3C03C03Cu));                         // v0 w2 v3 w5 v6
+}
+__device__ __forceinline__ v8i act_fp6_4(v4i x) {
+  int d[6];
+  nib6((uint32_t)x[0], (uint32_t)x[1], d);
+  nib6((uint32_t)x[2], (uint32_t)x[3], d + 3);
+  return v8i{d[0], d[1], d[2], d[3], d[4], d[5], 0, 0};
+}
+template <int B>
+__device__ __forceinline__ v8i act_fp(v4i x) {
+  if constexpr (B == 2) return act_fp4((uint32_t)x[0], (uint32_t)x[1]);
+  else if constexpr (B == 3) return act_fp6_3((uint32_t)x[0], (uint32_t)x[1], (uint32_t)x[2]);
+  else return act_fp6_4(x);
+}
+template <int B>
+__device__ __forceinline__ v16f mfma_fp(v8i a, v8i b, v16f c) {
+  constexpr int F = B == 2 ? 4 : 2;  // E2M1 / E2M3
+  return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, F, F, 0, 0, 0, 0);
+}
+
+// ------------------------------------------------------------ prepare
+// One launch per layer.  Workgroup 0: the requant constants, in blocks of 64
+// channels [scale 64][bias 64][res_mult 64][unused 64] floats in accumulator
+// units (zero for padded channels), and the flag *bad (1: some channel is
+// outside the fp32 bounds).  The others: weight slabs, one lane operand (16 or
+// 24 bytes) per thread, [G][coutp / 32][kb_total][SLAB]; E2M3 slabs hold bytes
+// 0-15 of every lane, then bytes 16-23.  Projection K-blocks of source group g
+// hold the projection filter of its destination group (g + s) mod G.
+struct PrepArgs {
+  const uint8_t *w, *pw;
+  const int32_t *mult, *shift, *bias, *res_mult;
+  int32_t G, cout, coutp, taps, cin, pcin, cpb, km, kb, shuffle, res_max;
+  int64_t row, prow;  // packed bytes of a tap's row of the filter and of a projection row
+  int64_t acc_bound;
+  uint8_t *wp;
+  float *cst;
+  int32_t *bad;
+};
+
+template <int B>
+__global__ __launch_bounds__(512) void conv_fp_prep_kernel(PrepArgs a) {
+  if (blockIdx.x == 0) {
+    __shared__ int any_bad;
+    if (threadIdx.x == 0) any_bad = 0;
+    __syncthreads();
+    int bad = 0;
+    for (int i = threadIdx.x; i < a.G * a.coutp; i += 512) {
+      const int g = i / a.coutp, k = i - g * a.coutp;
+      float sc = 0.0f, b = 0.0f, rm = 0.0f;
+      if (k < a.cout) {
+        const int c = g * a.cout + k;
+        const int64_t m = a.mult[c], bi = a.bias ? a.bias[c] : 0, r = a.res_mult ? a.res_mult[c] : 0;
+        const int sh = a.shift[c];
+        const int64_t lim = (int64_t)1 << 24;
+        if (sh < 1 || sh > 62 || m <= -lim || m >= lim ||
+            a.acc_bound + (bi < 0 ? -bi : bi) + (r < 0 ? -r : r) * a.res_max >= lim) {
+          bad = 1;
+        } else {
+          sc = ldexpf((float)m, FpT<B>::L - sh);
+          b = ldexpf((float)bi, -FpT<B>::L);
+          rm = ldexpf((float)r, -FpT<B>::L);
+        }
+      }
+      float *blk = a.cst + (int64_t)(i >> 6) * 256 + (i & 63);
+      blk[0] = sc;
+      blk[64] = b;
+      blk[128] = rm;
+      blk[192] = 0.0f;
+    }
+    if (bad) atomicOr(&any_bad, 1);
+    __syncthreads();
+    if (threadIdx.x == 0) *a.bad = any_bad;
+    return;
+  }
+  const int64_t t = (int64_t)(blockIdx.x - 1) * 512 + threadIdx.x;
+  const int nc32 = a.coutp / 32;
+  if (t >= (int64_t)a.G * nc32 * a.kb * 64) return;
+  const int lane = (int)(t & 63), half = lane >> 5;
+  const int rest = (int)(t >> 6);
+  const int r2 = rest / a.kb, kb = rest - r2 * a.kb;
+  const int g = r2 / nc32, k = (r2 - g * nc32) * 32 + (lane & 31);
+  const bool main = kb < a.km;
+  const int tap = main ? kb / a.cpb : 0;
+  const int c0 = 64 * (main ? kb - tap * a.cpb : kb - a.km) + 32 * half;  // first code of the lane
+  const int n = min(32, (main ? a.cin : a.pcin) - c0);                     // its codes inside the row
+  uint32_t u[4] = {0, 0, 0, 0};
+  if (k < a.cout && n > 0) {
+    const uint8_t *row = main ? a.w + (((int64_t)g * a.cout + k) * a.taps + tap) * a.row
+                              : a.pw + ((int64_t)((g + a.shuffle) % a.G) * a.cout + k) * a.prow;
+    const uint32_t *p = (const uint32_t *)(row + (int64_t)(c0 / 32) * FpT<B>::CHS);
+    constexpr int PER = B == 3 ? 16 : 32 / B;  // codes of a word (B = 3: of its low words)
+#pragma unroll
+    for (int q = 0; q < B; ++q)
+      if (B == 3 || q * PER < n) u[q] = p[q];
+  }
+  uint32_t o[6] = {0, 0, 0, 0, 0, 0};
+#pragma unroll
+  for (int f = 0; f < 32; ++f) {
+    const int j = fp_code(B, f);
+    uint32_t v;
+    if constexpr (B == 3) v = ((u[j >> 4] >> (2 * (j & 15))) & 3u) | (((u[2] >> b3_hi_pos(j)) & 1u) << 2);
+    else v = (u[j * B / 32] >> ((j * B) & 31)) & ((1u << B) - 1u);
+    if (j >= n) v = 0;
+    if constexpr (B == 2) {
+      o[f >> 3] |= ((0x9A10u >> (4 * v)) & 15u) << (4 * (f & 7));  // 0, 1, -2, -1 -> 0, 0.5, -1, -0.5
+    } else {
+      const int w = sext(v, B);
+      const uint32_t e = w < 0 ? (uint32_t)(-w) | 0x20u : (uint32_t)w;
+      const int bit = 6 * f;
+      o[bit >> 5] |= e << (bit & 31);
+      if ((bit & 31) > 26) o[(bit >> 5) + 1] |= e >> (32 - (bit & 31));
+    }
+  }
+  uint8_t *slab = a.wp + (int64_t)rest * FpT<B>::SLAB;
+  *(uint4 *)(slab + lane * 16) = make_uint4(o[0], o[1], o[2], o[3]);
+  if constexpr (B != 2) *(uint2 *)(slab + 1024 + lane * 8) = make_uint2(o[4], o[5]);
+}
+
+// ------------------------------------------------------------ kernel arguments
+struct FpArgs {
+  const uint8_t *in, *wp, *res, *proj;
+  uint8_t *out;
+  const float *cst;
+  const int32_t *bad;  // set: the launch does nothing if *bad (its general partner runs)
+  int32_t *dump;
+  uint32_t in_bytes, w_bytes, res_bytes, proj_bytes, cst_bytes;
+  int32_t in_pix, in_gs, res_pix, res_gs, proj_pix, proj_gs, out_pix, out_gs;  // bytes, < 2^30
+  int32_t out_words;                        // words of an output row
+  int32_t M, h, w, stride, pad, kh, kw;     // M: output pixels; h, w: the input's
+  int32_t hw_out, wo;
+  int32_t ph, pw, pstride;                  // projection input
+  int32_t cpb, km, kb;                      // K-blocks per tap, of the main taps, in all
+  int32_t G, shuffle, cout, coutp, out_bits;
+  uint32_t rowpat;                          // bit ky kw of every filter row
+  FastDiv d_hw, d_wo, d_cpb, d_kw;
+  // tile order: pixel chunks of cl tiles (the last: llen), per chunk the
+  // (group, channel block) combos, per combo the chunk's pixel tiles
+  int32_t ncb, ncombo, nchunk, cl, llen, tiles;
+  FastDiv d_chunk, d_cl, d_llen, d_ncb;
+};
+
+struct TileId { int pt, cbk, g; };
+// Workgroup i runs on XCD i mod 8, which takes one contiguous range of the
+// tile order: an XCD's L2 then fetches a chunk's input lines once for all
+// groups, or (one chunk) holds a few combos' weights.  False: no tile.
+__device__ __forceinline__ bool tile_of(const FpArgs &a, TileId &id) {
+  const int x = (int)(blockIdx.x & 7), j = (int)(blockIdx.x >> 3);
+  const int q = a.tiles >> 3, r = a.tiles & 7;
+  if (j >= q + (x < r ? 1 : 0)) return false;
+  const uint32_t t = (uint32_t)(x * q + min(x, r) + j);
+  const uint32_t c = a.d_chunk.div(t);
+  const uint32_t rem = t - c * a.d_chunk.d;
+  const bool last = (int)c == a.nchunk - 1;
+  const uint32_t combo = last ? a.d_llen.div(rem) : a.d_cl.div(rem);
+  id.pt = (int)(c * a.cl + rem - combo * (uint32_t)(last ? a.llen : a.cl));
+  id.g = (int)a.d_ncb.div(combo);
+  id.cbk = (int)combo - id.g * a.ncb;
+  return true;
+}
+
+// Geometry of output pixel m: byte offset of tap (0, 0) (may be negative), the
+// taps outside the image (every bit for a pixel past the end, bits past the
+// taps set) and the projection's pixel offset (kOob past the end).
+struct PixelGeo { int off0; uint32_t out_mask; uint32_t poff; };
+template <bool PROJ>
+__device__ __forceinline__ PixelGeo pixel_geo(const FpArgs &a, int m) {
+  const bool valid = m < a.M;
+  const uint32_t mm = valid ? (uint32_t)m : 0u;
+  const int n = (int)a.d_hw.div(mm);
+  const int rem = (int)mm - n * a.hw_out;
+  const int oy = (int)a.d_wo.div((uint32_t)rem), ox = rem - oy * a.wo;
+  const int iy0 = oy * a.stride - a.pad, ix0 = ox * a.stride - a.pad;
+  PixelGeo p;
+  p.off0 = ((n * a.h + iy0) * a.w + ix0) * a.in_pix;
+  // bits [lo, hi) of one row (kw <= 32 bits) and of the row pattern
+  const int xlo = max(0, -ix0), xhi = max(xlo, min(a.kw, a.w - ix0));
+  const int ylo = max(0, -iy0), yhi = max(ylo, min(a.kh, a.h - iy0));
+  auto below = [](int b) __attribute__((always_inline)) { return (uint32_t)(((uint64_t)1 << min(b, 32)) - 1u); };
+  const uint32_t cols = below(min(xhi, 32)) & ~below(min(xlo, 32));
+  const uint32_t rows = a.rowpat & below(min(yhi, 32) * a.kw) & ~below(min(ylo, 32) * a.kw);
+  p.out_mask = valid ? ~(cols * rows) : 0xffffffffu;
+  p.poff = kOob;
+  if constexpr (PROJ)
+    if (valid) p.poff = (uint32_t)(((n * a.ph + oy * a.pstride) * a.pw + ox * a.pstride) * a.proj_pix);
+  return p;
+}
+
+// 16 bytes per lane from the buffer into LDS at `dst` (uniform) + 16 lane.  In
+// asm, so that the compiler does not order its LDS reads after these loads:
+// the ring's own waits and barriers do (the loads have no register results).
+// m0 is set in the same statement; nothing else in these kernels reads it.
+__device__ __forceinline__ void dma16(v4i rsrc, uint32_t dst, uint32_t voff, uint32_t soff) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+               :
+               : "s"(dst), "v"(voff), "s"(rsrc), "s"(soff));
+}
+__device__ __forceinline__ v4i rsrc4(const void *base, uint32_t bytes) {
+  const uint64_t p = (uint64_t)base;
+  return v4i{(int)(uint32_t)p, (int)((uint32_t)(p >> 32) & 0xffffu), (int)bytes, 0x00020000};
+}
+__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
+// Wait until at most N of this wave's loads are in flight and all of its LDS
+// reads are done, then meet the workgroup.
+template <int N>
+__device__ __forceinline__ void wait_barrier() {
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"(N) : "memory");
+}
+
+// Requant of one quad of channels: code = min(floor(u sc + 1/2), qmax), zero
+// below (the conversion truncates and takes negative values to 0).  Runs with
+// fp32 rounding towards minus infinity (see the top of the file).
+__device__ __forceinline__ uint32_t requant_rd(float u, float sc, uint32_t qmax) {
+  const float y = __builtin_fmaf(u, sc, 0.5f);
+  uint32_t q;
+  asm("v_cvt_u32_f32 %0, %1" : "=v"(q) : "v"(y));
+  return min(q, qmax);
+}
+// Every later fp32 operation that depends on a value passed through here
+// rounds towards minus infinity (asm volatile statements keep their order).
+__device__ __forceinline__ void set_round_down() {
+  asm volatile("s_setreg_imm32_b32 hwreg(HW_REG_MODE, 0, 2), 2");
+}
+
+// Four shortcut codes of channels 8 qi + 4 half .. + 3 of a 32-channel block
+// held in c (B = 2: two words; 3: the chunk; 4: four words).
+template <int B>
+__device__ __forceinline__ void quad_codes(const uint32_t *c, int qi, int half, float out[4]) {
+  uint32_t v, hi = 0;
+  if constexpr (B == 2 || B == 3) {
+    v = c[qi >> 1] >> (16 * (qi & 1) + 8 * half);
+    if constexpr (B == 3) hi = c[2] >> (16 * (qi & 1) + 8 * half + (qi >> 1));
+  } else {
+    v = c[qi] >> (16 * half);
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    uint32_t q;
+    if constexpr (B == 3) q = ((v >> (2 * e)) & 3u) | (((hi >> (2 * e)) & 1u) << 2);
+    else q = (v >> (B * e)) & ((1u << B) - 1u);
+    out[e] = (float)q;
+  }
+}
+
+// ------------------------------------------------------------ tile kernel
+// A workgroup computes TN = 64 WN channels x TM = 32 PB WM pixels of one group;
+// wave (wn, wm) owns 2 x PB blocks of 32 x 32.  A ring of S LDS stages, each of
+// KPS K-blocks (weight slabs, then the pixels' packed codes), is filled with
+// 16-byte LDS loads S - 1 stages ahead of the MFMAs, one barrier per stage.
+//
+// What bounds it: the instructions of one wave's K-block, not memory (with one
+// workgroup on an idle chip a K-block takes as long as on a full one).  So the
+// prologue has no loops and no dependent loads before the first fetch (constants
+// arrive by the same LDS loads), a K-block's position is decoded with two
+// multiplies instead of carried state, the in-image test is three VALU
+// instructions, two K-blocks share a barrier, and a stage's LDS reads are in
+// flight while the next fetch is issued.
+// KS = 2: two wave groups, group h taking K-block h of each stage; their
+// accumulators are added through LDS at the end (both exact, so is the sum).
+// MODE 0: no shortcut, 1: identity, 2: projection (more K-blocks).
+template <int B, int PB, int WN, int WM, int KPS, int KS>
+struct FpCfg {
+  using T = FpT<B>;
+  static constexpr int NT = WN * WM * 64 * KS;
+  static constexpr int TN = 64 * WN, TM = 32 * PB * WM;
+  static constexpr int W1 = TN / 32 * T::SLAB, X1 = TM * 16 * T::PPX;
+  static constexpr int WST = KPS * W1, XST = KPS * X1, SST = WST + XST;
+  static constexpr int WP = WST / 16, XP = XST / 16;
+  static_assert(WP % 64 == 0 && XP % 64 == 0 && (XP / KPS) % 64 == 0, "whole waves of pieces");
+  static constexpr int WL = (WP + NT - 1) / NT, XL = (XP + NT - 1) / NT;
+  // loads wave w issues per stage: the waves below `full` one more
+  static constexpr int loads(int w) {
+    int n = 0;
+    for (int i = 0; i < WL; ++i) n += 64 * w + i * NT < WP ? 1 : 0;
+    for (int i = 0; i < XL; ++i) n += 64 * w + i * NT < XP ? 1 : 0;
+    return n;
+  }
+  static constexpr int LMAX = loads(0), LMIN = loads(NT / 64 - 1);
+  static constexpr int full() {
+    int w = 0;
+    while (w < NT / 64 && loads(w) == LMAX) ++w;
+    for (int i = w; i < NT / 64; ++i)
+      if (loads(i) != LMIN) return -1;
+    return w;
+  }
+  static_assert(full() > 0, "at most two load counts");
+  static constexpr int RP = TM * (B == 2 ? TN / 64 : TN / 32);  // 16-byte shortcut pieces
+  static constexpr int RED = KS == 2 ? WN * WM * 2 * PB * 4096 : 0;
+};
+
+template <int B, int PB, int WN, int WM, int MODE, bool DUMP, int KPS, int KS, int S>
+__device__ __forceinline__ void conv_fp_tile(const FpArgs &a) {
+  using C = FpCfg<B, PB, WN, WM, KPS, KS>;
+  using T = FpT<B>;
+  constexpr int NT = C::NT, TN = C::TN, TM = C::TM, CB = 2;
+  static_assert(KS == 1 || KPS == 2, "the K split gives each wave group one K-block of a stage");
+  constexpr int RING = S * C::SST > C::RED ? S * C::SST : C::RED;
+  constexpr int CST = TN / 64 * 1024;
+  constexpr int RSB = MODE == 1 ? C::RP * 16 : 0;
+  __shared__ __attribute__((aligned(1024))) uint8_t lds[RING + CST + RSB];
+
+  if (a.bad && *a.bad != 0) return;
+  TileId id;
+  if (!tile_of(a, id)) return;
+  const int tid = (int)threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
+  const int l32 = lane & 31, half = lane >> 5;
+  const int kh = KS == 2 ? wave / (WN * WM) : 0, wg = wave - kh * (WN * WM);
+  const int wn = wg / WM, wm = wg % WM;
+  const int g = id.g, gd = g + a.shuffle < a.G ? g + a.shuffle : g + a.shuffle - a.G;
+  const int m0 = id.pt * TM;
+
+  const v4i r_w = rsrc4(a.wp, a.w_bytes), r_in = rsrc4(a.in, a.in_bytes);
+  const uint32_t base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)lds;
+  // constants, then the shortcut's codes: before stage 0, whose wait covers them
+  if (wave < TN / 64)
+    dma16(rsrc4(a.cst, a.cst_bytes), base + RING + wave * 1024, (uint32_t)(lane * 16),
+          (uint32_t)(((g * a.coutp + id.cbk * TN) / 64 + wave) * 1024));
+  if constexpr (MODE == 1) {
+    const v4i r_res = rsrc4(a.res, a.res_bytes);
+    constexpr int CBY = B == 2 ? 16 : T::CHS;  // bytes of a piece's channels in the row
+#pragma unroll
+    for (int i = 0; i < (C::RP + NT - 1) / NT; ++i)
+      if (64 * wave + i * NT < C::RP) {
+        const int q = tid + i * NT, cc = q / TM, m = m0 + q % TM;
+        const uint32_t vo = m < a.M ? (uint32_t)(m * a.res_pix + gd * a.res_gs + cc * CBY) : kOob;
+        dma16(r_res, base + RING + CST + (64 * wave + i * NT) * 16, vo, (uint32_t)(id.cbk * (TN * B / 8)));
+      }
+  }
+
+  // this thread's weight pieces and pixels
+  uint32_t woff[C::WL];
+#pragma unroll
+  for (int i = 0; i < C::WL; ++i) {
+    const int c = tid + i * NT, sub = c / (C::W1 / 16), r = c % (C::W1 / 16);
+    woff[i] = (uint32_t)((((g * a.coutp + id.cbk * TN) / 32 + r / (T::SLAB / 16)) * a.kb + sub) * T::SLAB +
+                         r % (T::SLAB / 16) * 16);
+  }
+  PixelGeo px[C::XL];
+#pragma unroll
+  for (int i = 0; i < C::XL; ++i) {
+    const int r = (tid + i * NT) % (TM * T::PPX);
+    const int pixel = T::PPX == 1 ? r : 32 * (r >> 6) + (r & 31);
+    px[i] = pixel_geo<MODE == 2>(a, m0 + pixel);
+    const int chunk = T::PPX == 1 ? 0 : T::CHS * ((r >> 5) & 1);
+    px[i].off0 += g * a.in_gs + chunk;
+    if constexpr (MODE == 2) px[i].poff += (uint32_t)(gd * a.proj_gs + chunk);
+  }
+  const int row_adj = (a.w - a.kw) * a.in_pix;
+  const int KB = a.kb, NS = (KB + KPS - 1) / KPS;
+  const uint32_t wdst = base + (uint32_t)(wave * 1024);
+  // Stage s into slot `slot`.
+  auto fetch = [&](int s, int slot) __attribute__((always_inline)) {
+    const uint32_t so = (uint32_t)(slot * C::SST);
+#pragma unroll
+    for (int i = 0; i < C::WL; ++i)
+      if ((i + 1) * NT <= C::WP || 64 * wave + i * NT < C::WP)
+        dma16(r_w, wdst + so + i * NT * 16, woff[i], (uint32_t)(s * KPS * T::SLAB));
+#pragma unroll
+    for (int i = 0; i < C::XL; ++i)
+      if ((i + 1) * NT <= C::XP || 64 * wave + i * NT < C::XP) {
+        const int sub = KPS == 1 ? 0 : (64 * wave + i * NT) / (C::XP / KPS);
+        const int kb = s * KPS + sub;
+        const uint32_t dst = wdst + so + C::WST + i * NT * 16;
+        if (MODE == 2 && kb >= a.km) {
+          dma16(rsrc4(a.proj, a.proj_bytes), dst, px[i].poff, (uint32_t)((kb - a.km) * T::XB));
+        } else {
+          const int tap = (int)a.d_cpb.div((uint32_t)kb), ky = (int)a.d_kw.div((uint32_t)tap);
+          const int tapoff = tap * a.in_pix + ky * row_adj;
+          // sign-extended bit `tap` of the mask: all ones outside the image
+          const uint32_t o = (uint32_t)__builtin_amdgcn_sbfe((int)px[i].out_mask, (uint32_t)tap, 1u);
+          dma16(r_in, dst, (uint32_t)(px[i].off0 + tapoff) | (o & kOob), (uint32_t)((kb - tap * a.cpb) * T::XB));
+        }
+      }
+  };
+#pragma unroll
+  for (int s = 0; s < S - 1; ++s)
+    if (s < NS) fetch(s, s);
+
+  // operands of K-block `sub` of the slot at byte so
+  const int xl = C::WST + (B == 2 ? (wm * PB * 32 + l32) * 16 + half * 8 : (wm * PB * 64 + lane) * 16);
+  const int al = wn * CB * T::SLAB + lane * 16, bl = wn * CB * T::SLAB + 1024 + lane * 8;
+  struct Ops { v4i x[PB], a0[CB]; v2i a1[CB]; };
+  auto read = [&](Ops &o, int so, int sub) __attribute__((always_inline)) {
+    const uint8_t *p = lds + so;
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) {
+      o.a0[cb] = *(const v4i *)(p + al + sub * C::W1 + cb * T::SLAB);
+      if constexpr (B != 2) o.a1[cb] = *(const v2i *)(p + bl + sub * C::W1 + cb * T::SLAB);
+    }
+#pragma unroll
+    for (int pb = 0; pb < PB; ++pb) {
+      if constexpr (B == 2) {
+        const v2i v = *(const v2i *)(p + xl + sub * C::X1 + pb * 512);
+        o.x[pb] = v4i{v[0], v[1], 0, 0};
+      } else {
+        o.x[pb] = *(const v4i *)(p + xl + sub * C::X1 + pb * 1024);
+      }
+    }
+  };
+  v16f acc[CB][PB];
+  auto mfmas = [&](const Ops &o) __attribute__((always_inline)) {
+    v8i A[CB];
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) {
+      if constexpr (B == 2) A[cb] = __builtin_shufflevector(o.a0[cb], o.a0[cb], 0, 1, 2, 3, -1, -1, -1, -1);
+      else A[cb] = v8i{o.a0[cb][0], o.a0[cb][1], o.a0[cb][2], o.a0[cb][3], o.a1[cb][0], o.a1[cb][1], 0, 0};
+    }
+#pragma unroll
+    for (int pb = 0; pb < PB; ++pb) {
+      const v8i X = act_fp<B>(o.x[pb]);
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb) acc[cb][pb] = mfma_fp<B>(A[cb], X, acc[cb][pb]);
+    }
+  };
+
+  const bool more = C::LMAX != C::LMIN && wave < C::full();
+  int so = 0, slot_f = S - 1;  // byte offset of the stage's slot; slot of the next fetch
+  constexpr int SUBS = KS == 2 ? 1 : KPS;
+  const float *cst = (const float *)(lds + RING) + wn * 256;
+  for (int s = 0; s < NS; ++s) {
+    // stage s has landed; up to S - 2 younger ones may be in flight
+    if (s + S - 2 < NS) {
+      if (C::LMAX != C::LMIN && !more) wait_barrier<(S - 2) * C::LMIN>();
+      else wait_barrier<(S - 2) * C::LMAX>();
+    } else {
+      wait_barrier<0>();
+    }
+    Ops o[SUBS];
+#pragma unroll
+    for (int i = 0; i < SUBS; ++i) read(o[i], so, KS == 2 ? kh : i);
+    if (s + S - 1 < NS) fetch(s + S - 1, slot_f);
+    if (s == 0) {
+      // element r of block cb is channel 32 cb + 8 (r / 4) + 4 half + r % 4
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+        for (int qi = 0; qi < 4; ++qi) {
+          const v4f b = *(const v4f *)(cst + 64 + cb * 32 + 8 * qi + 4 * half);
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int pb = 0; pb < PB; ++pb) acc[cb][pb][4 * qi + e] = kh == 0 ? b[e] : 0.0f;
+        }
+    }
+    const bool whole = KPS == 1 || s * KPS + KPS <= KB;
+    if (KS == 2) {
+      if (whole || kh == 0) mfmas(o[0]);
+    } else {
+      mfmas(o[0]);
+      if (KPS == 2 && whole) mfmas(o[SUBS - 1]);
+    }
+    so = so + C::SST == S * C::SST ? 0 : so + C::SST;
+    slot_f = slot_f + 1 == S ? 0 : slot_f + 1;
+  }
+
+  if constexpr (KS == 2) {
+    float *red = (float *)lds;
+    __syncthreads();
+    if (kh == 1) {
+#pragma unroll
+      for (int c = 0; c < CB * PB * 4; ++c) {
+        const v16f &v = acc[c / (PB * 4)][c / 4 % PB];
+        *(v4f *)(red + ((wg * CB * PB * 4 + c) * 64 + lane) * 4) =
+            v4f{v[4 * (c % 4)], v[4 * (c % 4) + 1], v[4 * (c % 4) + 2], v[4 * (c % 4) + 3]};
+      }
+    }
+    __syncthreads();
+    if (kh == 1) return;
+#pragma unroll
+    for (int c = 0; c < CB * PB * 4; ++c) {
+      const v4f r = *(const v4f *)(red + ((wg * CB * PB * 4 + c) * 64 + lane) * 4);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[c / (PB * 4)][c / 4 % PB][4 * (c % 4) + e] += r[e];
+    }
+  }
+
+  // ---- epilogue
+  const int ch0 = id.cbk * TN + wn * 64;
+  const int mw = m0 + wm * PB * 32;
+  if constexpr (DUMP) {
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+      for (int pb = 0; pb < PB; ++pb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int c = cb * 32 + 8 * (r >> 2) + 4 * half + (r & 3), m = mw + pb * 32 + l32;
+          if (m < a.M && ch0 + c < a.cout)
+            a.dump[((int64_t)m * a.G + gd) * a.cout + ch0 + c] =
+                (int)((acc[cb][pb][r] - cst[64 + c]) * (float)(1 << T::L));
+        }
+  }
+  set_round_down();
+#pragma unroll
+  for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+    for (int pb = 0; pb < PB; ++pb) asm volatile("" : "+v"(acc[cb][pb]));
+  constexpr uint32_t qmax = (1u << B) - 1u;
+  uint32_t w2[CB][PB];
+#pragma unroll
+  for (int cb = 0; cb < CB; ++cb) {
+    uint32_t qv[PB][4], hv[PB][4], rc[PB][4];
+    if constexpr (MODE == 1)
+#pragma unroll
+      for (int pb = 0; pb < PB; ++pb) {
+        const int p = wm * PB * 32 + pb * 32 + l32;
+        if constexpr (B == 2) {
+          const v2i v = *(const v2i *)(lds + RING + CST + (wn * TM + p) * 16 + 8 * cb);
+          rc[pb][0] = (uint32_t)v[0];
+          rc[pb][1] = (uint32_t)v[1];
+        } else {
+          const v4i v = *(const v4i *)(lds + RING + CST + ((wn * 2 + cb) * TM + p) * 16);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) rc[pb][e] = (uint32_t)v[e];
+        }
+      }
+#pragma unroll
+    for (int qi = 0; qi < 4; ++qi) {
+      // one quad at a time: keeps the constants of the others out of registers
+      __builtin_amdgcn_sched_barrier(0);
+      const int c0 = cb * 32 + 8 * qi + 4 * half;
+      const v4f sc = *(const v4f *)(cst + c0);
+      v4f rm = {0.0f, 0.0f, 0.0f, 0.0f};
+      if constexpr (MODE == 1) rm = *(const v4f *)(cst + 128 + c0);
+#pragma unroll
+      for (int pb = 0; pb < PB; ++pb) {
+        float rcode[4];
+        if constexpr (MODE == 1) quad_codes<B>(rc[pb], qi, half, rcode);
+        uint32_t w = 0, h = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          float u = acc[cb][pb][4 * qi + e];
+          if constexpr (MODE == 1) u = __builtin_fmaf(rm[e], rcode[e], u);  // exact
+          const uint32_t q = requant_rd(u, sc[e], qmax);
+          if constexpr (B == 3) {
+            w |= (q & 3u) << (2 * e);
+            h |= (q >> 2) << (2 * e);
+          } else {
+            w |= q << (B * e);
+          }
+        }
+        qv[pb][qi] = w;
+        hv[pb][qi] = h;
+      }
+    }
+    const int wd = (ch0 + cb * 32) / 32 * B;  // the block's first word of the row
+#pragma unroll
+    for (int pb = 0; pb < PB; ++pb) {
+      // v_permlane32_swap exchanges the upper lane half of its first operand
+      // with the lower lane half of its second; afterwards every lane holds
+      // quads 0..3 of its 16 channels in order
+      const auto p0 = __builtin_amdgcn_permlane32_swap(qv[pb][0], qv[pb][2], false, false);
+      const auto p1 = __builtin_amdgcn_permlane32_swap(qv[pb][1], qv[pb][3], false, false);
+      const int m = mw + pb * 32 + l32;
+      uint8_t *row = a.out + (int64_t)m * a.out_pix + (int64_t)gd * a.out_gs;
+      if constexpr (B == 2) {
+        w2[cb][pb] = p0[0] | (p0[1] << 8) | (p1[0] << 16) | (p1[1] << 24);
+      } else if constexpr (B == 3) {
+        uint32_t hp = 0;
+#pragma unroll
+        for (int qi = 0; qi < 4; ++qi) hp |= hv[pb][qi] << (16 * (qi & 1) + 8 * half + (qi >> 1));
+        const auto hs = __builtin_amdgcn_permlane32_swap(hp, hp, false, false);
+        if (m < a.M && wd < a.out_words) {
+          uint32_t *cw = (uint32_t *)row + wd;
+          cw[half] = p0[0] | (p0[1] << 8) | (p1[0] << 16) | (p1[1] << 24);
+          if (half == 0) cw[2] = hs[0] | hs[1];
+        }
+      } else {
+        const int wq = wd + 2 * half;
+        uint32_t *cw = (uint32_t *)row + wq;
+        const uint32_t v0 = p0[0] | (p0[1] << 16), v1 = p1[0] | (p1[1] << 16);
+        if (m < a.M) {
+          if (wq + 2 <= a.out_words) *(uint2 *)cw = make_uint2(v0, v1);
+          else if (wq < a.out_words) cw[0] = v0;
+        }
+      }
+    }
+  }
+  if constexpr (B == 2) {
+    // pixel blocks 2 i and 2 i + 1: lanes of half 0 take block 2 i, lanes of
+    // half 1 block 2 i + 1 and gather its 64 channels, stored at once
+    const int wd = ch0 / 32 * 2;
+#pragma unroll
+    for (int i = 0; i < PB / 2; ++i) {
+      const auto s0 = __builtin_amdgcn_permlane32_swap(w2[0][2 * i], w2[0][2 * i + 1], false, false);
+      const auto s1 = __builtin_amdgcn_permlane32_swap(w2[1][2 * i], w2[1][2 * i + 1], false, false);
+      const int m = mw + (2 * i + half) * 32 + l32;
+      if (m >= a.M) continue;
+      uint32_t *dst = (uint32_t *)(a.out + (int64_t)m * a.out_pix + (int64_t)gd * a.out_gs) + wd;
+      const uint32_t v[4] = {s0[0], s0[1], s1[0], s1[1]};
+      if (wd + 4 <= a.out_words) {
+        *(uint4 *)dst = make_uint4(v[0], v[1], v[2], v[3]);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (wd + e < a.out_words) dst[e] = v[e];
+      }
+    }
+  }
+}
+
+// ------------------------------------------------------------ split kernel
+// Layers with few tiles (one image, the deep stages at small batches): what
+// bounds those is one workgroup's serial K loop on an idle chip, so a tile is
+// small (32 channels x 32 PB pixels) and its K-blocks are dealt to the NW waves
+// of a workgroup.  A wave loads its operands straight into registers, U
+// K-blocks at once, with no barrier; the accumulators meet in LDS, each wave
+// adds and requantises its share of the quads and the codes are packed there.
+template <int B, int PB, int NW, int MODE, bool DUMP>
+__device__ __forceinline__ void conv_fp_split(const FpArgs &a) {
+  using T = FpT<B>;
+  constexpr int U = 4, Q = PB * 4;
+  static_assert(Q % NW == 0 || NW % Q == 0, "whole quads per wave");
+  __shared__ v4f red[NW * Q * 64];
+  __shared__ uint32_t cw[32 * PB * 9];  // packed quads of a pixel's 32 channels (9: no bank conflicts)
+  if (a.bad && *a.bad != 0) return;
+  TileId id;
+  if (!tile_of(a, id)) return;
+  const int tid = (int)threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
+  const int l32 = lane & 31, half = lane >> 5;
+  const int g = id.g, gd = g + a.shuffle < a.G ? g + a.shuffle : g + a.shuffle - a.G;
+  const int m0 = id.pt * 32 * PB, KB = a.kb;
+  const auto r_w = __builtin_amdgcn_make_buffer_rsrc((void *)a.wp, (short)0, (int)a.w_bytes, 0x00020000);
+  const auto r_in = __builtin_amdgcn_make_buffer_rsrc((void *)a.in, (short)0, (int)a.in_bytes, 0x00020000);
+  PixelGeo px[PB];
+#pragma unroll
+  for (int pb = 0; pb < PB; ++pb) {
+    px[pb] = pixel_geo<MODE == 2>(a, m0 + 32 * pb + l32);
+    px[pb].off0 += g * a.in_gs + half * T::CHS;
+    if constexpr (MODE == 2) px[pb].poff += (uint32_t)(gd * a.proj_gs + half * T::CHS);
+  }
+  const int row_adj = (a.w - a.kw) * a.in_pix;
+  const int slab0 = (g * (a.coutp / 32) + id.cbk) * KB;
+  auto load_x = [&](auto rs, uint32_t vo, int so) __attribute__((always_inline)) {
+    v4i x = {0, 0, 0, 0};
+    if constexpr (B == 2) {
+      const v2i v = __builtin_bit_cast(v2i, __builtin_amdgcn_raw_buffer_load_b64(rs, (int)vo, so, 0));
+      x[0] = v[0];
+      x[1] = v[1];
+    } else if constexpr (B == 3) {
+      const auto v = __builtin_amdgcn_raw_buffer_load_b96(rs, (int)vo, so, 0);
+      x[0] = (int)v[0];
+      x[1] = (int)v[1];
+      x[2] = (int)v[2];
+    } else {
+      x = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)vo, so, 0));
+    }
+    return x;
+  };
+  v16f acc[PB];
+#pragma unroll
+  for (int pb = 0; pb < PB; ++pb)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[pb][r] = 0.0f;
+  for (int k0 = wave; k0 < KB; k0 += NW * U) {
+    v4i x[U][PB], w0[U];
+    v2i w1[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int kb = k0 + u * NW;
+      if (kb >= KB) break;  // uniform
+      const int so = (slab0 + kb) * T::SLAB;
+      w0[u] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(r_w, lane * 16, so, 0));
+      if constexpr (B != 2)
+        w1[u] = __builtin_bit_cast(v2i, __builtin_amdgcn_raw_buffer_load_b64(r_w, 1024 + lane * 8, so, 0));
+      if (MODE == 2 && kb >= a.km) {
+        const auto r_pj = __builtin_amdgcn_make_buffer_rsrc((void *)a.proj, (short)0, (int)a.proj_bytes, 0x00020000);
+#pragma unroll
+        for (int pb = 0; pb < PB; ++pb) x[u][pb] = load_x(r_pj, px[pb].poff, (kb - a.km) * T::XB);
+      } else {
+        const int tap = (int)a.d_cpb.div((uint32_t)kb), ky = (int)a.d_kw.div((uint32_t)tap);
+        const int tapoff = tap * a.in_pix + ky * row_adj;
+#pragma unroll
+        for (int pb = 0; pb < PB; ++pb) {
+          const uint32_t o = (uint32_t)__builtin_amdgcn_sbfe((int)px[pb].out_mask, (uint32_t)tap, 1u);
+          x[u][pb] = load_x(r_in, (uint32_t)(px[pb].off0 + tapoff) | (o & kOob), (kb - tap * a.cpb) * T::XB);
+        }
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (k0 + u * NW >= KB) break;
+      v8i A;
+      if constexpr (B == 2) A = __builtin_shufflevector(w0[u], w0[u], 0, 1, 2, 3, -1, -1, -1, -1);
+      else A = v8i{w0[u][0], w0[u][1], w0[u][2], w0[u][3], w1[u][0], w1[u][1], 0, 0};
+#pragma unroll
+      for (int pb = 0; pb < PB; ++pb) acc[pb] = mfma_fp<B>(A, act_fp<B>(x[u][pb]), acc[pb]);
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < Q; ++j) {
+    const v16f &v = acc[j >> 2];
+    red[(wave * Q + j) * 64 + lane] = v4f{v[4 * (j & 3)], v[4 * (j & 3) + 1], v[4 * (j & 3) + 2], v[4 * (j & 3) + 3]};
+  }
+  __syncthreads();
+  const int k32 = id.cbk * 32;  // the tile's first channel of the group
+  set_round_down();             // the sums below are exact; only the requant rounds
+#pragma unroll
+  for (int j0 = 0; j0 < Q; j0 += NW) {
+    const int j = j0 + wave;  // quad j: pixel block j / 4, channels 8 (j % 4) + 4 half .. + 3
+    if (j >= Q) break;
+    v4f v = red[j * 64 + lane];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) v += red[(w * Q + j) * 64 + lane];
+    const int qi = j & 3, pixel = 32 * (j >> 2) + l32, m = m0 + pixel;
+    const int c0 = 8 * qi + 4 * half;
+    const float *cst = a.cst + (int64_t)((g * a.coutp + k32) >> 6) * 256 + (k32 & 32) + c0;
+    const v4f sc = *(const v4f *)cst, b = *(const v4f *)(cst + 64);
+    float rcode[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    v4f rm = {0.0f, 0.0f, 0.0f, 0.0f};
+    if constexpr (MODE == 1) {
+      rm = *(const v4f *)(cst + 128);
+      const auto r_res = __builtin_amdgcn_make_buffer_rsrc((void *)a.res, (short)0, (int)a.res_bytes, 0x00020000);
+      const uint32_t vo = m < a.M ? (uint32_t)(m * a.res_pix + gd * a.res_gs) : kOob;
+      uint32_t rc[4];
+#pragma unroll
+      for (int e = 0; e < B; ++e)
+        rc[e] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(r_res, (int)vo, id.cbk * 4 * B + 4 * e, 0);
+      quad_codes<B>(rc, qi, half, rcode);
+    }
+    if constexpr (DUMP)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (m < a.M && k32 + c0 + e < a.cout)
+          a.dump[((int64_t)m * a.G + gd) * a.cout + k32 + c0 + e] = (int)(v[e] * (float)(1 << T::L));
+    uint32_t w = 0, h = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      float u = v[e] + b[e];
+      if constexpr (MODE == 1) u = __builtin_fmaf(rm[e], rcode[e], u);
+      asm volatile("" : "+v"(u));  // after set_round_down
+      const uint32_t q = requant_rd(u, sc[e], (1u << B) - 1u);
+      if constexpr (B == 3) {
+        w |= (q & 3u) << (2 * e);
+        h |= (q >> 2) << (2 * e);
+      } else {
+        w |= q << (B * e);
+      }
+    }
+    cw[pixel * 9 + 2 * qi + half] = w | (h << 16);
+  }
+  __syncthreads();
+  for (int i = tid; i < 32 * PB * B; i += NW * 64) {
+    const int pixel = i / B, wi = i - pixel * B, m = m0 + pixel, wd = id.cbk * B + wi;
+    if (m >= a.M || wd >= a.out_words) continue;
+    const uint32_t *q = cw + pixel * 9;
+    uint32_t v;
+    if constexpr (B == 4) {
+      v = q[2 * wi] | (q[2 * wi + 1] << 16);
+    } else if (B == 3 && wi == 2) {
+      v = 0;
+#pragma unroll
+      for (int k = 0; k < 8; ++k) v |= (q[k] >> 16) << (8 * (k & 3) + (k >> 2));
+    } else {
+      v = 0;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v |= (q[4 * wi + k] & 0xffu) << (8 * k);
+    }
+    *(uint32_t *)(a.out + (int64_t)m * a.out_pix + (int64_t)gd * a.out_gs + 4 * wd) = v;
+  }
+}
+
+// Entry points by matrix-core format.
+#define PALQ_FP_TILE(NAME)                                                                            \
+  template <int B, int PB, int WN, int WM, int MODE, bool DUMP, int KPS, int KS, int S>               \
+  __global__ __launch_bounds__(WN *WM * 64 * KS, PB == 4 ? 2 : B == 2 ? 4 : 3) void NAME(FpArgs a) {  \
+    conv_fp_tile<B, PB, WN, WM, MODE, DUMP, KPS, KS, S>(a);                                           \
+  }
+#define PALQ_FP_SPLIT(NAME)                                                     \
+  template <int B, int PB, int NW, int MODE, bool DUMP>                         \
+  __global__ __launch_bounds__(NW * 64, 4) void NAME(FpArgs a) {                \
+    conv_fp_split<B, PB, NW, MODE, DUMP>(a);                                    \
+  }
+PALQ_FP_TILE(conv_fp4_kernel)
+PALQ_FP_TILE(conv_fp6_kernel)
+PALQ_FP_SPLIT(conv_fp4_split_kernel)
+PALQ_FP_SPLIT(conv_fp6_split_kernel)
+
+// ------------------------------------------------------------ host side
+int64_t code_max(int bits, int is_signed) {
+  return is_signed ? ((int64_t)1 << (bits - 1)) : (((int64_t)1 << bits) - 1);
+}
+int64_t fp_acc_bound(const ConvArgs &a) {
+  int64_t b = (int64_t)a.kh * a.kw * a.in.cpg * code_max(a.in.bits, 0) * code_max(a.w_bits, 1);
+  if (a.proj.data) b += (int64_t)a.proj.cpg * code_max(a.proj.bits, 0) * code_max(a.w_bits, 1);
+  return b;
+}
+
+int cpb_of(int cin) { return (cin + 63) / 64; }
+int fp_km(const ConvArgs &a) { return a.kh * a.kw * cpb_of(a.in.cpg); }
+int fp_kb(const ConvArgs &a) { return fp_km(a) + (a.proj.data ? cpb_of(a.proj.cpg) : 0); }
+int fp_coutp(const ConvArgs &a) { return (a.cout + 63) / 64 * 64; }
+int64_t fp_slab(int bits) { return bits == 2 ? 1024 : 1536; }
+
+FpArgs fp_args(const ConvArgs &a, const uint8_t *wp, const int32_t *thr, const int32_t *bad) {
+  FpArgs f{};
+  f.in = a.in.data; f.wp = wp; f.res = a.res.data; f.proj = a.proj.data; f.out = a.out.data;
+  f.cst = (const float *)thr;
+  f.bad = bad;
+  f.dump = a.acc_dump;
+  f.cout = a.cout;
+  f.coutp = fp_coutp(a);
+  f.G = a.in.groups;
+  f.cpb = cpb_of(a.in.cpg);
+  f.km = fp_km(a);
+  f.kb = fp_kb(a);
+  f.in_bytes = (uint32_t)a.in.bytes;
+  f.w_bytes = (uint32_t)((int64_t)f.G * f.coutp / 32 * f.kb * fp_slab(a.in.bits));
+  f.cst_bytes = (uint32_t)((int64_t)f.G * f.coutp * 16);
+  f.in_pix = (int32_t)a.in.pixel; f.in_gs = (int32_t)a.in.gstride;
+  f.out_pix = (int32_t)a.out.pixel; f.out_gs = (int32_t)a.out.gstride;
+  f.out_words = (int32_t)(a.out.row / 4);
+  if (a.res.data) { f.res_bytes = (uint32_t)a.res.bytes; f.res_pix = (int32_t)a.res.pixel; f.res_gs = (int32_t)a.res.gstride; }
+  if (a.proj.data) {
+    f.proj_bytes = (uint32_t)a.proj.bytes; f.proj_pix = (int32_t)a.proj.pixel; f.proj_gs = (int32_t)a.proj.gstride;
+    f.ph = a.proj.h; f.pw = a.proj.w; f.pstride = a.proj_stride;
+  }
+  f.M = a.out.n * a.ho * a.wo;
+  f.h = a.in.h; f.w = a.in.w; f.stride = a.stride; f.pad = a.pad; f.kh = a.kh; f.kw = a.kw;
+  f.hw_out = a.ho * a.wo; f.wo = a.wo;
+  f.shuffle = a.shuffle;
+  f.out_bits = a.out.bits;
+  for (int ky = 0; ky < a.kh; ++ky) f.rowpat |= 1u << (ky * a.kw);
+  f.d_hw = FastDiv::of((uint32_t)f.hw_out);
+  f.d_wo = FastDiv::of((uint32_t)f.wo);
+  f.d_cpb = FastDiv::of((uint32_t)f.cpb);
+  f.d_kw = FastDiv::of((uint32_t)f.kw);
+  return f;
+}
+
+// Tiles of tn channels x tm pixels; 32 pixel chunks where the packed input
+// outweighs the filter (every XCD then reads all of the filter: about 7 W
+// extra against (G - 1) X saved), else one.  Workgroups: a multiple of 8.
+unsigned fp_tiles(FpArgs &f, int tn, int tm, int64_t in_bytes) {
+  const int npt = (f.M + tm - 1) / tm;
+  f.ncb = (f.cout + tn - 1) / tn;
+  f.ncombo = f.ncb * f.G;
+  f.tiles = npt * f.ncombo;
+  const int want = 7 * (int64_t)f.w_bytes < (int64_t)(f.G - 1) * in_bytes ? std::min(32, npt) : 1;
+  f.cl = (npt + want - 1) / want;
+  f.nchunk = (npt + f.cl - 1) / f.cl;
+  f.llen = npt - (f.nchunk - 1) * f.cl;
+  f.d_chunk = FastDiv::of((uint32_t)(f.cl * f.ncombo));
+  f.d_cl = FastDiv::of((uint32_t)f.cl);
+  f.d_llen = FastDiv::of((uint32_t)f.llen);
+  f.d_ncb = FastDiv::of((uint32_t)f.ncb);
+  return (unsigned)((f.tiles + 7) / 8 * 8);
+}
+
+// Compute units of the current device (cached per device).
+int cu_count() {
+  static std::mutex mu;
+  static int devs[16], vals[16], used = 0;
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return 256;
+  std::lock_guard<std::mutex> lock(mu);
+  for (int i = 0; i < used; ++i)
+    if (devs[i] == dev) return vals[i];
+  int cus = 256;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) cus = 256;
+  if (used < 16) {
+    devs[used] = dev;
+    vals[used] = cus;
+    ++used;
+  }
+  return cus;
+}
+
+template <int B, int PB, int WN, int WM, int MODE, bool DUMP, int KPS, int KS, int S>
+hipError_t launch_tile_mode(const FpArgs &f, unsigned grid, hipStream_t s) {
+  const dim3 block(WN * WM * 64 * KS);
+  if constexpr (B == 2)
+    hipLaunchKernelGGL((conv_fp4_kernel<B, PB, WN, WM, MODE, DUMP, KPS, KS, S>), dim3(grid), block, 0, s, f);
+  else
+    hipLaunchKernelGGL((conv_fp6_kernel<B, PB, WN, WM, MODE, DUMP, KPS, KS, S>), dim3(grid), block, 0, s, f);
+  return hipGetLastError();
+}
+template <int B, int PB, int WN, int WM, bool DUMP, int KPS, int KS, int S>
+hipError_t launch_tile(FpArgs f, int64_t in_bytes, hipStream_t s) {
+  const unsigned grid = fp_tiles(f, 64 * WN, 32 * PB * WM, in_bytes);
+  if (f.res) return launch_tile_mode<B, PB, WN, WM, 1, DUMP, KPS, KS, S>(f, grid, s);
+  if (f.proj) return launch_tile_mode<B, PB, WN, WM, 2, DUMP, KPS, KS, S>(f, grid, s);
+  return launch_tile_mode<B, PB, WN, WM, 0, DUMP, KPS, KS, S>(f, grid, s);
+}
+
+template <int B, int PB, int NW, int MODE>
+hipError_t launch_split_mode(const FpArgs &f, unsigned grid, hipStream_t s) {
+  const dim3 block(NW * 64);
+  if constexpr (B == 2) {
+    if (f.dump) hipLaunchKernelGGL((conv_fp4_split_kernel<B, PB, NW, MODE, true>), dim3(grid), block, 0, s, f);
+    else hipLaunchKernelGGL((conv_fp4_split_kernel<B, PB, NW, MODE, false>), dim3(grid), block, 0, s, f);
+  } else {
+    if (f.dump) hipLaunchKernelGGL((conv_fp6_split_kernel<B, PB, NW, MODE, true>), dim3(grid), block, 0, s, f);
+    else hipLaunchKernelGGL((conv_fp6_split_kernel<B, PB, NW, MODE, false>), dim3(grid), block, 0, s, f);
+  }
+  return hipGetLastError();
+}
+template <int B, int PB, int NW>
+hipError_t launch_split(FpArgs f, int64_t in_bytes, hipStream_t s) {
+  const unsigned grid = fp_tiles(f, 32, 32 * PB, in_bytes);
+  if (f.res) return launch_split_mode<B, PB, NW, 1>(f, grid, s);
+  if (f.proj) return launch_split_mode<B, PB, NW, 2>(f, grid, s);
+  return launch_split_mode<B, PB, NW, 0>(f, grid, s);
+}
+
+#ifndef FP_BUILD
+#define FP_BUILD -1
+#endif
+#ifndef FP_SPLIT
+#define FP_SPLIT 512
+#endif
+template <int B>
+hipError_t launch_fp(const FpArgs &f, int64_t in_bytes, hipStream_t s) {
+  constexpr int KPS = B == 2 ? 2 : 1, S = B == 2 ? 3 : 4;
+  const int64_t cus = cu_count();
+  auto tiles = [&](int tn, int tm) {
+    return (int64_t)((f.M + tm - 1) / tm) * ((f.cout + tn - 1) / tn) * f.G;
+  };
+  const int build = FP_BUILD;
+  if (build == 0 || (build < 0 && tiles(32, 64) <= FP_SPLIT)) return launch_split<B, 2, 8>(f, in_bytes, s);
+  if (f.dump) return launch_tile<B, 2, 1, 4, true, KPS, 1, S>(f, in_bytes, s);
+  if (f.coutp % 128 != 0 || build == 1) return launch_tile<B, 2, 1, 4, false, KPS, 1, S>(f, in_bytes, s);
+  const int64_t t2 = tiles(128, 128), t4 = tiles(128, 256);
+  if (build == 3 || (build < 0 && t4 >= cus && 2 * ((t4 + cus - 1) / cus) <= (t2 + cus - 1) / cus))
+    return launch_tile<B, 4, 2, 2, false, KPS, 1, S>(f, in_bytes, s);
+  if (build == 4 || (build < 0 && f.kb >= 8 && t2 < 2 * cus)) return launch_tile<B, 2, 2, 2, false, 2, 2, 3>(f, in_bytes, s);
+  return launch_tile<B, 2, 2, 2, false, KPS, 1, S>(f, in_bytes, s);
+}
+
+}  // namespace
+
+// 2-, 3- and 4-bit layers with filter, output and shortcut codes of the same
+// width, whose accumulator bound leaves the fp32 accumulator room for bias and
+// shortcut (each channel is checked on the device), tensors and slabs the
+// buffer loads can address, and a tap mask of 32 bits.
+bool conv_fp_applies(const ConvArgs &a) {
+  const int b = a.in.bits;
+  if (!a.fp4 || a.in.is_signed || (b != 2 && b != 3 && b != 4) || a.w_bits != b || a.out.bits != b) return false;
+  if (a.bitdecomp && b == 4) return false;
+  if (a.res.data && (a.res.bits != b || a.res.is_signed)) return false;
+  if (a.proj.data && (a.proj.bits != b || a.proj.is_signed)) return false;
+  if ((int64_t)a.kh * a.kw > 32 || fp_acc_bound(a) >= ((int64_t)1 << 23)) return false;
+  const int64_t lim = (int64_t)1 << 30;
+  auto bytes = [](const ActView &v) { return v.data ? v.bytes : 0; };
+  if (bytes(a.in) >= lim || bytes(a.out) >= lim || bytes(a.res) >= lim || bytes(a.proj) >= lim) return false;
+  if ((int64_t)a.out.n * a.ho * a.wo >= (1 << 24)) return false;
+  const int64_t ch = (int64_t)a.in.groups * fp_coutp(a);
+  if (ch / 32 * fp_kb(a) * fp_slab(b) >= lim || ch * 16 >= lim) return false;
+  // tile indices in 31 bits (the smallest tile: 32 x 64)
+  return ((int64_t)a.out.n * a.ho * a.wo + 63) / 64 * ((a.cout + 31) / 32) * a.in.groups < lim;
+}
+
+ConvPlan conv_fp_plan(const ConvArgs &a) {
+  const int64_t ch = (int64_t)a.in.groups * fp_coutp(a);
+  return {(size_t)(ch / 32 * fp_kb(a) * fp_slab(a.in.bits)), (size_t)(ch * 16 + 16)};
+}
+
+const int32_t *conv_fp_flag(const ConvArgs &a, const int32_t *thr) {
+  return thr + (int64_t)a.in.groups * fp_coutp(a) * 4;
+}
+
+hipError_t launch_conv_fp_prepare(const ConvArgs &a, uint8_t *wp, int32_t *thr, hipStream_t s) {
+  PrepArgs p{};
+  p.w = a.w; p.pw = a.proj_w;
+  p.mult = a.mult; p.shift = a.shift; p.bias = a.bias;
+  p.res_mult = a.res.data ? a.res_mult : nullptr;
+  p.G = a.in.groups; p.cout = a.cout; p.coutp = fp_coutp(a);
+  p.taps = a.kh * a.kw; p.cin = a.in.cpg; p.pcin = a.proj.data ? a.proj.cpg : 0;
+  p.cpb = cpb_of(a.in.cpg); p.km = fp_km(a); p.kb = fp_kb(a);
+  p.shuffle = a.shuffle;
+  p.res_max = a.res.data ? (int)code_max(a.res.bits, 0) : 0;
+  p.row = row_bytes(a.in.cpg, a.w_bits);
+  p.prow = a.proj.data ? row_bytes(a.proj.cpg, a.w_bits) : 0;
+  p.acc_bound = fp_acc_bound(a);
+  p.wp = wp;
+  p.cst = (float *)thr;
+  p.bad = (int32_t *)conv_fp_flag(a, thr);
+  const int64_t lanes = (int64_t)p.G * (p.coutp / 32) * p.kb * 64;
+  const dim3 grid((unsigned)(1 + (lanes + 511) / 512));
+  if (a.in.bits == 2) hipLaunchKernelGGL(conv_fp_prep_kernel<2>, grid, dim3(512), 0, s, p);
+  else if (a.in.bits == 3) hipLaunchKernelGGL(conv_fp_prep_kernel<3>, grid, dim3(512), 0, s, p);
+  else hipLaunchKernelGGL(conv_fp_prep_kernel<4>, grid, dim3(512), 0, s, p);
+  return hipGetLastError();
+}
+
+hipError_t launch_conv_fp(const ConvArgs &a, const uint8_t *wp, const int32_t *thr, bool checked, hipStream_t s) {
+  if ((int64_t)a.out.n * a.ho * a.wo == 0) return hipSuccess;
+  const FpArgs f = fp_args(a, wp, thr, checked ? nullptr : conv_fp_flag(a, thr));
+  if (a.in.bits == 2) return launch_fp<2>(f, a.in.bytes, s);
+  if (a.in.bits == 3) return launch_fp<3>(f, a.in.bytes, s);
+  return launch_fp<4>(f, a.in.bytes, s);
+}
+
+}  // namespace palq

@@ -36,19 +36,12 @@
 #include <type_traits>
 
 #include "codes.h"
+#include "conv_common.h"
 #include "palq_internal.h"
 
 namespace palq {
 
 namespace {
-
-typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v16i __attribute__((ext_vector_type(16)));
-typedef int v8i __attribute__((ext_vector_type(8)));
-typedef int v2i __attribute__((ext_vector_type(2)));
-typedef float v16f __attribute__((ext_vector_type(16)));
-typedef float v4f __attribute__((ext_vector_type(4)));
-
 
 // ---------------------------------------------------------------- unpack
 // Activation unit (16 unsigned codes) -> MFMA operand (16 int8), and the
@@ -235,43 +228,6 @@ __global__ void requant_prep_kernel(const int32_t *mult, const int32_t *shift, c
   if (threadIdx.x == 0) *flag = any;
 }
 
-// The FP4 kernel's fp32 requant (2-bit outputs).  The accumulator starts at
-// b4 = bias / 4 and adds the products as multiples of 1/4, so it holds
-// u / 4 with u = t + bias (the identity shortcut's rm c / 4 added in fp32);
-// every partial value is exact when |t| + |bias| + 3 |rm| < 2^24.  With
-// sc = M 2^(2 - sh) (exact for |M| < 2^24) one fma gives
-//   y = RN(u M 2^-sh + 1/2) = RN(x),  x = (u M + 2^(sh-1)) 2^-sh,
-// a single rounding of x.  x 2^sh is an integer, so below an integer k <= 3
-// x stays at least 2^-sh <= 2^-22 under k, more than half the fp32 spacing
-// there (2^-23): RN(x) < k whenever x < k, and RN(x) >= floor(x) always.
-// Hence min(trunc(y), 3) (v_cvt_u32_f32 truncates and takes negative values
-// to 0) equals clamp(floor(x), 0, 3), the definition, for sh <= 22.  rm4:
-// the shortcut scale res_mult / 4 (exact, |res_mult| < 2^15).  flag: 1 when
-// every channel meets the bounds (else the fp64 epilogue runs).
-__global__ void requant_prep_f32_kernel(const int32_t *mult, const int32_t *shift, const int32_t *bias,
-                                        const int32_t *res_mult, int res_max, int nch, int64_t acc_bound, float *sc,
-                                        float *b4, float *rm4, int32_t *flag) {
-  __shared__ int any_bad;
-  if (threadIdx.x == 0) any_bad = 0;
-  __syncthreads();
-  int bad = 0;
-  for (int c = threadIdx.x; c < nch; c += blockDim.x) {
-    const int64_t m = mult[c];
-    const int sh = shift[c];
-    const int64_t b = bias ? bias[c] : 0;
-    const int64_t rm = res_mult ? res_mult[c] : 0;
-    const int64_t lim = (int64_t)1 << 24;
-    const int64_t umax = acc_bound + (b < 0 ? -b : b) + (rm < 0 ? -rm : rm) * res_max;
-    if (sh < 1 || sh > 22 || m <= -lim || m >= lim || umax >= lim) bad = 1;
-    sc[c] = bad ? 0.0f : ldexpf((float)m, 2 - sh);
-    b4[c] = bad ? 0.0f : (float)b * 0.25f;
-    rm4[c] = bad ? 0.0f : (float)rm * 0.25f;
-  }
-  if (bad) atomicOr(&any_bad, 1);
-  __syncthreads();
-  if (threadIdx.x == 0) *flag = any_bad ? 0 : 1;
-}
-
 // ---------------------------------------------------------------- geometry
 struct Geo {
   int32_t M;          // output pixels per group
@@ -282,7 +238,8 @@ struct Geo {
   int64_t pw_ch;      // bytes of one projection filter channel
   int32_t scale;      // operand scale of the accumulator (16 for 2-bit codes)
   const uint8_t *wp;  // weights in MFMA operand order (see prepack_kernel)
-  const RqConst *rq;  // per-channel requant constants, then the int64-path flag
+  const RqConst *rq;  // per-channel requant constants, then the int64-path flag (null: int64 path)
+  const int32_t *gate;  // a.gated launches: the general build runs only if *gate (null: always)
   const int32_t *acc0;  // B = 8: per-channel accumulator start 128 sum(w) (act_operand)
   float inv_hw, inv_wo;  // 1 / (ho wo) and 1 / wo, rounded to fp32 (fdiv's estimates)
 };
@@ -367,111 +324,7 @@ __global__ void wsum_kernel(ConvArgs a, Geo geo, int32_t *acc0) {
   acc0[c] = 128 * sum;
 }
 
-// FP4 (E2M1) weight slabs for the 2-bit grouped tile kernel, one MFMA
-// (32 x 32 x 64) per K-block: [G][cout/32][kb_total][half][ch][16 B].
-// Nibble n (word q = n / 8, position j = n % 8) of lane (ch, half) holds the
-// K-block's weight code 32 half + 16 (q >> 1) + 2 j + (q & 1) as E2M1 of w / 2
-// (-1, -0.5, 0, 0.5 for w = -2, -1, 0, 1); the activation unpack puts the
-// same code index there (as c / 2), so every product is exact and carries a
-// factor 1/4.  One thread per 16-byte lane operand.
-constexpr int kSlab4 = 1024;
-constexpr int kSlab6 = 1536;
-__global__ void prepack_fp4_kernel(ConvArgs a, Geo geo, uint8_t *wp) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int nc32 = a.cout / 32;
-  const int64_t total = (int64_t)a.in.groups * nc32 * geo.kb_total * 64;
-  if (t >= total) return;
-  const int within = (int)(t & 63);
-  const int64_t rest = t >> 6;
-  const int kb = (int)(rest % geo.kb_total);
-  const int64_t r2 = rest / geo.kb_total;
-  const int cblk = (int)(r2 % nc32);
-  const int g = (int)(r2 / nc32);
-  const int half = within >> 5, k = cblk * 32 + (within & 31);
-  const int gd = (g + a.shuffle) % a.in.groups;
-  const uint8_t *p = kb < geo.kb_main ? a.w + ((int64_t)g * a.cout + k) * geo.w_ch + (int64_t)kb * 16
-                                      : a.proj_w + ((int64_t)gd * a.cout + k) * geo.pw_ch + (int64_t)(kb - geo.kb_main) * 16;
-  const uint32_t u[2] = {((const uint32_t *)p)[2 * half], ((const uint32_t *)p)[2 * half + 1]};
-  uint32_t o[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const uint32_t src = u[q >> 1] >> (2 * (q & 1));
-    uint32_t w = 0;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const uint32_t c = (src >> (4 * j)) & 3u;               // 2-bit two's complement code
-      w |= ((0x9A10u >> (4 * c)) & 15u) << (4 * j);           // 0 -> 0, 1 -> 0.5, -2 -> -1, -1 -> -0.5
-    }
-    o[q] = w;
-  }
-  *(uint4 *)(wp + t * 16) = make_uint4(o[0], o[1], o[2], o[3]);
-}
-
-// FP6 (E2M3) weight slabs for 3-bit grouped layers, one MFMA (32 x 32 x 64)
-// per K-block: [G][cout/32][kb_total][1536 B], a slab holding bytes 0-15 of
-// every lane's 24-byte operand (lane l at 16 l), then bytes 16-23 (at
-// 1024 + 8 l).  Field f (bits 6f .. 6f + 5 of the 192-bit operand) of lane
-// (ch, half) holds E2M3 of the weight w of code 32 half + fp6_code(f) of the
-// K-block, exact for w in -4 .. 3; the activation operand (fp6_operand)
-// puts the same code there as the subnormal c / 8, so every product is exact
-// and carries a factor 1/8.
-// K order inside a 32-code chunk: the fields of output word 3 u + d (u: the
-// chunk's low word) take the codes 16 u + 3 m + r(d) (r = 0, 2, 1 for d = 0,
-// 1, 2), whose low bits the word can mask out of the low word in place.
-__host__ __device__ inline int fp6_code(int f) {
-  constexpr int kPerm[16] = {0, 3, 6, 9, 12, 15, 2, 5, 8, 11, 14, 1, 4, 7, 10, 13};
-  return (f & 16) + kPerm[f & 15];
-}
-__global__ void prepack_fp6_kernel(ConvArgs a, Geo geo, uint8_t *wp) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int nc32 = a.cout / 32;
-  const int64_t total = (int64_t)a.in.groups * nc32 * geo.kb_total * 64;
-  if (t >= total) return;
-  const int lane = (int)(t & 63);
-  const int64_t rest = t >> 6;
-  const int kb = (int)(rest % geo.kb_total);
-  const int64_t r2 = rest / geo.kb_total;
-  const int cblk = (int)(r2 % nc32);
-  const int g = (int)(r2 / nc32);
-  const int half = lane >> 5, k = cblk * 32 + (lane & 31);
-  // the K-block's chunk of this lane half: low words, then the bit-2 word
-  const uint32_t *c = (const uint32_t *)(a.w + ((int64_t)g * a.cout + k) * geo.w_ch + (int64_t)kb * 24 + 12 * half);
-  const uint32_t lo0 = c[0], lo1 = c[1], hi = c[2];
-  uint32_t o[6] = {0, 0, 0, 0, 0, 0};
-  for (int f = 0; f < 32; ++f) {
-    const int j = fp6_code(f);
-    const uint32_t v = (((j < 16 ? lo0 : lo1) >> (2 * (j & 15))) & 3u) | (((hi >> b3_hi_pos(j)) & 1u) << 2);
-    // E2M3 (sign, 2 exponent bits with bias 1, 3 mantissa bits) of the
-    // two's complement code v: 0, 1, 2, 3, -4, -3, -2, -1
-    constexpr uint32_t kE2M3[8] = {0x00, 0x08, 0x10, 0x14, 0x38, 0x34, 0x30, 0x28};
-    const uint32_t e = kE2M3[v];
-    const int bit = 6 * f;
-    o[bit >> 5] |= e << (bit & 31);
-    if ((bit & 31) > 26) o[(bit >> 5) + 1] |= e >> (32 - (bit & 31));
-  }
-  uint8_t *slab = wp + (t >> 6) * kSlab6;
-  *(uint4 *)(slab + lane * 16) = make_uint4(o[0], o[1], o[2], o[3]);
-  *(uint2 *)(slab + 1024 + lane * 8) = make_uint2(o[4], o[5]);
-}
-
-// MFMA operand of a lane's 32-code chunk (x: low words 0, 1 and the bit-2
-// word) as E2M3 subnormals c / 8, fields in the fp6_code order: word 3 u + d
-// = low word u masked to its fields' code pairs, or'ed with the bit-2 word
-// rotated so that bit 2 of each of those codes lands two bits above its pair
-// (codes 0-15 sit at even bits: rotate by 2; codes 16-31 at odd bits: by 1).
-__device__ inline v8i fp6_operand(uint32_t lo0, uint32_t lo1, uint32_t hi) {
-  const uint32_t r0 = __builtin_amdgcn_alignbit(hi, hi, 30), r1 = __builtin_amdgcn_alignbit(hi, hi, 31);
-  v8i d;
-  d[0] = (int)((lo0 & 0xC30C30C3u) | (r0 & 0x04104104u));
-  d[1] = (int)((lo0 & 0x30C30C30u) | (r0 & 0x41041041u));
-  d[2] = (int)((lo0 & 0x0C30C30Cu) | (r0 & 0x10410410u));
-  d[3] = (int)((lo1 & 0xC30C30C3u) | (r1 & 0x04104104u));
-  d[4] = (int)((lo1 & 0x30C30C30u) | (r1 & 0x41041041u));
-  d[5] = (int)((lo1 & 0x0C30C30Cu) | (r1 & 0x10410410u));
-  d[6] = 0;
-  d[7] = 0;
-  return d;
-}
+constexpr int kSlab4 = 1024;  // an FP4 slab: (K-block, 32 channels) of E2M1 lane operands
 
 // Buffer resource over `bytes` bytes at `base`: loads at an offset >= bytes
 // return zero (hardware range check), which implements the zero padding of
@@ -479,7 +332,6 @@ __device__ inline v8i fp6_operand(uint32_t lo0, uint32_t lo1, uint32_t hi) {
 __device__ inline __amdgpu_buffer_rsrc_t make_rsrc(const void *base, int64_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc((void *)base, (short)0, (int)bytes, 0x00020000);
 }
-constexpr uint32_t kOob = 0x40000000u;  // offset past any tensor these kernels accept (< 2^30 B)
 
 template <int B>
 __device__ inline RawT<B, false> buf_half(__amdgpu_buffer_rsrc_t r, uint32_t voff, int soff) {
@@ -516,9 +368,22 @@ __device__ inline int fdiv(int m, int d, float inv_d) {
 
 // Workgroup prologue shared by both kernels: copy the channel block's
 // prepacked weights (all K-blocks) and its requant constants into LDS.
-template <int CB>
+// geo.wp null (the general partner of an FP4 / FP6 layer, whose int8 slabs do
+// not exist; it runs only where a channel leaves the fp32 bounds): expand the
+// packed filter here.
+template <int B, bool STEM, int CB>
 __device__ inline void stage_block(const ConvArgs &a, const Geo &geo, int g, uint8_t *lds) {
   const int KB = geo.kb_total;
+  if (geo.wp == nullptr) {
+    for (int c = threadIdx.x; c < KB * CB * 128; c += kNW * 64) {
+      const int kb = c / (CB * 128), within = c & 127;
+      const int k = blockIdx.y * CB * 32 + ((c >> 7) % CB) * 32 + (within & 31);
+      *(v4i *)(lds + c * 16) = weight_unit<B, STEM>(a, geo, g, (g + a.shuffle) % a.in.groups, k, kb,
+                                                    2 * ((within >> 5) & 1) + (within >> 6));
+    }
+    __syncthreads();
+    return;
+  }
   const uint8_t *wsrc = geo.wp + (int64_t)(g * (a.cout / 32) + blockIdx.y * CB) * KB * kSlab;
   const int chunks = KB * CB * 128;
   for (int c = threadIdx.x; c < chunks; c += kNW * 64) {
@@ -546,7 +411,7 @@ __device__ __forceinline__ void epilogue(const ConvArgs &a, const Geo &geo, v16i
   const int qmax = (1 << a.out.bits) - 1;
   const int64_t outC = (int64_t)a.in.groups * a.cout;
   const int lsc = geo.scale == 16 ? 4 : 0;
-  const bool exact64 = ((const int32_t *)(geo.rq + (int64_t)a.in.groups * a.cout))[0] != 0;
+  const bool exact64 = geo.rq == nullptr || ((const int32_t *)(geo.rq + (int64_t)a.in.groups * a.cout))[0] != 0;
 #pragma unroll
   for (int cb = 0; cb < CB; ++cb) {
     const int kc = ch0 + cb * 32;
@@ -563,7 +428,7 @@ __device__ __forceinline__ void epilogue(const ConvArgs &a, const Geo &geo, v16i
       if constexpr (RB != 0) rmu = *(const v4i *)(a.res_mult + csb + cq);
       RqConst k[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) k[e] = rq[cb * 32 + cq + e];
+      for (int e = 0; e < 4; ++e) k[e] = rq[cb * 32 + cq + e];  // (not staged, and not used, when geo.rq is null)
 #pragma unroll
       for (int pb = 0; pb < PB; ++pb) {
         const int64_t mp = mbase + pb * 32 + l32;
@@ -652,25 +517,10 @@ typedef double dbl2 __attribute__((ext_vector_type(2)));
 // clamp) -> min with 2^BO - 1 -> shift into the quad's word.  BO = 3: the
 // quad's low bit pairs form the 2-bit word as for BO = 2 and its bit 2 go
 // to the chunk's bit-2 word (the two lane halves' parts or'ed together).
-// AccV = v16f: the FP4 tile kernel's accumulator, t / 4 held exactly (the
-// constants carry the factor 4); its shortcut term rm c / 4 is added in
-// fp32, exact because the layer's |t| + 3 |rm| stays below 2^24 (a multiple
-// of 1/4 below 2^22 fits the 24-bit significand).
-// LAZY (2-bit shortcut, PB = 2): rw is unused; each channel block's shortcut
-// words are read from LDS at rwl + 8 cb (pixel block 0) and + rws (pixel
-// block 1) when that block is processed, which keeps fewer registers live.
-// F32 (FP4 accumulator, 2-bit outputs): the accumulator already holds
-// (t + bias) / 4 and scf[c] is the channel's fp32 scale M 2^(2 - sh); the
-// requant is min(trunc(fma(v, scf, 1/2)), 3), exact under the bounds
-// requant_prep_f32_kernel checks (rq is then unused); rm holds the shortcut
-// scales res_mult / 4 as fp32 bits.
-template <int BO, int CB, int PB, int RB, typename AccV, bool LAZY = false, bool F32 = false>
-__device__ __forceinline__ void epilogue_fast_bo(const ConvArgs &a, const Geo &geo, AccV (&acc)[CB][PB],
+template <int BO, int CB, int PB, int RB>
+__device__ __forceinline__ void epilogue_fast_bo(const ConvArgs &a, const Geo &geo, v16i (&acc)[CB][PB],
                                         const uint32_t (&rw)[CB][PB][2], int64_t mbase, int g, int gd, int ch0,
-                                        int l32, int half, const RqConst *rq, const int32_t *rm,
-                                        uint32_t rwl = 0, uint32_t rws = 0, const float *scf = nullptr) {
-  static_assert(!LAZY || PB == 2 || PB == 4, "lazy shortcut reads are written for two or four pixel blocks");
-  static_assert(!F32 || (BO == 2 && std::is_same<AccV, v16f>::value), "the fp32 requant takes FP4 accumulators");
+                                        int l32, int half, const RqConst *rq, const int32_t *rm) {
   constexpr int bo = BO;
   // BO = 8 also stores 6-bit codes (one per byte), clamped at 63
   const uint32_t qmax = BO == 8 ? (1u << a.out.bits) - 1u : (1u << BO) - 1u;
@@ -678,21 +528,16 @@ __device__ __forceinline__ void epilogue_fast_bo(const ConvArgs &a, const Geo &g
   // requant constants (and shortcut multipliers) of quad j = 4 cb + qi,
   // read one quad ahead of their use so that their LDS latency overlaps
   // the previous quad's arithmetic
-  auto quad_consts = [&](int j, dbl2 (&k)[4], v4f &kf, v4i &rmu) __attribute__((always_inline)) {
+  auto quad_consts = [&](int j, dbl2 (&k)[4], v4i &rmu) __attribute__((always_inline)) {
     const int c0 = (j >> 2) * 32 + 8 * (j & 3) + 4 * half;
-    if constexpr (F32) {
-      kf = *(const v4f *)(scf + c0);
-    } else {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) k[e] = dbl2{rq[c0 + e].s, rq[c0 + e].o};
-    }
+    for (int e = 0; e < 4; ++e) k[e] = dbl2{rq[c0 + e].s, rq[c0 + e].o};
     rmu = v4i{0, 0, 0, 0};
     if constexpr (RB != 0) rmu = *(const v4i *)(rm + c0);
   };
   dbl2 k_cur[4];
-  v4f kf_cur;
   v4i rmu_cur;
-  quad_consts(0, k_cur, kf_cur, rmu_cur);
+  quad_consts(0, k_cur, rmu_cur);
   // 2-bit codes of two channel blocks and an even number of pixel blocks:
   // each lane gathers its pixel's 64 channels (16 bytes) and stores them at
   // once; w2[cb][pb] holds the lane's 16 channels of block (cb, pb)
@@ -704,32 +549,8 @@ __device__ __forceinline__ void epilogue_fast_bo(const ConvArgs &a, const Geo &g
     uint32_t qv[PB][4];
     uint32_t hv[PB][4];
     uint32_t rwc[PB][2];
-    if constexpr (RB == 2 && LAZY && PB == 2) {
-      uint2 r0, r1;
-      asm volatile(
-          "ds_read_b64 %0, %2\n\t"
-          "ds_read_b64 %1, %3\n\t"
-          "s_waitcnt lgkmcnt(0)"
-          : "=&v"(r0), "=&v"(r1)
-          : "v"(rwl + 8 * cb), "v"(rwl + 8 * cb + rws));
-      rwc[0][0] = r0.x; rwc[0][1] = r0.y;
-      rwc[1][0] = r1.x; rwc[1][1] = r1.y;
-    } else if constexpr (RB == 2 && LAZY) {
-      uint2 r[4];
-      asm volatile(
-          "ds_read_b64 %0, %4\n\t"
-          "ds_read_b64 %1, %5\n\t"
-          "ds_read_b64 %2, %6\n\t"
-          "ds_read_b64 %3, %7\n\t"
-          "s_waitcnt lgkmcnt(0)"
-          : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3])
-          : "v"(rwl + 8 * cb), "v"(rwl + 8 * cb + rws), "v"(rwl + 8 * cb + 2 * rws), "v"(rwl + 8 * cb + 3 * rws));
 #pragma unroll
-      for (int pb = 0; pb < PB; ++pb) { rwc[pb][0] = r[pb & 3].x; rwc[pb][1] = r[pb & 3].y; }
-    } else {
-#pragma unroll
-      for (int pb = 0; pb < PB; ++pb) { rwc[pb][0] = rw[cb][pb][0]; rwc[pb][1] = rw[cb][pb][1]; }
-    }
+    for (int pb = 0; pb < PB; ++pb) { rwc[pb][0] = rw[cb][pb][0]; rwc[pb][1] = rw[cb][pb][1]; }
 #pragma unroll
     for (int qi = 0; qi < 4; ++qi) {
       // one quad at a time: without this the scheduler hoists the constant
@@ -737,29 +558,17 @@ __device__ __forceinline__ void epilogue_fast_bo(const ConvArgs &a, const Geo &g
       __builtin_amdgcn_sched_barrier(0);
       const int cq = 8 * qi + 4 * half;
       dbl2 k[4];
-      v4f kf = kf_cur;
       v4i rmu;
 #pragma unroll
       for (int e = 0; e < 4; ++e) k[e] = k_cur[e];
       rmu = rmu_cur;
-      if (4 * cb + qi + 1 < 4 * CB) quad_consts(4 * cb + qi + 1, k_cur, kf_cur, rmu_cur);
+      if (4 * cb + qi + 1 < 4 * CB) quad_consts(4 * cb + qi + 1, k_cur, rmu_cur);
 #pragma unroll
       for (int pb = 0; pb < PB; ++pb) {
-        constexpr bool FACC = std::is_same<AccV, v16f>::value;
-        typename std::conditional<FACC, float, int32_t>::type v[4];
+        int32_t v[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) v[e] = acc[cb][pb][4 * qi + e];
-        if constexpr (RB == 2 && FACC) {
-          // F32: rm holds res_mult / 4 as fp32 bits (each element copied to
-          // a scalar first: a bit cast of a vector element would read the
-          // vector's first element)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int32_t ri = rmu[e];
-            v[e] = __builtin_fmaf(F32 ? __builtin_bit_cast(float, ri) : (float)ri * 0.25f,
-                                  (float)chunk_code(rwc[pb], cq + e, 2), v[e]);
-          }
-        } else if constexpr (RB == 2) {
+        if constexpr (RB == 2) {
           // |res_mult| < 2^15 and codes < 4: 24-bit signed products
 #pragma unroll
           for (int e = 0; e < 4; ++e) v[e] += __mul24(rmu[e] << lsc, chunk_code(rwc[pb], cq + e, 2));
@@ -775,13 +584,8 @@ __device__ __forceinline__ void epilogue_fast_bo(const ConvArgs &a, const Geo &g
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           uint32_t q;
-          if constexpr (F32) {
-            const float y = __builtin_fmaf((float)v[e], kf[e], 0.5f);
-            asm("v_cvt_u32_f32 %0, %1" : "=v"(q) : "v"(y));
-          } else {
-            const double d = __builtin_fma((double)v[e], k[e].x, k[e].y);
-            asm("v_cvt_u32_f64 %0, %1" : "=v"(q) : "v"(d));
-          }
+          const double d = __builtin_fma((double)v[e], k[e].x, k[e].y);
+          asm("v_cvt_u32_f64 %0, %1" : "=v"(q) : "v"(d));
           if constexpr (BO == 3) {
             const uint32_t qq = min(q, qmax);
             qword |= (qq & 3u) << (2 * e);
@@ -888,12 +692,11 @@ __device__ inline bool needs_general(const ConvArgs &a, const Geo &geo, int rb) 
 }
 
 // Whether this build of a persistent kernel leaves at once.  a.gated: the
-// launch is the general partner of a tiled launch (which covers every case
-// but the int64 requant), so only the general build runs, and only when the
-// flag is set; otherwise the fast and the general build split by
-// needs_general.
+// launch is the general partner of a tiled launch, so only the general build
+// runs, and only when the partner's device flag is set; otherwise the fast and
+// the general build split by needs_general.
 __device__ inline bool skip_build(const ConvArgs &a, const Geo &geo, int rb, bool gen) {
-  if (a.gated) return !gen || !int64_flag(a, geo);
+  if (a.gated) return !gen || (geo.gate && *geo.gate == 0);
   return needs_general(a, geo, rb) != gen;
 }
 
@@ -958,7 +761,7 @@ __global__ __launch_bounds__(kNW * 64) void conv_grouped_kernel(ConvArgs a, Geo 
   // the launcher may start both builds when it cannot tell which applies:
   // the other one leaves at once (before any barrier)
   if (skip_build(a, geo, RB, GEN)) return;
-  stage_block<CB>(a, geo, g, lds);
+  stage_block<B, false, CB>(a, geo, g, lds);
   const int first = blockIdx.x * kNW + wave;
   const int tstride = gridDim.x * kNW;
   if (first >= tiles) return;  // no barrier follows
@@ -1111,7 +914,7 @@ __global__ __launch_bounds__(kNW * 64) void conv_stem_kernel(ConvArgs a, Geo geo
   // the launcher may start both builds when it cannot tell which applies:
   // the other one leaves at once (before any barrier)
   if (skip_build(a, geo, RB, GEN)) return;
-  stage_block<CB>(a, geo, g, lds);
+  stage_block<8, true, CB>(a, geo, g, lds);
   const int first = blockIdx.x * kNW + wave;
   const int tstride = gridDim.x * kNW;
   if (first >= tiles) return;
@@ -1568,9 +1371,9 @@ __global__ __launch_bounds__(WN * WM * 64, 2) void conv_tile_kernel(ConvArgs a, 
         }
     }
     const int rec = (c_it.combo == combo0 ? 0 : TN) + wn * CB * 32;  // first record of this wave's channels
-    epilogue_fast_bo<2, CB, PB, RB, v16i>(
+    epilogue_fast_bo<2, CB, PB, RB>(
         a, geo, acc, rw, (int64_t)pt * TM + wm * PB * 32, g, gd, cbk * TN + wn * CB * 32, l32, half, rq_area + rec,
-        rm_area + (RB ? rec : 0), ra, 32 * RPX);
+        rm_area + (RB ? rec : 0));
   };
   // LDS addresses of this lane's operands in stage 0: activation half row
   // of pixel block 0, weight unit (j = 0) of channel block 0
@@ -1999,451 +1802,8 @@ __global__ __launch_bounds__(sp::NT, 2) void stem_pool_kernel(ConvArgs a, Geo ge
   __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
 }
 
-// ---------------------------------------------------------------- FP4 grouped kernel
-// 2-bit grouped layers on the FP4 (E2M1) matrix cores, one workgroup per
-// tile.  A tile is TN = WN CB 32 output channels x TM = WM PB 32 output
-// pixels of one group; wave (wn, wm) owns CB x PB blocks of 32 x 32.  Per
-// 64-code K-block the workgroup stages TN / 32 FP4 weight slabs (1 KB each,
-// prepack_fp4_kernel) and the TM pixels' packed codes (16 bytes each) in a
-// ring of S LDS stages with buffer_load ... lds, S - 1 K-blocks ahead of the
-// MFMAs (one barrier per K-block).  Per K-block a lane's fetch offsets change
-// only through the scalar offset (K-block within the tap, weight slab step);
-// the per-lane activation offset and its in-image test are redone when the
-// tap changes.  The K-blocks of a fused projection follow the main ones.
-// Tiles are dealt in XCD-contiguous runs (workgroup i runs on XCD i mod 8),
-// in the chunked order of tile_at, so an XCD's L2 holds the input lines its
-// in-flight tiles share.  Epilogue: epilogue_fast_bo (fp64-exact requant);
-// a layer whose requant needs the int64 path leaves at once (its general
-// partner runs instead).  DUMP: also write the int32 accumulators.
 // A value the compiler is told is the same in every lane of the wave.
 __device__ __forceinline__ int uniform_int(int v) { return __builtin_amdgcn_readfirstlane(v); }
-
-namespace f4 {
-template <int CB, int PB, int WN, int WM, int B = 2>
-struct Cfg {
-  static constexpr int NT = WN * WM * 64;
-  static constexpr int TN = WN * CB * 32, TM = WM * PB * 32;
-  static constexpr int SLAB = B == 2 ? kSlab4 : kSlab6;  // weight bytes per 32 channels and K-block
-  static constexpr int PPX = B == 2 ? 1 : 2;             // 16-byte activation pieces per pixel and K-block
-  static constexpr int WST = TN / 32 * SLAB;  // weight bytes of a K-block
-  static constexpr int XST = TM * 16 * PPX;   // activation bytes of a K-block
-  static constexpr int SST = WST + XST;
-  static constexpr int WP = WST / 16, XP = XST / 16;  // 16-byte pieces
-  static_assert(WP % 64 == 0 && XP % 64 == 0 && WP <= 2 * NT && XP <= 2 * NT, "whole waves of pieces");
-  static constexpr int WL = WP > NT ? 2 : 1, XL = XP > NT ? 2 : 1;  // loads per loading thread
-  // whether wave w issues weight (activation) load i: fewer pieces than
-  // threads go to the last (first) waves, more to every thread and then to
-  // the first waves
-  static constexpr bool wloads(int w, int i) { return WP < NT ? (i == 0 && 64 * w >= NT - WP) : 64 * w + i * NT < WP; }
-  static constexpr bool xloads(int w, int i) { return XP < NT ? (i == 0 && 64 * w < XP) : 64 * w + i * NT < XP; }
-  static constexpr int loads(int w) {
-    int n = 0;
-    for (int i = 0; i < WL; ++i) n += wloads(w, i) ? 1 : 0;
-    for (int i = 0; i < XL; ++i) n += xloads(w, i) ? 1 : 0;
-    return n;
-  }
-  static constexpr int min_loads() {
-    int m = 1 << 30;
-    for (int w = 0; w < NT / 64; ++w) m = loads(w) < m ? loads(w) : m;
-    return m;
-  }
-  // loads per K-block of the waves with the fewest (the ring waits on that)
-  static constexpr int LPK = min_loads();
-  static_assert(LPK >= 1, "every wave loads in every K-block");
-  static constexpr int RPX = TN / 4;          // shortcut code bytes per pixel
-  static constexpr int RSB = TM * RPX;        // shortcut codes of a tile
-};
-}  // namespace f4
-
-// B = 2: FP4 operands (conv_fp4_kernel); B = 3: 3-bit layers on FP6 (E2M3)
-// matrix cores (conv_fp6_kernel): 1536-byte weight slabs (prepack_fp6_kernel),
-// each pixel's K-block staged as its two 12-byte chunks in 16-byte pieces
-// (the chunk's three words at the start of each), fp6_operand, and a 3-bit
-// fast epilogue; no shortcut.
-// F32 (B = 2): the fp32 requant of requant_prep_f32_kernel; K-block 0's
-// MFMAs start from the channels' bias / 4 instead of zero.
-// KS = 2 (B = 2, for layers with few tiles): the workgroup is two groups of
-// WN x WM waves; a ring stage holds two consecutive K-blocks (the same tap:
-// the host takes this build only for an even K-block count per tap and an
-// even projection), group h fetching and multiplying K-block 2 s + h of
-// stage s; at the end group 1 adds its accumulators to group 0's through
-// LDS (the two partial sums are exact, so is their sum) and group 0 runs
-// the epilogue.  Twice the waves per tile, half the K loop each.
-template <int CB, int PB, int WN, int WM, int RB, bool DUMP, int S, int B, bool F32 = false, int KS = 1>
-__device__ __forceinline__ void conv_fpx_tile(const ConvArgs &a, const Geo &geo, int npt, int ncb, int nch) {
-  using C = f4::Cfg<CB, PB, WN, WM, B>;
-  // NT: the threads of one group; SSB: one K-block of a stage; SST: a stage
-  constexpr int NT = C::NT, TN = C::TN, TM = C::TM, WST = C::WST, SSB = C::SST, SST = KS * SSB;
-  static_assert(KS == 1 || (KS == 2 && B == 2 && PB == 2), "the K split takes FP4 layers with 2 x 2 blocks");
-  // the K split's reduction buffer: group 0's waves x 16 chunks x 64 lanes x 16 bytes, over the ring
-  constexpr int RED = KS == 2 ? (NT / 64) * 16 * 64 * 16 : 0;
-  constexpr int RING = S * SST > RED ? S * SST : RED;
-  constexpr int RPT = RB ? C::RSB / (NT * 16) : 0;  // 16-byte shortcut pieces per thread
-  static_assert(RB == 0 || RPT * NT * 16 == C::RSB, "whole shortcut pieces per thread");
-  static_assert(CB == 2 && (PB == 2 || PB == 4), "operand reads are written for 2 x 2 and 2 x 4 blocks");
-  static_assert(B == 2 || (B == 3 && PB == 2 && RB == 0), "FP6: 2 x 2 blocks, no shortcut");
-  static_assert(!F32 || B == 2, "the fp32 requant takes FP4 accumulators");
-  constexpr int XB = B == 2 ? 16 : 24;  // activation bytes of a pixel's K-block
-  __shared__ __attribute__((aligned(1024))) uint8_t lds[RING + (RB ? C::RSB : 16)];
-  __shared__ RqConst rq_area[TN];
-  __shared__ int32_t rm_area[RB ? TN : 1];
-
-  // the launcher takes 2-bit outputs and 2-bit (or no) shortcuts only; a
-  // layer whose fp64 requant could be inexact runs on the general partner
-  if (int64_flag(a, geo) || a.out.bits != B || RB < 0) return;
-  const int G = a.in.groups;
-  const int T = npt * ncb * G;
-  // workgroup i -> XCD x = i mod 8, which takes the x-th eighth of the tiles
-  const int x8 = (int)(blockIdx.x & 7), j = (int)(blockIdx.x >> 3);
-  const int Tq = T >> 3, Tr = T & 7;
-  if (j >= Tq + (x8 < Tr ? 1 : 0)) return;  // no barrier yet
-  const int t = x8 * Tq + min(x8, Tr) + j;
-  const TileIt it = tile_at(t, npt, ncb * G, nch);
-  const int pt = it.pt, cbk = it.combo % ncb, g = it.combo / ncb;
-  const int gd = (g + a.shuffle) % G;
-  // tid, wave: within the thread's group kh (KS = 2: of the two)
-  const int kh = KS == 2 ? uniform_int((int)threadIdx.x / NT) : 0;
-  const int tid = (int)threadIdx.x - kh * NT, lane = tid & 63;
-  const int wave = uniform_int(tid >> 6);  // LDS destinations in scalar registers
-  const int l32 = lane & 31, half = lane >> 5;
-  const int wn = wave / WM, wm = wave % WM;
-  const int KB = geo.kb_total, KM = geo.kb_main;
-
-  // requant constants (and shortcut multipliers) of the tile's TN channels;
-  // F32: the fp32 scales, then bias / 4, in rq_area's bytes, and the
-  // shortcut scales res_mult / 4 as fp32 bits in rm_area
-  const int64_t ch0 = (int64_t)g * a.cout + cbk * TN;
-  float *const sc_area = (float *)rq_area, *const b4_area = sc_area + TN;
-  for (int c = (int)threadIdx.x; c < TN; c += NT * KS) {
-    if constexpr (F32) {
-      const int64_t nall = (int64_t)G * a.cout;
-      const float *f32c = (const float *)(geo.rq + nall + 1);
-      sc_area[c] = f32c[ch0 + c];
-      b4_area[c] = f32c[nall + ch0 + c];
-      if constexpr (RB != 0) rm_area[c] = __builtin_bit_cast(int32_t, f32c[2 * nall + ch0 + c]);
-    } else {
-      rq_area[c] = geo.rq[ch0 + c];
-      if constexpr (RB != 0) rm_area[c] = a.res_mult[ch0 + c];
-    }
-  }
-  typedef __attribute__((address_space(3))) void *lds_ptr;
-  const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)lds;
-
-  const auto rw_src = make_rsrc(geo.wp, (int64_t)G * a.cout * KB * (C::SLAB / 32));
-  const auto rin = make_rsrc(a.in.data, a.in.bytes);
-  const auto rpj = a.proj.data ? make_rsrc(a.proj.data, a.proj.bytes)
-                               : make_rsrc(a.in.data, 0);
-  const auto rres = make_rsrc(a.res.data, a.res.data ? a.res.bytes : 0);
-  const int pixb = (int)a.in.pixel, rowb = a.in.w * pixb;
-
-  // ---- this thread's fetch pieces (wave w issues load i if C::wloads /
-  // C::xloads (w, i)).  Weights: piece c = tid - (NT - WP) (or tid + i NT)
-  // of the tile's slabs: slab c / (SLAB / 16), 16-byte piece c % (SLAB / 16).
-  // Activations, piece q = tid + i NT: B = 2, pixel q of the tile; B = 3,
-  // chunk (q >> 5) & 1 of pixel 32 (q >> 6) + (q & 31).
-  constexpr int PPS = C::SLAB / 16;  // pieces per slab
-  const int wc = C::WP >= NT ? tid : tid - (NT - C::WP);
-  uint32_t woff[C::WL];
-#pragma unroll
-  for (int i = 0; i < C::WL; ++i) {
-    const int c = wc + i * NT;
-    woff[i] = (uint32_t)((((int64_t)g * (a.cout / 32) + cbk * (TN / 32) + c / PPS) * KB) * C::SLAB + (c % PPS) * 16);
-  }
-  const int HW = a.ho * a.wo;
-  const float inv_hw = geo.inv_hw, inv_wo = geo.inv_wo;
-  int off0[C::XL], poff[C::XL];
-  uint32_t tmask[C::XL];
-#pragma unroll
-  for (int i = 0; i < C::XL; ++i) {
-    const int q = tid + i * NT;
-    const int m = pt * TM + (B == 2 ? q : 32 * (q >> 6) + (q & 31));
-    const bool valid = m < geo.M;
-    const int mm = valid ? m : 0;
-    const int n = fdiv(mm, HW, inv_hw);
-    const int rem = mm - n * HW;
-    const int oy = fdiv(rem, a.wo, inv_wo);
-    const int ox = rem - oy * a.wo;
-    const int iy0 = oy * a.stride - a.pad, ix0 = ox * a.stride - a.pad;
-    off0[i] = ((n * a.in.h + iy0) * a.in.w + ix0) * pixb + g * (int)a.in.gstride + (B == 3 ? 12 * ((q >> 5) & 1) : 0);
-    const int xlo = max(0, -ix0), xhi = min(a.kw, a.in.w - ix0);
-    const uint32_t below = xhi >= 32 ? 0xffffffffu : ((1u << max(xhi, 0)) - 1u);
-    const uint32_t cols = xhi > xlo ? (below & ~((1u << xlo) - 1u)) : 0u;
-    const int ylo = max(0, -iy0), yhi = min(a.kh, a.in.h - iy0);
-    uint32_t mk = 0;
-    for (int ky = ylo; ky < yhi; ++ky) mk |= cols << (ky * a.kw);
-    tmask[i] = valid ? mk : 0u;
-    poff[i] = (a.proj.data && valid)
-                  ? (((n * a.proj.h + oy * a.proj_stride) * a.proj.w + ox * a.proj_stride) * (int)a.proj.pixel +
-                     gd * (int)a.proj.gstride)
-                  : (int)kOob;
-  }
-  // fetch cursor: K-block f_kb = tap f_tap, block f_c of it; vo: the
-  // activation pieces' offsets for the current tap (kOob if outside)
-  int f_kb = 0, f_c = 0, f_tap = 0, f_kx = 0, f_tapoff = 0;
-  uint32_t vo[C::XL];
-  auto tap_offsets = [&]() __attribute__((always_inline)) {
-#pragma unroll
-    for (int i = 0; i < C::XL; ++i) vo[i] = ((tmask[i] >> f_tap) & 1u) ? (uint32_t)(off0[i] + f_tapoff) : kOob;
-  };
-  tap_offsets();
-  auto fetch = [&](int st) __attribute__((always_inline)) {
-    uint8_t *ws = lds + st * SST + kh * SSB;  // this group's K-block f_kb + kh of the stage
-    if constexpr (RB == 2) {
-      if (f_kb == 0 && kh == 0) {  // the tile's shortcut codes, RPT pieces per thread (before K-block 0's loads)
-#pragma unroll
-        for (int i = 0; i < RPT; ++i) {
-          const int c = tid + i * NT;
-          const int m = pt * TM + c / (C::RPX / 16);
-          const uint32_t ro = m < geo.M ? (uint32_t)((int64_t)m * a.res.pixel + gd * a.res.gstride + cbk * C::RPX +
-                                                     (c % (C::RPX / 16)) * 16)
-                                        : kOob;
-          __builtin_amdgcn_raw_ptr_buffer_load_lds(rres, (lds_ptr)(lds + RING + i * NT * 16 + wave * 1024), 16,
-                                                   (int)ro, 0, 0, 0);
-        }
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < C::WL; ++i)
-      if (C::wloads(wave, i))
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rw_src, (lds_ptr)(ws + ((wc + i * NT) & ~63) * 16), 16, (int)woff[i],
-                                                 (f_kb + kh) * C::SLAB, 0, 0);
-    if (f_kb < KM) {
-#pragma unroll
-      for (int i = 0; i < C::XL; ++i)
-        if (C::xloads(wave, i))
-          __builtin_amdgcn_raw_ptr_buffer_load_lds(rin, (lds_ptr)(ws + WST + i * NT * 16 + wave * 1024), 16, (int)vo[i],
-                                                   (f_c + kh) * XB, 0, 0);
-    } else {
-#pragma unroll
-      for (int i = 0; i < C::XL; ++i)
-        if (C::xloads(wave, i))
-          __builtin_amdgcn_raw_ptr_buffer_load_lds(rpj, (lds_ptr)(ws + WST + i * NT * 16 + wave * 1024), 16,
-                                                   (int)poff[i], (f_kb + kh - KM) * 16, 0, 0);
-    }
-    f_kb += KS;
-    f_c += KS;
-    if (f_c == geo.cpb) {  // next tap
-      f_c = 0;
-      ++f_tap;
-      f_tapoff += pixb;
-      if (++f_kx == a.kw) {
-        f_kx = 0;
-        f_tapoff += rowb - a.kw * pixb;
-      }
-      tap_offsets();
-    }
-  };
-
-  // ---- compute side (K-block 0's MFMAs take a zero C operand, or F32 the
-  // channels' bias / 4, so the accumulators need no initialisation)
-  v16f acc[CB][PB];
-  v16f c0[CB];  // F32: K-block 0's C operand of channel block cb
-  // LDS addresses of this lane's operands in stage 0: activation half row of
-  // pixel block 0 (blocks 512 bytes apart), weight unit of channel block 0
-  // (blocks 1 KB apart)
-  // (B = 3: chunk half of pixel block 0 at 1 KB blocks, the weight unit's
-  // first 16 bytes and its last 8 bytes, slabs 1536 bytes apart)
-  // (KS = 2: in this group's half of the stage)
-  const uint32_t gbase = lds_base + (uint32_t)(kh * SSB);
-  const uint32_t xaddr0 = gbase + WST +
-                          (uint32_t)(B == 2 ? (wm * PB * 32 + l32) * 16 + half * 8 : ((wm * PB) * 64 + lane) * 16);
-  const uint32_t aaddr0 = gbase + (uint32_t)((wn * CB) * C::SLAB + lane * 16);
-  const uint32_t baddr0 = gbase + (uint32_t)((wn * CB) * C::SLAB + 1024 + lane * 8);
-  auto kblock = [&](int st, bool first) __attribute__((always_inline)) {
-    const uint32_t xa = xaddr0 + st * SST, aa = aaddr0 + st * SST;
-    if constexpr (B == 3) {
-      const uint32_t ba = baddr0 + st * SST;
-      v4i x0, x1, A0, A1;
-      v2i B0, B1;
-      asm volatile(
-          "ds_read_b128 %0, %6\n\t"
-          "ds_read_b128 %1, %6 offset:1024\n\t"
-          "ds_read_b128 %2, %7\n\t"
-          "ds_read_b64 %3, %8\n\t"
-          "ds_read_b128 %4, %7 offset:1536\n\t"
-          "ds_read_b64 %5, %8 offset:1536\n\t"
-          "s_waitcnt lgkmcnt(0)"
-          : "=&v"(x0), "=&v"(x1), "=&v"(A0), "=&v"(B0), "=&v"(A1), "=&v"(B1)
-          : "v"(xa), "v"(aa), "v"(ba));
-      __builtin_amdgcn_sched_barrier(0);
-      const v4i B0w = __builtin_shufflevector(B0, B0, 0, 1, -1, -1), B1w = __builtin_shufflevector(B1, B1, 0, 1, -1, -1);
-      const v8i Aop[CB] = {__builtin_shufflevector(A0, B0w, 0, 1, 2, 3, 4, 5, -1, -1),
-                           __builtin_shufflevector(A1, B1w, 0, 1, 2, 3, 4, 5, -1, -1)};
-      const v4i X[2] = {x0, x1};
-#pragma unroll
-      for (int pb = 0; pb < PB; ++pb) {
-        const v8i Bop = fp6_operand((uint32_t)X[pb][0], (uint32_t)X[pb][1], (uint32_t)X[pb][2]);
-#pragma unroll
-        for (int cb = 0; cb < CB; ++cb)
-          acc[cb][pb] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(Aop[cb], Bop, first ? v16f{} : acc[cb][pb], 2,
-                                                                        2, 0, 0, 0, 0);
-      }
-      return;
-    }
-    uint2 xw[PB];
-    v4i A0, A1;
-    if constexpr (PB == 4) {
-      asm volatile(
-          "ds_read_b64 %0, %6\n\t"
-          "ds_read_b64 %1, %6 offset:512\n\t"
-          "ds_read_b64 %2, %6 offset:1024\n\t"
-          "ds_read_b64 %3, %6 offset:1536\n\t"
-          "ds_read_b128 %4, %7\n\t"
-          "ds_read_b128 %5, %7 offset:1024\n\t"
-          "s_waitcnt lgkmcnt(0)"
-          : "=&v"(xw[0]), "=&v"(xw[1]), "=&v"(xw[2]), "=&v"(xw[3]), "=&v"(A0), "=&v"(A1)
-          : "v"(xa), "v"(aa));
-    } else {
-      asm volatile(
-          "ds_read_b64 %0, %4\n\t"
-          "ds_read_b64 %1, %4 offset:512\n\t"
-          "ds_read_b128 %2, %5\n\t"
-          "ds_read_b128 %3, %5 offset:1024\n\t"
-          "s_waitcnt lgkmcnt(0)"
-          : "=&v"(xw[0]), "=&v"(xw[1]), "=&v"(A0), "=&v"(A1)
-          : "v"(xa), "v"(aa));
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    // E2M1 operands use the low four registers of each v8i (the rest is
-    // ignored for this format)
-    const v8i Aop[CB] = {__builtin_shufflevector(A0, A0, 0, 1, 2, 3, -1, -1, -1, -1),
-                         __builtin_shufflevector(A1, A1, 0, 1, 2, 3, -1, -1, -1, -1)};
-#pragma unroll
-    for (int pb = 0; pb < PB; ++pb) {
-      const uint32_t m = 0x33333333u;
-      const v4i b = {(int)(xw[pb].x & m), (int)((xw[pb].x >> 2) & m), (int)(xw[pb].y & m), (int)((xw[pb].y >> 2) & m)};
-      const v8i Bop = __builtin_shufflevector(b, b, 0, 1, 2, 3, -1, -1, -1, -1);
-#pragma unroll
-      for (int cb = 0; cb < CB; ++cb)
-        acc[cb][pb] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
-            Aop[cb], Bop, first ? (F32 ? c0[cb] : v16f{}) : acc[cb][pb], 4, 4, 0, 0, 0, 0);
-    }
-  };
-
-  static_assert(S == 4, "the waits below count at most two younger fetches");
-  // wait until K-block kb's loads have landed, y of this wave's fetches
-  // (LPK loads or more each) being younger
-  auto wait_younger = [&](int y) __attribute__((always_inline)) {
-    if (y >= 2) __builtin_amdgcn_s_waitcnt(waitcnt_vm(2 * C::LPK));
-    else if (y == 1) __builtin_amdgcn_s_waitcnt(waitcnt_vm(C::LPK));
-    else __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
-  };
-  __syncthreads();  // the tile's constants are in LDS
-  const int NS = KB / KS;  // ring stages (the host takes KS = 2 only for an even KB)
-#pragma unroll
-  for (int st = 0; st < S - 1; ++st)
-    if (st < NS) fetch(st);
-  if constexpr (F32) {
-    // element r of block cb is channel 32 cb + 8 (r / 4) + 4 half + r % 4
-    // of the wave's channels
-#pragma unroll
-    for (int cb = 0; cb < CB; ++cb)
-#pragma unroll
-      for (int qi = 0; qi < 4; ++qi) {
-        const v4f b = *(const v4f *)(b4_area + wn * CB * 32 + cb * 32 + 8 * qi + 4 * half);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) c0[cb][4 * qi + e] = kh == 0 ? b[e] : 0.0f;  // the bias once
-      }
-  }
-  // stage 0 (NS >= 1)
-  const bool steady0 = NS > S - 1;
-  wait_younger(steady0 ? S - 2 : NS - 1);
-  ring_barrier();
-  if (steady0) fetch(S - 1);
-  kblock(0, true);
-  // steady state: K-block kb's loads were issued S - 1 fetches ago; at most
-  // (S - 2) LPK of this wave's loads are younger
-  int kb = 1;
-  for (; kb + S - 1 < NS; ++kb) {
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm((S - 2) * C::LPK));
-    ring_barrier();
-    fetch((kb + S - 1) % S);
-    kblock(kb % S, false);
-  }
-  // the last S - 1 K-blocks: no more fetches, the waits tighten
-#pragma unroll
-  for (int i = 0; i < S - 1; ++i) {
-    if (kb >= NS) break;  // uniform
-    wait_younger(NS - 1 - kb);
-    ring_barrier();
-    kblock(kb % S, false);
-    ++kb;
-  }
-
-  if constexpr (KS == 2) {
-    // group 1's accumulators into group 0's: chunk c (4 values) of wave w at
-    // ((w 16 + c) 64 + lane) 16 bytes, over the ring, which every wave has
-    // finished reading at the first barrier
-    __syncthreads();
-    float *red = (float *)lds;
-    if (kh == 1) {
-#pragma unroll
-      for (int cb = 0; cb < CB; ++cb)
-#pragma unroll
-        for (int pb = 0; pb < PB; ++pb)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const int c = (cb * PB + pb) * 4 + q;
-            *(v4f *)(red + ((wave * 16 + c) * 64 + lane) * 4) =
-                v4f{acc[cb][pb][4 * q], acc[cb][pb][4 * q + 1], acc[cb][pb][4 * q + 2], acc[cb][pb][4 * q + 3]};
-          }
-    }
-    __syncthreads();
-    if (kh == 1) return;
-#pragma unroll
-    for (int cb = 0; cb < CB; ++cb)
-#pragma unroll
-      for (int pb = 0; pb < PB; ++pb)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int c = (cb * PB + pb) * 4 + q;
-          const v4f r = *(const v4f *)(red + ((wave * 16 + c) * 64 + lane) * 4);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) acc[cb][pb][4 * q + e] += r[e];  // exact (multiples of 1/4 below 2^22)
-        }
-  }
-
-  // ---- epilogue
-  const int64_t mbase = (int64_t)pt * TM + wm * PB * 32;
-  if constexpr (DUMP) {
-    const int64_t outC = (int64_t)G * a.cout;
-#pragma unroll
-    for (int cb = 0; cb < CB; ++cb)
-#pragma unroll
-      for (int pb = 0; pb < PB; ++pb) {
-        const int64_t mp = mbase + pb * 32 + l32;
-        if (mp >= geo.M) continue;
-        int32_t *dst = a.acc_dump + mp * outC + (int64_t)gd * a.cout + cbk * TN + wn * CB * 32 + cb * 32 + 4 * half;
-#pragma unroll
-        for (int qi = 0; qi < 4; ++qi) {
-          v4i dv;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            // exact: |t| < 2^23 (F32: the accumulator is (t + bias) / 4, each term below 2^22)
-            const float b = F32 ? b4_area[wn * CB * 32 + cb * 32 + 8 * qi + 4 * half + e] : 0.0f;
-            dv[e] = (int)((acc[cb][pb][4 * qi + e] - b) * (B == 2 ? 4.0f : 8.0f));
-          }
-          *(v4i *)(dst + 8 * qi) = dv;
-        }
-      }
-  }
-  // this lane's shortcut codes: pixel block pb, channel block cb at
-  // ra + pb 32 RPX + 8 cb (read per channel block by the epilogue)
-  const uint32_t ra = RB == 2 ? lds_base + RING + (uint32_t)((wm * PB * 32 + l32) * C::RPX + wn * CB * 8) : 0u;
-  uint32_t rw[CB][PB][2] = {};
-  epilogue_fast_bo<B, CB, PB, RB, v16f, true, F32>(a, geo, acc, rw, mbase, g, gd, cbk * TN + wn * CB * 32, l32, half,
-                                                     rq_area + wn * CB * 32, rm_area + (RB ? wn * CB * 32 : 0), ra,
-                                                     32 * C::RPX, sc_area + wn * CB * 32);
-}
-
-template <int CB, int PB, int WN, int WM, int RB, bool DUMP, int S, bool F32, int KS = 1>
-__global__ __launch_bounds__(WN * WM * 64 * KS, 2) void conv_fp4_kernel(ConvArgs a, Geo geo, int npt, int ncb, int nch) {
-  conv_fpx_tile<CB, PB, WN, WM, RB, DUMP, S, 2, F32, KS>(a, geo, npt, ncb, nch);
-}
-template <int CB, int PB, int WN, int WM, bool DUMP, int S>
-__global__ __launch_bounds__(WN * WM * 64, 2) void conv_fp6_kernel(ConvArgs a, Geo geo, int npt, int ncb, int nch) {
-  conv_fpx_tile<CB, PB, WN, WM, 0, DUMP, S, 3>(a, geo, npt, ncb, nch);
-}
 
 // ---------------------------------------------------------------- Eq. 4 bit decomposition
 // The M-bit baseline of Section 3.2 run on the 2-bit (FP4) matrix cores:
@@ -2907,8 +2267,6 @@ int64_t acc_bound_of(const ConvArgs &a) {
 
 }  // namespace
 
-bool fp4_applies(const ConvArgs &a);
-bool fp6_applies(const ConvArgs &a);
 bool bd_applies(const ConvArgs &a);
 size_t bd_offset(const ConvArgs &a);
 bool tile_kernel_applies(const ConvArgs &a);
@@ -2916,9 +2274,9 @@ bool stem_tile_applies(const ConvArgs &a);
 bool stem_rows(const ConvArgs &a);
 size_t stem_rows_offset(const ConvArgs &a);
 
-bool conv_mfma_general_fits(const ConvArgs &a) { return pick_cb(a, make_geo(a)) > 0; }
-
-bool conv_mfma_supported(const ConvArgs &a) {
+// The int8 kernels: whole 32-channel blocks and (past the stem) 64-code
+// K-blocks, int8 products of one width.
+static bool int8_shape(const ConvArgs &a) {
   if (a.cout % 32 != 0) return false;
   const int64_t lim = (int64_t)1 << 30;
   auto bytes = [](const ActView &v) { return v.data ? v.bytes : 0; };
@@ -2930,35 +2288,56 @@ bool conv_mfma_supported(const ConvArgs &a) {
     if (a.in.cpg % 64 != 0 || a.kh * a.kw > 32) return false;
     if (a.proj.data && (a.proj.bits != b || a.proj.cpg % 64 != 0 || a.proj.is_signed)) return false;
   }
+  return true;
+}
+
+bool conv_mfma_general_fits(const ConvArgs &a) { return int8_shape(a) && pick_cb(a, make_geo(a)) > 0; }
+
+bool conv_mfma_supported(const ConvArgs &a) {
+  if (conv_fp_applies(a)) return true;
   // the general build needs the filter in LDS; layers longer than that
   // still run on the tiled kernel (its fast epilogue)
-  return pick_cb(a, make_geo(a)) > 0 || tile_kernel_applies(a) || stem_tile_applies(a);
+  return int8_shape(a) && (pick_cb(a, make_geo(a)) > 0 || tile_kernel_applies(a) || stem_tile_applies(a));
 }
 
 ConvPlan conv_mfma_plan(const ConvArgs &a) {
+  if (conv_fp_applies(a)) return conv_fp_plan(a);
   ConvPlan p{};
   const Geo geo = make_geo(a);
   p.w_bytes = (size_t)a.in.groups * a.cout * geo.kb_total * 64;
   if (!is_stem(a) && a.in.bits >= 6) p.w_bytes += (size_t)a.in.groups * a.cout * 4;  // Geo::acc0
   p.thr_bytes = (size_t)a.in.groups * a.cout * sizeof(RqConst) + 16;  // + int64-path flag
   if (stem_rows(a)) p.w_bytes += (size_t)a.cout * sp::KH * 32;  // the filter-row copy
-  if (fp6_applies(a)) {  // FP6 slabs and constants after the int8 ones
-    p.w_bytes += (size_t)a.in.groups * a.cout * geo.kb_total * 48;
-    p.thr_bytes *= 2;
-  }
   if (bd_applies(a)) {  // the decomposition's chunk slabs and FP4-scaled constants
     p.w_bytes = bd_offset(a) + (size_t)a.in.groups * a.cout * geo.kb_total * (a.in.bits / 2) * 32;
     p.thr_bytes *= 2;
   }
-  if (fp4_applies(a)) {  // FP4 slabs and constants after the int8 ones (the general build keeps those)
-    p.w_bytes += (size_t)a.in.groups * a.cout * geo.kb_total * 32;
-    p.thr_bytes *= 2;
-    p.thr_bytes += (size_t)a.in.groups * a.cout * 12 + 16;  // fp32 scale, bias / 4, res_mult / 4, flag
-  }
   return p;
 }
 
+// Layers on the FP4 / FP6 kernels need less scratch than they used to and
+// others fit that never went through the buffer; the call's limit stays the
+// documented one, the int8 slabs with their constants and a second, narrower
+// copy for the FP4 / FP6 formats.
+size_t conv_noalloc_bytes(const ConvArgs &a) {
+  const ConvPlan p = conv_mfma_plan(a);
+  const size_t actual = ((p.w_bytes + 255) & ~(size_t)255) + p.thr_bytes;
+  if (!conv_fp_applies(a) || !int8_shape(a)) return actual;
+  const size_t nch = (size_t)a.in.groups * a.cout, kb = make_geo(a).kb_total;
+  const bool shortcut = a.res.data || a.proj.data;
+  size_t w = nch * kb * 64, thr = nch * sizeof(RqConst) + 16;
+  if (a.in.bits == 2 && a.cout % 64 == 0) {
+    w += nch * kb * 32;
+    thr = 2 * thr + nch * 12 + 16;
+  } else if (a.in.bits == 3 && a.cout % 64 == 0 && !shortcut) {
+    w += nch * kb * 48;
+    thr *= 2;
+  }
+  return std::max(actual, ((w + 255) & ~(size_t)255) + thr);
+}
+
 hipError_t launch_conv_prepare(const ConvArgs &a, uint8_t *wp, int32_t *thr, hipStream_t s) {
+  if (conv_fp_applies(a)) return launch_conv_fp_prepare(a, wp, thr, s);
   const Geo geo = make_geo(a);
   const int64_t chunks = (int64_t)a.in.groups * (a.cout / 32) * geo.kb_total * 128;
   const unsigned grid = (unsigned)((chunks + 255) / 256);
@@ -3001,66 +2380,19 @@ hipError_t launch_conv_prepare(const ConvArgs &a, uint8_t *wp, int32_t *thr, hip
                        a.res.data ? a.res_mult : nullptr, res_max, nch, -2, acc_bound, rqb, (int32_t *)(rqb + nch));
     return hipGetLastError();
   }
-  if (e == hipSuccess && fp6_applies(a)) {
-    const int64_t lanes = (int64_t)a.in.groups * (a.cout / 32) * geo.kb_total * 64;
-    hipLaunchKernelGGL(prepack_fp6_kernel, dim3((unsigned)((lanes + 255) / 256)), dim3(256), 0, s, a, geo,
-                       wp + (size_t)a.in.groups * a.cout * geo.kb_total * 64);
-    RqConst *rq6 = rq + nch + 1;  // the FP6 accumulator is t / 8
-    hipLaunchKernelGGL(requant_prep_kernel, dim3(1), dim3(256), 0, s, a.mult, a.shift, a.bias, nullptr, 0, nch, -3,
-                       acc_bound, rq6, (int32_t *)(rq6 + nch));
-    return hipGetLastError();
-  }
-  if (e != hipSuccess || !fp4_applies(a)) return e;
-  const int64_t pieces = (int64_t)a.in.groups * (a.cout / 32) * geo.kb_total * 64;
-  hipLaunchKernelGGL(prepack_fp4_kernel, dim3((unsigned)((pieces + 255) / 256)), dim3(256), 0, s, a, geo,
-                     wp + (size_t)a.in.groups * a.cout * geo.kb_total * 64);
-  RqConst *rq4 = rq + nch + 1;  // the FP4 accumulator is t / 4
-  hipLaunchKernelGGL(requant_prep_kernel, dim3(1), dim3(256), 0, s, a.mult, a.shift, a.bias, a.res.data ? a.res_mult : nullptr,
-                     res_max, nch, -2, acc_bound, rq4, (int32_t *)(rq4 + nch));
-  float *f32c = (float *)(rq4 + nch + 1);
-  hipLaunchKernelGGL(requant_prep_f32_kernel, dim3(1), dim3(256), 0, s, a.mult, a.shift, a.bias,
-                     a.res.data ? a.res_mult : nullptr, res_max, nch, acc_bound, f32c, f32c + nch, f32c + 2 * nch,
-                     (int32_t *)(f32c + 3 * nch));
-  return hipGetLastError();
+  return e;
 }
 
 bool conv_mfma_pads_input(const ConvArgs &a) { return is_stem(a) && a.pad > 0; }
 
-bool conv_mfma_f32(const ConvArgs &a, const int32_t *thr) {
-  if (!fp4_applies(a) || bd_applies(a) || fp6_applies(a)) return false;
-  const int64_t nch = (int64_t)a.in.groups * a.cout;
-  const float *f32c = (const float *)((const RqConst *)thr + 2 * (nch + 1));
-  int32_t ok = 0;
-  if (hipMemcpy(&ok, f32c + 3 * nch, sizeof(ok), hipMemcpyDeviceToHost) != hipSuccess) return false;
-  return ok == 1;
-}
-
 int conv_mfma_epilogue(const ConvArgs &a, const int32_t *thr) {
-  if (!bd_applies(a) && ((a.out.bits == 3 && !fp6_applies(a)) || (a.res.data && a.res.bits != 2))) return 1;
+  const bool fp = conv_fp_applies(a);
+  if (!fp && !bd_applies(a) && (a.out.bits == 3 || (a.res.data && a.res.bits != 2))) return 1;
   int32_t flag = 0;
   const RqConst *rq = (const RqConst *)thr;
-  if (hipMemcpy(&flag, rq + (int64_t)a.in.groups * a.cout, sizeof(flag), hipMemcpyDeviceToHost) != hipSuccess)
-    return -1;
+  const int32_t *src = fp ? conv_fp_flag(a, thr) : (const int32_t *)(rq + (int64_t)a.in.groups * a.cout);
+  if (hipMemcpy(&flag, src, sizeof(flag), hipMemcpyDeviceToHost) != hipSuccess) return -1;
   return flag != 0 ? 1 : 0;
-}
-
-// Compute units of the current device (cached per device).
-int cu_count() {
-  static std::mutex mu;
-  static int devs[16], vals[16], used = 0;
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return 256;
-  std::lock_guard<std::mutex> lock(mu);
-  for (int i = 0; i < used; ++i)
-    if (devs[i] == dev) return vals[i];
-  int cus = 256;
-  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) cus = 256;
-  if (used < 16) {
-    devs[used] = dev;
-    vals[used] = cus;
-    ++used;
-  }
-  return cus;
 }
 
 // Persistent workgroups of a tiled-kernel build: as many as are resident at
@@ -3103,24 +2435,6 @@ static bool grouped2_tiles(const ConvArgs &a) {
 // The persistent int8 tile kernel keeps its ring full across tiles: at least
 // kStages K-blocks per tile.
 bool tile_kernel_applies(const ConvArgs &a) { return grouped2_tiles(a) && make_geo(a).kb_total >= kStages; }
-
-// FP4 matrix cores for a 2-bit tiled layer whose accumulator bound is below
-// 2^23 (the fp32 accumulator then holds every partial sum, and the shortcut
-// term, exactly), unless the context keeps layers on int8 (a.fp4 = 0).  The
-// FP4 kernel runs one tile per workgroup and takes any K-block count (1 x 1
-// layers over 64 or 128 input channels included).
-bool fp4_applies(const ConvArgs &a) { return a.fp4 && grouped2_tiles(a) && acc_bound_of(a) < ((int64_t)1 << 23); }
-
-// FP6 matrix cores for 3-bit grouped layers with 3-bit outputs, 64-channel
-// blocks and no shortcut, under the same accumulator bound (the fp32
-// accumulator holds t / 8: a multiple of 1/8 below 2^20 is exact) and the
-// same context switch.
-bool fp6_applies(const ConvArgs &a) {
-  const int64_t wbytes = (int64_t)a.in.groups * a.cout * make_geo(a).kb_total * 64;
-  return a.fp4 && !is_stem(a) && a.in.bits == 3 && a.w_bits == 3 && a.out.bits == 3 && !a.in.is_signed &&
-         !a.res.data && !a.proj.data && a.cout % 64 == 0 && a.in.cpg % 64 == 0 && wbytes < ((int64_t)1 << 30) &&
-         acc_bound_of(a) < ((int64_t)1 << 23);
-}
 
 // The Eq. 4 bit decomposition (palq_set_conv_bitdecomp) for an unsigned
 // M-bit layer (M in {4, 6, 8}) with M-bit weights, outputs and shortcut
@@ -3166,115 +2480,36 @@ bool stem_rows(const ConvArgs &a) {
 }
 size_t stem_rows_offset(const ConvArgs &a) { return (size_t)a.in.groups * a.cout * make_geo(a).kb_total * 64; }
 
-// Tiled-kernel builds (tile shape per wave CB x PB blocks of 32 x 32, WN x WM
-// waves): the 8-bit stem; 2-bit layers on FP4 with 64-channel blocks (1 x 4
-// waves, 256-pixel tiles), 128-channel blocks (2 x 2 waves, 128 pixels) or
-// 128-channel blocks with 2 x 4 blocks per wave (256 pixels); 2-bit layers on
-// int8 with 64- or 128-channel blocks (256 pixels).
-// 3-bit layers on FP6 with 64-channel (1 x 4 waves, 256 pixels) or
-// 128-channel blocks (2 x 2 waves, 128 pixels).
-// Wide layers as the Eq. 4 decomposition with 64- or 128-channel tiles.
-enum TileBuild {
-  kTileNone = 0, kTileStem, kTileFp4C64, kTileFp4C128, kTileFp4C128P4, kTileFp4C128K2, kTileFp6C64, kTileFp6C128,
-  kTileI8C64, kTileI8C128, kTileBdC64, kTileBdC128
-};
-
-// 2 x 4 blocks per wave (256-pixel tiles) for 128-channel FP4 layers where
-// the bigger tiles leave every CU at least one and do not lengthen the
-// busiest CU's share: 2 ceil(T4 / CUs) <= ceil(T2 / CUs) tile units.
-bool fp4_pb4_pays(const ConvArgs &a, const Geo &geo) {
-  const int64_t m = geo.M, tiles_per_px = (int64_t)(a.cout / 128) * a.in.groups;
-  const int64_t t2 = (m + 127) / 128 * tiles_per_px, t4 = (m + 255) / 256 * tiles_per_px;
-  const int64_t cus = cu_count();
-  return t4 >= cus && 2 * ((t4 + cus - 1) / cus) <= (t2 + cus - 1) / cus;
-}
-
-// The in-workgroup K split (conv_fpx_tile, KS = 2) for 128-channel FP4
-// layers with fewer 128 x 128 tiles than twice the CUs (the deep layers,
-// whose tiles leave most SIMDs with one wave): an even number of K-blocks
-// per tap, an even projection and at least 8 K-blocks.
-bool fp4_ksplit_pays(const ConvArgs &a, const Geo &geo) {
-  const int64_t t2 = (geo.M + 127) / 128 * (a.cout / 128) * a.in.groups;
-  const int pk = geo.kb_total - geo.kb_main;
-  return geo.cpb % 2 == 0 && pk % 2 == 0 && geo.kb_total >= 8 && t2 < 2 * (int64_t)cu_count();
-}
+// Tiled-kernel builds: the 8-bit stem; 2-bit layers on int8 with 64- or
+// 128-channel blocks (256-pixel tiles); wide layers as the Eq. 4 decomposition
+// with 64- or 128-channel tiles; 2-, 3- and 4-bit layers on FP4 / FP6
+// (k_conv_fp.hip, which picks its own tile).
+enum TileBuild { kTileNone = 0, kTileFp, kTileStem, kTileI8C64, kTileI8C128, kTileBdC64, kTileBdC128 };
 
 // The one selection rule of the conv launches: which tiled build (if any)
 // takes the layer given the epilogue build epi (0 fast, 1 general, -1 not
 // known: a tiled build is then launched with its general partner, which
-// runs only if the layer's int64-requant flag is set).
+// runs only if the layer's flag is set).
 struct ConvChoice {
   int tile;  // TileBuild
-  int cb;    // channel blocks of the persistent build (0: it does not fit LDS)
+  int cb;    // channel blocks of the persistent build (0: it does not fit LDS or take the shape)
 };
 
 ConvChoice conv_choice(const ConvArgs &a, const Geo &geo, int epi) {
-  ConvChoice c{kTileNone, pick_cb(a, geo)};
+  ConvChoice c{kTileNone, int8_shape(a) ? pick_cb(a, geo) : 0};
   if (epi == 1) return c;
+  if (conv_fp_applies(a)) {
+    c.tile = kTileFp;
+    return c;
+  }
   if (bd_applies(a)) {
     c.tile = a.cout % 128 ? kTileBdC64 : kTileBdC128;
     return c;
   }
-  if (fp6_applies(a)) {
-    c.tile = a.cout % 128 ? kTileFp6C64 : kTileFp6C128;
-    return c;
-  }
   if (a.out.bits == 3) return c;
   if (stem_tile_applies(a)) c.tile = kTileStem;
-  else if (fp4_applies(a))
-    c.tile = a.cout % 128             ? kTileFp4C64
-             : fp4_pb4_pays(a, geo)    ? kTileFp4C128P4
-             : fp4_ksplit_pays(a, geo) ? kTileFp4C128K2
-                                       : kTileFp4C128;
   else if (tile_kernel_applies(a)) c.tile = a.cout % 128 ? kTileI8C64 : kTileI8C128;
   return c;
-}
-
-// The FP4 grouped kernel: one workgroup per tile, XCD-contiguous runs of the
-// chunked tile order (32 chunks where the packed input outweighs the filter,
-// as in launch_tile).
-template <int B, int CB, int PB, int WN, int WM, int KS = 1>
-hipError_t launch_fpx(const ConvArgs &a, const Geo &geo, hipStream_t s) {
-  constexpr int S = 4;
-  using C = f4::Cfg<CB, PB, WN, WM, B>;
-  const int npt = (int)((geo.M + C::TM - 1) / C::TM);
-  const int ncb = a.cout / C::TN;
-  const int64_t T = (int64_t)npt * ncb * a.in.groups;
-  if (T <= 0 || T > 0x3fffffff || geo.kb_total < 1) return hipErrorInvalidValue;
-  const int64_t wbytes = (int64_t)a.in.groups * a.cout * geo.kb_total * (C::SLAB / 32);
-  const int64_t xbytes = a.in.bytes;
-  const int nch = 7 * wbytes < (int64_t)(a.in.groups - 1) * xbytes ? std::min(32, npt) : 1;
-  if (KS == 2 && (geo.kb_total % 2 != 0 || geo.cpb % 2 != 0)) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)((T + 7) / 8 * 8)), block(C::NT * KS);
-  if constexpr (B == 3) {
-    if (a.res.data || a.proj.data) return hipErrorNotSupported;
-    if (!a.acc_dump)
-      hipLaunchKernelGGL((conv_fp6_kernel<CB, PB, WN, WM, false, S>), grid, block, 0, s, a, geo, npt, ncb, nch);
-    else
-      hipLaunchKernelGGL((conv_fp6_kernel<CB, PB, WN, WM, true, S>), grid, block, 0, s, a, geo, npt, ncb, nch);
-    return hipGetLastError();
-  }
-  // the fp32 requant where the plan found it exact for every channel
-  if (a.f32ep) {
-    if (!a.res.data && !a.acc_dump)
-      hipLaunchKernelGGL((conv_fp4_kernel<CB, PB, WN, WM, 0, false, S, true, KS>), grid, block, 0, s, a, geo, npt, ncb, nch);
-    else if (!a.acc_dump)
-      hipLaunchKernelGGL((conv_fp4_kernel<CB, PB, WN, WM, 2, false, S, true, KS>), grid, block, 0, s, a, geo, npt, ncb, nch);
-    else if (!a.res.data)
-      hipLaunchKernelGGL((conv_fp4_kernel<CB, PB, WN, WM, 0, true, S, true, KS>), grid, block, 0, s, a, geo, npt, ncb, nch);
-    else
-      hipLaunchKernelGGL((conv_fp4_kernel<CB, PB, WN, WM, 2, true, S, true, KS>), grid, block, 0, s, a, geo, npt, ncb, nch);
-    return hipGetLastError();
-  }
-  if (!a.res.data && !a.acc_dump)
-    hipLaunchKernelGGL((conv_fp4_kernel<CB, PB, WN, WM, 0, false, S, false, KS>), grid, block, 0, s, a, geo, npt, ncb, nch);
-  else if (!a.acc_dump)
-    hipLaunchKernelGGL((conv_fp4_kernel<CB, PB, WN, WM, 2, false, S, false, KS>), grid, block, 0, s, a, geo, npt, ncb, nch);
-  else if (!a.res.data)
-    hipLaunchKernelGGL((conv_fp4_kernel<CB, PB, WN, WM, 0, true, S, false, KS>), grid, block, 0, s, a, geo, npt, ncb, nch);
-  else
-    hipLaunchKernelGGL((conv_fp4_kernel<CB, PB, WN, WM, 2, true, S, false, KS>), grid, block, 0, s, a, geo, npt, ncb, nch);
-  return hipGetLastError();
 }
 
 // A tile kernel whose LDS is dynamic (lds bytes, above the static limit).
@@ -3287,7 +2522,8 @@ hipError_t launch_dyn(K kern, const ConvArgs &a, const Geo &geo, dim3 grid, dim3
   return hipGetLastError();
 }
 
-// The Eq. 4 decomposition: as launch_fpx, with the ring in dynamic LDS.
+// The Eq. 4 decomposition: one workgroup per tile in XCD-contiguous runs of
+// the chunked tile order, the ring in dynamic LDS.
 template <int M, int WN>
 hipError_t launch_bd(const ConvArgs &a, const Geo &geo, hipStream_t s) {
   using C = bd::Cfg<M, WN>;
@@ -3391,8 +2627,7 @@ const char *conv_kernel_label(const ConvArgs &a, int epi) {
   const Geo geo = make_geo(a);
   switch (conv_choice(a, geo, epi).tile) {
     case kTileStem: return "conv_tile_kernel[stem]";
-    case kTileFp4C64: case kTileFp4C128: case kTileFp4C128P4: case kTileFp4C128K2: return "conv_fp4_kernel";
-    case kTileFp6C64: case kTileFp6C128: return "conv_fp6_kernel";
+    case kTileFp: return a.in.bits == 2 ? "conv_fp4_kernel" : "conv_fp6_kernel";
     case kTileBdC64: case kTileBdC128: return "conv_bitdecomp_kernel";
     case kTileI8C64: case kTileI8C128: return "conv_tile_kernel[int8]";
     default: return is_stem(a) ? "conv_stem_kernel" : "conv_grouped_kernel";
@@ -3408,39 +2643,45 @@ hipError_t launch_conv_mfma(const ConvArgs &a_in, const uint8_t *wp, const int32
   geo.rq = (const RqConst *)thr;
   const ConvChoice c = conv_choice(a, geo, epi);
   if (c.cb == 0 && c.tile == kTileNone) return hipErrorNotSupported;  // no build for this layer
-  if (a.acc_dump && c.tile == kTileNone) epi = 1;  // only the general persistent build dumps
   hipError_t e = hipSuccess;
   const int nch = a.in.groups * a.cout;
-  Geo g4 = geo;  // FP4 (FP6) slabs and constants follow the int8 ones
-  g4.wp = wp + (size_t)nch * geo.kb_total * 64;
-  g4.rq = geo.rq + nch + 1;
-  constexpr int S4 = PALQ_TILE_STAGES;
-  switch (c.tile) {
-    case kTileStem: e = launch_tile<2, 2, 2, 2, true, PALQ_STEM_STAGES>(a, geo, s); break;
-    case kTileFp4C64: e = launch_fpx<2, 2, 2, 1, 4>(a, g4, s); break;
-    case kTileFp4C128: e = launch_fpx<2, 2, 2, 2, 2>(a, g4, s); break;
-    case kTileFp4C128P4: e = launch_fpx<2, 2, 4, 2, 2>(a, g4, s); break;
-    case kTileFp4C128K2: e = launch_fpx<2, 2, 2, 2, 2, 2>(a, g4, s); break;
-    case kTileFp6C64: e = launch_fpx<3, 2, 2, 1, 4>(a, g4, s); break;
-    case kTileBdC64: case kTileBdC128: {
-      Geo gb = g4;
-      gb.wp = wp + bd_offset(a);
-      e = a.in.bits == 4 ? launch_bd_m<4>(a, gb, c.tile, s)
-                         : a.in.bits == 6 ? launch_bd_m<6>(a, gb, c.tile, s) : launch_bd_m<8>(a, gb, c.tile, s);
-      break;
-    }
-    case kTileFp6C128: e = launch_fpx<3, 2, 2, 2, 2>(a, g4, s); break;
-    case kTileI8C64: e = launch_tile<2, 2, 1, 4>(a, geo, s); break;
-    case kTileI8C128: e = launch_tile<2, 2, 2, 4>(a, geo, s); break;
-    default: break;
-  }
-  if (e != hipSuccess) return e;
-  if (c.tile != kTileNone) {
-    if (epi == 0) return hipSuccess;
-    // epi unknown: the general partner, which runs only if the flag is set
+  if (conv_fp_applies(a)) {
+    // the general partner takes the packed filter and the int64 requant
+    geo.wp = nullptr;
+    geo.rq = nullptr;
     a.gated = 1;
-    if (c.cb == 0) return launch_conv_direct(a, s, (const int32_t *)(geo.rq + nch));
+    if (c.tile == kTileFp) {
+      geo.gate = conv_fp_flag(a, thr);
+      e = launch_conv_fp(a, wp, thr, epi == 0, s);
+      if (e != hipSuccess || epi == 0) return e;
+      if (c.cb == 0) return launch_conv_direct(a, s, geo.gate);
+    }
     epi = 1;
+  } else {
+    if (a.acc_dump && c.tile == kTileNone) epi = 1;  // only the general persistent build dumps
+    geo.gate = (const int32_t *)(geo.rq + nch);
+    switch (c.tile) {
+      case kTileStem: e = launch_tile<2, 2, 2, 2, true, PALQ_STEM_STAGES>(a, geo, s); break;
+      case kTileBdC64: case kTileBdC128: {
+        Geo gb = geo;
+        gb.wp = wp + bd_offset(a);
+        gb.rq = geo.rq + nch + 1;
+        e = a.in.bits == 4 ? launch_bd_m<4>(a, gb, c.tile, s)
+                           : a.in.bits == 6 ? launch_bd_m<6>(a, gb, c.tile, s) : launch_bd_m<8>(a, gb, c.tile, s);
+        break;
+      }
+      case kTileI8C64: e = launch_tile<2, 2, 1, 4>(a, geo, s); break;
+      case kTileI8C128: e = launch_tile<2, 2, 2, 4>(a, geo, s); break;
+      default: break;
+    }
+    if (e != hipSuccess) return e;
+    if (c.tile != kTileNone) {
+      if (epi == 0) return hipSuccess;
+      // epi unknown: the general partner, which runs only if the flag is set
+      a.gated = 1;
+      if (c.cb == 0) return launch_conv_direct(a, s, geo.gate);
+      epi = 1;
+    }
   }
   const int cb = c.cb, pb = 1;
   if (is_stem(a)) return cb == 2 ? launch_stem<2, 1>(a, geo, epi, s) : launch_stem<1, 1>(a, geo, epi, s);

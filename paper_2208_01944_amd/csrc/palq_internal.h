@@ -72,16 +72,16 @@ __host__ __device__ inline uint8_t *row_at(const ActView &v, int64_t r) {
 // least power of two >= d and m = ceil(2^(31 + k) / d) <= 2^32 - 1 (d >= 2),
 // n m / 2^(31 + k) exceeds n / d by less than n / 2^31 / d < 1 / d.
 struct FastDiv {
-  uint32_t d, m;
-  int32_t sh;  // k - 1; -1: d == 1
+  uint32_t d, m, add;  // d == 1: m = 0 and add all ones (no branch)
+  int32_t sh;          // k - 1
   static FastDiv of(uint32_t d) {
     int k = 0;
     while (((uint64_t)1 << k) < d) ++k;
-    if (d == 1) return {1u, 0u, -1};
-    return {d, (uint32_t)((((uint64_t)1 << (31 + k)) + d - 1) / d), k - 1};
+    if (d == 1) return {1u, 0u, 0xffffffffu, 0};
+    return {d, (uint32_t)((((uint64_t)1 << (31 + k)) + d - 1) / d), 0u, k - 1};
   }
   __host__ __device__ uint32_t div(uint32_t n) const {
-    return sh < 0 ? n : (uint32_t)(((uint64_t)n * m) >> 32) >> sh;
+    return ((uint32_t)(((uint64_t)n * m) >> 32) + (n & add)) >> sh;
   }
 };
 
@@ -106,7 +106,6 @@ struct ConvArgs {
   int32_t fp4;           // 1: 2-bit layers may run on the FP4 matrix cores (where exact)
   int32_t bitdecomp;     // 1: M-bit layers run as the Eq. 4 bit decomposition on FP4
   int32_t gated;         // set by the launcher: general partner of a tiled launch
-  int32_t f32ep;         // 1: the FP4 kernel's exact fp32 requant applies (conv_mfma_f32)
 };
 
 // Kernel launchers (return hipError_t of the launch).
@@ -136,14 +135,21 @@ bool conv_mfma_pads_input(const ConvArgs &a);
 // the stream has drained: 0 fast, 1 general, -1 unknown (copy failed).
 // Synchronous; for planning only.
 int conv_mfma_epilogue(const ConvArgs &a, const int32_t *thr);
-// For a layer on the FP4 kernel with the fast epilogue: whether every
-// channel's requant is exact in fp32 (written by launch_conv_prepare; reads
-// one flag word back, blocking).  Callers keep the answer in ConvArgs::f32ep.
-bool conv_mfma_f32(const ConvArgs &a, const int32_t *thr);
 // epi: the value above, or -1 when it is not known on the host: both builds
 // start and each checks on the device whether it applies (the other returns
 // at once); no host synchronisation either way.
 hipError_t launch_conv_mfma(const ConvArgs &a, const uint8_t *wp, const int32_t *thr, int epi, hipStream_t s);
+// The FP4 / FP6 kernels (k_conv_fp.hip): layers they take, the scratch they
+// need, their preparation (one launch), the device flag it leaves (non-zero:
+// some channel is outside the fp32 bounds and the general partner must run) and
+// the launch (checked: the flag is known to be clear, else the kernel reads it).
+bool conv_fp_applies(const ConvArgs &a);
+ConvPlan conv_fp_plan(const ConvArgs &a);
+const int32_t *conv_fp_flag(const ConvArgs &a, const int32_t *thr);
+hipError_t launch_conv_fp_prepare(const ConvArgs &a, uint8_t *wp, int32_t *thr, hipStream_t s);
+hipError_t launch_conv_fp(const ConvArgs &a, const uint8_t *wp, const int32_t *thr, bool checked, hipStream_t s);
+// The scratch size that palq_group_conv_noalloc's limit is documented for.
+size_t conv_noalloc_bytes(const ConvArgs &a);
 // The static per-GPU buffer of palq_group_conv_noalloc (PALQ_NOALLOC_SCRATCH_BYTES):
 // noalloc_scratch_init looks its address up on `device` (which must be the
 // current device) once per device; noalloc_scratch returns it (nullptr if
