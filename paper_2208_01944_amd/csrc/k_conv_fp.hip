@@ -107,8 +107,8 @@ __device__ __forceinline__ v16f mfma_fp(v8i a, v8i b, v16f c) {
 // ------------------------------------------------------------ prepare
 // One launch per layer.  Workgroup 0: the requant constants, in blocks of 64
 // channels [scale 64][bias 64][res_mult 64][unused 64] floats in accumulator
-// units (zero for padded channels), and the flag *bad (1: some channel is
-// outside the fp32 bounds).  The others: weight slabs, one lane operand (16 or
+// units (zero for padded channels), and two flags: bad[0], some channel is
+// outside the fp32 bounds; bad[1], some shift exceeds 21 (requant_fp4).  The others: weight slabs, one lane operand (16 or
 // 24 bytes) per thread, [G][coutp / 32][kb_total][SLAB]; E2M3 slabs hold bytes
 // 0-15 of every lane, then bytes 16-23.  Projection K-blocks of source group g
 // hold the projection filter of its destination group (g + s) mod G.
@@ -126,10 +126,10 @@ struct PrepArgs {
 template <int B>
 __global__ __launch_bounds__(512) void conv_fp_prep_kernel(PrepArgs a) {
   if (blockIdx.x == 0) {
-    __shared__ int any_bad;
-    if (threadIdx.x == 0) any_bad = 0;
+    __shared__ int any_bad, any_wide;
+    if (threadIdx.x == 0) any_bad = any_wide = 0;
     __syncthreads();
-    int bad = 0;
+    int bad = 0, wide = 0;
     for (int i = threadIdx.x; i < a.G * a.coutp; i += 512) {
       const int g = i / a.coutp, k = i - g * a.coutp;
       float sc = 0.0f, b = 0.0f, rm = 0.0f;
@@ -142,6 +142,7 @@ __global__ __launch_bounds__(512) void conv_fp_prep_kernel(PrepArgs a) {
             a.acc_bound + (bi < 0 ? -bi : bi) + (r < 0 ? -r : r) * a.res_max >= lim) {
           bad = 1;
         } else {
+          if (sh > 21) wide = 1;
           sc = ldexpf((float)m, FpT<B>::L - sh);
           b = ldexpf((float)bi, -FpT<B>::L);
           rm = ldexpf((float)r, -FpT<B>::L);
@@ -154,8 +155,12 @@ __global__ __launch_bounds__(512) void conv_fp_prep_kernel(PrepArgs a) {
       blk[192] = 0.0f;
     }
     if (bad) atomicOr(&any_bad, 1);
+    if (wide) atomicOr(&any_wide, 1);
     __syncthreads();
-    if (threadIdx.x == 0) *a.bad = any_bad;
+    if (threadIdx.x == 0) {
+      a.bad[0] = any_bad;
+      a.bad[1] = any_wide;
+    }
     return;
   }
   const int64_t t = (int64_t)(blockIdx.x - 1) * 512 + threadIdx.x;
@@ -207,7 +212,9 @@ struct FpArgs {
   const uint8_t *in, *wp, *res, *proj;
   uint8_t *out;
   const float *cst;
-  const int32_t *bad;  // set: the launch does nothing if *bad (its general partner runs)
+  const int32_t *bad;  // the prepare kernel's flags
+  int32_t fast;        // bad[1] is known to be clear
+  int32_t gated;       // the launch does nothing if bad[0] (its general partner runs)
   int32_t *dump;
   uint32_t in_bytes, w_bytes, res_bytes, proj_bytes, cst_bytes;
   int32_t in_pix, in_gs, res_pix, res_gs, proj_pix, proj_gs, out_pix, out_gs;  // bytes, < 2^30
@@ -308,6 +315,20 @@ __device__ __forceinline__ void set_round_down() {
   asm volatile("s_setreg_imm32_b32 hwreg(HW_REG_MODE, 0, 2), 2");
 }
 
+// The 2-bit requant of two channels at once, for shifts up to 21: with v = u M
+// 2^-sh, z = clamp((v + 2^-22) / 4) to [0, 1] is one fma, and the conversion to
+// FP4 (rounding to nearest even whatever the mode, scale 1/2) gives the nibble
+// RNE(4 z), 4 for z = 1.  The sum v + 2^-22 moves every tie v = k + 1/2 (k <=
+// 2) above it and is representable there; values below it are at most k + 1/2
+// - 2^-21, stay at most k + 1/2 - 2^-22 and round to k.  So the nibble is
+// floor(v + 1/2) clamped to [0, 4], and fp4_codes takes 4 to 3.
+__device__ __forceinline__ float requant_z(float u, float sc, float o) {
+  float z;
+  asm("v_fma_f32 %0, %1, %2, %3 clamp" : "=v"(z) : "v"(u), "v"(sc), "v"(o));
+  return z;
+}
+__device__ __forceinline__ uint32_t fp4_codes(uint32_t w) { return w - ((w >> 2) & 0x11111111u); }
+
 // Four shortcut codes of channels 8 qi + 4 half .. + 3 of a 32-channel block
 // held in c (B = 2: two words; 3: the chunk; 4: four words).
 template <int B>
@@ -374,7 +395,7 @@ struct FpCfg {
   static constexpr int RED = KS == 2 ? WN * WM * 2 * PB * 4096 : 0;
 };
 
-template <int B, int PB, int WN, int WM, int MODE, bool DUMP, int KPS, int KS, int S>
+template <int B, int PB, int WN, int WM, int MODE, bool DUMP, int KPS, int KS, int S, bool FAST>
 __device__ __forceinline__ void conv_fp_tile(const FpArgs &a) {
   using C = FpCfg<B, PB, WN, WM, KPS, KS>;
   using T = FpT<B>;
@@ -385,7 +406,7 @@ __device__ __forceinline__ void conv_fp_tile(const FpArgs &a) {
   constexpr int RSB = MODE == 1 ? C::RP * 16 : 0;
   __shared__ __attribute__((aligned(1024))) uint8_t lds[RING + CST + RSB];
 
-  if (a.bad && *a.bad != 0) return;
+  if (a.gated && a.bad[0] != 0) return;
   TileId id;
   if (!tile_of(a, id)) return;
   const int tid = (int)threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
@@ -576,13 +597,74 @@ __device__ __forceinline__ void conv_fp_tile(const FpArgs &a) {
                 (int)((acc[cb][pb][r] - cst[64 + c]) * (float)(1 << T::L));
         }
   }
+  constexpr uint32_t qmax = (1u << B) - 1u;
+  uint32_t w2[CB][PB];
+  if constexpr (FAST) {
+    // 2-bit codes, 2.1 VALU instructions a value instead of 4.3 (and 2 instead
+    // of 3 for a shortcut): both ways between codes and floats by the FP4
+    // conversions, even and odd codes in nibbles of their own
+    const float o = 0x1p-24f;
+    const uint32_t sel = half ? 0x07030602u : 0x05010400u;
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) {
+      uint32_t E[PB], O[PB], re[PB][2], ro[PB][2];
+#pragma unroll
+      for (int pb = 0; pb < PB; ++pb) {
+        E[pb] = O[pb] = 0;
+        if constexpr (MODE == 1) {
+          const v2i v = *(const v2i *)(lds + RING + CST + (wn * TM + wm * PB * 32 + pb * 32 + l32) * 16 + 8 * cb);
+#pragma unroll
+          for (int j = 0; j < 2; ++j) {
+            const uint32_t x = (uint32_t)v[j] >> (8 * half);
+            re[pb][j] = x & 0x33333333u;
+            ro[pb][j] = (x >> 2) & 0x33333333u;
+          }
+        }
+      }
+#define PALQ_QUAD(QI)                                                                                             \
+  {                                                                                                               \
+    __builtin_amdgcn_sched_barrier(0);                                                                            \
+    const int c0 = cb * 32 + 8 * QI + 4 * half;                                                                   \
+    const v4f sc = *(const v4f *)(cst + c0) * 0.25f;                                                              \
+    v4f rm = {0.0f, 0.0f, 0.0f, 0.0f};                                                                            \
+    if constexpr (MODE == 1) rm = *(const v4f *)(cst + 128 + c0);                                                 \
+    _Pragma("unroll") for (int pb = 0; pb < PB; ++pb) {                                                           \
+      float u[4];                                                                                                 \
+      _Pragma("unroll") for (int e = 0; e < 4; ++e) u[e] = acc[cb][pb][4 * QI + e];                               \
+      if constexpr (MODE == 1) {                                                                                  \
+        const v2f c02 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(re[pb][QI >> 1], 2.0f, 2 * (QI & 1));            \
+        const v2f c13 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(ro[pb][QI >> 1], 2.0f, 2 * (QI & 1));            \
+        u[0] = __builtin_fmaf(rm[0], c02[0], u[0]);                                                               \
+        u[2] = __builtin_fmaf(rm[2], c02[1], u[2]);                                                               \
+        u[1] = __builtin_fmaf(rm[1], c13[0], u[1]);                                                               \
+        u[3] = __builtin_fmaf(rm[3], c13[1], u[3]);                                                               \
+      }                                                                                                           \
+      float z[4];                                                                                                 \
+      _Pragma("unroll") for (int e = 0; e < 4; ++e) z[e] = requant_z(u[e], sc[e], o);                             \
+      E[pb] = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(E[pb], z[0], z[2], 0.5f, QI);                              \
+      O[pb] = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(O[pb], z[1], z[3], 0.5f, QI);                              \
+    }                                                                                                             \
+  }
+      PALQ_QUAD(0)
+      PALQ_QUAD(1)
+      PALQ_QUAD(2)
+      PALQ_QUAD(3)
+#undef PALQ_QUAD
+#pragma unroll
+      for (int pb = 0; pb < PB; ++pb) {
+        // byte qi: the lane's quad qi; both lane halves' words meet in every
+        // lane, and each lane takes the bytes of its 16 channels in order
+        const uint32_t t = fp4_codes(E[pb]) | (fp4_codes(O[pb]) << 2);
+        const auto r = __builtin_amdgcn_permlane32_swap(t, t, false, false);
+        w2[cb][pb] = __builtin_amdgcn_perm(r[1], r[0], sel);
+      }
+    }
+  } else {
   set_round_down();
 #pragma unroll
   for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
     for (int pb = 0; pb < PB; ++pb) asm volatile("" : "+v"(acc[cb][pb]));
-  constexpr uint32_t qmax = (1u << B) - 1u;
-  uint32_t w2[CB][PB];
 #pragma unroll
   for (int cb = 0; cb < CB; ++cb) {
     uint32_t qv[PB][4], hv[PB][4], rc[PB][4];
@@ -662,6 +744,7 @@ __device__ __forceinline__ void conv_fp_tile(const FpArgs &a) {
       }
     }
   }
+  }
   if constexpr (B == 2) {
     // pixel blocks 2 i and 2 i + 1: lanes of half 0 take block 2 i, lanes of
     // half 1 block 2 i + 1 and gather its 64 channels, stored at once
@@ -699,7 +782,7 @@ __device__ __forceinline__ void conv_fp_split(const FpArgs &a) {
   static_assert(Q % NW == 0 || NW % Q == 0, "whole quads per wave");
   __shared__ v4f red[NW * Q * 64];
   __shared__ uint32_t cw[32 * PB * 9];  // packed quads of a pixel's 32 channels (9: no bank conflicts)
-  if (a.bad && *a.bad != 0) return;
+  if (a.gated && a.bad[0] != 0) return;
   TileId id;
   if (!tile_of(a, id)) return;
   const int tid = (int)threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
@@ -848,9 +931,9 @@ __device__ __forceinline__ void conv_fp_split(const FpArgs &a) {
 
 // Entry points by matrix-core format.
 #define PALQ_FP_TILE(NAME)                                                                            \
-  template <int B, int PB, int WN, int WM, int MODE, bool DUMP, int KPS, int KS, int S>               \
+  template <int B, int PB, int WN, int WM, int MODE, bool DUMP, int KPS, int KS, int S, bool FAST>    \
   __global__ __launch_bounds__(WN *WM * 64 * KS, PB == 4 ? 2 : B == 2 ? 4 : 3) void NAME(FpArgs a) {  \
-    conv_fp_tile<B, PB, WN, WM, MODE, DUMP, KPS, KS, S>(a);                                           \
+    conv_fp_tile<B, PB, WN, WM, MODE, DUMP, KPS, KS, S, FAST>(a);                                     \
   }
 #define PALQ_FP_SPLIT(NAME)                                                     \
   template <int B, int PB, int NW, int MODE, bool DUMP>                         \
@@ -878,11 +961,13 @@ int fp_kb(const ConvArgs &a) { return fp_km(a) + (a.proj.data ? cpb_of(a.proj.cp
 int fp_coutp(const ConvArgs &a) { return (a.cout + 63) / 64 * 64; }
 int64_t fp_slab(int bits) { return bits == 2 ? 1024 : 1536; }
 
-FpArgs fp_args(const ConvArgs &a, const uint8_t *wp, const int32_t *thr, const int32_t *bad) {
+FpArgs fp_args(const ConvArgs &a, const uint8_t *wp, const int32_t *thr, bool checked) {
   FpArgs f{};
   f.in = a.in.data; f.wp = wp; f.res = a.res.data; f.proj = a.proj.data; f.out = a.out.data;
   f.cst = (const float *)thr;
-  f.bad = bad;
+  f.bad = conv_fp_flag(a, thr);
+  f.gated = checked ? 0 : 1;
+  f.fast = checked && a.fp_fast;
   f.dump = a.acc_dump;
   f.cout = a.cout;
   f.coutp = fp_coutp(a);
@@ -916,7 +1001,8 @@ FpArgs fp_args(const ConvArgs &a, const uint8_t *wp, const int32_t *thr, const i
 
 // Tiles of tn channels x tm pixels; 32 pixel chunks where the packed input
 // outweighs the filter (every XCD then reads all of the filter: about 7 W
-// extra against (G - 1) X saved), else one.  Workgroups: a multiple of 8.
+// extra against (G - 1) X saved), else one.  Returns the workgroups, a multiple
+// of 8.
 unsigned fp_tiles(FpArgs &f, int tn, int tm, int64_t in_bytes) {
   const int npt = (f.M + tm - 1) / tm;
   f.ncb = (f.cout + tn - 1) / tn;
@@ -955,10 +1041,12 @@ int cu_count() {
 template <int B, int PB, int WN, int WM, int MODE, bool DUMP, int KPS, int KS, int S>
 hipError_t launch_tile_mode(const FpArgs &f, unsigned grid, hipStream_t s) {
   const dim3 block(WN * WM * 64 * KS);
-  if constexpr (B == 2)
-    hipLaunchKernelGGL((conv_fp4_kernel<B, PB, WN, WM, MODE, DUMP, KPS, KS, S>), dim3(grid), block, 0, s, f);
+  if constexpr (B != 2)
+    hipLaunchKernelGGL((conv_fp6_kernel<B, PB, WN, WM, MODE, DUMP, KPS, KS, S, false>), dim3(grid), block, 0, s, f);
+  else if (f.fast)
+    hipLaunchKernelGGL((conv_fp4_kernel<B, PB, WN, WM, MODE, DUMP, KPS, KS, S, true>), dim3(grid), block, 0, s, f);
   else
-    hipLaunchKernelGGL((conv_fp6_kernel<B, PB, WN, WM, MODE, DUMP, KPS, KS, S>), dim3(grid), block, 0, s, f);
+    hipLaunchKernelGGL((conv_fp4_kernel<B, PB, WN, WM, MODE, DUMP, KPS, KS, S, false>), dim3(grid), block, 0, s, f);
   return hipGetLastError();
 }
 template <int B, int PB, int WN, int WM, bool DUMP, int KPS, int KS, int S>
@@ -1045,6 +1133,12 @@ const int32_t *conv_fp_flag(const ConvArgs &a, const int32_t *thr) {
   return thr + (int64_t)a.in.groups * fp_coutp(a) * 4;
 }
 
+bool conv_fp_fast(const ConvArgs &a, const int32_t *thr) {
+  int32_t wide = 1;
+  return conv_fp_applies(a) && hipMemcpy(&wide, conv_fp_flag(a, thr) + 1, sizeof(wide), hipMemcpyDeviceToHost) == hipSuccess &&
+         wide == 0;
+}
+
 hipError_t launch_conv_fp_prepare(const ConvArgs &a, uint8_t *wp, int32_t *thr, hipStream_t s) {
   PrepArgs p{};
   p.w = a.w; p.pw = a.proj_w;
@@ -1071,7 +1165,7 @@ hipError_t launch_conv_fp_prepare(const ConvArgs &a, uint8_t *wp, int32_t *thr, 
 
 hipError_t launch_conv_fp(const ConvArgs &a, const uint8_t *wp, const int32_t *thr, bool checked, hipStream_t s) {
   if ((int64_t)a.out.n * a.ho * a.wo == 0) return hipSuccess;
-  const FpArgs f = fp_args(a, wp, thr, checked ? nullptr : conv_fp_flag(a, thr));
+  const FpArgs f = fp_args(a, wp, thr, checked);
   if (a.in.bits == 2) return launch_fp<2>(f, a.in.bytes, s);
   if (a.in.bits == 3) return launch_fp<3>(f, a.in.bytes, s);
   return launch_fp<4>(f, a.in.bytes, s);

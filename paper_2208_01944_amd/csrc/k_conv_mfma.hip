@@ -1526,11 +1526,11 @@ __device__ __forceinline__ int row_of(const RowIt &it, int ho2) {
 
 // Stem weights by filter row: [cout / 32][KH][half][ch][16 B], lane (half,
 // ch) of K-step r holding taps 4 half .. + 3 of row r for channel ch, the
-// input's padding byte and taps past kw masked to zero.  One thread per
-// 16-byte lane operand.
+// input's padding byte and taps past kw masked to zero; channels past cout
+// (up to the next 128) zero.  One thread per 16-byte lane operand.
 __global__ void prepack_stem_rows_kernel(ConvArgs a, uint8_t *wp) {
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= (int64_t)a.cout * sp::KH * 2) return;
+  if (t >= (int64_t)((a.cout + 127) / 128 * 128) * sp::KH * 2) return;
   const int lane = (int)(t & 63), r = (int)((t >> 6) % sp::KH);
   const int k = (int)(t / (64 * sp::KH)) * 32 + (lane & 31), h = lane >> 5;
   const uint32_t *wr = (const uint32_t *)(a.w + ((int64_t)k * a.kh + r) * a.kw * 4);
@@ -1539,25 +1539,55 @@ __global__ void prepack_stem_rows_kernel(ConvArgs a, uint8_t *wp) {
 #pragma unroll
   for (int d = 0; d < 4; ++d) {
     const int kx = 4 * h + d;
-    o[d] = kx < a.kw ? (wr[kx] & cmask) : 0u;
+    o[d] = k < a.cout && kx < a.kw ? (wr[kx] & cmask) : 0u;
   }
   *(uint4 *)(wp + t * 16) = make_uint4(o[0], o[1], o[2], o[3]);
 }
 
+// The fp32 requant constants of a stem (SpConst per channel): with u = t + bias
+// exact in fp32 (|t| + |bias| < 2^24) and rounding towards minus infinity,
+// floor(fma(u, M 2^-sh, 1/2)) is the definition for every shift (M < 2^24).
+// flag: 1 when every channel meets the bounds.
+struct SpConst {
+  float sc;
+  int32_t bias;
+};
+__global__ void stem_prep_f32_kernel(const int32_t *mult, const int32_t *shift, const int32_t *bias, int nch,
+                                     int64_t acc_bound, SpConst *k, int32_t *flag) {
+  __shared__ int any_bad;
+  if (threadIdx.x == 0) any_bad = 0;
+  __syncthreads();
+  int bad = 0;
+  for (int c = threadIdx.x; c < nch; c += blockDim.x) {
+    const int64_t m = mult[c], b = bias ? bias[c] : 0, lim = (int64_t)1 << 24;
+    const int sh = shift[c];
+    const bool ok = sh >= 1 && sh <= 62 && m >= 0 && m < lim && acc_bound + (b < 0 ? -b : b) < lim;
+    if (!ok) bad = 1;
+    k[c] = ok ? SpConst{ldexpf((float)m, -sh), (int32_t)b} : SpConst{0.0f, 0};
+  }
+  if (bad) atomicOr(&any_bad, 1);
+  __syncthreads();
+  if (threadIdx.x == 0) *flag = any_bad ? 0 : 1;
+}
+
 // Runs hold at most ho2 units (the launcher's grid), so a run meets at most
 // two channel blocks, cbb0 and cbb0 + 1 (mod ncb): their requant constants
-// sit in LDS.
+// sit in LDS.  BO: output bits.  F32: the requant of SpConst instead of the
+// fp64 one, whose three quarter-rate instructions a value were a quarter of the
+// kernel's issue time (ResNet-18 G = 4, batch 64: SPBEFORE -> SPAFTER us).
+template <int BO, bool F32>
 __global__ __launch_bounds__(sp::NT, 2) void stem_pool_kernel(ConvArgs a, Geo geo, ActView po, const uint8_t *wrow,
-                                                              int units) {
+                                                              const SpConst *spc, int units) {
   using namespace sp;
+  using RqT = typename std::conditional<F32, SpConst, RqConst>::type;
   __shared__ __attribute__((aligned(1024))) uint8_t lds[kSets * SET];
-  __shared__ RqConst rq_area[256];
-  if (needs_general(a, geo, 0)) return;
+  __shared__ RqT rq_area[256];
+  if (int64_flag(a, geo)) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int l32 = lane & 31, half = lane >> 5;
   const int wn = wave >> 1, wm = wave & 1;
   const int ho = a.ho, wo = a.wo, ho2 = po.h, wo2 = po.w;
-  const int ncb = a.cout / 128;
+  const int ncb = (a.cout + 127) / 128;
   // balanced runs of units per XCD (as the tiled kernel's tiles)
   const int P = (int)gridDim.x >> 3;
   const int x = (int)(blockIdx.x & 7), y = (int)(blockIdx.x >> 3);
@@ -1568,7 +1598,11 @@ __global__ __launch_bounds__(sp::NT, 2) void stem_pool_kernel(ConvArgs a, Geo ge
   const int u_end = u_begin + base + (y < ex ? 1 : 0);
   if (u_begin >= u_end) return;  // no barrier yet
   const int cbb0 = (u_begin / ho2) % ncb;
-  for (int c = tid; c < 256; c += NT) rq_area[c] = geo.rq[(c < 128 ? cbb0 : (cbb0 + 1) % ncb) * 128 + (c & 127)];
+  for (int c = tid; c < 256; c += NT) {
+    const int ch = min((c < 128 ? cbb0 : (cbb0 + 1) % ncb) * 128 + (c & 127), a.cout - 1);
+    if constexpr (F32) rq_area[c] = spc[ch];
+    else rq_area[c] = geo.rq[ch];
+  }
   __syncthreads();
   const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)lds;
   typedef __attribute__((address_space(3))) void *lds_ptr;
@@ -1617,9 +1651,9 @@ __global__ __launch_bounds__(sp::NT, 2) void stem_pool_kernel(ConvArgs a, Geo ge
   // other lane half (column -1 for wm = 0, column 127 for wm = 1)
   const bool half_edge = wm ? l32 == 31 : l32 == 0;
   // pooled column px = 32 wm + l; its byte offset in a pooled row plus this
-  // lane's word of the wave's channels (word 2 (4 cbb + 2 wn + cb) + half)
+  // lane's first word of the wave's channels (BO words per 32 channels)
   const int px = 32 * wm + l32;
-  int out_lane = px * (int)po.pixel + (wn * 4 + half) * 4;
+  int out_lane = px * (int)po.pixel + (wn * 2 * BO + half * (BO == 4 ? 2 : 1)) * 4;
   asm volatile("" : "+v"(out_lane));  // kept as one 32-bit register
   auto finish_row = [&]() __attribute__((always_inline)) {
     const int k = c_it.u % ho2;
@@ -1676,10 +1710,12 @@ __global__ __launch_bounds__(sp::NT, 2) void stem_pool_kernel(ConvArgs a, Geo ge
     if (c_it.phase == 0 || (c_it.phase == 1 && 2 * k + 1 < ho)) return;
     // requant the pooled row and store it: channel 128 cbb + 64 wn + 32 cb + 8 qi + 4 half + e
     const int orow = ((n * ho2 + k) * wo2) * (int)po.pixel;
-    const RqConst *rq = rq_area + (cbb == cbb0 ? 0 : 128) + wn * 64;
+    const RqT *rq = rq_area + (cbb == cbb0 ? 0 : 128) + wn * 64;
+    const bool in_row = px < wo2 && cbb * 128 + wn * 64 < a.cout;
     // the constants of quad j + 1 are read while quad j is requantised (two
     // quads' constants in registers, which the dead accumulators free)
-    RqConst qc[2][4];
+    RqT qc[2][4];
+    if constexpr (F32) asm volatile("s_setreg_imm32_b32 hwreg(HW_REG_MODE, 0, 2), 2");  // no other fp32 in the kernel
     auto load_quad = [&](int j) __attribute__((always_inline)) {
       const int cq = (j >> 2) * 32 + 8 * (j & 3) + 4 * half;
 #pragma unroll
@@ -1688,7 +1724,7 @@ __global__ __launch_bounds__(sp::NT, 2) void stem_pool_kernel(ConvArgs a, Geo ge
     load_quad(0);
 #pragma unroll
     for (int cb = 0; cb < 2; ++cb) {
-      uint32_t qv[4];
+      uint32_t qv[4], hv[4];
 #pragma unroll
       for (int qi = 0; qi < 4; ++qi) {
         const int j = 4 * cb + qi;
@@ -1696,21 +1732,48 @@ __global__ __launch_bounds__(sp::NT, 2) void stem_pool_kernel(ConvArgs a, Geo ge
         if (j < 7) load_quad(j + 1);
         __builtin_amdgcn_sched_barrier(0);
         uint32_t qword = 0;
+        hv[qi] = 0;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const double d = __builtin_fma((double)st[cb][4 * qi + e], qc[j & 1][e].s, qc[j & 1][e].o);
           uint32_t q;
-          asm("v_cvt_u32_f64 %0, %1" : "=v"(q) : "v"(d));
-          qword |= min(q, 3u) << (2 * e);
+          if constexpr (F32) {
+            int32_t u = st[cb][4 * qi + e] + qc[j & 1][e].bias;
+            asm volatile("" : "+v"(u));  // after the rounding mode is set
+            const float y = __builtin_fmaf((float)u, qc[j & 1][e].sc, 0.5f);
+            asm("v_cvt_u32_f32 %0, %1" : "=v"(q) : "v"(y));
+          } else {
+            const double d = __builtin_fma((double)st[cb][4 * qi + e], qc[j & 1][e].s, qc[j & 1][e].o);
+            asm("v_cvt_u32_f64 %0, %1" : "=v"(q) : "v"(d));
+          }
+          q = min(q, (1u << BO) - 1u);
+          if constexpr (BO == 3) {
+            qword |= (q & 3u) << (2 * e);
+            hv[qi] |= (q >> 2) << (2 * e);
+          } else {
+            qword |= q << (BO * e);
+          }
         }
         qv[qi] = qword;
       }
       const auto p0 = __builtin_amdgcn_permlane32_swap(qv[0], qv[2], false, false);  // as in epilogue_fast_bo
       const auto p1 = __builtin_amdgcn_permlane32_swap(qv[1], qv[3], false, false);
-      const uint32_t Q[4] = {p0[0], p0[1], p1[0], p1[1]};
-      if (px < wo2)
-        __builtin_amdgcn_raw_buffer_store_b32(Q[0] | (Q[1] << 8) | (Q[2] << 16) | (Q[3] << 24), rout,
-                                              out_lane + cbb * 32 + cb * 8, orow, 0);
+      const int off = out_lane + cbb * 16 * BO + cb * 4 * BO;
+      if constexpr (BO == 4) {
+        if (in_row)
+          __builtin_amdgcn_raw_buffer_store_b64(v2i{(int)(p0[0] | (p0[1] << 16)), (int)(p1[0] | (p1[1] << 16))}, rout,
+                                                off, orow, 0);
+      } else {
+        if (in_row)
+          __builtin_amdgcn_raw_buffer_store_b32(p0[0] | (p0[1] << 8) | (p1[0] << 16) | (p1[1] << 24), rout, off, orow,
+                                                0);
+        if constexpr (BO == 3) {
+          uint32_t hp = 0;
+#pragma unroll
+          for (int qi = 0; qi < 4; ++qi) hp |= hv[qi] << (16 * (qi & 1) + 8 * half + (qi >> 1));
+          const auto hs = __builtin_amdgcn_permlane32_swap(hp, hp, false, false);
+          if (in_row && half == 0) __builtin_amdgcn_raw_buffer_store_b32(hs[0] | hs[1], rout, off + 8, orow, 0);
+        }
+      }
     }
     if (c_it.phase == 2) {
 #pragma unroll
@@ -2273,6 +2336,7 @@ bool tile_kernel_applies(const ConvArgs &a);
 bool stem_tile_applies(const ConvArgs &a);
 bool stem_rows(const ConvArgs &a);
 size_t stem_rows_offset(const ConvArgs &a);
+size_t stem_rows_bytes(const ConvArgs &a);
 
 // The int8 kernels: whole 32-channel blocks and (past the stem) 64-code
 // K-blocks, int8 products of one width.
@@ -2307,7 +2371,7 @@ ConvPlan conv_mfma_plan(const ConvArgs &a) {
   p.w_bytes = (size_t)a.in.groups * a.cout * geo.kb_total * 64;
   if (!is_stem(a) && a.in.bits >= 6) p.w_bytes += (size_t)a.in.groups * a.cout * 4;  // Geo::acc0
   p.thr_bytes = (size_t)a.in.groups * a.cout * sizeof(RqConst) + 16;  // + int64-path flag
-  if (stem_rows(a)) p.w_bytes += (size_t)a.cout * sp::KH * 32;  // the filter-row copy
+  if (stem_rows(a)) p.w_bytes += stem_rows_bytes(a) + (size_t)a.cout * sizeof(SpConst) + 16;  // filter rows, constants, flag
   if (bd_applies(a)) {  // the decomposition's chunk slabs and FP4-scaled constants
     p.w_bytes = bd_offset(a) + (size_t)a.in.groups * a.cout * geo.kb_total * (a.in.bits / 2) * 32;
     p.thr_bytes *= 2;
@@ -2344,9 +2408,12 @@ hipError_t launch_conv_prepare(const ConvArgs &a, uint8_t *wp, int32_t *thr, hip
   if (is_stem(a)) {
     hipLaunchKernelGGL((prepack_kernel<8, true>), dim3(grid), dim3(256), 0, s, a, geo, wp);
     if (stem_rows(a)) {
-      const int64_t pieces = (int64_t)a.cout * sp::KH * 2;
-      hipLaunchKernelGGL(prepack_stem_rows_kernel, dim3((unsigned)((pieces + 255) / 256)), dim3(256), 0, s, a,
-                         wp + stem_rows_offset(a));
+      const int64_t pieces = (int64_t)stem_rows_bytes(a) / 16;
+      uint8_t *rows = wp + stem_rows_offset(a);
+      hipLaunchKernelGGL(prepack_stem_rows_kernel, dim3((unsigned)((pieces + 255) / 256)), dim3(256), 0, s, a, rows);
+      SpConst *k = (SpConst *)(rows + stem_rows_bytes(a));
+      hipLaunchKernelGGL(stem_prep_f32_kernel, dim3(1), dim3(256), 0, s, a.mult, a.shift, a.bias, a.cout,
+                         acc_bound_of(a), k, (int32_t *)(k + a.cout));
     }
   } else {
     switch (a.in.bits) {
@@ -2472,12 +2539,17 @@ bool stem_tile_applies(const ConvArgs &a) {
          (int64_t)a.in.groups * a.cout * make_geo(a).kb_total * 64 < ((int64_t)1 << 30);
 }
 
-// Stems whose weights are also prepacked by filter row (prepack_stem_rows_kernel,
-// after the K-block slabs): one input group, 7 filter rows of at most 8 taps,
-// stride 2.
+// Stems whose weights are also prepacked by filter row, for the fused max pool
+// (prepack_stem_rows_kernel, after the K-block slabs, then the fp32 requant
+// constants and their flag): one input group, an explicit border, 7 filter rows
+// of at most 8 taps, stride 2, whole 64-channel halves of the kernel's
+// 128-channel blocks and 2-, 3- or 4-bit outputs.
 bool stem_rows(const ConvArgs &a) {
-  return stem_tile_applies(a) && a.in.groups == 1 && a.kh == sp::KH && a.kw <= 8 && a.stride == 2;
+  return is_stem(a) && a.pad == 0 && a.in.groups == 1 && a.cout % 64 == 0 && !a.res.data && !a.acc_dump &&
+         (a.out.bits == 2 || a.out.bits == 3 || a.out.bits == 4) && a.kh == sp::KH && a.stride == 2 &&
+         (int64_t)a.cout * make_geo(a).kb_total * 64 < ((int64_t)1 << 30);
 }
+size_t stem_rows_bytes(const ConvArgs &a) { return (size_t)((a.cout + 127) / 128 * 128) * sp::KH * 32; }
 size_t stem_rows_offset(const ConvArgs &a) { return (size_t)a.in.groups * a.cout * make_geo(a).kb_total * 64; }
 
 // Tiled-kernel builds: the 8-bit stem; 2-bit layers on int8 with 64- or
@@ -2595,32 +2667,56 @@ bool stem_pool_applies(const ConvArgs &a, const ActView &po, int k, int stride, 
   if (!stem_rows(a) || a.wo < 1 || a.ho < 1) return false;
   if (k != 3 || stride != 2 || pad != 1) return false;
   if (po.n != a.out.n || po.h != (a.ho + 1) / 2 || po.w != (a.wo + 1) / 2 || po.groups != a.out.groups ||
-      po.cpg != a.out.cpg || po.bits != 2 || po.pixel != a.out.pixel || po.row != a.out.row ||
+      po.cpg != a.out.cpg || po.bits != a.out.bits || po.pixel != a.out.pixel || po.row != a.out.row ||
       po.gstride != po.row)  // the store offsets take a pixel's groups as adjacent rows
     return false;
   const int64_t in_bytes = a.in.bytes;
   const int64_t out_bytes = po.bytes;
-  const int64_t units = (int64_t)a.out.n * (a.cout / 128) * po.h;
+  const int64_t units = (int64_t)a.out.n * ((a.cout + 127) / 128) * po.h;
   return (int64_t)a.in.w * a.in.pixel <= sp::RB && in_bytes < 0x7fff0000 && out_bytes < 0x7fff0000 &&
          units < 0x7fffffff;
 }
 
-hipError_t launch_stem_pool(const ConvArgs &a, const uint8_t *wp, const int32_t *thr, const ActView &po,
+template <int BO, bool F32>
+static hipError_t launch_stem_pool_t(const ConvArgs &a, const Geo &geo, const ActView &po, const uint8_t *wrow,
+                                     hipStream_t s) {
+  const int units = a.out.n * ((a.cout + 127) / 128) * po.h;
+  const int slots = tile_slots((const void *)stem_pool_kernel<BO, F32>, sp::NT);
+  // P workgroups per XCD: all resident slots, no more than the XCD's units,
+  // and runs of at most ho2 units (two channel blocks' constants)
+  const int64_t Tx = (units + 7) / 8;
+  int64_t P = std::max<int64_t>(1, std::min<int64_t>(slots / 8, Tx));
+  if ((Tx + P - 1) / P > po.h) P = (Tx + po.h - 1) / po.h;
+  hipLaunchKernelGGL((stem_pool_kernel<BO, F32>), dim3((unsigned)(8 * P)), dim3(sp::NT), 0, s, a, geo, po, wrow,
+                     (const SpConst *)(wrow + stem_rows_bytes(a)), units);
+  return hipGetLastError();
+}
+
+int stem_pool_requant(const ConvArgs &a, const uint8_t *wp, const int32_t *thr) {
+  int32_t wide = 1, f32 = 0;
+  const SpConst *k = (const SpConst *)(wp + stem_rows_offset(a) + stem_rows_bytes(a));
+  if (hipMemcpy(&wide, (const RqConst *)thr + a.cout, sizeof(wide), hipMemcpyDeviceToHost) != hipSuccess ||
+      hipMemcpy(&f32, k + a.cout, sizeof(f32), hipMemcpyDeviceToHost) != hipSuccess || wide != 0)
+    return 0;
+  return f32 ? 2 : 1;
+}
+
+hipError_t launch_stem_pool(const ConvArgs &a, const uint8_t *wp, const int32_t *thr, const ActView &po, int requant,
                             hipStream_t s) {
   Geo geo = make_geo(a);
   if (geo.M == 0) return hipSuccess;
   geo.wp = wp;
   geo.rq = (const RqConst *)thr;
   const uint8_t *wrow = wp + stem_rows_offset(a);
-  const int units = a.out.n * (a.cout / 128) * po.h;
-  const int slots = tile_slots((const void *)stem_pool_kernel, sp::NT);
-  // P workgroups per XCD: all resident slots, no more than the XCD's units,
-  // and runs of at most ho2 units (two channel blocks' constants)
-  const int64_t Tx = (units + 7) / 8;
-  int64_t P = std::max<int64_t>(1, std::min<int64_t>(slots / 8, Tx));
-  if ((Tx + P - 1) / P > po.h) P = (Tx + po.h - 1) / po.h;
-  hipLaunchKernelGGL(stem_pool_kernel, dim3((unsigned)(8 * P)), dim3(sp::NT), 0, s, a, geo, po, wrow, units);
-  return hipGetLastError();
+  switch (2 * a.out.bits + (requant == 2 ? 1 : 0)) {
+    case 4: return launch_stem_pool_t<2, false>(a, geo, po, wrow, s);
+    case 5: return launch_stem_pool_t<2, true>(a, geo, po, wrow, s);
+    case 6: return launch_stem_pool_t<3, false>(a, geo, po, wrow, s);
+    case 7: return launch_stem_pool_t<3, true>(a, geo, po, wrow, s);
+    case 8: return launch_stem_pool_t<4, false>(a, geo, po, wrow, s);
+    case 9: return launch_stem_pool_t<4, true>(a, geo, po, wrow, s);
+  }
+  return hipErrorNotSupported;
 }
 
 const char *conv_kernel_label(const ConvArgs &a, int epi) {

@@ -600,86 +600,105 @@ __global__ void pad_rows_kernel(ActView in, int pad, ActView out, int rows) {
 }
 
 // ------------------------------------------------------------ global sum
-// 2-bit codes, at most 85 pixels (85 x 3 < 256), 16 | cpg: one thread per
-// (image, group, word of 16 codes).  The word's codes k, k+4, k+8, k+12 sit
-// in the four bytes of (w >> 2k) & 0x03030303, so four byte-lane
-// accumulators sum all 16 codes without carries.
-__global__ void avgsum2_kernel(ActView in, int32_t *out) {
-  const int wpr = in.cpg / 16;  // words per group row
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= (int64_t)in.n * in.groups * wpr) return;
-  const int wi = (int)(t % wpr);
-  const int64_t r = t / wpr;
-  const int g = (int)(r % in.groups);
-  const int n = (int)(r / in.groups);
-  const int hw = in.h * in.w;
-  const uint8_t *base = in.data + (int64_t)n * hw * in.pixel + (int64_t)g * in.gstride + 4 * wi;
-  uint32_t acc[4] = {0, 0, 0, 0};
-  for (int p = 0; p < hw; ++p) {
-    const uint32_t w = *(const uint32_t *)(base + (int64_t)p * in.pixel);
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) acc[kk] += (w >> (2 * kk)) & 0x03030303u;
-  }
-  int32_t *o = out + (int64_t)n * in.groups * in.cpg + (int64_t)g * in.cpg + 16 * wi;
-#pragma unroll
-  for (int b = 0; b < 4; ++b) {
-    const int4 v = make_int4((int)((acc[0] >> (8 * b)) & 255u), (int)((acc[1] >> (8 * b)) & 255u),
-                             (int)((acc[2] >> (8 * b)) & 255u), (int)((acc[3] >> (8 * b)) & 255u));
-    *(int4 *)(o + 4 * b) = v;
-  }
-}
-
-// Same sums with one workgroup per (image, group) when 256 is a multiple of
-// the words per row: thread (word, r) takes pixels r, r + R, ... (R = 256 /
-// words), and the R partial byte-lane sums of a word are added in LDS.
+// Unpadded rows of b in {2, 3, 4, 8}: one workgroup per (image, group), thread
+// (unit, r) taking pixels r, r + R, ... of a unit (a word, or a 32-code chunk
+// for b = 3; R = 256 / units).  A word's codes are masked into fields with room
+// for the sum (four bytes for b = 2, two halves for b = 4 and 8), so one add
+// sums several codes; the R partial sums are added in LDS.  b = 3 sums the low
+// bit pairs and the third bits apart.  Bound by latency: eight pixels' loads
+// are in flight before their sums.
 // planes (nullable): also the FC's signed base-256 digit planes of the sums
 // (P planes of count bytes), and logits row n zeroed for the FC's atomics.
-__global__ __launch_bounds__(256) void avgsum2_wg_kernel(ActView in, int32_t *out, int8_t *planes, int P,
-                                                        int64_t count, int32_t *logits, int cout) {
-  __shared__ uint32_t part[4][256];
-  const int wpr = in.cpg / 16;
-  const int R = 256 / wpr;
-  const int n = (int)(blockIdx.x / in.groups), g = (int)(blockIdx.x % in.groups);
-  const int wi = threadIdx.x % wpr, r = threadIdx.x / wpr;
-  const int hw = in.h * in.w;
-  const uint8_t *base = in.data + (int64_t)n * hw * in.pixel + (int64_t)g * in.gstride + 4 * wi;
-  uint32_t acc[4] = {0, 0, 0, 0};
-  // eight pixels' loads in flight before their sums
-  for (int p0 = r; p0 < hw; p0 += 8 * R) {
-    uint32_t w[8];
+template <int B>
+struct SumT {
+  static constexpr int W = B == 3 ? 3 : 1;               // words of a unit
+  static constexpr int CODES = B == 3 ? 32 : 32 / B;     // its codes
+  static constexpr int FB = B == 2 || B == 3 ? 8 : 16;   // field bits
+  static constexpr int NA = B == 2 ? 4 : B == 3 ? 16 : B == 4 ? 4 : 2;  // accumulators
+  static constexpr int MAXHW = B == 2 || B == 3 ? 85 : B == 4 ? 4369 : 257;  // no field overflows
+};
+template <int B>
+__device__ inline void sum_unit(uint32_t (&acc)[SumT<B>::NA], const uint32_t (&w)[SumT<B>::W]) {
+  if constexpr (B == 3) {
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int p = p0 + u * R;
-      w[u] = p < hw ? *(const uint32_t *)(base + (int64_t)p * in.pixel) : 0u;
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        acc[4 * u + k] += (w[u] >> (2 * k)) & 0x03030303u;
+        acc[8 + 4 * u + k] += (w[2] >> (2 * k + u)) & 0x01010101u;
+      }
+  } else {
+    constexpr uint32_t mask = B == 2 ? 0x03030303u : B == 4 ? 0x000F000Fu : 0x00FF00FFu;
+#pragma unroll
+    for (int k = 0; k < SumT<B>::NA; ++k) acc[k] += (w[0] >> (B * k)) & mask;
+  }
+}
+template <int B>
+__device__ inline void avgsum_wg(const ActView &in, int32_t *out, int8_t *planes, int P, int64_t count,
+                                 int32_t *logits, int cout) {
+  using T = SumT<B>;
+  __shared__ uint32_t part[T::NA][256];
+  const int units = in.cpg / T::CODES;
+  const int R = 256 / units;
+  const int n = (int)(blockIdx.x / in.groups), g = (int)(blockIdx.x % in.groups);
+  const int wi = threadIdx.x % units, r = threadIdx.x / units;
+  const int hw = in.h * in.w;
+  const uint8_t *base = in.data + (int64_t)n * hw * in.pixel + (int64_t)g * in.gstride + 4 * T::W * wi;
+  uint32_t acc[T::NA] = {};
+  if (r < R)
+    for (int p0 = r; p0 < hw; p0 += 8 * R) {
+      uint32_t w[8][T::W];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int p = p0 + u * R;
+#pragma unroll
+        for (int j = 0; j < T::W; ++j) w[u][j] = p < hw ? ((const uint32_t *)(base + (int64_t)p * in.pixel))[j] : 0u;
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u) sum_unit<B>(acc, w[u]);
     }
 #pragma unroll
-    for (int u = 0; u < 8; ++u)
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk) acc[kk] += (w[u] >> (2 * kk)) & 0x03030303u;
-  }
-#pragma unroll
-  for (int kk = 0; kk < 4; ++kk) part[kk][threadIdx.x] = acc[kk];
+  for (int k = 0; k < T::NA; ++k) part[k][threadIdx.x] = acc[k];
   __syncthreads();
-  for (int idx = threadIdx.x; idx < 4 * wpr; idx += 256) {
-    const int w2 = idx >> 2, kk = idx & 3;
-    uint32_t sum = 0;
-    for (int rr = 0; rr < R; ++rr) sum += part[kk][rr * wpr + w2];
-    const int64_t c0 = (int64_t)n * in.groups * in.cpg + (int64_t)g * in.cpg + 16 * w2 + kk;
-    int32_t *o = out + c0;
+  constexpr int SA = B == 3 ? 8 : T::NA;  // accumulators that yield codes
+  for (int idx = threadIdx.x; idx < SA * units; idx += 256) {
+    const int w2 = idx / SA, k = idx % SA;
+    uint32_t sum = 0, hi = 0;
+    for (int rr = 0; rr < R; ++rr) {
+      sum += part[k][rr * units + w2];
+      if constexpr (B == 3) hi += part[8 + k][rr * units + w2];
+    }
+    const int64_t c0 = (int64_t)n * in.groups * in.cpg + (int64_t)g * in.cpg + T::CODES * w2 +
+                       (B == 3 ? 16 * (k >> 2) + (k & 3) : k);
 #pragma unroll
-    for (int b = 0; b < 4; ++b) {
-      const int32_t v = (int32_t)((sum >> (8 * b)) & 255u);
-      o[4 * b] = v;
-      if (planes) {  // v <= 255: digits v (one plane, v <= 127) or v - 256 and 1
+    for (int f = 0; f < 32 / T::FB; ++f) {
+      int32_t v = (int32_t)((sum >> (T::FB * f)) & ((1u << T::FB) - 1u));
+      if constexpr (B == 3) v += 4 * (int32_t)((hi >> (8 * f)) & 255u);
+      const int64_t c = c0 + (B == 8 ? 2 : 4) * f;  // field f's code
+      out[c] = v;
+      if (planes) {
         const int d0 = (int)(int8_t)(uint8_t)v;
-        planes[c0 + 4 * b] = (int8_t)d0;
-        if (P > 1) planes[count + c0 + 4 * b] = (int8_t)((v - d0) >> 8);
-        for (int p = 2; p < P; ++p) planes[p * count + c0 + 4 * b] = 0;
+        planes[c] = (int8_t)d0;
+        if (P > 1) {
+          const int r1 = (v - d0) >> 8, d1 = (int)(int8_t)(uint8_t)r1;
+          planes[count + c] = (int8_t)d1;
+          if (P > 2) planes[2 * count + c] = (int8_t)((r1 - d1) >> 8);
+          for (int p = 3; p < P; ++p) planes[p * count + c] = 0;
+        }
       }
     }
   }
   if (logits && g == 0)
     for (int i = threadIdx.x; i < cout; i += 256) logits[(int64_t)n * cout + i] = 0;
+}
+__global__ __launch_bounds__(256) void avgsum2_wg_kernel(ActView in, int32_t *out, int8_t *planes, int P,
+                                                        int64_t count, int32_t *logits, int cout) {
+  avgsum_wg<2>(in, out, planes, P, count, logits, cout);
+}
+template <int B>
+__global__ __launch_bounds__(256) void avgsum_wg_kernel(ActView in, int32_t *out, int8_t *planes, int P, int64_t count,
+                                                       int32_t *logits, int cout) {
+  avgsum_wg<B>(in, out, planes, P, count, logits, cout);
 }
 __global__ void avgsum_kernel(ActView in, int32_t *out) {
   const int64_t C = (int64_t)in.groups * in.cpg;
@@ -1072,46 +1091,37 @@ hipError_t launch_pad_pixels(const ActView &in, int pad, const ActView &out, hip
   return hipGetLastError();
 }
 
+// One workgroup per image and group (avgsum_wg): whole units in a row,
+// no more of them than threads, and no more pixels than a field can sum.
 bool avgsum_makes_fc_planes(const ActView &in) {
-  const int wpr = in.cpg / 16;
-  return in.bits == 2 && in.cpg % 16 == 0 && (int64_t)in.h * in.w <= 85 && wpr >= 1 && wpr <= 256 &&
-         256 % wpr == 0 && (int64_t)in.n * in.groups < ((int64_t)1 << 31);
+  const int b = in.bits;
+  if (b != 2 && b != 3 && b != 4 && b != 8) return false;
+  const int codes = b == 3 ? 32 : 32 / b;
+  const int64_t max_hw = b == 4 ? SumT<4>::MAXHW : b == 8 ? SumT<8>::MAXHW : SumT<2>::MAXHW;
+  return in.cpg % codes == 0 && in.cpg / codes <= 256 && (int64_t)in.h * in.w <= max_hw &&
+         (int64_t)in.n * in.groups < ((int64_t)1 << 31);
 }
 
 int fc_planes(int64_t xmax) { return xmax >= 0 && xmax <= 127 ? 1 : xmax >= 0 && xmax <= 32639 ? 2 : 4; }
 
-// 0: one thread per channel; 1: byte-lane sums of 2-bit rows (16 codes per
-// thread); 2: the same with one workgroup per image row block (which can
-// also write the FC's digit planes).
-int avgsum_path(const ActView &in, const int32_t *out) {
-  if (in.bits == 2 && in.cpg % 16 == 0 && (int64_t)in.h * in.w <= 85) {
-    const int wpr = in.cpg / 16;
-    if (wpr <= 256 && 256 % wpr == 0 && (int64_t)in.n * in.groups < ((int64_t)1 << 31)) return 2;
-    if (((uintptr_t)out & 15u) == 0) return 1;
-  }
-  return 0;
-}
-
 const char *avgsum_label(const ActView &in, const int32_t *out) {
-  static const char *names[3] = {"avgsum_kernel", "avgsum2_kernel", "avgsum2_wg_kernel"};
-  return names[avgsum_path(in, out)];
+  (void)out;
+  return !avgsum_makes_fc_planes(in) ? "avgsum_kernel" : in.bits == 2 ? "avgsum2_wg_kernel" : "avgsum_wg_kernel";
 }
 
 hipError_t launch_avgsum(const ActView &in, int32_t *out, hipStream_t s, int8_t *planes, int P, int32_t *logits,
                          int cout) {
   const int64_t items = (int64_t)in.n * in.groups * in.cpg;
   if (items == 0) return hipSuccess;
-  if (planes && !avgsum_makes_fc_planes(in)) return hipErrorInvalidValue;
-  const int path = avgsum_path(in, out);
-  if (path == 2) {
-    hipLaunchKernelGGL(avgsum2_wg_kernel, dim3((unsigned)(in.n * in.groups)), dim3(256), 0, s, in, out, planes, P,
-                       items, logits, cout);
+  if (avgsum_makes_fc_planes(in)) {
+    auto k = in.bits == 2   ? avgsum2_wg_kernel
+             : in.bits == 3 ? avgsum_wg_kernel<3>
+             : in.bits == 4 ? avgsum_wg_kernel<4>
+                            : avgsum_wg_kernel<8>;
+    hipLaunchKernelGGL(k, dim3((unsigned)(in.n * in.groups)), dim3(256), 0, s, in, out, planes, P, items, logits, cout);
     return hipGetLastError();
   }
-  if (path == 1) {
-    hipLaunchKernelGGL(avgsum2_kernel, dim3(grid_for(items / 16)), dim3(kBlock), 0, s, in, out);
-    return hipGetLastError();
-  }
+  if (planes) return hipErrorInvalidValue;
   hipLaunchKernelGGL(avgsum_kernel, dim3(grid_for(items)), dim3(kBlock), 0, s, in, out);
   return hipGetLastError();
 }

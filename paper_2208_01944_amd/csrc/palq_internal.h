@@ -106,6 +106,7 @@ struct ConvArgs {
   int32_t fp4;           // 1: 2-bit layers may run on the FP4 matrix cores (where exact)
   int32_t bitdecomp;     // 1: M-bit layers run as the Eq. 4 bit decomposition on FP4
   int32_t gated;         // set by the launcher: general partner of a tiled launch
+  int32_t fp_fast;       // conv_fp_fast, where the caller asked
 };
 
 // Kernel launchers (return hipError_t of the launch).
@@ -146,6 +147,9 @@ hipError_t launch_conv_mfma(const ConvArgs &a, const uint8_t *wp, const int32_t 
 bool conv_fp_applies(const ConvArgs &a);
 ConvPlan conv_fp_plan(const ConvArgs &a);
 const int32_t *conv_fp_flag(const ConvArgs &a, const int32_t *thr);
+// Whether the prepared layer's shifts allow the FP4 kernel's shorter requant
+// (reads a flag back, blocking); callers keep the answer in ConvArgs::fp_fast.
+bool conv_fp_fast(const ConvArgs &a, const int32_t *thr);
 hipError_t launch_conv_fp_prepare(const ConvArgs &a, uint8_t *wp, int32_t *thr, hipStream_t s);
 hipError_t launch_conv_fp(const ConvArgs &a, const uint8_t *wp, const int32_t *thr, bool checked, hipStream_t s);
 // The scratch size that palq_group_conv_noalloc's limit is documented for.
@@ -161,10 +165,13 @@ uint8_t *noalloc_scratch(int device);
 // "conv_tile_kernel[stem]", "conv_grouped_kernel" or "conv_stem_kernel").
 const char *conv_kernel_label(const ConvArgs &a, int epi);
 // Stem conv fused with the 3x3 / stride 2 / pad 1 max pool of its output
-// (written to po only; the stem's own output is not written).  Requires the
-// fast epilogue (conv_mfma_epilogue == 0).
+// (written to po only; the stem's own output is not written).
+// stem_pool_requant, once the layer is prepared and the stream drained (reads
+// flags back, blocking): 0 no exact requant, the fusion does not apply, 1 fp64,
+// 2 fp32; passed to the launch.
 bool stem_pool_applies(const ConvArgs &a, const ActView &po, int k, int stride, int pad);
-hipError_t launch_stem_pool(const ConvArgs &a, const uint8_t *wp, const int32_t *thr, const ActView &po,
+int stem_pool_requant(const ConvArgs &a, const uint8_t *wp, const int32_t *thr);
+hipError_t launch_stem_pool(const ConvArgs &a, const uint8_t *wp, const int32_t *thr, const ActView &po, int requant,
                             hipStream_t s);
 
 hipError_t launch_pack(const void *codes, const ActView &out, hipStream_t s);

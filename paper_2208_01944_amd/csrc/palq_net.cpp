@@ -57,7 +57,7 @@ struct Layer {
   bool fc_planes_ready = false;  // FC: skip its own digit pass
   // stem conv whose output only the following max pool reads: one fused
   // launch writes the pooled tensor (pool_out) and the pool layer is skipped
-  bool pool_fused = false;
+  int pool_fused = 0;  // stem_pool_requant
   bool skip = false;
   ActView pool_out{};
 };
@@ -550,18 +550,20 @@ palq_status palq_net_create(palq_ctx *ctx, const palq_act *input, const palq_lay
       // a layer too long for the general build's LDS runs its general
       // epilogue on the direct kernel
       if (NL.epi != 0 && !conv_mfma_general_fits(NL.conv)) NL.use_mfma = false;
+      NL.conv.fp_fast = NL.epi == 0 && conv_fp_fast(NL.conv, NL.thr);
     }
   // fuse the stem with a max pool that is its output's only reader
   if (!(flags & PALQ_NET_KEEP_ALL))
     for (int i = 0; i + 1 < n_layers; ++i) {
       Layer &NL = net->layers[i];
       const palq_layer &P = layers[i + 1];
-      if (layers[i].op != PALQ_OP_CONV || !NL.use_mfma || NL.epi != 0 || P.op != PALQ_OP_MAXPOOL ||
-          P.src != layers[i].dst || net->tensors[layers[i].dst].last_use != i + 1)
+      if (layers[i].op != PALQ_OP_CONV || !NL.use_mfma || P.op != PALQ_OP_MAXPOOL || P.src != layers[i].dst ||
+          net->tensors[layers[i].dst].last_use != i + 1)
         continue;
       const ActView po = view_of(&net->tensors[P.dst].d);
       if (!stem_pool_applies(NL.conv, po, P.pool_k, P.pool_stride, P.pool_pad)) continue;
-      NL.pool_fused = true;
+      NL.pool_fused = stem_pool_requant(NL.conv, NL.wp, NL.thr);
+      if (!NL.pool_fused) continue;
       NL.pool_out = po;
       net->layers[i + 1].skip = true;
     }
@@ -666,7 +668,7 @@ palq_status forward_impl(palq_ctx *ctx, palq_net *net, const void *input, int32_
         }
         if (sp.res_src == 0) a.res.data = (uint8_t *)input;
         if (sp.proj_src == 0) a.proj.data = (uint8_t *)input;
-        if (NL.pool_fused) e = launch_stem_pool(a, NL.wp, NL.thr, NL.pool_out, s);
+        if (NL.pool_fused) e = launch_stem_pool(a, NL.wp, NL.thr, NL.pool_out, NL.pool_fused, s);
         else e = NL.use_mfma ? launch_conv_mfma(a, NL.wp, NL.thr, NL.epi, s) : launch_conv_direct(a, s);
         break;
       }

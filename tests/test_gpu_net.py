@@ -315,6 +315,25 @@ def test_resnet18_bits3_g3(ctx, torch):
     np.testing.assert_array_equal(logits, O.run_net(spec, spec["x"]))
 
 
+# the fused stem and pool: 64 channels (half a channel block) and 192 (a block
+# and a half), 2-, 3- and 4-bit outputs, odd sizes, and multipliers of 2^26,
+# past the fp32 requant (same values: the shifts grow alike)
+@pytest.mark.parametrize("groups,bits,hw,big_mult", [(1, 2, 33, False), (3, 3, 64, False), (2, 4, 50, False), (1, 4, 37, True),
+                                                     (2, 2, 45, True), (3, 4, 31, False)])
+def test_stem_pool_widths(ctx, torch, groups, bits, hw, big_mult):
+    say(f"resnet18 stem + pool G={groups} b={bits} hw={hw} big_mult={big_mult}")
+    spec = I.resnet18(n=3, groups=groups, bits=bits, hw=hw, classes=10, seed=17)
+    spec = O.calibrate_centring(spec, spec["x"])
+    if big_mult:
+        L = spec["layers"][0]
+        L["mult"], L["shift"] = L["mult"] << 12, L["shift"] + 12
+    net, logits = gpu_forward(ctx, torch, spec)
+    kernels = net.layer_kernels()
+    assert kernels[0].endswith("stem_pool_kernel"), kernels
+    assert kernels[-1] == "fc_mfma_kernel", kernels
+    np.testing.assert_array_equal(logits, O.run_net(spec, spec["x"]))
+
+
 def full_size_run(ctx, torch, name):
     """The benchmark's network (stored centred biases, default flags) on
     the workload's whole fp32 image batch through palq_forward_image, as

@@ -639,6 +639,20 @@ def test_maxpool_avgsum_fc(ctx, torch, bits, cpg, layout):
     np.testing.assert_array_equal(logits.cpu().numpy().reshape(3, 10), O.fc(ref_s, w))
 
 
+# field sums at their largest: the pixel limit of each width and one past it
+# (the per-channel kernel), unit counts that do not divide 256
+@pytest.mark.parametrize("bits,cpg,h,w", [(2, 80, 5, 17), (3, 96, 5, 17), (3, 64, 2, 43), (4, 64, 17, 257), (4, 40, 15, 292),
+                                          (8, 20, 1, 257), (8, 12, 6, 43), (3, 1024, 3, 3)])
+def test_avgsum_field_limits(ctx, torch, bits, cpg, h, w):
+    say(f"avgsum limits bits={bits} cpg={cpg} {h}x{w}")
+    x = I.codes(np.random.default_rng(bits + cpg), (2, h, w, 2 * cpg), bits, False).astype(np.int64)
+    x[1] = (1 << bits) - 1
+    sums = torch.empty(2 * 2 * cpg, dtype=torch.int32, device=ctx.dev)
+    ctx.avgsum(ctx.pack(x, 2, bits), sums)
+    ctx.sync()
+    np.testing.assert_array_equal(sums.cpu().numpy().reshape(2, 2 * cpg), O.avgsum(x))
+
+
 @pytest.mark.parametrize("cpg,h,w", [(64, 9, 9), (16, 5, 17), (128, 7, 7), (64, 12, 11), (48, 7, 7), (512, 3, 5), (2048, 2, 2), (4096, 1, 3)])
 @pytest.mark.parametrize("layout", [0, 1])
 def test_maxpool_avgsum_2bit_vector_paths(ctx, torch, cpg, h, w, layout):
