@@ -362,13 +362,11 @@ __device__ __forceinline__ void quad_codes(const uint32_t *c, int qi, int half, 
 // multiplies instead of carried state, the in-image test is three VALU
 // instructions, two K-blocks share a barrier, and a stage's LDS reads are in
 // flight while the next fetch is issued.
-// KS = 2: two wave groups, group h taking K-block h of each stage; their
-// accumulators are added through LDS at the end (both exact, so is the sum).
 // MODE 0: no shortcut, 1: identity, 2: projection (more K-blocks).
-template <int B, int PB, int WN, int WM, int KPS, int KS>
+template <int B, int PB, int WN, int WM, int KPS>
 struct FpCfg {
   using T = FpT<B>;
-  static constexpr int NT = WN * WM * 64 * KS;
+  static constexpr int NT = WN * WM * 64;
   static constexpr int TN = 64 * WN, TM = 32 * PB * WM;
   static constexpr int W1 = TN / 32 * T::SLAB, X1 = TM * 16 * T::PPX;
   static constexpr int WST = KPS * W1, XST = KPS * X1, SST = WST + XST;
@@ -392,16 +390,14 @@ struct FpCfg {
   }
   static_assert(full() > 0, "at most two load counts");
   static constexpr int RP = TM * (B == 2 ? TN / 64 : TN / 32);  // 16-byte shortcut pieces
-  static constexpr int RED = KS == 2 ? WN * WM * 2 * PB * 4096 : 0;
 };
 
-template <int B, int PB, int WN, int WM, int MODE, bool DUMP, int KPS, int KS, int S, bool FAST>
+template <int B, int PB, int WN, int WM, int MODE, bool DUMP, int KPS, int S, bool FAST>
 __device__ __forceinline__ void conv_fp_tile(const FpArgs &a) {
-  using C = FpCfg<B, PB, WN, WM, KPS, KS>;
+  using C = FpCfg<B, PB, WN, WM, KPS>;
   using T = FpT<B>;
   constexpr int NT = C::NT, TN = C::TN, TM = C::TM, CB = 2;
-  static_assert(KS == 1 || KPS == 2, "the K split gives each wave group one K-block of a stage");
-  constexpr int RING = S * C::SST > C::RED ? S * C::SST : C::RED;
+  constexpr int RING = S * C::SST;
   constexpr int CST = TN / 64 * 1024;
   constexpr int RSB = MODE == 1 ? C::RP * 16 : 0;
   __shared__ __attribute__((aligned(1024))) uint8_t lds[RING + CST + RSB];
@@ -411,8 +407,7 @@ __device__ __forceinline__ void conv_fp_tile(const FpArgs &a) {
   if (!tile_of(a, id)) return;
   const int tid = (int)threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
   const int l32 = lane & 31, half = lane >> 5;
-  const int kh = KS == 2 ? wave / (WN * WM) : 0, wg = wave - kh * (WN * WM);
-  const int wn = wg / WM, wm = wg % WM;
+  const int wn = wave / WM, wm = wave % WM;
   const int g = id.g, gd = g + a.shuffle < a.G ? g + a.shuffle : g + a.shuffle - a.G;
   const int m0 = id.pt * TM;
 
@@ -522,7 +517,6 @@ __device__ __forceinline__ void conv_fp_tile(const FpArgs &a) {
 
   const bool more = C::LMAX != C::LMIN && wave < C::full();
   int so = 0, slot_f = S - 1;  // byte offset of the stage's slot; slot of the next fetch
-  constexpr int SUBS = KS == 2 ? 1 : KPS;
   const float *cst = (const float *)(lds + RING) + wn * 256;
   for (int s = 0; s < NS; ++s) {
     // stage s has landed; up to S - 2 younger ones may be in flight
@@ -532,9 +526,10 @@ __device__ __forceinline__ void conv_fp_tile(const FpArgs &a) {
     } else {
       wait_barrier<0>();
     }
-    Ops o[SUBS];
+    // two K-blocks' reads in flight before the next fetch, then one ahead
+    Ops o[KPS];
 #pragma unroll
-    for (int i = 0; i < SUBS; ++i) read(o[i], so, KS == 2 ? kh : i);
+    for (int i = 0; i < KPS; ++i) read(o[i], so, i);
     if (s + S - 1 < NS) fetch(s + S - 1, slot_f);
     if (s == 0) {
       // element r of block cb is channel 32 cb + 8 (r / 4) + 4 half + r % 4
@@ -546,39 +541,16 @@ __device__ __forceinline__ void conv_fp_tile(const FpArgs &a) {
 #pragma unroll
           for (int e = 0; e < 4; ++e)
 #pragma unroll
-            for (int pb = 0; pb < PB; ++pb) acc[cb][pb][4 * qi + e] = kh == 0 ? b[e] : 0.0f;
+            for (int pb = 0; pb < PB; ++pb) acc[cb][pb][4 * qi + e] = b[e];
         }
     }
-    const bool whole = KPS == 1 || s * KPS + KPS <= KB;
-    if (KS == 2) {
-      if (whole || kh == 0) mfmas(o[0]);
-    } else {
-      mfmas(o[0]);
-      if (KPS == 2 && whole) mfmas(o[SUBS - 1]);
+#pragma unroll
+    for (int i = 0; i < KPS; ++i) {
+      if (i > 0 && s * KPS + i >= KB) break;  // uniform; an odd last K-block
+      mfmas(o[i]);
     }
     so = so + C::SST == S * C::SST ? 0 : so + C::SST;
     slot_f = slot_f + 1 == S ? 0 : slot_f + 1;
-  }
-
-  if constexpr (KS == 2) {
-    float *red = (float *)lds;
-    __syncthreads();
-    if (kh == 1) {
-#pragma unroll
-      for (int c = 0; c < CB * PB * 4; ++c) {
-        const v16f &v = acc[c / (PB * 4)][c / 4 % PB];
-        *(v4f *)(red + ((wg * CB * PB * 4 + c) * 64 + lane) * 4) =
-            v4f{v[4 * (c % 4)], v[4 * (c % 4) + 1], v[4 * (c % 4) + 2], v[4 * (c % 4) + 3]};
-      }
-    }
-    __syncthreads();
-    if (kh == 1) return;
-#pragma unroll
-    for (int c = 0; c < CB * PB * 4; ++c) {
-      const v4f r = *(const v4f *)(red + ((wg * CB * PB * 4 + c) * 64 + lane) * 4);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) acc[c / (PB * 4)][c / 4 % PB][4 * (c % 4) + e] += r[e];
-    }
   }
 
   // ---- epilogue
@@ -931,9 +903,9 @@ __device__ __forceinline__ void conv_fp_split(const FpArgs &a) {
 
 // Entry points by matrix-core format.
 #define PALQ_FP_TILE(NAME)                                                                            \
-  template <int B, int PB, int WN, int WM, int MODE, bool DUMP, int KPS, int KS, int S, bool FAST>    \
-  __global__ __launch_bounds__(WN *WM * 64 * KS, PB == 4 ? 2 : B == 2 ? 4 : 3) void NAME(FpArgs a) {  \
-    conv_fp_tile<B, PB, WN, WM, MODE, DUMP, KPS, KS, S, FAST>(a);                                     \
+  template <int B, int PB, int WN, int WM, int MODE, bool DUMP, int KPS, int S, bool FAST>    \
+  __global__ __launch_bounds__(WN *WM * 64, B == 2 ? 4 : 3) void NAME(FpArgs a) {  \
+    conv_fp_tile<B, PB, WN, WM, MODE, DUMP, KPS, S, FAST>(a);                                     \
   }
 #define PALQ_FP_SPLIT(NAME)                                                     \
   template <int B, int PB, int NW, int MODE, bool DUMP>                         \
@@ -1038,23 +1010,23 @@ int cu_count() {
   return cus;
 }
 
-template <int B, int PB, int WN, int WM, int MODE, bool DUMP, int KPS, int KS, int S>
+template <int B, int PB, int WN, int WM, int MODE, bool DUMP, int KPS, int S>
 hipError_t launch_tile_mode(const FpArgs &f, unsigned grid, hipStream_t s) {
-  const dim3 block(WN * WM * 64 * KS);
+  const dim3 block(WN * WM * 64);
   if constexpr (B != 2)
-    hipLaunchKernelGGL((conv_fp6_kernel<B, PB, WN, WM, MODE, DUMP, KPS, KS, S, false>), dim3(grid), block, 0, s, f);
+    hipLaunchKernelGGL((conv_fp6_kernel<B, PB, WN, WM, MODE, DUMP, KPS, S, false>), dim3(grid), block, 0, s, f);
   else if (f.fast)
-    hipLaunchKernelGGL((conv_fp4_kernel<B, PB, WN, WM, MODE, DUMP, KPS, KS, S, true>), dim3(grid), block, 0, s, f);
+    hipLaunchKernelGGL((conv_fp4_kernel<B, PB, WN, WM, MODE, DUMP, KPS, S, true>), dim3(grid), block, 0, s, f);
   else
-    hipLaunchKernelGGL((conv_fp4_kernel<B, PB, WN, WM, MODE, DUMP, KPS, KS, S, false>), dim3(grid), block, 0, s, f);
+    hipLaunchKernelGGL((conv_fp4_kernel<B, PB, WN, WM, MODE, DUMP, KPS, S, false>), dim3(grid), block, 0, s, f);
   return hipGetLastError();
 }
-template <int B, int PB, int WN, int WM, bool DUMP, int KPS, int KS, int S>
+template <int B, int PB, int WN, int WM, bool DUMP, int KPS, int S>
 hipError_t launch_tile(FpArgs f, int64_t in_bytes, hipStream_t s) {
   const unsigned grid = fp_tiles(f, 64 * WN, 32 * PB * WM, in_bytes);
-  if (f.res) return launch_tile_mode<B, PB, WN, WM, 1, DUMP, KPS, KS, S>(f, grid, s);
-  if (f.proj) return launch_tile_mode<B, PB, WN, WM, 2, DUMP, KPS, KS, S>(f, grid, s);
-  return launch_tile_mode<B, PB, WN, WM, 0, DUMP, KPS, KS, S>(f, grid, s);
+  if (f.res) return launch_tile_mode<B, PB, WN, WM, 1, DUMP, KPS, S>(f, grid, s);
+  if (f.proj) return launch_tile_mode<B, PB, WN, WM, 2, DUMP, KPS, S>(f, grid, s);
+  return launch_tile_mode<B, PB, WN, WM, 0, DUMP, KPS, S>(f, grid, s);
 }
 
 template <int B, int PB, int NW, int MODE>
@@ -1077,28 +1049,29 @@ hipError_t launch_split(FpArgs f, int64_t in_bytes, hipStream_t s) {
   return launch_split_mode<B, PB, NW, 0>(f, grid, s);
 }
 
-#ifndef FP_BUILD
-#define FP_BUILD -1
-#endif
-#ifndef FP_SPLIT
-#define FP_SPLIT 512
-#endif
+// Which build takes a layer (times for the 14x14, 256-channel layer unless
+// stated; K-blocks of 64 codes):
+//  * few 32 x 64 tiles: the split kernel up to two per CU, or four with a long
+//    K loop (7x7, 512 channels, 2-bit: batch 1, 64 tiles, 6.8 us against 14.3 on
+//    128 x 128 tiles; batch 8, 448 tiles, 11.4 against 14.7; at 800 tiles 17.4
+//    against 20.8 with 72 K-blocks, but 10.0 against 9.2 with 36);
+//  * 128 x 128 tiles, else (channel blocks that are no multiple of 128) 64 x 256;
+//  * from 12 K-blocks on, two stages of two K-blocks: half the barriers (batch 64,
+//    2-bit, 18.2 us against 20.4 with three stages of one); below, three stages
+//    of one, which leave LDS for more workgroups (56x56, 64 -> 256 channels 1x1
+//    with a shortcut, batch 128, 43.5 us against 49.1).
 template <int B>
 hipError_t launch_fp(const FpArgs &f, int64_t in_bytes, hipStream_t s) {
-  constexpr int KPS = B == 2 ? 2 : 1, S = B == 2 ? 3 : 4;
   const int64_t cus = cu_count();
-  auto tiles = [&](int tn, int tm) {
-    return (int64_t)((f.M + tm - 1) / tm) * ((f.cout + tn - 1) / tn) * f.G;
-  };
-  const int build = FP_BUILD;
-  if (build == 0 || (build < 0 && tiles(32, 64) <= FP_SPLIT)) return launch_split<B, 2, 8>(f, in_bytes, s);
-  if (f.dump) return launch_tile<B, 2, 1, 4, true, KPS, 1, S>(f, in_bytes, s);
-  if (f.coutp % 128 != 0 || build == 1) return launch_tile<B, 2, 1, 4, false, KPS, 1, S>(f, in_bytes, s);
-  const int64_t t2 = tiles(128, 128), t4 = tiles(128, 256);
-  if (build == 3 || (build < 0 && t4 >= cus && 2 * ((t4 + cus - 1) / cus) <= (t2 + cus - 1) / cus))
-    return launch_tile<B, 4, 2, 2, false, KPS, 1, S>(f, in_bytes, s);
-  if (build == 4 || (build < 0 && f.kb >= 8 && t2 < 2 * cus)) return launch_tile<B, 2, 2, 2, false, 2, 2, 3>(f, in_bytes, s);
-  return launch_tile<B, 2, 2, 2, false, KPS, 1, S>(f, in_bytes, s);
+  const int64_t few = (int64_t)((f.M + 63) / 64) * ((f.cout + 31) / 32) * f.G;
+  if (few <= 2 * cus || (few <= 4 * cus && f.kb >= 64)) return launch_split<B, 2, 8>(f, in_bytes, s);
+  if (f.dump) return launch_tile<B, 2, 1, 4, true, 2, 2>(f, in_bytes, s);
+  const bool wide = f.coutp % 128 == 0;
+  if (f.kb < 12)
+    return wide ? launch_tile<B, 2, 2, 2, false, 1, 3>(f, in_bytes, s)
+                : launch_tile<B, 2, 1, 4, false, 1, 3>(f, in_bytes, s);
+  return wide ? launch_tile<B, 2, 2, 2, false, 2, 2>(f, in_bytes, s)
+              : launch_tile<B, 2, 1, 4, false, 2, 2>(f, in_bytes, s);
 }
 
 }  // namespace

@@ -1508,19 +1508,29 @@ constexpr int SET = 8 * 2 * RB;      // an output row's input rows 0 .. 7, two c
 constexpr int kSets = 3;             // ring of staged output rows, two ahead of the MFMAs
 
 // Row steps of a run: phase 0 recomputes row 2k - 1, 1 is row 2k, 2 row 2k + 1.
+// Unit u is pooled row k of channel block cbb of image n, carried along (scalar
+// divisions in every step cost more than its MFMAs hide).
 struct RowIt {
-  int u, phase;
+  int u, phase, k, cbb, n;
 };
-__device__ __forceinline__ RowIt row_first(int u, int ho2) { return {u, (u % ho2) > 0 ? 0 : 1}; }
-__device__ __forceinline__ void row_next(RowIt &it, int ho, int ho2) {
+__device__ __forceinline__ RowIt row_first(int u, int ho2, int ncb) {
+  const int r = u / ho2;
+  const int k = u - r * ho2;
+  return {u, k > 0 ? 0 : 1, k, r % ncb, r / ncb};
+}
+__device__ __forceinline__ void row_next(RowIt &it, int ho, int ho2, int ncb) {
   if (it.phase == 0) { it.phase = 1; return; }
-  if (it.phase == 1 && 2 * (it.u % ho2) + 1 < ho) { it.phase = 2; return; }
+  if (it.phase == 1 && 2 * it.k + 1 < ho) { it.phase = 2; return; }
   ++it.u;
   it.phase = 1;
+  if (++it.k < ho2) return;
+  it.k = 0;
+  if (++it.cbb < ncb) return;
+  it.cbb = 0;
+  ++it.n;
 }
-__device__ __forceinline__ int row_of(const RowIt &it, int ho2) {
-  const int k = it.u % ho2;
-  return it.phase == 0 ? 2 * k - 1 : 2 * k + (it.phase - 1);
+__device__ __forceinline__ int row_of(const RowIt &it) {
+  return it.phase == 0 ? 2 * it.k - 1 : 2 * it.k + (it.phase - 1);
 }
 }  // namespace sp
 
@@ -1583,7 +1593,7 @@ __global__ __launch_bounds__(sp::NT, 2) void stem_pool_kernel(ConvArgs a, Geo ge
   __shared__ __attribute__((aligned(1024))) uint8_t lds[kSets * SET];
   __shared__ RqT rq_area[256];
   if (int64_flag(a, geo)) return;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, half = lane >> 5;
   const int wn = wave >> 1, wm = wave & 1;
   const int ho = a.ho, wo = a.wo, ho2 = po.h, wo2 = po.w;
@@ -1597,7 +1607,8 @@ __global__ __launch_bounds__(sp::NT, 2) void stem_pool_kernel(ConvArgs a, Geo ge
   const int u_begin = x * Tq + min(x, Tr) + y * base + min(y, ex);
   const int u_end = u_begin + base + (y < ex ? 1 : 0);
   if (u_begin >= u_end) return;  // no barrier yet
-  const int cbb0 = (u_begin / ho2) % ncb;
+  const RowIt first = row_first(u_begin, ho2, ncb);
+  const int cbb0 = first.cbb;
   for (int c = tid; c < 256; c += NT) {
     const int ch = min((c < 128 ? cbb0 : (cbb0 + 1) % ncb) * 128 + (c & 127), a.cout - 1);
     if constexpr (F32) rq_area[c] = spc[ch];
@@ -1614,12 +1625,11 @@ __global__ __launch_bounds__(sp::NT, 2) void stem_pool_kernel(ConvArgs a, Geo ge
   // the row's window (row 7 is never read: no filter row 7); copy 1 of a row
   // starts 8 bytes on.  Lanes past the row's end load the next row's first
   // bytes (or zeros past the tensor), which no operand reads.
-  RowIt f_it = row_first(u_begin, ho2);
+  RowIt f_it = first;
   int f_set = 0;
   auto fetch = [&]() __attribute__((always_inline)) {
     const bool live = f_it.u < u_end;
-    const int n = f_it.u / (ho2 * ncb);
-    const uint32_t rbase = live ? (uint32_t)((n * a.in.h + 2 * row_of(f_it, ho2) + wave) * rowb + lane * 16) : kOob;
+    const uint32_t rbase = live ? (uint32_t)((f_it.n * a.in.h + 2 * row_of(f_it) + wave) * rowb + lane * 16) : kOob;
     uint8_t *ws = lds + f_set * SET + wave * 2 * RB;
 #pragma unroll
     for (int i = 0; i < 2; ++i)
@@ -1627,12 +1637,12 @@ __global__ __launch_bounds__(sp::NT, 2) void stem_pool_kernel(ConvArgs a, Geo ge
       for (int cp = 0; cp < 2; ++cp)
         __builtin_amdgcn_raw_ptr_buffer_load_lds(rin, (lds_ptr)(ws + (8 * i + cp) * RB), 16,
                                                  (int)(rbase + (uint32_t)(4 * i * rowb + 8 * cp)), 0, 0, 0);
-    if (live) row_next(f_it, ho, ho2);
+    if (live) row_next(f_it, ho, ho2, ncb);
     f_set = f_set == kSets - 1 ? 0 : f_set + 1;
   };
 
   // ---- compute side
-  RowIt c_it = row_first(u_begin, ho2);
+  RowIt c_it = first;
   int c_set = 0, w_cbb = -1;
   v16i acc[2][2];     // [cb][pb]
   int32_t st[2][16];  // per cb: row 2k - 1 pooled across columns, or the running max of rows 2k - 1, 2k
@@ -1656,8 +1666,7 @@ __global__ __launch_bounds__(sp::NT, 2) void stem_pool_kernel(ConvArgs a, Geo ge
   int out_lane = px * (int)po.pixel + (wn * 2 * BO + half * (BO == 4 ? 2 : 1)) * 4;
   asm volatile("" : "+v"(out_lane));  // kept as one 32-bit register
   auto finish_row = [&]() __attribute__((always_inline)) {
-    const int k = c_it.u % ho2;
-    const int cbb = (c_it.u / ho2) % ncb, n = c_it.u / (ho2 * ncb);
+    const int k = c_it.k, cbb = c_it.cbb, n = c_it.n;
     // columns 2p - 1 .. 2p + 1 of pooled column p = 32 wm + l: the lane's
     // two columns and column 2p - 1 from lane l - 1 (wm = 0) or 2p + 1 from
     // lane l + 1 (wm = 1); then the rows.  st: row 2k - 1 (pooled across
@@ -1784,13 +1793,13 @@ __global__ __launch_bounds__(sp::NT, 2) void stem_pool_kernel(ConvArgs a, Geo ge
   };
 
   int rows = 0;
-  for (RowIt it = row_first(u_begin, ho2); it.u < u_end; row_next(it, ho, ho2)) ++rows;
+  for (RowIt it = first; it.u < u_end; row_next(it, ho, ho2, ncb)) ++rows;
   fetch();
   fetch();
   for (int gk = 0; gk < rows; ++gk) {
     // the wave's weights, loaded when the channel block changes (at most
     // twice a run)
-    const int cbb = (c_it.u / ho2) % ncb;
+    const int cbb = c_it.cbb;
     if (cbb != w_cbb) {
       w_cbb = cbb;
       const uint8_t *wsrc = wrow + ((int64_t)(cbb * 4 + 2 * wn) * KH * 64 + lane) * 16;
@@ -1858,7 +1867,7 @@ __global__ __launch_bounds__(sp::NT, 2) void stem_pool_kernel(ConvArgs a, Geo ge
         for (int cb = 0; cb < 2; ++cb)
           acc[cb][pb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(W[r][cb], X[r][pb], acc[cb][pb], 0, 0, 0);
     finish_row();
-    row_next(c_it, ho, ho2);
+    row_next(c_it, ho, ho2, ncb);
     c_set = c_set == kSets - 1 ? 0 : c_set + 1;
   }
   // no staging load may land after the workgroup's LDS is released

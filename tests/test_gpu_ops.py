@@ -453,22 +453,24 @@ def test_conv_fp6_builds(ctx, torch, name):
 
 
 # The FP4 / FP6 builds at the edges of their tiles: few tiles (the split
-# kernel: K-blocks on 8 waves, fewer and more of them than waves), 64-channel,
-# 128 x 128, 128 x 256 and K-split tiles with a ragged last pixel tile, odd
-# K-block counts, channel counts that are no multiple of 64, 32, 16 or 8 (words
-# and channel blocks past the row), a 1x1 layer of one K-block, strides, and
-# each shortcut.
+# kernel: fewer and more K-blocks than its 8 waves), 64- and 128-channel tiles
+# with stages of one and of two K-blocks (from 12 K-blocks on; odd counts) and a
+# ragged last pixel tile, channel counts that are no multiple of 64, 32, 16 or 8
+# (words and channel blocks past the row), one K-block, strides, and each
+# shortcut.
 FP_EDGE_CASES = {
     "split_ragged": dict(n=1, h=7, w=9, groups=3, cin=24, cout=40, residual="identity"),
     "split_one_kblock": dict(n=2, h=9, w=8, groups=2, cin=20, cout=33, k=1, pad=0),
     "split_deep": dict(n=1, h=7, w=7, groups=2, cin=264, cout=96, stride=2, residual="projection"),
     "split_5x5": dict(n=2, h=11, w=10, groups=2, cin=70, cout=100, k=5, pad=2, stride=3),
     "c64_ragged": dict(n=3, h=43, w=41, groups=3, cin=72, cout=200, residual="identity"),
-    "c64_projection": dict(n=6, h=63, w=61, groups=4, cin=136, cout=56, stride=2, residual="projection"),
-    "c128_odd": dict(n=7, h=31, w=30, groups=2, cin=64, cout=380, residual="identity"),
-    "c128p4_ragged": dict(n=9, h=44, w=43, groups=2, cin=40, cout=250, k=3, residual="projection"),
-    "k2_ragged": dict(n=15, h=14, w=15, groups=3, cin=100, cout=500, residual="identity"),
-    "k2_odd": dict(n=15, h=14, w=14, groups=3, cin=64, cout=512),
+    "c64_short_projection": dict(n=13, h=63, w=61, groups=4, cin=40, cout=56, stride=2, residual="projection"),
+    "c64_projection": dict(n=13, h=63, w=61, groups=4, cin=100, cout=56, stride=2, residual="projection"),
+    "c128_short": dict(n=7, h=31, w=30, groups=2, cin=64, cout=380, residual="identity"),
+    "c128_one_kblock": dict(n=7, h=31, w=30, groups=2, cin=33, cout=128, k=1, pad=0, residual="identity"),
+    "c128_ragged_projection": dict(n=9, h=44, w=43, groups=2, cin=40, cout=250, k=3, residual="projection"),
+    "c128_ragged": dict(n=15, h=14, w=15, groups=3, cin=100, cout=500, residual="identity"),
+    "c128_5x5_odd": dict(n=15, h=14, w=14, groups=3, cin=64, cout=512, k=5, pad=2),
 }
 
 
