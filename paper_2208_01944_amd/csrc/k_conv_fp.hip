@@ -1,4 +1,5 @@
-// Grouped B-bit convolution (B = 2, 3, 4) on the FP4 / FP6 matrix cores.
+// Grouped B-bit convolution: B = 2, 3, 4 on the FP4 / FP6 matrix cores, 6- and
+// 8-bit codes (B = 8 below) on int8.
 //
 // Per group the layer is D[k][m] = sum_K W[k][K] X[K][m] (Eq. 1), k an output
 // channel, m an output pixel, K = (ky, kx, c), in K-blocks of 64 codes of one
@@ -11,6 +12,11 @@
 //    sign in bit 5; accumulator t / 64.
 //  Products are exact multiples of 1/4 (1/64) and the fp32 accumulator holds
 //  every partial sum exactly while |t| + |bias| + qmax |res_mult| < 2^24.
+//
+//  * B = 8 (also 6-bit codes, stored as bytes): x - 128 as int8 (the top bit
+//    flipped), two v_mfma_i32_32x32x32_i8 a K-block, accumulators starting at
+//    bias + 128 sum(w), which also restores taps outside the image (their code
+//    0 reads as -128); requant in fp64, exact while |u| M < 2^52.
 //
 // Any channel count: K-blocks and channel blocks are padded with zero weights,
 // so what an operand load brings in past the end of a row (the row's padding,
@@ -26,6 +32,7 @@
 
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 
 #include "codes.h"
 #include "conv_common.h"
@@ -38,11 +45,13 @@ namespace {
 // ------------------------------------------------------------ per-width facts
 template <int B>
 struct FpT {
-  static constexpr int SLAB = B == 2 ? 1024 : 1536;  // weight bytes of (K-block, 32 channels)
-  static constexpr int PPX = B == 2 ? 1 : 2;         // 16-byte LDS pieces of a pixel's K-block
-  static constexpr int XB = 8 * B;                   // its bytes in memory
-  static constexpr int CHS = 4 * B;                  // bytes of a lane half's 32 codes
-  static constexpr int L = B == 2 ? 2 : 6;           // the accumulator is 2^-L t
+  static constexpr int SLAB = B == 2 ? 1024 : B == 8 ? 2048 : 1536;  // weight bytes of (K-block, 32 channels)
+  static constexpr int PPX = B == 2 ? 1 : B == 8 ? 4 : 2;  // 16-byte LDS pieces of a pixel's K-block
+  static constexpr int XB = 8 * B;                         // its bytes in memory
+  static constexpr int CHS = 4 * B;                        // bytes of a lane half's 32 codes
+  static constexpr int L = B == 2 ? 2 : B == 8 ? 0 : 6;    // the accumulator is 2^-L t
+  static constexpr int J = B == 8 ? 2 : 1;                 // MFMAs (operands) of a K-block
+  using Acc = typename std::conditional<B == 8, v16i, v16f>::type;
 };
 
 // K order of a lane's 32 codes: field f of the operand holds code fp_code(f).
@@ -94,9 +103,19 @@ __device__ __forceinline__ v8i act_fp6_4(v4i x) {
 }
 template <int B>
 __device__ __forceinline__ v8i act_fp(v4i x) {
+  static_assert(B != 8, "FP4 and FP6 operands");
   if constexpr (B == 2) return act_fp4((uint32_t)x[0], (uint32_t)x[1]);
   else if constexpr (B == 3) return act_fp6_3((uint32_t)x[0], (uint32_t)x[1], (uint32_t)x[2]);
   else return act_fp6_4(x);
+}
+template <int B>
+__device__ __forceinline__ v8i wt_fp(v4i a, v2i b) {
+  if constexpr (B == 2) return __builtin_shufflevector(a, a, 0, 1, 2, 3, -1, -1, -1, -1);
+  else return v8i{a[0], a[1], a[2], a[3], b[0], b[1], 0, 0};
+}
+__device__ __forceinline__ v4i flip_i8(v4i x) {
+  const int m = (int)0x80808080u;
+  return v4i{x[0] ^ m, x[1] ^ m, x[2] ^ m, x[3] ^ m};
 }
 template <int B>
 __device__ __forceinline__ v16f mfma_fp(v8i a, v8i b, v16f c) {
@@ -104,11 +123,15 @@ __device__ __forceinline__ v16f mfma_fp(v8i a, v8i b, v16f c) {
   return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, F, F, 0, 0, 0, 0);
 }
 
+// Constants of 64 channels, one 1 KB block: [scale 64][bias 64][res_mult
+// 64][unused 64] floats in accumulator units, or (B = 8) [scale 64] doubles,
+// [bias + 128 sum(w) 64][res_mult 64] int32.
+constexpr int kCstBlock = 1024;
+
 // ------------------------------------------------------------ prepare
-// One launch per layer.  Workgroup 0: the requant constants, in blocks of 64
-// channels [scale 64][bias 64][res_mult 64][unused 64] floats in accumulator
-// units (zero for padded channels), and two flags: bad[0], some channel is
-// outside the fp32 bounds; bad[1], some shift exceeds 21 (requant_fp4).  The others: weight slabs, one lane operand (16 or
+// One launch per layer (B = 8: wsum_i8_kernel before it).  Workgroup 0: the
+// requant constants (zero for padded channels) and two flags: bad[0], some channel is
+// outside the exact requant's bounds; bad[1], some shift exceeds 21 (requant_fp4).  The others: weight slabs, one lane operand (16 or
 // 24 bytes) per thread, [G][coutp / 32][kb_total][SLAB]; E2M3 slabs hold bytes
 // 0-15 of every lane, then bytes 16-23.  Projection K-blocks of source group g
 // hold the projection filter of its destination group (g + s) mod G.
@@ -121,7 +144,27 @@ struct PrepArgs {
   uint8_t *wp;
   float *cst;
   int32_t *bad;
+  int32_t w_bits;
+  int32_t *wsum;  // B = 8: 128 sum(w) per channel
 };
+
+// 128 times the sum of each output channel's weights (the projection's of the
+// destination group included), one wave per channel.
+__global__ __launch_bounds__(256) void wsum_i8_kernel(PrepArgs a) {
+  const int c = (int)blockIdx.x * 4 + (int)(threadIdx.x >> 6), lane = (int)(threadIdx.x & 63);
+  if (c >= a.G * a.cout) return;
+  const int g = c / a.cout, k = c - g * a.cout, sh = 8 - a.w_bits;
+  int32_t sum = 0;
+  const int8_t *w = (const int8_t *)(a.w + (int64_t)c * a.taps * a.row);
+  for (int tap = 0; tap < a.taps; ++tap)
+    for (int i = lane; i < a.cin; i += 64) sum += (int32_t)(int8_t)(w[tap * a.row + i] << sh) >> sh;
+  if (a.pw) {
+    const int8_t *p = (const int8_t *)(a.pw + ((int64_t)((g + a.shuffle) % a.G) * a.cout + k) * a.prow);
+    for (int i = lane; i < a.pcin; i += 64) sum += (int32_t)(int8_t)(p[i] << sh) >> sh;
+  }
+  for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
+  if (lane == 0) a.wsum[c] = 128 * sum;
+}
 
 template <int B>
 __global__ __launch_bounds__(512) void conv_fp_prep_kernel(PrepArgs a) {
@@ -132,6 +175,28 @@ __global__ __launch_bounds__(512) void conv_fp_prep_kernel(PrepArgs a) {
     int bad = 0, wide = 0;
     for (int i = threadIdx.x; i < a.G * a.coutp; i += 512) {
       const int g = i / a.coutp, k = i - g * a.coutp;
+      if constexpr (B == 8) {
+        double s = 0.0;
+        int32_t b = 0, rm = 0;
+        if (k < a.cout) {
+          const int c = g * a.cout + k;
+          const int64_t m = a.mult[c], bi = a.bias ? a.bias[c] : 0, r = a.res_mult ? a.res_mult[c] : 0;
+          const int sh = a.shift[c];
+          const int64_t umax = a.acc_bound + (bi < 0 ? -bi : bi) + (r < 0 ? -r : r) * a.res_max;
+          if (sh < 1 || sh > 52 || m < 0 || umax >= ((int64_t)1 << 31) || umax * m >= ((int64_t)1 << 52)) {
+            bad = 1;
+          } else {
+            s = ldexp((double)m, -sh);
+            b = (int32_t)bi + a.wsum[c];
+            rm = (int32_t)r;
+          }
+        }
+        uint8_t *blk = (uint8_t *)a.cst + (int64_t)(i >> 6) * kCstBlock;
+        ((double *)blk)[i & 63] = s;
+        ((int32_t *)blk)[128 + (i & 63)] = b;
+        ((int32_t *)blk)[192 + (i & 63)] = rm;
+        continue;
+      }
       float sc = 0.0f, b = 0.0f, rm = 0.0f;
       if (k < a.cout) {
         const int c = g * a.cout + k;
@@ -165,13 +230,29 @@ __global__ __launch_bounds__(512) void conv_fp_prep_kernel(PrepArgs a) {
   }
   const int64_t t = (int64_t)(blockIdx.x - 1) * 512 + threadIdx.x;
   const int nc32 = a.coutp / 32;
-  if (t >= (int64_t)a.G * nc32 * a.kb * 64) return;
+  if (t >= (int64_t)a.G * nc32 * a.kb * 64 * FpT<B>::J) return;
   const int lane = (int)(t & 63), half = lane >> 5;
-  const int rest = (int)(t >> 6);
+  const int jj = (int)(t >> 6) % FpT<B>::J;  // operand of the K-block
+  const int rest = (int)(t >> 6) / FpT<B>::J;
   const int r2 = rest / a.kb, kb = rest - r2 * a.kb;
   const int g = r2 / nc32, k = (r2 - g * nc32) * 32 + (lane & 31);
   const bool main = kb < a.km;
   const int tap = main ? kb / a.cpb : 0;
+  if constexpr (B == 8) {
+    // codes 32 half + 16 jj .. + 15 of the K-block, sign-extended from w_bits
+    const int c0 = 64 * (main ? kb - tap * a.cpb : kb - a.km) + 32 * half + 16 * jj;
+    const int n = min(16, (main ? a.cin : a.pcin) - c0);
+    const uint8_t *row = main ? a.w + (((int64_t)g * a.cout + k) * a.taps + tap) * a.row
+                              : a.pw + ((int64_t)((g + a.shuffle) % a.G) * a.cout + k) * a.prow;
+    const int sh = 8 - a.w_bits;
+    uint32_t o[4] = {0, 0, 0, 0};
+    if (k < a.cout)
+#pragma unroll
+      for (int e = 0; e < 16; ++e)
+        if (e < n) o[e >> 2] |= (uint32_t)(uint8_t)((int32_t)(int8_t)(row[c0 + e] << sh) >> sh) << (8 * (e & 3));
+    *(uint4 *)(a.wp + (int64_t)rest * FpT<B>::SLAB + (jj * 64 + lane) * 16) = make_uint4(o[0], o[1], o[2], o[3]);
+    return;
+  }
   const int c0 = 64 * (main ? kb - tap * a.cpb : kb - a.km) + 32 * half;  // first code of the lane
   const int n = min(32, (main ? a.cin : a.pcin) - c0);                     // its codes inside the row
   uint32_t u[4] = {0, 0, 0, 0};
@@ -218,6 +299,7 @@ struct FpArgs {
   int32_t *dump;
   uint32_t in_bytes, w_bytes, res_bytes, proj_bytes, cst_bytes;
   int32_t in_pix, in_gs, res_pix, res_gs, proj_pix, proj_gs, out_pix, out_gs;  // bytes, < 2^30
+  const int32_t *wsum;                      // B = 8: 128 sum(w) per channel (DUMP)
   int32_t out_words;                        // words of an output row
   int32_t M, h, w, stride, pad, kh, kw;     // M: output pixels; h, w: the input's
   int32_t hw_out, wo;
@@ -309,6 +391,13 @@ __device__ __forceinline__ uint32_t requant_rd(float u, float sc, uint32_t qmax)
   asm("v_cvt_u32_f32 %0, %1" : "=v"(q) : "v"(y));
   return min(q, qmax);
 }
+// B = 8: floor(u s + 1/2) in fp64 (s = M 2^-sh; exact below 2^52).
+__device__ __forceinline__ uint32_t requant_f64(int32_t u, double s) {
+  const double d = __builtin_fma((double)u, s, 0.5);
+  uint32_t q;
+  asm("v_cvt_u32_f64 %0, %1" : "=v"(q) : "v"(d));
+  return q;
+}
 // Every later fp32 operation that depends on a value passed through here
 // rounds towards minus infinity (asm volatile statements keep their order).
 __device__ __forceinline__ void set_round_down() {
@@ -389,7 +478,7 @@ struct FpCfg {
     return w;
   }
   static_assert(full() > 0, "at most two load counts");
-  static constexpr int RP = TM * (B == 2 ? TN / 64 : TN / 32);  // 16-byte shortcut pieces
+  static constexpr int RP = TM * (B == 2 ? TN / 64 : B == 8 ? TN / 16 : TN / 32);  // 16-byte shortcut pieces
 };
 
 template <int B, int PB, int WN, int WM, int MODE, bool DUMP, int KPS, int S, bool FAST>
@@ -419,7 +508,7 @@ __device__ __forceinline__ void conv_fp_tile(const FpArgs &a) {
           (uint32_t)(((g * a.coutp + id.cbk * TN) / 64 + wave) * 1024));
   if constexpr (MODE == 1) {
     const v4i r_res = rsrc4(a.res, a.res_bytes);
-    constexpr int CBY = B == 2 ? 16 : T::CHS;  // bytes of a piece's channels in the row
+    constexpr int CBY = B == 2 || B == 8 ? 16 : T::CHS;  // bytes of a piece's channels in the row
 #pragma unroll
     for (int i = 0; i < (C::RP + NT - 1) / NT; ++i)
       if (64 * wave + i * NT < C::RP) {
@@ -440,10 +529,12 @@ __device__ __forceinline__ void conv_fp_tile(const FpArgs &a) {
   PixelGeo px[C::XL];
 #pragma unroll
   for (int i = 0; i < C::XL; ++i) {
+    // piece r of a K-block: PPX = 2, lane half r / 32 of 32-pixel block r / 64;
+    // PPX = 4, of MFMA (r / 64) % 2 of block r / 128 (codes 32 half + 16 j ..)
     const int r = (tid + i * NT) % (TM * T::PPX);
-    const int pixel = T::PPX == 1 ? r : 32 * (r >> 6) + (r & 31);
+    const int pixel = T::PPX == 1 ? r : 32 * (r >> (T::PPX == 4 ? 7 : 6)) + (r & 31);
     px[i] = pixel_geo<MODE == 2>(a, m0 + pixel);
-    const int chunk = T::PPX == 1 ? 0 : T::CHS * ((r >> 5) & 1);
+    const int chunk = T::PPX == 1 ? 0 : T::CHS * ((r >> 5) & 1) + (T::PPX == 4 ? 16 * ((r >> 6) & 1) : 0);
     px[i].off0 += g * a.in_gs + chunk;
     if constexpr (MODE == 2) px[i].poff += (uint32_t)(gd * a.proj_gs + chunk);
   }
@@ -479,45 +570,54 @@ __device__ __forceinline__ void conv_fp_tile(const FpArgs &a) {
     if (s < NS) fetch(s, s);
 
   // operands of K-block `sub` of the slot at byte so
-  const int xl = C::WST + (B == 2 ? (wm * PB * 32 + l32) * 16 + half * 8 : (wm * PB * 64 + lane) * 16);
+  constexpr int J = T::J;
+  const int xl = C::WST + (B == 2 ? (wm * PB * 32 + l32) * 16 + half * 8 : (wm * PB * J * 64 + lane) * 16);
   const int al = wn * CB * T::SLAB + lane * 16, bl = wn * CB * T::SLAB + 1024 + lane * 8;
-  struct Ops { v4i x[PB], a0[CB]; v2i a1[CB]; };
+  struct Ops { v4i x[PB][J], a0[CB][J]; v2i a1[CB]; };
   auto read = [&](Ops &o, int so, int sub) __attribute__((always_inline)) {
     const uint8_t *p = lds + so;
 #pragma unroll
     for (int cb = 0; cb < CB; ++cb) {
-      o.a0[cb] = *(const v4i *)(p + al + sub * C::W1 + cb * T::SLAB);
-      if constexpr (B != 2) o.a1[cb] = *(const v2i *)(p + bl + sub * C::W1 + cb * T::SLAB);
+#pragma unroll
+      for (int j = 0; j < J; ++j) o.a0[cb][j] = *(const v4i *)(p + al + sub * C::W1 + cb * T::SLAB + j * 1024);
+      if constexpr (B == 3 || B == 4) o.a1[cb] = *(const v2i *)(p + bl + sub * C::W1 + cb * T::SLAB);
     }
 #pragma unroll
-    for (int pb = 0; pb < PB; ++pb) {
-      if constexpr (B == 2) {
-        const v2i v = *(const v2i *)(p + xl + sub * C::X1 + pb * 512);
-        o.x[pb] = v4i{v[0], v[1], 0, 0};
-      } else {
-        o.x[pb] = *(const v4i *)(p + xl + sub * C::X1 + pb * 1024);
+    for (int pb = 0; pb < PB; ++pb)
+#pragma unroll
+      for (int j = 0; j < J; ++j) {
+        if constexpr (B == 2) {
+          const v2i v = *(const v2i *)(p + xl + sub * C::X1 + pb * 512);
+          o.x[pb][j] = v4i{v[0], v[1], 0, 0};
+        } else {
+          o.x[pb][j] = *(const v4i *)(p + xl + sub * C::X1 + (pb * J + j) * 1024);
+        }
       }
-    }
   };
-  v16f acc[CB][PB];
+  typename T::Acc acc[CB][PB];
   auto mfmas = [&](const Ops &o) __attribute__((always_inline)) {
-    v8i A[CB];
 #pragma unroll
-    for (int cb = 0; cb < CB; ++cb) {
-      if constexpr (B == 2) A[cb] = __builtin_shufflevector(o.a0[cb], o.a0[cb], 0, 1, 2, 3, -1, -1, -1, -1);
-      else A[cb] = v8i{o.a0[cb][0], o.a0[cb][1], o.a0[cb][2], o.a0[cb][3], o.a1[cb][0], o.a1[cb][1], 0, 0};
-    }
+    for (int pb = 0; pb < PB; ++pb)
 #pragma unroll
-    for (int pb = 0; pb < PB; ++pb) {
-      const v8i X = act_fp<B>(o.x[pb]);
+      for (int j = 0; j < J; ++j) {
+        if constexpr (B == 8) {
+          const v4i X = flip_i8(o.x[pb][j]);
 #pragma unroll
-      for (int cb = 0; cb < CB; ++cb) acc[cb][pb] = mfma_fp<B>(A[cb], X, acc[cb][pb]);
-    }
+          for (int cb = 0; cb < CB; ++cb)
+            acc[cb][pb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(o.a0[cb][j], X, acc[cb][pb], 0, 0, 0);
+        } else {
+          const v8i X = act_fp<B>(o.x[pb][j]);
+#pragma unroll
+          for (int cb = 0; cb < CB; ++cb) acc[cb][pb] = mfma_fp<B>(wt_fp<B>(o.a0[cb][j], o.a1[cb]), X, acc[cb][pb]);
+        }
+      }
   };
 
   const bool more = C::LMAX != C::LMIN && wave < C::full();
   int so = 0, slot_f = S - 1;  // byte offset of the stage's slot; slot of the next fetch
   const float *cst = (const float *)(lds + RING) + wn * 256;
+  const double *csd = (const double *)cst;                // B = 8
+  const int32_t *csi = (const int32_t *)cst;
   for (int s = 0; s < NS; ++s) {
     // stage s has landed; up to S - 2 younger ones may be in flight
     if (s + S - 2 < NS) {
@@ -537,11 +637,14 @@ __device__ __forceinline__ void conv_fp_tile(const FpArgs &a) {
       for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
         for (int qi = 0; qi < 4; ++qi) {
-          const v4f b = *(const v4f *)(cst + 64 + cb * 32 + 8 * qi + 4 * half);
+          const int c0 = cb * 32 + 8 * qi + 4 * half;
 #pragma unroll
           for (int e = 0; e < 4; ++e)
 #pragma unroll
-            for (int pb = 0; pb < PB; ++pb) acc[cb][pb][4 * qi + e] = b[e];
+            for (int pb = 0; pb < PB; ++pb) {
+              if constexpr (B == 8) acc[cb][pb][4 * qi + e] = csi[128 + c0 + e];
+              else acc[cb][pb][4 * qi + e] = cst[64 + c0 + e];
+            }
         }
     }
 #pragma unroll
@@ -565,13 +668,65 @@ __device__ __forceinline__ void conv_fp_tile(const FpArgs &a) {
         for (int r = 0; r < 16; ++r) {
           const int c = cb * 32 + 8 * (r >> 2) + 4 * half + (r & 3), m = mw + pb * 32 + l32;
           if (m < a.M && ch0 + c < a.cout)
-            a.dump[((int64_t)m * a.G + gd) * a.cout + ch0 + c] =
-                (int)((acc[cb][pb][r] - cst[64 + c]) * (float)(1 << T::L));
+            if constexpr (B == 8)  // without bias and 128 sum(w), exact modulo 2^32
+              a.dump[((int64_t)m * a.G + gd) * a.cout + ch0 + c] =
+                  acc[cb][pb][r] - csi[128 + c] + a.wsum[g * a.cout + ch0 + c];
+            else
+              a.dump[((int64_t)m * a.G + gd) * a.cout + ch0 + c] =
+                  (int)((acc[cb][pb][r] - cst[64 + c]) * (float)(1 << T::L));
         }
   }
   constexpr uint32_t qmax = (1u << B) - 1u;
   uint32_t w2[CB][PB];
-  if constexpr (FAST) {
+  if constexpr (B == 8) {
+    const uint32_t q8 = (1u << a.out_bits) - 1u;
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) {
+      uint32_t qv[PB][4];
+#pragma unroll
+      for (int qi = 0; qi < 4; ++qi) {
+        __builtin_amdgcn_sched_barrier(0);
+        const int c0 = cb * 32 + 8 * qi + 4 * half;
+        double sc[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sc[e] = csd[c0 + e];
+        v4i rm = {0, 0, 0, 0};
+        if constexpr (MODE == 1) rm = *(const v4i *)(csi + 192 + c0);
+#pragma unroll
+        for (int pb = 0; pb < PB; ++pb) {
+          uint32_t rc = 0, w = 0;
+          if constexpr (MODE == 1)
+            rc = *(const uint32_t *)(lds + RING + CST +
+                                     ((wn * 4 + cb * 2 + (qi >> 1)) * TM + wm * PB * 32 + pb * 32 + l32) * 16 +
+                                     8 * (qi & 1) + 4 * half);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            int32_t u = acc[cb][pb][4 * qi + e];
+            if constexpr (MODE == 1) u += rm[e] * (int32_t)((rc >> (8 * e)) & 255u);
+            w |= min(requant_f64(u, sc[e]), q8) << (8 * e);
+          }
+          qv[pb][qi] = w;
+        }
+      }
+      const int wq = (ch0 + cb * 32) / 4 + 4 * half;  // the lane's 16 channels: their first word of the row
+#pragma unroll
+      for (int pb = 0; pb < PB; ++pb) {
+        const auto p0 = __builtin_amdgcn_permlane32_swap(qv[pb][0], qv[pb][2], false, false);  // as below
+        const auto p1 = __builtin_amdgcn_permlane32_swap(qv[pb][1], qv[pb][3], false, false);
+        const int m = mw + pb * 32 + l32;
+        if (m >= a.M) continue;
+        uint32_t *cw = (uint32_t *)(a.out + (int64_t)m * a.out_pix + (int64_t)gd * a.out_gs) + wq;
+        const uint32_t v[4] = {p0[0], p0[1], p1[0], p1[1]};
+        if (wq + 4 <= a.out_words) {
+          *(uint4 *)cw = make_uint4(v[0], v[1], v[2], v[3]);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (wq + e < a.out_words) cw[e] = v[e];
+        }
+      }
+    }
+  } else if constexpr (FAST) {
     // 2-bit codes, 2.1 VALU instructions a value instead of 4.3 (and 2 instead
     // of 3 for a shortcut): both ways between codes and floats by the FP4
     // conversions, even and odd codes in nibbles of their own
@@ -750,9 +905,10 @@ __device__ __forceinline__ void conv_fp_tile(const FpArgs &a) {
 template <int B, int PB, int NW, int MODE, bool DUMP>
 __device__ __forceinline__ void conv_fp_split(const FpArgs &a) {
   using T = FpT<B>;
-  constexpr int U = 4, Q = PB * 4;
+  constexpr int U = B == 8 ? 2 : 4, Q = PB * 4;
+  using V4 = typename std::conditional<B == 8, v4i, v4f>::type;
   static_assert(Q % NW == 0 || NW % Q == 0, "whole quads per wave");
-  __shared__ v4f red[NW * Q * 64];
+  __shared__ V4 red[NW * Q * 64];
   __shared__ uint32_t cw[32 * PB * 9];  // packed quads of a pixel's 32 channels (9: no bank conflicts)
   if (a.gated && a.bad[0] != 0) return;
   TileId id;
@@ -772,6 +928,7 @@ __device__ __forceinline__ void conv_fp_split(const FpArgs &a) {
   }
   const int row_adj = (a.w - a.kw) * a.in_pix;
   const int slab0 = (g * (a.coutp / 32) + id.cbk) * KB;
+  constexpr int J = T::J;
   auto load_x = [&](auto rs, uint32_t vo, int so) __attribute__((always_inline)) {
     v4i x = {0, 0, 0, 0};
     if constexpr (B == 2) {
@@ -788,50 +945,60 @@ __device__ __forceinline__ void conv_fp_split(const FpArgs &a) {
     }
     return x;
   };
-  v16f acc[PB];
+  typename T::Acc acc[PB];
 #pragma unroll
   for (int pb = 0; pb < PB; ++pb)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[pb][r] = 0.0f;
+    for (int r = 0; r < 16; ++r) acc[pb][r] = 0;
   for (int k0 = wave; k0 < KB; k0 += NW * U) {
-    v4i x[U][PB], w0[U];
+    v4i x[U][PB][J], w0[U][J];
     v2i w1[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int kb = k0 + u * NW;
       if (kb >= KB) break;  // uniform
       const int so = (slab0 + kb) * T::SLAB;
-      w0[u] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(r_w, lane * 16, so, 0));
-      if constexpr (B != 2)
+#pragma unroll
+      for (int j = 0; j < J; ++j)
+        w0[u][j] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(r_w, lane * 16 + j * 1024, so, 0));
+      if constexpr (B == 3 || B == 4)
         w1[u] = __builtin_bit_cast(v2i, __builtin_amdgcn_raw_buffer_load_b64(r_w, 1024 + lane * 8, so, 0));
       if (MODE == 2 && kb >= a.km) {
         const auto r_pj = __builtin_amdgcn_make_buffer_rsrc((void *)a.proj, (short)0, (int)a.proj_bytes, 0x00020000);
 #pragma unroll
-        for (int pb = 0; pb < PB; ++pb) x[u][pb] = load_x(r_pj, px[pb].poff, (kb - a.km) * T::XB);
+        for (int pb = 0; pb < PB; ++pb)
+#pragma unroll
+          for (int j = 0; j < J; ++j) x[u][pb][j] = load_x(r_pj, px[pb].poff + 16 * j, (kb - a.km) * T::XB);
       } else {
         const int tap = (int)a.d_cpb.div((uint32_t)kb), ky = (int)a.d_kw.div((uint32_t)tap);
         const int tapoff = tap * a.in_pix + ky * row_adj;
 #pragma unroll
         for (int pb = 0; pb < PB; ++pb) {
           const uint32_t o = (uint32_t)__builtin_amdgcn_sbfe((int)px[pb].out_mask, (uint32_t)tap, 1u);
-          x[u][pb] = load_x(r_in, (uint32_t)(px[pb].off0 + tapoff) | (o & kOob), (kb - tap * a.cpb) * T::XB);
+#pragma unroll
+          for (int j = 0; j < J; ++j)
+            x[u][pb][j] = load_x(r_in, (uint32_t)(px[pb].off0 + tapoff + 16 * j) | (o & kOob), (kb - tap * a.cpb) * T::XB);
         }
       }
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if (k0 + u * NW >= KB) break;
-      v8i A;
-      if constexpr (B == 2) A = __builtin_shufflevector(w0[u], w0[u], 0, 1, 2, 3, -1, -1, -1, -1);
-      else A = v8i{w0[u][0], w0[u][1], w0[u][2], w0[u][3], w1[u][0], w1[u][1], 0, 0};
 #pragma unroll
-      for (int pb = 0; pb < PB; ++pb) acc[pb] = mfma_fp<B>(A, act_fp<B>(x[u][pb]), acc[pb]);
+      for (int pb = 0; pb < PB; ++pb)
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+          if constexpr (B == 8)
+            acc[pb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(w0[u][j], flip_i8(x[u][pb][j]), acc[pb], 0, 0, 0);
+          else
+            acc[pb] = mfma_fp<B>(wt_fp<B>(w0[u][j], w1[u]), act_fp<B>(x[u][pb][j]), acc[pb]);
+        }
     }
   }
 #pragma unroll
   for (int j = 0; j < Q; ++j) {
-    const v16f &v = acc[j >> 2];
-    red[(wave * Q + j) * 64 + lane] = v4f{v[4 * (j & 3)], v[4 * (j & 3) + 1], v[4 * (j & 3) + 2], v[4 * (j & 3) + 3]};
+    const auto &v = acc[j >> 2];
+    red[(wave * Q + j) * 64 + lane] = V4{v[4 * (j & 3)], v[4 * (j & 3) + 1], v[4 * (j & 3) + 2], v[4 * (j & 3) + 3]};
   }
   __syncthreads();
   const int k32 = id.cbk * 32;  // the tile's first channel of the group
@@ -840,12 +1007,35 @@ __device__ __forceinline__ void conv_fp_split(const FpArgs &a) {
   for (int j0 = 0; j0 < Q; j0 += NW) {
     const int j = j0 + wave;  // quad j: pixel block j / 4, channels 8 (j % 4) + 4 half .. + 3
     if (j >= Q) break;
-    v4f v = red[j * 64 + lane];
+    V4 v = red[j * 64 + lane];
 #pragma unroll
     for (int w = 1; w < NW; ++w) v += red[(w * Q + j) * 64 + lane];
     const int qi = j & 3, pixel = 32 * (j >> 2) + l32, m = m0 + pixel;
     const int c0 = 8 * qi + 4 * half;
-    const float *cst = a.cst + (int64_t)((g * a.coutp + k32) >> 6) * 256 + (k32 & 32) + c0;
+    const float *blk = a.cst + (int64_t)((g * a.coutp + k32) >> 6) * (kCstBlock / 4);
+    if constexpr (B == 8) {
+      const double *sc = (const double *)blk + (k32 & 32) + c0;
+      const int32_t *ci = (const int32_t *)blk + 128 + (k32 & 32) + c0;
+      const uint32_t q8 = (1u << a.out_bits) - 1u;
+      uint32_t rc = 0, w = 0;
+      if constexpr (MODE == 1) {
+        const auto r_res = __builtin_amdgcn_make_buffer_rsrc((void *)a.res, (short)0, (int)a.res_bytes, 0x00020000);
+        const uint32_t vo = m < a.M ? (uint32_t)(m * a.res_pix + gd * a.res_gs + c0) : kOob;
+        rc = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(r_res, (int)vo, k32, 0);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        int32_t u = v[e] + ci[e];
+        if constexpr (DUMP)
+          if (m < a.M && k32 + c0 + e < a.cout)
+            a.dump[((int64_t)m * a.G + gd) * a.cout + k32 + c0 + e] = v[e] + a.wsum[g * a.cout + k32 + c0 + e];
+        if constexpr (MODE == 1) u += ci[64 + e] * (int32_t)((rc >> (8 * e)) & 255u);
+        w |= min(requant_f64(u, sc[e]), q8) << (8 * e);
+      }
+      cw[pixel * 9 + 2 * qi + half] = w;
+      continue;
+    } else {
+    const float *cst = blk + (k32 & 32) + c0;
     const v4f sc = *(const v4f *)cst, b = *(const v4f *)(cst + 64);
     float rcode[4] = {0.0f, 0.0f, 0.0f, 0.0f};
     v4f rm = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -879,6 +1069,7 @@ __device__ __forceinline__ void conv_fp_split(const FpArgs &a) {
       }
     }
     cw[pixel * 9 + 2 * qi + half] = w | (h << 16);
+    }
   }
   __syncthreads();
   for (int i = tid; i < 32 * PB * B; i += NW * 64) {
@@ -886,7 +1077,9 @@ __device__ __forceinline__ void conv_fp_split(const FpArgs &a) {
     if (m >= a.M || wd >= a.out_words) continue;
     const uint32_t *q = cw + pixel * 9;
     uint32_t v;
-    if constexpr (B == 4) {
+    if constexpr (B == 8) {
+      v = q[wi];
+    } else if constexpr (B == 4) {
       v = q[2 * wi] | (q[2 * wi + 1] << 16);
     } else if (B == 3 && wi == 2) {
       v = 0;
@@ -904,7 +1097,7 @@ __device__ __forceinline__ void conv_fp_split(const FpArgs &a) {
 // Entry points by matrix-core format.
 #define PALQ_FP_TILE(NAME)                                                                            \
   template <int B, int PB, int WN, int WM, int MODE, bool DUMP, int KPS, int S, bool FAST>    \
-  __global__ __launch_bounds__(WN *WM * 64, B == 2 ? 4 : 3) void NAME(FpArgs a) {  \
+  __global__ __launch_bounds__(WN *WM * 64, B == 2 ? 4 : B == 8 ? 2 : 3) void NAME(FpArgs a) {  \
     conv_fp_tile<B, PB, WN, WM, MODE, DUMP, KPS, S, FAST>(a);                                     \
   }
 #define PALQ_FP_SPLIT(NAME)                                                     \
@@ -914,8 +1107,10 @@ __device__ __forceinline__ void conv_fp_split(const FpArgs &a) {
   }
 PALQ_FP_TILE(conv_fp4_kernel)
 PALQ_FP_TILE(conv_fp6_kernel)
+PALQ_FP_TILE(conv_i8_kernel)
 PALQ_FP_SPLIT(conv_fp4_split_kernel)
 PALQ_FP_SPLIT(conv_fp6_split_kernel)
+PALQ_FP_SPLIT(conv_i8_split_kernel)
 
 // ------------------------------------------------------------ host side
 int64_t code_max(int bits, int is_signed) {
@@ -931,7 +1126,7 @@ int cpb_of(int cin) { return (cin + 63) / 64; }
 int fp_km(const ConvArgs &a) { return a.kh * a.kw * cpb_of(a.in.cpg); }
 int fp_kb(const ConvArgs &a) { return fp_km(a) + (a.proj.data ? cpb_of(a.proj.cpg) : 0); }
 int fp_coutp(const ConvArgs &a) { return (a.cout + 63) / 64 * 64; }
-int64_t fp_slab(int bits) { return bits == 2 ? 1024 : 1536; }
+int64_t fp_slab(int bits) { return bits == 2 ? 1024 : bits >= 6 ? 2048 : 1536; }
 
 FpArgs fp_args(const ConvArgs &a, const uint8_t *wp, const int32_t *thr, bool checked) {
   FpArgs f{};
@@ -1013,7 +1208,9 @@ int cu_count() {
 template <int B, int PB, int WN, int WM, int MODE, bool DUMP, int KPS, int S>
 hipError_t launch_tile_mode(const FpArgs &f, unsigned grid, hipStream_t s) {
   const dim3 block(WN * WM * 64);
-  if constexpr (B != 2)
+  if constexpr (B == 8)
+    hipLaunchKernelGGL((conv_i8_kernel<B, PB, WN, WM, MODE, DUMP, KPS, S, false>), dim3(grid), block, 0, s, f);
+  else if constexpr (B != 2)
     hipLaunchKernelGGL((conv_fp6_kernel<B, PB, WN, WM, MODE, DUMP, KPS, S, false>), dim3(grid), block, 0, s, f);
   else if (f.fast)
     hipLaunchKernelGGL((conv_fp4_kernel<B, PB, WN, WM, MODE, DUMP, KPS, S, true>), dim3(grid), block, 0, s, f);
@@ -1035,6 +1232,9 @@ hipError_t launch_split_mode(const FpArgs &f, unsigned grid, hipStream_t s) {
   if constexpr (B == 2) {
     if (f.dump) hipLaunchKernelGGL((conv_fp4_split_kernel<B, PB, NW, MODE, true>), dim3(grid), block, 0, s, f);
     else hipLaunchKernelGGL((conv_fp4_split_kernel<B, PB, NW, MODE, false>), dim3(grid), block, 0, s, f);
+  } else if constexpr (B == 8) {
+    if (f.dump) hipLaunchKernelGGL((conv_i8_split_kernel<B, PB, NW, MODE, true>), dim3(grid), block, 0, s, f);
+    else hipLaunchKernelGGL((conv_i8_split_kernel<B, PB, NW, MODE, false>), dim3(grid), block, 0, s, f);
   } else {
     if (f.dump) hipLaunchKernelGGL((conv_fp6_split_kernel<B, PB, NW, MODE, true>), dim3(grid), block, 0, s, f);
     else hipLaunchKernelGGL((conv_fp6_split_kernel<B, PB, NW, MODE, false>), dim3(grid), block, 0, s, f);
@@ -1065,28 +1265,39 @@ hipError_t launch_fp(const FpArgs &f, int64_t in_bytes, hipStream_t s) {
   const int64_t cus = cu_count();
   const int64_t few = (int64_t)((f.M + 63) / 64) * ((f.cout + 31) / 32) * f.G;
   if (few <= 2 * cus || (few <= 4 * cus && f.kb >= 64)) return launch_split<B, 2, 8>(f, in_bytes, s);
-  if (f.dump) return launch_tile<B, 2, 1, 4, true, 2, 2>(f, in_bytes, s);
+  if (f.dump) return launch_tile<B, 2, 1, 4, true, B == 8 ? 1 : 2, B == 8 ? 3 : 2>(f, in_bytes, s);
   const bool wide = f.coutp % 128 == 0;
-  if (f.kb < 12)
+  if (B == 8 || f.kb < 12)
     return wide ? launch_tile<B, 2, 2, 2, false, 1, 3>(f, in_bytes, s)
                 : launch_tile<B, 2, 1, 4, false, 1, 3>(f, in_bytes, s);
-  return wide ? launch_tile<B, 2, 2, 2, false, 2, 2>(f, in_bytes, s)
-              : launch_tile<B, 2, 1, 4, false, 2, 2>(f, in_bytes, s);
+  if constexpr (B != 8)
+    return wide ? launch_tile<B, 2, 2, 2, false, 2, 2>(f, in_bytes, s)
+                : launch_tile<B, 2, 1, 4, false, 2, 2>(f, in_bytes, s);
+  return hipErrorNotSupported;
 }
 
 }  // namespace
 
-// 2-, 3- and 4-bit layers with filter, output and shortcut codes of the same
+// Layers on the int8 form (6- and 8-bit codes): 128 sum(w) per channel follows the slabs.
+static bool fp_is_i8(const ConvArgs &a) { return a.in.bits >= 6; }
+static size_t fp_slab_bytes(const ConvArgs &a) {
+  return (size_t)a.in.groups * fp_coutp(a) / 32 * fp_kb(a) * fp_slab(a.in.bits);
+}
+
+// 2-, 3- and 4-bit layers (unless the context keeps them on int8) and 6- and
+// 8-bit ones, with filter, output and shortcut codes of the same
 // width, whose accumulator bound leaves the fp32 accumulator room for bias and
 // shortcut (each channel is checked on the device), tensors and slabs the
 // buffer loads can address, and a tap mask of 32 bits.
 bool conv_fp_applies(const ConvArgs &a) {
   const int b = a.in.bits;
-  if (!a.fp4 || a.in.is_signed || (b != 2 && b != 3 && b != 4) || a.w_bits != b || a.out.bits != b) return false;
-  if (a.bitdecomp && b == 4) return false;
+  const bool i8 = b == 6 || b == 8;
+  if (a.in.is_signed || (!i8 && (!a.fp4 || (b != 2 && b != 3 && b != 4))) || a.w_bits != b || a.out.bits != b)
+    return false;
+  if (a.bitdecomp && b >= 4) return false;
   if (a.res.data && (a.res.bits != b || a.res.is_signed)) return false;
   if (a.proj.data && (a.proj.bits != b || a.proj.is_signed)) return false;
-  if ((int64_t)a.kh * a.kw > 32 || fp_acc_bound(a) >= ((int64_t)1 << 23)) return false;
+  if ((int64_t)a.kh * a.kw > 32 || fp_acc_bound(a) >= ((int64_t)1 << (i8 ? 30 : 23))) return false;
   const int64_t lim = (int64_t)1 << 30;
   auto bytes = [](const ActView &v) { return v.data ? v.bytes : 0; };
   if (bytes(a.in) >= lim || bytes(a.out) >= lim || bytes(a.res) >= lim || bytes(a.proj) >= lim) return false;
@@ -1099,7 +1310,11 @@ bool conv_fp_applies(const ConvArgs &a) {
 
 ConvPlan conv_fp_plan(const ConvArgs &a) {
   const int64_t ch = (int64_t)a.in.groups * fp_coutp(a);
-  return {(size_t)(ch / 32 * fp_kb(a) * fp_slab(a.in.bits)), (size_t)(ch * 16 + 16)};
+  return {fp_slab_bytes(a) + (fp_is_i8(a) ? (size_t)a.in.groups * a.cout * 4 : 0), (size_t)(ch * 16 + 16)};
+}
+
+const int32_t *conv_fp_wsum(const ConvArgs &a, const uint8_t *wp) {
+  return fp_is_i8(a) ? (const int32_t *)(wp + fp_slab_bytes(a)) : nullptr;
 }
 
 const int32_t *conv_fp_flag(const ConvArgs &a, const int32_t *thr) {
@@ -1128,17 +1343,27 @@ hipError_t launch_conv_fp_prepare(const ConvArgs &a, uint8_t *wp, int32_t *thr, 
   p.wp = wp;
   p.cst = (float *)thr;
   p.bad = (int32_t *)conv_fp_flag(a, thr);
-  const int64_t lanes = (int64_t)p.G * (p.coutp / 32) * p.kb * 64;
+  p.w_bits = a.w_bits;
+  if (fp_is_i8(a)) {
+    p.wsum = (int32_t *)(wp + fp_slab_bytes(a));
+    hipLaunchKernelGGL(wsum_i8_kernel, dim3((unsigned)((p.G * p.cout + 3) / 4)), dim3(256), 0, s, p);
+  }
+  const int64_t lanes = (int64_t)p.G * (p.coutp / 32) * p.kb * 64 * (fp_is_i8(a) ? 2 : 1);
   const dim3 grid((unsigned)(1 + (lanes + 511) / 512));
   if (a.in.bits == 2) hipLaunchKernelGGL(conv_fp_prep_kernel<2>, grid, dim3(512), 0, s, p);
   else if (a.in.bits == 3) hipLaunchKernelGGL(conv_fp_prep_kernel<3>, grid, dim3(512), 0, s, p);
-  else hipLaunchKernelGGL(conv_fp_prep_kernel<4>, grid, dim3(512), 0, s, p);
+  else if (a.in.bits == 4) hipLaunchKernelGGL(conv_fp_prep_kernel<4>, grid, dim3(512), 0, s, p);
+  else hipLaunchKernelGGL(conv_fp_prep_kernel<8>, grid, dim3(512), 0, s, p);
   return hipGetLastError();
 }
 
 hipError_t launch_conv_fp(const ConvArgs &a, const uint8_t *wp, const int32_t *thr, bool checked, hipStream_t s) {
   if ((int64_t)a.out.n * a.ho * a.wo == 0) return hipSuccess;
-  const FpArgs f = fp_args(a, wp, thr, checked);
+  FpArgs f = fp_args(a, wp, thr, checked);
+  if (fp_is_i8(a)) {
+    f.wsum = conv_fp_wsum(a, wp);
+    return launch_fp<8>(f, a.in.bytes, s);
+  }
   if (a.in.bits == 2) return launch_fp<2>(f, a.in.bytes, s);
   if (a.in.bits == 3) return launch_fp<3>(f, a.in.bytes, s);
   return launch_fp<4>(f, a.in.bytes, s);

@@ -2398,7 +2398,7 @@ size_t conv_noalloc_bytes(const ConvArgs &a) {
   if (!conv_fp_applies(a) || !int8_shape(a)) return actual;
   const size_t nch = (size_t)a.in.groups * a.cout, kb = make_geo(a).kb_total;
   const bool shortcut = a.res.data || a.proj.data;
-  size_t w = nch * kb * 64, thr = nch * sizeof(RqConst) + 16;
+  size_t w = nch * kb * 64 + (a.in.bits >= 6 ? nch * 4 : 0), thr = nch * sizeof(RqConst) + 16;
   if (a.in.bits == 2 && a.cout % 64 == 0) {
     w += nch * kb * 32;
     thr = 2 * thr + nch * 12 + 16;
@@ -2406,7 +2406,7 @@ size_t conv_noalloc_bytes(const ConvArgs &a) {
     w += nch * kb * 48;
     thr *= 2;
   }
-  return std::max(actual, ((w + 255) & ~(size_t)255) + thr);
+  return ((w + 255) & ~(size_t)255) + thr;
 }
 
 hipError_t launch_conv_prepare(const ConvArgs &a, uint8_t *wp, int32_t *thr, hipStream_t s) {
@@ -2732,7 +2732,8 @@ const char *conv_kernel_label(const ConvArgs &a, int epi) {
   const Geo geo = make_geo(a);
   switch (conv_choice(a, geo, epi).tile) {
     case kTileStem: return "conv_tile_kernel[stem]";
-    case kTileFp: return a.in.bits == 2 ? "conv_fp4_kernel" : "conv_fp6_kernel";
+    case kTileFp:
+      return a.in.bits == 2 ? "conv_fp4_kernel" : a.in.bits >= 6 ? "conv_i8_kernel" : "conv_fp6_kernel";
     case kTileBdC64: case kTileBdC128: return "conv_bitdecomp_kernel";
     case kTileI8C64: case kTileI8C128: return "conv_tile_kernel[int8]";
     default: return is_stem(a) ? "conv_stem_kernel" : "conv_grouped_kernel";
@@ -2754,6 +2755,7 @@ hipError_t launch_conv_mfma(const ConvArgs &a_in, const uint8_t *wp, const int32
     // the general partner takes the packed filter and the int64 requant
     geo.wp = nullptr;
     geo.rq = nullptr;
+    geo.acc0 = conv_fp_wsum(a, wp);
     a.gated = 1;
     if (c.tile == kTileFp) {
       geo.gate = conv_fp_flag(a, thr);
@@ -2795,7 +2797,7 @@ hipError_t launch_conv_mfma(const ConvArgs &a_in, const uint8_t *wp, const int32
     case 3: return dispatch_bits<3>(a, geo, cb, pb, epi, s);
     case 4: return dispatch_bits<4>(a, geo, cb, pb, epi, s);
     case 6: case 8:
-      geo.acc0 = (const int32_t *)(wp + (size_t)nch * geo.kb_total * 64);
+      if (!geo.acc0) geo.acc0 = (const int32_t *)(wp + (size_t)nch * geo.kb_total * 64);
       return dispatch_bits<8>(a, geo, cb, pb, epi, s);
   }
   return hipErrorNotSupported;

@@ -384,18 +384,21 @@ palq_status group_conv_impl(palq_ctx *ctx, const palq_act *in, const palq_filter
   if (pin) { a.proj = view_of(pin); a.proj_w = (const uint8_t *)pw->data; a.proj_stride = res->proj_stride; }
   a.acc_dump = acc_dump;
   bool mfma = conv_mfma_supported(a);
-  // a layer that only the FP4 / FP6 kernels take and whose slabs exceed the
-  // static buffer runs on the direct kernel, which needs none
-  if (noalloc && mfma && !conv_mfma_general_fits(a) && conv_noalloc_bytes(a) > (size_t)PALQ_NOALLOC_SCRATCH_BYTES &&
-      (a.in.cpg % 64 != 0 || a.cout % 32 != 0 || (a.proj.data && a.proj.cpg % 64 != 0)))
-    mfma = false;
-  const ConvPlan plan = mfma ? conv_mfma_plan(a) : ConvPlan{0, 0};
-  const size_t wbytes = (plan.w_bytes + 255) & ~(size_t)255;
-  const size_t need = wbytes + plan.thr_bytes;
+  if (noalloc && mfma && (a.in.cpg % 64 != 0 || a.cout % 32 != 0 || (a.proj.data && a.proj.cpg % 64 != 0))) {
+    // a channel count that only the padded kernels take: without room for its
+    // slabs it runs on the direct kernel, which needs none
+    const ConvPlan p = conv_mfma_plan(a);
+    if (((p.w_bytes + 255) & ~(size_t)255) + p.thr_bytes > (size_t)PALQ_NOALLOC_SCRATCH_BYTES) mfma = false;
+  }
   if (noalloc && mfma && conv_noalloc_bytes(a) > (size_t)PALQ_NOALLOC_SCRATCH_BYTES)
     return fail(ctx, PALQ_ERR_UNSUPPORTED,
                 "no-alloc call: the prepacked filter and requant constants need " + std::to_string(conv_noalloc_bytes(a)) +
                     " bytes; the library's static buffer holds " + std::to_string((long long)PALQ_NOALLOC_SCRATCH_BYTES));
+  const ConvPlan plan = mfma ? conv_mfma_plan(a) : ConvPlan{0, 0};
+  const size_t wbytes = (plan.w_bytes + 255) & ~(size_t)255;
+  const size_t need = wbytes + plan.thr_bytes;
+  // (slabs padded to 64 channels may pass the buffer where the documented size does not)
+  if (noalloc && need > (size_t)PALQ_NOALLOC_SCRATCH_BYTES) mfma = false;
   if (ctx->device < 0 || out->n == 0) return PALQ_OK;
   hipSetDevice(ctx->device);
   hipError_t e;

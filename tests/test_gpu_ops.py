@@ -452,7 +452,7 @@ def test_conv_fp6_builds(ctx, torch, name):
     check_full(ctx, torch, case)
 
 
-# The FP4 / FP6 builds at the edges of their tiles: few tiles (the split
+# The FP4 / FP6 / int8 builds at the edges of their tiles: few tiles (the split
 # kernel: fewer and more K-blocks than its 8 waves), 64- and 128-channel tiles
 # with stages of one and of two K-blocks (from 12 K-blocks on; odd counts) and a
 # ragged last pixel tile, channel counts that are no multiple of 64, 32, 16 or 8
@@ -460,7 +460,8 @@ def test_conv_fp6_builds(ctx, torch, name):
 # shortcut.
 FP_EDGE_CASES = {
     "split_ragged": dict(n=1, h=7, w=9, groups=3, cin=24, cout=40, residual="identity"),
-    "split_one_kblock": dict(n=2, h=9, w=8, groups=2, cin=20, cout=33, k=1, pad=0),
+    # (28 thousand outputs, over a hundred for each of the 256 8-bit codes)
+    "split_one_kblock": dict(n=6, h=9, w=8, groups=2, cin=20, cout=33, k=1, pad=0),
     "split_deep": dict(n=1, h=7, w=7, groups=2, cin=264, cout=96, stride=2, residual="projection"),
     "split_5x5": dict(n=2, h=11, w=10, groups=2, cin=70, cout=100, k=5, pad=2, stride=3),
     "c64_ragged": dict(n=3, h=43, w=41, groups=3, cin=72, cout=200, residual="identity"),
@@ -474,7 +475,7 @@ FP_EDGE_CASES = {
 }
 
 
-@pytest.mark.parametrize("bits", [2, 3, 4])
+@pytest.mark.parametrize("bits", [2, 3, 4, 6, 8])
 @pytest.mark.parametrize("name", sorted(FP_EDGE_CASES))
 def test_conv_fp_edges(ctx, torch, name, bits):
     case = I.single_layer(2600 + sorted(FP_EDGE_CASES).index(name), bits=bits, **FP_EDGE_CASES[name])
