@@ -2366,12 +2366,15 @@ static bool int8_shape(const ConvArgs &a) {
 
 bool conv_mfma_general_fits(const ConvArgs &a) { return int8_shape(a) && pick_cb(a, make_geo(a)) > 0; }
 
-bool conv_mfma_supported(const ConvArgs &a) {
-  if (conv_fp_applies(a)) return true;
-  // the general build needs the filter in LDS; layers longer than that
-  // still run on the tiled kernel (its fast epilogue)
+// The general build needs the filter in LDS; layers longer than that still
+// run on the tiled kernel (its fast epilogue).
+static bool int8_build(const ConvArgs &a) {
   return int8_shape(a) && (pick_cb(a, make_geo(a)) > 0 || tile_kernel_applies(a) || stem_tile_applies(a));
 }
+
+bool conv_mfma_supported(const ConvArgs &a) { return conv_fp_applies(a) || int8_build(a); }
+
+bool conv_direct_partner(const ConvArgs &a) { return !int8_build(a); }
 
 ConvPlan conv_mfma_plan(const ConvArgs &a) {
   if (conv_fp_applies(a)) return conv_fp_plan(a);

@@ -384,13 +384,14 @@ palq_status group_conv_impl(palq_ctx *ctx, const palq_act *in, const palq_filter
   if (pin) { a.proj = view_of(pin); a.proj_w = (const uint8_t *)pw->data; a.proj_stride = res->proj_stride; }
   a.acc_dump = acc_dump;
   bool mfma = conv_mfma_supported(a);
-  if (noalloc && mfma && (a.in.cpg % 64 != 0 || a.cout % 32 != 0 || (a.proj.data && a.proj.cpg % 64 != 0))) {
-    // a channel count that only the padded kernels take: without room for its
-    // slabs it runs on the direct kernel, which needs none
+  // a layer that only the padded kernels take: without room for its slabs it
+  // runs on the direct kernel, which needs none
+  const bool direct_ok = mfma && conv_direct_partner(a);
+  if (noalloc && direct_ok) {
     const ConvPlan p = conv_mfma_plan(a);
     if (((p.w_bytes + 255) & ~(size_t)255) + p.thr_bytes > (size_t)PALQ_NOALLOC_SCRATCH_BYTES) mfma = false;
   }
-  if (noalloc && mfma && conv_noalloc_bytes(a) > (size_t)PALQ_NOALLOC_SCRATCH_BYTES)
+  if (noalloc && mfma && !direct_ok && conv_noalloc_bytes(a) > (size_t)PALQ_NOALLOC_SCRATCH_BYTES)
     return fail(ctx, PALQ_ERR_UNSUPPORTED,
                 "no-alloc call: the prepacked filter and requant constants need " + std::to_string(conv_noalloc_bytes(a)) +
                     " bytes; the library's static buffer holds " + std::to_string((long long)PALQ_NOALLOC_SCRATCH_BYTES));
@@ -409,15 +410,28 @@ palq_status group_conv_impl(palq_ctx *ctx, const palq_act *in, const palq_filter
     int32_t *thr = (int32_t *)(base + wbytes);
     e = launch_conv_prepare(a, wp, thr, ctx->stream);
     if (e == hipSuccess) e = launch_conv_mfma(a, wp, thr, -1, ctx->stream);
-  } else if (mfma) {
-    if (need > ctx->conv_scratch_bytes) {
+    return e == hipSuccess ? PALQ_OK : device_fail(ctx, e, "group conv");
+  }
+  if (mfma && need > ctx->conv_scratch_bytes) {
+    // a capture allows no allocation
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (direct_ok && hipStreamIsCapturing(ctx->stream, &cap) == hipSuccess && cap != hipStreamCaptureStatusNone) {
+      mfma = false;
+    } else {
       if (ctx->conv_scratch) hipFree(ctx->conv_scratch);  // waits for work still reading it
       ctx->conv_scratch = nullptr;
       ctx->conv_scratch_bytes = 0;
-      if (hipMalloc(&ctx->conv_scratch, need) != hipSuccess)
-        return fail(ctx, PALQ_ERR_NOMEM, "conv scratch");
-      ctx->conv_scratch_bytes = need;
+      if (hipMalloc(&ctx->conv_scratch, need) == hipSuccess) {
+        ctx->conv_scratch_bytes = need;
+      } else {
+        ctx->conv_scratch = nullptr;
+        if (!direct_ok) return fail(ctx, PALQ_ERR_NOMEM, "conv scratch");
+        (void)hipGetLastError();
+        mfma = false;
+      }
     }
+  }
+  if (mfma) {
     uint8_t *wp = ctx->conv_scratch;
     int32_t *thr = (int32_t *)(ctx->conv_scratch + wbytes);
     e = launch_conv_prepare(a, wp, thr, ctx->stream);

@@ -115,6 +115,9 @@ struct ConvArgs {
 hipError_t launch_conv_direct(const ConvArgs &a, hipStream_t s, const int32_t *only_if_flag = nullptr);
 // Whether the MFMA kernels take this layer.
 bool conv_mfma_supported(const ConvArgs &a);
+// Whether, of those, only the padded kernels of k_conv_fp.hip do: where their
+// slabs have no room the layer runs on the direct kernel.
+bool conv_direct_partner(const ConvArgs &a);
 // Whether the general (persistent, filter-in-LDS) build fits this layer;
 // when it does not, a supported layer runs only on the tiled kernel's fast
 // epilogue and launch_conv_mfma needs epi == 0.

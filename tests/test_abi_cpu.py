@@ -342,7 +342,7 @@ def test_validate_only_group_conv_noalloc(P, vctx):
     a layer whose prepacked filter and requant constants exceed the static
     buffer is refused on the host (nothing enqueued)."""
     def call(x, f, out):
-        rq = P.Requant(_fake(30), _fake(31), None, 2)
+        rq = P.Requant(_fake(30), _fake(31), None, out.bits)
         return P._group_conv_noalloc(vctx.h, ctypes.byref(x), ctypes.byref(f), 1, 1, ctypes.byref(rq), None, 1,
                                      ctypes.byref(out), None)
     assert call(_act(P), P.Filter(2, 32, 64, 3, 3, 2, _fake(10)), _act(P, c=32, slot=20)) == P.OK
@@ -355,6 +355,12 @@ def test_validate_only_group_conv_noalloc(P, vctx):
     assert call(_act(P, g=8, c=512), too_big, _act(P, g=8, c=512, slot=20)) == P.ERR_UNSUPPORTED
     assert "static buffer" in vctx.last_error()
     assert P.NOALLOC_SCRATCH_BYTES == 16 << 20
+    # beyond the buffer, but also layers of the direct kernel, which needs none: a
+    # filter too long for the int8 builds and a channel count of none of them
+    long8 = P.Filter(1, 2048, 1024, 3, 3, 8, _fake(10))
+    assert call(_act(P, g=1, c=1024, bits=8), long8, _act(P, g=1, c=2048, bits=8, slot=20)) == P.OK
+    odd = P.Filter(8, 520, 520, 3, 3, 2, _fake(10))
+    assert call(_act(P, g=8, c=520), odd, _act(P, g=8, c=520, slot=20)) == P.OK
 
 
 def test_validate_only_conv_plan(P, vctx):

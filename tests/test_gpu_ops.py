@@ -907,6 +907,34 @@ def test_conv_plan_runs(ctx, torch, kind):
         ctx.sync()
 
 
+def test_group_conv_captured_without_scratch(ctx, torch):
+    """palq_group_conv on a context without scratch inside a capture, which
+    allows no allocation: a channel count that only the padded kernels take
+    runs on the direct kernel."""
+    from paper_2208_01944_amd import palq
+    say("group_conv captured on a fresh context")
+    c = I.single_layer(4300, n=2, h=9, w=9, groups=3, cin=48, cout=80, shuffle=1)
+    L = c["layer"]
+    ref = O.conv_layer(c["x"], L["w"], 1, 1, L["mult"], L["shift"], L["bias"], 2, 1)[0]
+    t = _layer_tensors(ctx, c, L["bias"])
+    ctx.sync()
+    fresh = palq.Context(0)
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.stream(side):
+        fresh.set_stream(side)
+        graph.capture_begin()
+        fresh.group_conv(t["x"], t["w"], 1, 1, t["mult"], t["shift"], t["bias"], t["out"], shuffle=1)
+        graph.capture_end()
+    for r in range(3):
+        t["out"].buf.fill_(0)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(ctx.unpack(t["out"]), ref, err_msg=f"replay {r}")
+        ctx.group_conv(t["x"], t["w"], 1, 1, t["mult"], t["shift"], t["bias"], t["out"], shuffle=1)
+        ctx.sync()
+
+
 def test_set_stream_orders_context_scratch(ctx, torch):
     """Two group_conv calls with different filters on two streams: the
     second call's prepack reuses the context's scratch, so the new stream
