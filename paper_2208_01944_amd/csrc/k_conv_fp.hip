@@ -596,21 +596,27 @@ __device__ __forceinline__ void conv_fp_tile(const FpArgs &a) {
   };
   typename T::Acc acc[CB][PB];
   auto mfmas = [&](const Ops &o) __attribute__((always_inline)) {
+    if constexpr (B == 8) {
 #pragma unroll
-    for (int pb = 0; pb < PB; ++pb)
+      for (int pb = 0; pb < PB; ++pb)
 #pragma unroll
-      for (int j = 0; j < J; ++j) {
-        if constexpr (B == 8) {
+        for (int j = 0; j < J; ++j) {
           const v4i X = flip_i8(o.x[pb][j]);
 #pragma unroll
           for (int cb = 0; cb < CB; ++cb)
             acc[cb][pb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(o.a0[cb][j], X, acc[cb][pb], 0, 0, 0);
-        } else {
-          const v8i X = act_fp<B>(o.x[pb][j]);
-#pragma unroll
-          for (int cb = 0; cb < CB; ++cb) acc[cb][pb] = mfma_fp<B>(wt_fp<B>(o.a0[cb][j], o.a1[cb]), X, acc[cb][pb]);
         }
+    } else {
+      v8i A[CB];
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb) A[cb] = wt_fp<B>(o.a0[cb][0], o.a1[cb]);
+#pragma unroll
+      for (int pb = 0; pb < PB; ++pb) {
+        const v8i X = act_fp<B>(o.x[pb][0]);
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) acc[cb][pb] = mfma_fp<B>(A[cb], X, acc[cb][pb]);
       }
+    }
   };
 
   const bool more = C::LMAX != C::LMIN && wave < C::full();
