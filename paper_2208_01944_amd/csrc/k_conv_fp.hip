@@ -444,13 +444,18 @@ __device__ __forceinline__ void quad_codes(const uint32_t *c, int qi, int half, 
 // KPS K-blocks (weight slabs, then the pixels' packed codes), is filled with
 // 16-byte LDS loads S - 1 stages ahead of the MFMAs, one barrier per stage.
 //
-// What bounds it: the instructions of one wave's K-block, not memory (with one
-// workgroup on an idle chip a K-block takes as long as on a full one).  So the
-// prologue has no loops and no dependent loads before the first fetch (constants
-// arrive by the same LDS loads), a K-block's position is decoded with two
-// multiplies instead of carried state, the in-image test is three VALU
-// instructions, two K-blocks share a barrier, and a stage's LDS reads are in
-// flight while the next fetch is issued.
+// What bounds it: the fetch path into LDS and the latency of a stage.  Counters
+// of the 14x14, 256-channel 2-bit layer (G = 4, batch 128), cycles per CU: MFMAs 28k
+// and LDS reads 23k, but the vector memory data unit busy for 58k of 64k with
+// one 16-byte piece of a 64-byte pixel row per lane, as each piece takes a
+// line of its own; 40k of 55k with a pixel's four pieces in neighbouring lanes
+// (PAIR: 43k vector L1 accesses -> 24k; the layer 31.2 -> 30.5 us, 7x7 512
+// channels of ResNet-50 at batch 128 29 -> 21).  Deeper rings (three and four
+// stages of two K-blocks) measured equal or slower.  The prologue has no loops
+// and no dependent loads before the first fetch (constants arrive by the same LDS
+// loads), a K-block's position is decoded with two multiplies instead of carried
+// state, the in-image test is three VALU instructions, and a stage's LDS reads are
+// in flight while the next fetch is issued.
 // MODE 0: no shortcut, 1: identity, 2: projection (more K-blocks).
 template <int B, int PB, int WN, int WM, int KPS>
 struct FpCfg {
@@ -481,14 +486,24 @@ struct FpCfg {
   static constexpr int RP = TM * (B == 2 ? TN / 64 : B == 8 ? TN / 16 : TN / 32);  // 16-byte shortcut pieces
 };
 
-template <int B, int PB, int WN, int WM, int MODE, bool DUMP, int KPS, int S, bool FAST>
+// PAIR (K-blocks per tap a multiple of KPS): a stage's pieces are ordered by
+// pixel, so that neighbouring lanes fetch a pixel's adjacent pieces from one
+// line; a pixel's NP pieces are swizzled so that 16 consecutive pixels' reads of
+// one piece meet all banks.
+template <int NP>
+__device__ __forceinline__ int piece_swizzle(int pixel) { return (pixel / (16 / NP)) & (NP - 1); }
+template <int B, int PB, int WN, int WM, int MODE, bool DUMP, int KPS, int S, bool FAST, bool PAIR>
 __device__ __forceinline__ void conv_fp_tile(const FpArgs &a) {
   using C = FpCfg<B, PB, WN, WM, KPS>;
   using T = FpT<B>;
   constexpr int NT = C::NT, TN = C::TN, TM = C::TM, CB = 2;
   constexpr int RING = S * C::SST;
   constexpr int CST = TN / 64 * 1024;
-  constexpr int RSB = MODE == 1 ? C::RP * 16 : 0;
+  // the shortcut's codes: a buffer of their own, or (where that would cost a
+  // workgroup per CU) the free slot of the last stage
+  constexpr bool LATE = MODE == 1 && S == 2 && KPS == 4;
+  static_assert(!LATE || C::RP * 16 <= C::SST, "a free slot during the last stage");
+  constexpr int RSB = MODE == 1 && !LATE ? C::RP * 16 : 0;
   __shared__ __attribute__((aligned(1024))) uint8_t lds[RING + CST + RSB];
 
   if (a.gated && a.bad[0] != 0) return;
@@ -506,7 +521,7 @@ __device__ __forceinline__ void conv_fp_tile(const FpArgs &a) {
   if (wave < TN / 64)
     dma16(rsrc4(a.cst, a.cst_bytes), base + RING + wave * 1024, (uint32_t)(lane * 16),
           (uint32_t)(((g * a.coutp + id.cbk * TN) / 64 + wave) * 1024));
-  if constexpr (MODE == 1) {
+  auto fetch_res = [&](int at) __attribute__((always_inline)) {
     const v4i r_res = rsrc4(a.res, a.res_bytes);
     constexpr int CBY = B == 2 || B == 8 ? 16 : T::CHS;  // bytes of a piece's channels in the row
 #pragma unroll
@@ -514,9 +529,11 @@ __device__ __forceinline__ void conv_fp_tile(const FpArgs &a) {
       if (64 * wave + i * NT < C::RP) {
         const int q = tid + i * NT, cc = q / TM, m = m0 + q % TM;
         const uint32_t vo = m < a.M ? (uint32_t)(m * a.res_pix + gd * a.res_gs + cc * CBY) : kOob;
-        dma16(r_res, base + RING + CST + (64 * wave + i * NT) * 16, vo, (uint32_t)(id.cbk * (TN * B / 8)));
+        dma16(r_res, base + (uint32_t)at + (64 * wave + i * NT) * 16, vo, (uint32_t)(id.cbk * (TN * B / 8)));
       }
-  }
+  };
+  int res_at = RING + CST;
+  if constexpr (MODE == 1 && !LATE) fetch_res(res_at);
 
   // this thread's weight pieces and pixels
   uint32_t woff[C::WL];
@@ -526,15 +543,17 @@ __device__ __forceinline__ void conv_fp_tile(const FpArgs &a) {
     woff[i] = (uint32_t)((((g * a.coutp + id.cbk * TN) / 32 + r / (T::SLAB / 16)) * a.kb + sub) * T::SLAB +
                          r % (T::SLAB / 16) * 16);
   }
+  constexpr int NP = T::PPX * KPS;
+  static_assert(PAIR || T::PPX == 1, "a piece per K-block");
   PixelGeo px[C::XL];
 #pragma unroll
   for (int i = 0; i < C::XL; ++i) {
-    // piece r of a K-block: PPX = 2, lane half r / 32 of 32-pixel block r / 64;
-    // PPX = 4, of MFMA (r / 64) % 2 of block r / 128 (codes 32 half + 16 j ..)
-    const int r = (tid + i * NT) % (TM * T::PPX);
-    const int pixel = T::PPX == 1 ? r : 32 * (r >> (T::PPX == 4 ? 7 : 6)) + (r & 31);
+    int pixel = (tid + i * NT) % TM, chunk = 0;
+    if constexpr (PAIR) {
+      pixel = (tid + i * NT) / NP;
+      chunk = (((tid + i * NT) % NP) ^ piece_swizzle<NP>(pixel)) * (T::XB / T::PPX);
+    }
     px[i] = pixel_geo<MODE == 2>(a, m0 + pixel);
-    const int chunk = T::PPX == 1 ? 0 : T::CHS * ((r >> 5) & 1) + (T::PPX == 4 ? 16 * ((r >> 6) & 1) : 0);
     px[i].off0 += g * a.in_gs + chunk;
     if constexpr (MODE == 2) px[i].poff += (uint32_t)(gd * a.proj_gs + chunk);
   }
@@ -551,7 +570,7 @@ __device__ __forceinline__ void conv_fp_tile(const FpArgs &a) {
 #pragma unroll
     for (int i = 0; i < C::XL; ++i)
       if ((i + 1) * NT <= C::XP || 64 * wave + i * NT < C::XP) {
-        const int sub = KPS == 1 ? 0 : (64 * wave + i * NT) / (C::XP / KPS);
+        const int sub = KPS == 1 || PAIR ? 0 : (64 * wave + i * NT) / (C::XP / KPS);
         const int kb = s * KPS + sub;
         const uint32_t dst = wdst + so + C::WST + i * NT * 16;
         if (MODE == 2 && kb >= a.km) {
@@ -566,12 +585,14 @@ __device__ __forceinline__ void conv_fp_tile(const FpArgs &a) {
       }
   };
 #pragma unroll
-  for (int s = 0; s < S - 1; ++s)
+  for (int s = 0; s < (S == 1 ? 1 : S - 1); ++s)
     if (s < NS) fetch(s, s);
 
   // operands of K-block `sub` of the slot at byte so
   constexpr int J = T::J;
-  const int xl = C::WST + (B == 2 ? (wm * PB * 32 + l32) * 16 + half * 8 : (wm * PB * J * 64 + lane) * 16);
+  const int xl = C::WST + (wm * PB * 32 + l32) * 16 * (PAIR ? NP : 1) + (B == 2 ? half * 8 : 0);
+  // piece PPX sub + j' of the lane's pixel: B = 3, 4, j' = half; B = 8, j' = 2 half + j
+  const int xsw = PAIR ? 16 * (piece_swizzle<NP>(l32) ^ (B == 2 ? 0 : B == 8 ? 2 * half : half)) : 0;
   const int al = wn * CB * T::SLAB + lane * 16, bl = wn * CB * T::SLAB + 1024 + lane * 8;
   struct Ops { v4i x[PB][J], a0[CB][J]; v2i a1[CB]; };
   auto read = [&](Ops &o, int so, int sub) __attribute__((always_inline)) {
@@ -586,11 +607,13 @@ __device__ __forceinline__ void conv_fp_tile(const FpArgs &a) {
     for (int pb = 0; pb < PB; ++pb)
 #pragma unroll
       for (int j = 0; j < J; ++j) {
+        const uint8_t *q = PAIR ? p + xl + ((16 * (T::PPX * sub + j)) ^ xsw) + pb * 512 * NP
+                                : p + xl + sub * C::X1 + pb * 512;
         if constexpr (B == 2) {
-          const v2i v = *(const v2i *)(p + xl + sub * C::X1 + pb * 512);
+          const v2i v = *(const v2i *)q;
           o.x[pb][j] = v4i{v[0], v[1], 0, 0};
         } else {
-          o.x[pb][j] = *(const v4i *)(p + xl + sub * C::X1 + (pb * J + j) * 1024);
+          o.x[pb][j] = *(const v4i *)q;
         }
       }
   };
@@ -626,9 +649,9 @@ __device__ __forceinline__ void conv_fp_tile(const FpArgs &a) {
   const int32_t *csi = (const int32_t *)cst;
   for (int s = 0; s < NS; ++s) {
     // stage s has landed; up to S - 2 younger ones may be in flight
-    if (s + S - 2 < NS) {
-      if (C::LMAX != C::LMIN && !more) wait_barrier<(S - 2) * C::LMIN>();
-      else wait_barrier<(S - 2) * C::LMAX>();
+    if (S > 1 && s + S - 2 < NS) {
+      if (C::LMAX != C::LMIN && !more) wait_barrier<(S > 1 ? S - 2 : 0) * C::LMIN>();
+      else wait_barrier<(S > 1 ? S - 2 : 0) * C::LMAX>();
     } else {
       wait_barrier<0>();
     }
@@ -636,7 +659,12 @@ __device__ __forceinline__ void conv_fp_tile(const FpArgs &a) {
     Ops o[KPS];
 #pragma unroll
     for (int i = 0; i < KPS; ++i) read(o[i], so, i);
-    if (s + S - 1 < NS) fetch(s + S - 1, slot_f);
+    if (S > 1 && s + S - 1 < NS) {
+      fetch(s + S - 1, slot_f);
+    } else if constexpr (LATE) {
+      res_at = slot_f * C::SST;
+      fetch_res(res_at);
+    }
     if (s == 0) {
       // element r of block cb is channel 32 cb + 8 (r / 4) + 4 half + r % 4
 #pragma unroll
@@ -663,6 +691,7 @@ __device__ __forceinline__ void conv_fp_tile(const FpArgs &a) {
   }
 
   // ---- epilogue
+  if constexpr (LATE) wait_barrier<0>();
   const int ch0 = id.cbk * TN + wn * 64;
   const int mw = m0 + wm * PB * 32;
   if constexpr (DUMP) {
@@ -702,7 +731,7 @@ __device__ __forceinline__ void conv_fp_tile(const FpArgs &a) {
         for (int pb = 0; pb < PB; ++pb) {
           uint32_t rc = 0, w = 0;
           if constexpr (MODE == 1)
-            rc = *(const uint32_t *)(lds + RING + CST +
+            rc = *(const uint32_t *)(lds + res_at +
                                      ((wn * 4 + cb * 2 + (qi >> 1)) * TM + wm * PB * 32 + pb * 32 + l32) * 16 +
                                      8 * (qi & 1) + 4 * half);
 #pragma unroll
@@ -745,7 +774,7 @@ __device__ __forceinline__ void conv_fp_tile(const FpArgs &a) {
       for (int pb = 0; pb < PB; ++pb) {
         E[pb] = O[pb] = 0;
         if constexpr (MODE == 1) {
-          const v2i v = *(const v2i *)(lds + RING + CST + (wn * TM + wm * PB * 32 + pb * 32 + l32) * 16 + 8 * cb);
+          const v2i v = *(const v2i *)(lds + res_at + (wn * TM + wm * PB * 32 + pb * 32 + l32) * 16 + 8 * cb);
 #pragma unroll
           for (int j = 0; j < 2; ++j) {
             const uint32_t x = (uint32_t)v[j] >> (8 * half);
@@ -806,11 +835,11 @@ __device__ __forceinline__ void conv_fp_tile(const FpArgs &a) {
       for (int pb = 0; pb < PB; ++pb) {
         const int p = wm * PB * 32 + pb * 32 + l32;
         if constexpr (B == 2) {
-          const v2i v = *(const v2i *)(lds + RING + CST + (wn * TM + p) * 16 + 8 * cb);
+          const v2i v = *(const v2i *)(lds + res_at + (wn * TM + p) * 16 + 8 * cb);
           rc[pb][0] = (uint32_t)v[0];
           rc[pb][1] = (uint32_t)v[1];
         } else {
-          const v4i v = *(const v4i *)(lds + RING + CST + ((wn * 2 + cb) * TM + p) * 16);
+          const v4i v = *(const v4i *)(lds + res_at + ((wn * 2 + cb) * TM + p) * 16);
 #pragma unroll
           for (int e = 0; e < 4; ++e) rc[pb][e] = (uint32_t)v[e];
         }
@@ -1102,9 +1131,9 @@ __device__ __forceinline__ void conv_fp_split(const FpArgs &a) {
 
 // Entry points by matrix-core format.
 #define PALQ_FP_TILE(NAME)                                                                            \
-  template <int B, int PB, int WN, int WM, int MODE, bool DUMP, int KPS, int S, bool FAST>    \
+  template <int B, int PB, int WN, int WM, int MODE, bool DUMP, int KPS, int S, bool FAST, bool PAIR>    \
   __global__ __launch_bounds__(WN *WM * 64, B == 2 ? 4 : B == 8 ? 2 : 3) void NAME(FpArgs a) {  \
-    conv_fp_tile<B, PB, WN, WM, MODE, DUMP, KPS, S, FAST>(a);                                     \
+    conv_fp_tile<B, PB, WN, WM, MODE, DUMP, KPS, S, FAST, PAIR>(a);                                     \
   }
 #define PALQ_FP_SPLIT(NAME)                                                     \
   template <int B, int PB, int NW, int MODE, bool DUMP>                         \
@@ -1211,25 +1240,25 @@ int cu_count() {
   return cus;
 }
 
-template <int B, int PB, int WN, int WM, int MODE, bool DUMP, int KPS, int S>
+template <int B, int PB, int WN, int WM, int MODE, bool DUMP, int KPS, int S, bool PAIR>
 hipError_t launch_tile_mode(const FpArgs &f, unsigned grid, hipStream_t s) {
   const dim3 block(WN * WM * 64);
   if constexpr (B == 8)
-    hipLaunchKernelGGL((conv_i8_kernel<B, PB, WN, WM, MODE, DUMP, KPS, S, false>), dim3(grid), block, 0, s, f);
+    hipLaunchKernelGGL((conv_i8_kernel<B, PB, WN, WM, MODE, DUMP, KPS, S, false, PAIR>), dim3(grid), block, 0, s, f);
   else if constexpr (B != 2)
-    hipLaunchKernelGGL((conv_fp6_kernel<B, PB, WN, WM, MODE, DUMP, KPS, S, false>), dim3(grid), block, 0, s, f);
+    hipLaunchKernelGGL((conv_fp6_kernel<B, PB, WN, WM, MODE, DUMP, KPS, S, false, PAIR>), dim3(grid), block, 0, s, f);
   else if (f.fast)
-    hipLaunchKernelGGL((conv_fp4_kernel<B, PB, WN, WM, MODE, DUMP, KPS, S, true>), dim3(grid), block, 0, s, f);
+    hipLaunchKernelGGL((conv_fp4_kernel<B, PB, WN, WM, MODE, DUMP, KPS, S, true, PAIR>), dim3(grid), block, 0, s, f);
   else
-    hipLaunchKernelGGL((conv_fp4_kernel<B, PB, WN, WM, MODE, DUMP, KPS, S, false>), dim3(grid), block, 0, s, f);
+    hipLaunchKernelGGL((conv_fp4_kernel<B, PB, WN, WM, MODE, DUMP, KPS, S, false, PAIR>), dim3(grid), block, 0, s, f);
   return hipGetLastError();
 }
-template <int B, int PB, int WN, int WM, bool DUMP, int KPS, int S>
+template <int B, int PB, int WN, int WM, bool DUMP, int KPS, int S, bool PAIR>
 hipError_t launch_tile(FpArgs f, int64_t in_bytes, hipStream_t s) {
   const unsigned grid = fp_tiles(f, 64 * WN, 32 * PB * WM, in_bytes);
-  if (f.res) return launch_tile_mode<B, PB, WN, WM, 1, DUMP, KPS, S>(f, grid, s);
-  if (f.proj) return launch_tile_mode<B, PB, WN, WM, 2, DUMP, KPS, S>(f, grid, s);
-  return launch_tile_mode<B, PB, WN, WM, 0, DUMP, KPS, S>(f, grid, s);
+  if (f.res) return launch_tile_mode<B, PB, WN, WM, 1, DUMP, KPS, S, PAIR>(f, grid, s);
+  if (f.proj) return launch_tile_mode<B, PB, WN, WM, 2, DUMP, KPS, S, PAIR>(f, grid, s);
+  return launch_tile_mode<B, PB, WN, WM, 0, DUMP, KPS, S, PAIR>(f, grid, s);
 }
 
 template <int B, int PB, int NW, int MODE>
@@ -1262,24 +1291,48 @@ hipError_t launch_split(FpArgs f, int64_t in_bytes, hipStream_t s) {
 //    128 x 128 tiles; batch 8, 448 tiles, 11.4 against 14.7; at 800 tiles 17.4
 //    against 20.8 with 72 K-blocks, but 10.0 against 9.2 with 36);
 //  * 128 x 128 tiles, else (channel blocks that are no multiple of 128) 64 x 256;
-//  * from 12 K-blocks on, two stages of two K-blocks: half the barriers (batch 64,
+//  * 2-bit, four or more K-blocks per tap in fours: stages of four K-blocks,
+//    whose pieces fill whole lines.  Two stages take a third of a CU's LDS, so
+//    between three and six tiles per CU a second, nearly empty round costs more
+//    (ResNet-50 batch 128, 3x3: 392 tiles 29.2 -> 20.7 us, 1568 with a projection
+//    32.6 -> 28.6, but 784 19.2 -> 22.0); four K-blocks in all are one stage (14x14
+//    256 -> 1024 with shortcut, 3136 tiles, 19.6 -> 18.9; for 64-channel tiles and
+//    two K-blocks in all one stage measured the same as three of one);
+//  * else from 12 K-blocks on, two stages of two K-blocks: half the barriers (batch 64,
 //    2-bit, 18.2 us against 20.4 with three stages of one); below, three stages
 //    of one, which leave LDS for more workgroups (56x56, 64 -> 256 channels 1x1
-//    with a shortcut, batch 128, 43.5 us against 49.1).
+//    with a shortcut, batch 128, 43.5 us against 49.1).  3- and 4-bit stages of
+//    two need an even number of K-blocks per tap (pieces by pixel: ResNet-18 G = 2
+//    4-bit batch 32, stage 3, 16.2 -> 13.7 us; 14x14 3-bit batch 128 with shortcut
+//    55.9 -> 51.5).
 template <int B>
 hipError_t launch_fp(const FpArgs &f, int64_t in_bytes, hipStream_t s) {
   const int64_t cus = cu_count();
   const int64_t few = (int64_t)((f.M + 63) / 64) * ((f.cout + 31) / 32) * f.G;
   if (few <= 2 * cus || (few <= 4 * cus && f.kb >= 64)) return launch_split<B, 2, 8>(f, in_bytes, s);
-  if (f.dump) return launch_tile<B, 2, 1, 4, true, B == 8 ? 1 : 2, B == 8 ? 3 : 2>(f, in_bytes, s);
   const bool wide = f.coutp % 128 == 0;
-  if (B == 8 || f.kb < 12)
-    return wide ? launch_tile<B, 2, 2, 2, false, 1, 3>(f, in_bytes, s)
-                : launch_tile<B, 2, 1, 4, false, 1, 3>(f, in_bytes, s);
-  if constexpr (B != 8)
-    return wide ? launch_tile<B, 2, 2, 2, false, 2, 2>(f, in_bytes, s)
-                : launch_tile<B, 2, 1, 4, false, 2, 2>(f, in_bytes, s);
-  return hipErrorNotSupported;
+  if constexpr (B == 2) {
+    if (f.dump) return launch_tile<B, 2, 1, 4, true, 2, 2, false>(f, in_bytes, s);
+    if (wide && f.cpb % 4 == 0) {
+      if (f.kb == 4) return launch_tile<B, 2, 2, 2, false, 4, 1, true>(f, in_bytes, s);
+      const int64_t tiles = (int64_t)((f.M + 127) / 128) * (f.coutp / 128) * f.G;
+      if (f.kb >= 8 && (tiles <= 3 * cus || tiles >= 6 * cus))
+        return launch_tile<B, 2, 2, 2, false, 4, 2, true>(f, in_bytes, s);
+    }
+    if (f.kb < 12)
+      return wide ? launch_tile<B, 2, 2, 2, false, 1, 3, false>(f, in_bytes, s)
+                  : launch_tile<B, 2, 1, 4, false, 1, 3, false>(f, in_bytes, s);
+    return wide ? launch_tile<B, 2, 2, 2, false, 2, 2, false>(f, in_bytes, s)
+                : launch_tile<B, 2, 1, 4, false, 2, 2, false>(f, in_bytes, s);
+  } else {
+    if (f.dump) return launch_tile<B, 2, 1, 4, true, 1, 3, true>(f, in_bytes, s);
+    if constexpr (B != 8)
+      if (f.kb >= 12 && f.cpb % 2 == 0)
+        return wide ? launch_tile<B, 2, 2, 2, false, 2, 2, true>(f, in_bytes, s)
+                    : launch_tile<B, 2, 1, 4, false, 2, 2, true>(f, in_bytes, s);
+    return wide ? launch_tile<B, 2, 2, 2, false, 1, 3, true>(f, in_bytes, s)
+                : launch_tile<B, 2, 1, 4, false, 1, 3, true>(f, in_bytes, s);
+  }
 }
 
 }  // namespace

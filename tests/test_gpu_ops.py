@@ -471,6 +471,12 @@ FP_EDGE_CASES = {
     "c128_one_kblock": dict(n=7, h=31, w=30, groups=2, cin=33, cout=128, k=1, pad=0, residual="identity"),
     "c128_ragged_projection": dict(n=9, h=44, w=43, groups=2, cin=40, cout=250, k=3, residual="projection"),
     "c128_ragged": dict(n=15, h=14, w=15, groups=3, cin=100, cout=500, residual="identity"),
+    # stages of four K-blocks: one stage, two, and nine with a ragged last tile
+    "c128_four_kblocks": dict(n=5, h=31, w=29, groups=2, cin=250, cout=250, k=1, pad=0, residual="identity"),
+    "c128_two_stages": dict(n=5, h=31, w=29, groups=2, cin=450, cout=128, k=1, pad=0, residual="identity"),
+    "c128_stages_of_four": dict(n=11, h=14, w=15, groups=2, cin=200, cout=256, residual="identity"),
+    "c128_stages_of_four_projection": dict(n=11, h=28, w=27, groups=2, cin=200, cout=256, stride=2,
+                                           residual="projection"),
     "c128_5x5_odd": dict(n=15, h=14, w=14, groups=3, cin=64, cout=512, k=5, pad=2),
 }
 
