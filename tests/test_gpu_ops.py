@@ -683,7 +683,8 @@ def test_maxpool_avgsum_2bit_vector_paths(ctx, torch, cpg, h, w, layout):
     np.testing.assert_array_equal(sums.cpu().numpy().reshape(3, 2 * cpg), O.avgsum(x))
 
 
-@pytest.mark.parametrize("n,cin,cout", [(37, 96, 70), (3, 40, 5), (64, 2048, 1000)])
+# one K step to many per wave, remainders of a load round, several K slices
+@pytest.mark.parametrize("n,cin,cout", [(37, 96, 70), (3, 40, 5), (64, 2048, 1000), (33, 2592, 40), (5, 4128, 70)])
 def test_fc_full_range_modular(ctx, torch, n, cin, cout):
     """Features over the whole int32 range (the matrix-core path splits them
     into signed byte digits when cin % 32 == 0): logits equal the exact sum

@@ -62,3 +62,35 @@ def test_fp32_requant_shift_bound_is_needed():
             if np.any(_fp32_path(u, m, sh) != _definition(u, m, sh)):
                 found = True
     assert found
+
+
+def test_round_down_requant_equals_definition_for_every_shift():
+    """The tile kernels' other form: one fma rounding towards minus infinity.
+    Integers are representable in fp32, so floor(RD(x)) = floor(x)."""
+    rng = np.random.default_rng(11)
+    for sh in list(range(1, 63)):
+        for m in [1, 3, 46341, (1 << 24) - 1, int(rng.integers(1, 1 << 24))]:
+            us = [0, 1, (1 << 24) - 1] + [int(v) for v in rng.integers(1, 1 << 24, 20)]
+            for k in (1, 2, 3, 8, 15):  # the step to code k, both sides
+                th = -(-((2 * k - 1) << (sh - 1)) // m)
+                us += [v for v in (th - 1, th, th + 1) if 0 <= v < 1 << 24]
+            for u in us:
+                num = u * m + (1 << (sh - 1))
+                drop = max(0, num.bit_length() - 24)
+                assert min(((num >> drop) << drop) >> sh, 15) == min(num >> sh, 15), (sh, m, u)
+
+
+def test_fp4_conversion_requant_equals_definition():
+    """The 2-bit form by the FP4 conversion, shifts up to 21: z = clamp(RN32(v / 4
+    + 2^-24)) to [0, 1], v = u M 2^-sh, and the nibble RNE(4 z) with 4 taken to
+    3."""
+    rng = np.random.default_rng(13)
+    for sh in range(1, 22):
+        for m in MULTS + [int(v) for v in rng.integers(1, 1 << 24, 4)]:
+            u = _cases(m, sh, rng)
+            v = (u * m).astype(np.float64) / 2.0 ** sh + 2.0 ** -22  # exact
+            z = np.clip((v / 4).astype(np.float32), np.float32(0), np.float32(1))
+            got = np.minimum(np.rint(z.astype(np.float64) * 4), 3).astype(np.int64)
+            want = _definition(u, m, sh)
+            bad = np.nonzero(got != want)[0]
+            assert bad.size == 0, (sh, m, u[bad[:5]], got[bad[:5]], want[bad[:5]])
