@@ -69,7 +69,7 @@ def parse():
 
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "conv_fp4_kernel_resnet18_g4_b2_traffic.txt")
 DOMINANT = "conv_fp4_kernel"
-KERNEL_SOURCE = os.path.join(ROOT, "paper_2208_01944_amd", "csrc", "k_conv_mfma.hip")
+KERNEL_SOURCE = os.path.join(ROOT, "paper_2208_01944_amd", "csrc", "k_conv_fp.hip")
 
 
 def measured_traffic():

@@ -1891,7 +1891,7 @@ __device__ __forceinline__ int uniform_int(int v) { return __builtin_amdgcn_read
 // c / 2 (chunks 0..3 and the top chunk -2..1), so the fp32 accumulator
 // holds T / 4 with T the integer sum; M = 8 keeps the pairs with i + j >= 3
 // in a second accumulator scaled by 4^-3, so that each stays below 2^24 in T
-// (bd_applies checks the bounds).  Tiles as conv_fpx_tile (128 x 128,
+// (bd_applies checks the bounds).  Tiles as the FP4 kernel (128 x 128,
 // XCD-contiguous runs in the chunked order).  Epilogue in fp64: lo + 64 hi,
 // plus the identity shortcut rm c / 4 (M-bit codes), then the FP4-scaled
 // requant constants.  A fused projection adds its own decomposed K-blocks.

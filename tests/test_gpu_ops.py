@@ -399,8 +399,8 @@ def test_conv_c2_full_batch_every_image(ctx, torch, layer):
 @pytest.mark.parametrize("bits", [2, 3, 4])
 def test_conv_c4_sweep_every_image(ctx, torch, groups, bits):
     """The G x B sweep on the 14x14 / 256-channel layer at batch 128: every
-    image, on the FP4 (2-bit) and FP6 (3-bit) matrix cores and on int8
-    (4-bit layers have only the int8 path)."""
+    image, on the FP4 (2-bit) and FP6 (3- and 4-bit) matrix cores and, 2 and
+    3 bits, on int8."""
     say(f"conv C4 G={groups} b={bits} batch 128 (every image)")
     check_full(ctx, torch, I.config_c4(groups, bits), (True, False) if bits in (2, 3) else (True,))
 
