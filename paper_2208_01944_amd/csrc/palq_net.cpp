@@ -455,6 +455,10 @@ palq_status palq_net_create(palq_ctx *ctx, const palq_act *input, const palq_lay
   }
   for (auto &t : net->tensors)
     if (t.exists && t.buf >= 0) t.d.data = net->bufs[t.buf];
+  // the input's address comes with each call; until then a stand-in, so that a
+  // layer is prepared with the shortcut and the kernel choice of its launches
+  // (both go by which tensors are there)
+  t0.d.data = fake_ptr(0);
 
   // ---- patch tensor pointers into the prepared launches
   for (int i = 0; i < n_layers; ++i) {

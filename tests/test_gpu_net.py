@@ -334,6 +334,53 @@ def test_stem_pool_widths(ctx, torch, groups, bits, hw, big_mult):
     np.testing.assert_array_equal(logits, O.run_net(spec, spec["x"]))
 
 
+def codes_input_net(ctx, spec, groups, bits):
+    """A network over `spec` whose input tensor is unsigned codes of several
+    groups (the binding describes every input as a signed 8-bit image)."""
+    from paper_2208_01944_amd import palq
+    make = palq.make_act
+
+    def input_act(n, h, w, g, c, b, signed=False, *rest, **kw):
+        if (n, h, w, c) == spec["x"].shape and signed:
+            return make(n, h, w, groups, c // groups, bits)
+        return make(n, h, w, g, c, b, signed, *rest, **kw)
+
+    palq.make_act = input_act
+    try:
+        return palq.Net(ctx, spec)
+    finally:
+        palq.make_act = make
+
+
+# layers whose shortcut is the network's own input: its address is known only
+# at the call, after the layers are prepared
+@pytest.mark.parametrize("kind", ["identity", "module", "projection"])
+@pytest.mark.parametrize("bits", [2, 3, 4, 8])
+@pytest.mark.parametrize("n,hw", [(2, 9), (64, 30)])  # the split and the tile kernels
+def test_shortcut_from_the_network_input(ctx, torch, kind, bits, n, hw):
+    say(f"shortcut from tensor 0 {kind} b={bits} n={n} hw={hw}")
+    G, C = 2, 64
+    g = I.rng(600 + bits)
+    x = I.codes(g, (n, hw, hw, G * C), bits, False)
+    common = dict(groups=G, cout=C, k=3, pad=1, in_bits=bits, in_signed=False, w_bits=bits, out_bits=bits, shuffle=1)
+    if kind == "module":
+        layers = [I.shuffle_module_spec(g, src=0, dst=1, groups=G, ch=C, bits=bits)]
+    else:
+        s = 2 if kind == "projection" else 1
+        layers = [I.conv_layer_spec(g, src=0, dst=1, cin=C, stride=s, **common),
+                  I.conv_layer_spec(g, src=1, dst=2, cin=C, stride=1, res=0 if kind == "identity" else -1,
+                                    proj_src=0 if kind == "projection" else -1, proj_cin=C, proj_stride=s, **common)]
+    k = layers[-1]["dst"]
+    layers += [dict(op="avgsum", src=k, dst=k + 1),
+               dict(op="fc", src=k + 1, dst=k + 2, w=I.codes(g, (10, G * C), 8, True))]
+    spec = O.calibrate_centring(dict(n=n, hw=hw, groups=G, bits=bits, x=x, layers=layers, classes=10), x)
+    net = codes_input_net(ctx, spec, G, bits)
+    logits = torch.empty(n * 10, dtype=torch.int32, device=ctx.dev)
+    net.forward(ctx.pack(x, G, bits).buf, logits)
+    ctx.sync()
+    np.testing.assert_array_equal(logits.cpu().numpy().astype(np.int64).reshape(n, 10), O.run_net(spec, x))
+
+
 def full_size_run(ctx, torch, name):
     """The benchmark's network (stored centred biases, default flags) on
     the workload's whole fp32 image batch through palq_forward_image, as
