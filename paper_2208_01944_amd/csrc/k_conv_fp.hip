@@ -16,7 +16,7 @@
 //  * B = 8 (also 6-bit codes, stored as bytes): x - 128 as int8 (the top bit
 //    flipped), two v_mfma_i32_32x32x32_i8 a K-block, accumulators starting at
 //    bias + 128 sum(w), which also restores taps outside the image (their code
-//    0 reads as -128); requant in fp64, exact while |u| M < 2^52.
+//    0 reads as -128); requant in fp64.
 //
 // Any channel count: K-blocks and channel blocks are padded with zero weights,
 // so what an operand load brings in past the end of a row (the row's padding,
@@ -27,7 +27,14 @@
 // Requant: the accumulator starts at bias, u = t + bias (+ res_mult code), and
 // one fma with rounding towards minus infinity gives RD(x), x = u M 2^-sh +
 // 1/2.  Integers are representable, so floor(RD(x)) = floor(x): the definition,
-// for every shift (M < 2^24).
+// for every shift (M < 2^24).  Layers with a channel past those bounds (M up to
+// 2^31, bias up to 2^30) take the wide builds: the accumulator starts at 0, u is
+// an int32 (B = 8: formed in fp64) and the same fma in fp64 holds for every u and
+// M the interface admits (both below 2^53).  14x14, 256 channels, 2-bit, G = 4,
+// batch 128: 38.1 us against 34.6 for 15-bit multipliers (119 with the int64
+// requant of the int8 kernels, which took such layers); 4-bit with a shortcut
+// 59.9 against 52.3 (145); 14x14, 1024 channels, batch 8, 39 us (67 ms on the
+// direct kernel, as its filter does not fit the int8 kernels' LDS).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -124,17 +131,23 @@ __device__ __forceinline__ v16f mfma_fp(v8i a, v8i b, v16f c) {
 }
 
 // Constants of 64 channels, one 1 KB block: [scale 64][bias 64][res_mult
-// 64][unused 64] floats in accumulator units, or (B = 8) [scale 64] doubles,
-// [bias + 128 sum(w) 64][res_mult 64] int32.
+// 64][unused 64] floats in accumulator units, or (B = 8 and the wide builds)
+// [M 2^-sh 64] doubles, [bias 64][res_mult 64] int32 (B = 8: bias + 128 sum(w)).
 constexpr int kCstBlock = 1024;
+
+// The requant of a build.  kBase: fp32, B = 8: fp64 on an int32 u.  kFp4: the
+// 2-bit form by FP4 conversions (requant_z).  kWide: any parameters.
+enum Ep { kBase, kFp4, kWide };
 
 // ------------------------------------------------------------ prepare
 // One launch per layer (B = 8: wsum_i8_kernel before it).  Workgroup 0: the
-// requant constants (zero for padded channels) and two flags: bad[0], some channel is
-// outside the exact requant's bounds; bad[1], some shift exceeds 21 (requant_fp4).  The others: weight slabs, one lane operand (16 or
-// 24 bytes) per thread, [G][coutp / 32][kb_total][SLAB]; E2M3 slabs hold bytes
-// 0-15 of every lane, then bytes 16-23.  Projection K-blocks of source group g
-// hold the projection filter of its destination group (g + s) mod G.
+// requant constants (zero for padded channels; B < 8: of the base builds, then
+// of the wide ones) and two flags: bad[0], some channel is outside the base
+// builds' bounds; bad[1], some shift exceeds 21 (requant_z).  The others: weight
+// slabs, one lane operand (16 or 24 bytes) per thread, [G][coutp /
+// 32][kb_total][SLAB]; E2M3 slabs hold bytes 0-15 of every lane, then bytes
+// 16-23.  Projection K-blocks of source group g hold the projection filter of
+// its destination group (g + s) mod G.
 struct PrepArgs {
   const uint8_t *w, *pw;
   const int32_t *mult, *shift, *bias, *res_mult;
@@ -142,7 +155,8 @@ struct PrepArgs {
   int64_t row, prow;  // packed bytes of a tap's row of the filter and of a projection row
   int64_t acc_bound;
   uint8_t *wp;
-  float *cst;
+  float *cst;     // B < 8: constants of the base builds
+  uint8_t *wide;  // constants of the wide builds and of B = 8
   int32_t *bad;
   int32_t w_bits;
   int32_t *wsum;  // B = 8: 128 sum(w) per channel
@@ -175,44 +189,32 @@ __global__ __launch_bounds__(512) void conv_fp_prep_kernel(PrepArgs a) {
     int bad = 0, wide = 0;
     for (int i = threadIdx.x; i < a.G * a.coutp; i += 512) {
       const int g = i / a.coutp, k = i - g * a.coutp;
-      if constexpr (B == 8) {
-        double s = 0.0;
-        int32_t b = 0, rm = 0;
-        if (k < a.cout) {
-          const int c = g * a.cout + k;
-          const int64_t m = a.mult[c], bi = a.bias ? a.bias[c] : 0, r = a.res_mult ? a.res_mult[c] : 0;
-          const int sh = a.shift[c];
-          const int64_t umax = a.acc_bound + (bi < 0 ? -bi : bi) + (r < 0 ? -r : r) * a.res_max;
-          if (sh < 1 || sh > 52 || m < 0 || umax >= ((int64_t)1 << 31) || umax * m >= ((int64_t)1 << 52)) {
-            bad = 1;
-          } else {
-            s = ldexp((double)m, -sh);
-            b = (int32_t)bi + a.wsum[c];
-            rm = (int32_t)r;
-          }
-        }
-        uint8_t *blk = (uint8_t *)a.cst + (int64_t)(i >> 6) * kCstBlock;
-        ((double *)blk)[i & 63] = s;
-        ((int32_t *)blk)[128 + (i & 63)] = b;
-        ((int32_t *)blk)[192 + (i & 63)] = rm;
-        continue;
-      }
+      double s = 0.0;
       float sc = 0.0f, b = 0.0f, rm = 0.0f;
+      int32_t bw = 0, rw = 0;
       if (k < a.cout) {
         const int c = g * a.cout + k;
         const int64_t m = a.mult[c], bi = a.bias ? a.bias[c] : 0, r = a.res_mult ? a.res_mult[c] : 0;
         const int sh = a.shift[c];
-        const int64_t lim = (int64_t)1 << 24;
-        if (sh < 1 || sh > 62 || m <= -lim || m >= lim ||
-            a.acc_bound + (bi < 0 ? -bi : bi) + (r < 0 ? -r : r) * a.res_max >= lim) {
+        const int64_t lim = (int64_t)1 << (B == 8 ? 31 : 24);
+        const int64_t umax = a.acc_bound + (bi < 0 ? -bi : bi) + (r < 0 ? -r : r) * a.res_max;
+        s = ldexp((double)m, -sh);
+        bw = (int32_t)((uint32_t)bi + (B == 8 ? (uint32_t)a.wsum[c] : 0u));
+        rw = (int32_t)r;
+        if (umax >= lim || (B != 8 && (sh < 1 || sh > 62 || m <= -lim || m >= lim))) {
           bad = 1;
-        } else {
+        } else if constexpr (B != 8) {
           if (sh > 21) wide = 1;
           sc = ldexpf((float)m, FpT<B>::L - sh);
           b = ldexpf((float)bi, -FpT<B>::L);
           rm = ldexpf((float)r, -FpT<B>::L);
         }
       }
+      uint8_t *wb = a.wide + (int64_t)(i >> 6) * kCstBlock;
+      ((double *)wb)[i & 63] = s;
+      ((int32_t *)wb)[128 + (i & 63)] = bw;
+      ((int32_t *)wb)[192 + (i & 63)] = rw;
+      if constexpr (B == 8) continue;
       float *blk = a.cst + (int64_t)(i >> 6) * 256 + (i & 63);
       blk[0] = sc;
       blk[64] = b;
@@ -295,7 +297,7 @@ struct FpArgs {
   const float *cst;
   const int32_t *bad;  // the prepare kernel's flags
   int32_t fast;        // bad[1] is known to be clear
-  int32_t gated;       // the launch does nothing if bad[0] (its general partner runs)
+  int32_t gate;        // 0: run; 1: run unless bad[0]; 2: run if bad[0] (the two launches of a one-off call)
   int32_t *dump;
   uint32_t in_bytes, w_bytes, res_bytes, proj_bytes, cst_bytes;
   int32_t in_pix, in_gs, res_pix, res_gs, proj_pix, proj_gs, out_pix, out_gs;  // bytes, < 2^30
@@ -331,6 +333,10 @@ __device__ __forceinline__ bool tile_of(const FpArgs &a, TileId &id) {
   id.g = (int)a.d_ncb.div(combo);
   id.cbk = (int)combo - id.g * a.ncb;
   return true;
+}
+
+__device__ __forceinline__ bool gated_off(const FpArgs &a) {
+  return a.gate != 0 && (a.bad[0] != 0) != (a.gate == 2);
 }
 
 // Geometry of output pixel m: byte offset of tap (0, 0) (may be negative), the
@@ -391,17 +397,17 @@ __device__ __forceinline__ uint32_t requant_rd(float u, float sc, uint32_t qmax)
   asm("v_cvt_u32_f32 %0, %1" : "=v"(q) : "v"(y));
   return min(q, qmax);
 }
-// B = 8: floor(u s + 1/2) in fp64 (s = M 2^-sh; exact below 2^52).
-__device__ __forceinline__ uint32_t requant_f64(int32_t u, double s) {
-  const double d = __builtin_fma((double)u, s, 0.5);
+// The same in fp64, s = M 2^-sh.
+__device__ __forceinline__ uint32_t requant_f64(double u, double s, uint32_t qmax) {
+  const double d = __builtin_fma(u, s, 0.5);
   uint32_t q;
   asm("v_cvt_u32_f64 %0, %1" : "=v"(q) : "v"(d));
-  return q;
+  return min(q, qmax);
 }
-// Every later fp32 operation that depends on a value passed through here
-// rounds towards minus infinity (asm volatile statements keep their order).
+// Every later fp32 and fp64 operation that depends on a value passed through
+// here rounds towards minus infinity (asm volatile statements keep their order).
 __device__ __forceinline__ void set_round_down() {
-  asm volatile("s_setreg_imm32_b32 hwreg(HW_REG_MODE, 0, 2), 2");
+  asm volatile("s_setreg_imm32_b32 hwreg(HW_REG_MODE, 0, 4), 10");
 }
 
 // The 2-bit requant of two channels at once, for shifts up to 21: with v = u M
@@ -420,8 +426,8 @@ __device__ __forceinline__ uint32_t fp4_codes(uint32_t w) { return w - ((w >> 2)
 
 // Four shortcut codes of channels 8 qi + 4 half .. + 3 of a 32-channel block
 // held in c (B = 2: two words; 3: the chunk; 4: four words).
-template <int B>
-__device__ __forceinline__ void quad_codes(const uint32_t *c, int qi, int half, float out[4]) {
+template <int B, typename V>
+__device__ __forceinline__ void quad_codes(const uint32_t *c, int qi, int half, V out[4]) {
   uint32_t v, hi = 0;
   if constexpr (B == 2 || B == 3) {
     v = c[qi >> 1] >> (16 * (qi & 1) + 8 * half);
@@ -434,7 +440,7 @@ __device__ __forceinline__ void quad_codes(const uint32_t *c, int qi, int half, 
     uint32_t q;
     if constexpr (B == 3) q = ((v >> (2 * e)) & 3u) | (((hi >> (2 * e)) & 1u) << 2);
     else q = (v >> (B * e)) & ((1u << B) - 1u);
-    out[e] = (float)q;
+    out[e] = (V)q;
   }
 }
 
@@ -492,8 +498,9 @@ struct FpCfg {
 // one piece meet all banks.
 template <int NP>
 __device__ __forceinline__ int piece_swizzle(int pixel) { return (pixel / (16 / NP)) & (NP - 1); }
-template <int B, int PB, int WN, int WM, int MODE, bool DUMP, int KPS, int S, bool FAST, bool PAIR>
+template <int B, int PB, int WN, int WM, int MODE, bool DUMP, int KPS, int S, Ep EP, bool PAIR>
 __device__ __forceinline__ void conv_fp_tile(const FpArgs &a) {
+  static_assert(!DUMP || EP == kWide, "one build with the dump, for every layer");
   using C = FpCfg<B, PB, WN, WM, KPS>;
   using T = FpT<B>;
   constexpr int NT = C::NT, TN = C::TN, TM = C::TM, CB = 2;
@@ -506,7 +513,7 @@ __device__ __forceinline__ void conv_fp_tile(const FpArgs &a) {
   constexpr int RSB = MODE == 1 && !LATE ? C::RP * 16 : 0;
   __shared__ __attribute__((aligned(1024))) uint8_t lds[RING + CST + RSB];
 
-  if (a.gated && a.bad[0] != 0) return;
+  if (gated_off(a)) return;
   TileId id;
   if (!tile_of(a, id)) return;
   const int tid = (int)threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
@@ -645,7 +652,7 @@ __device__ __forceinline__ void conv_fp_tile(const FpArgs &a) {
   const bool more = C::LMAX != C::LMIN && wave < C::full();
   int so = 0, slot_f = S - 1;  // byte offset of the stage's slot; slot of the next fetch
   const float *cst = (const float *)(lds + RING) + wn * 256;
-  const double *csd = (const double *)cst;                // B = 8
+  const double *csd = (const double *)cst;                // B = 8 and kWide
   const int32_t *csi = (const int32_t *)cst;
   for (int s = 0; s < NS; ++s) {
     // stage s has landed; up to S - 2 younger ones may be in flight
@@ -677,6 +684,7 @@ __device__ __forceinline__ void conv_fp_tile(const FpArgs &a) {
 #pragma unroll
             for (int pb = 0; pb < PB; ++pb) {
               if constexpr (B == 8) acc[cb][pb][4 * qi + e] = csi[128 + c0 + e];
+              else if constexpr (EP == kWide) acc[cb][pb][4 * qi + e] = 0.0f;
               else acc[cb][pb][4 * qi + e] = cst[64 + c0 + e];
             }
         }
@@ -707,12 +715,18 @@ __device__ __forceinline__ void conv_fp_tile(const FpArgs &a) {
               a.dump[((int64_t)m * a.G + gd) * a.cout + ch0 + c] =
                   acc[cb][pb][r] - csi[128 + c] + a.wsum[g * a.cout + ch0 + c];
             else
-              a.dump[((int64_t)m * a.G + gd) * a.cout + ch0 + c] =
-                  (int)((acc[cb][pb][r] - cst[64 + c]) * (float)(1 << T::L));
+              a.dump[((int64_t)m * a.G + gd) * a.cout + ch0 + c] = (int)(acc[cb][pb][r] * (float)(1 << T::L));
         }
   }
   constexpr uint32_t qmax = (1u << B) - 1u;
   uint32_t w2[CB][PB];
+  if constexpr (EP != kFp4) {
+    set_round_down();
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+      for (int pb = 0; pb < PB; ++pb) asm volatile("" : "+v"(acc[cb][pb]));
+  }
   if constexpr (B == 8) {
     const uint32_t q8 = (1u << a.out_bits) - 1u;
 #pragma unroll
@@ -736,9 +750,11 @@ __device__ __forceinline__ void conv_fp_tile(const FpArgs &a) {
                                      8 * (qi & 1) + 4 * half);
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            int32_t u = acc[cb][pb][4 * qi + e];
-            if constexpr (MODE == 1) u += rm[e] * (int32_t)((rc >> (8 * e)) & 255u);
-            w |= min(requant_f64(u, sc[e]), q8) << (8 * e);
+            const int32_t v = acc[cb][pb][4 * qi + e], code = (int32_t)((rc >> (8 * e)) & 255u);
+            double u;
+            if constexpr (MODE == 1 && EP == kWide) u = __builtin_fma((double)rm[e], (double)code, (double)v);
+            else u = (double)(MODE == 1 ? v + rm[e] * code : v);
+            w |= requant_f64(u, sc[e], q8) << (8 * e);
           }
           qv[pb][qi] = w;
         }
@@ -761,7 +777,7 @@ __device__ __forceinline__ void conv_fp_tile(const FpArgs &a) {
         }
       }
     }
-  } else if constexpr (FAST) {
+  } else if constexpr (EP == kFp4) {
     // 2-bit codes, 2.1 VALU instructions a value instead of 4.3 (and 2 instead
     // of 3 for a shortcut): both ways between codes and floats by the FP4
     // conversions, even and odd codes in nibbles of their own
@@ -822,11 +838,6 @@ __device__ __forceinline__ void conv_fp_tile(const FpArgs &a) {
       }
     }
   } else {
-  set_round_down();
-#pragma unroll
-  for (int cb = 0; cb < CB; ++cb)
-#pragma unroll
-    for (int pb = 0; pb < PB; ++pb) asm volatile("" : "+v"(acc[cb][pb]));
 #pragma unroll
   for (int cb = 0; cb < CB; ++cb) {
     uint32_t qv[PB][4], hv[PB][4], rc[PB][4];
@@ -849,19 +860,35 @@ __device__ __forceinline__ void conv_fp_tile(const FpArgs &a) {
       // one quad at a time: keeps the constants of the others out of registers
       __builtin_amdgcn_sched_barrier(0);
       const int c0 = cb * 32 + 8 * qi + 4 * half;
-      const v4f sc = *(const v4f *)(cst + c0);
-      v4f rm = {0.0f, 0.0f, 0.0f, 0.0f};
-      if constexpr (MODE == 1) rm = *(const v4f *)(cst + 128 + c0);
+      v4f sc, rm = {0.0f, 0.0f, 0.0f, 0.0f};
+      double sd[4];
+      v4i bw, rw = {0, 0, 0, 0};
+      if constexpr (EP == kWide) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sd[e] = csd[c0 + e];
+        bw = *(const v4i *)(csi + 128 + c0);
+        if constexpr (MODE == 1) rw = *(const v4i *)(csi + 192 + c0);
+      } else {
+        sc = *(const v4f *)(cst + c0);
+        if constexpr (MODE == 1) rm = *(const v4f *)(cst + 128 + c0);
+      }
 #pragma unroll
       for (int pb = 0; pb < PB; ++pb) {
-        float rcode[4];
+        typename std::conditional<EP == kWide, int32_t, float>::type rcode[4];
         if constexpr (MODE == 1) quad_codes<B>(rc[pb], qi, half, rcode);
         uint32_t w = 0, h = 0;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           float u = acc[cb][pb][4 * qi + e];
-          if constexpr (MODE == 1) u = __builtin_fmaf(rm[e], rcode[e], u);  // exact
-          const uint32_t q = requant_rd(u, sc[e], qmax);
+          uint32_t q;
+          if constexpr (EP == kWide) {
+            int32_t v = (int32_t)(u * (float)(1 << T::L)) + bw[e];
+            if constexpr (MODE == 1) v += __mul24(rw[e], rcode[e]);  // |res_mult| < 2^15
+            q = requant_f64((double)v, sd[e], qmax);
+          } else {
+            if constexpr (MODE == 1) u = __builtin_fmaf(rm[e], rcode[e], u);  // exact
+            q = requant_rd(u, sc[e], qmax);
+          }
           if constexpr (B == 3) {
             w |= (q & 3u) << (2 * e);
             h |= (q >> 2) << (2 * e);
@@ -937,15 +964,16 @@ __device__ __forceinline__ void conv_fp_tile(const FpArgs &a) {
 // of a workgroup.  A wave loads its operands straight into registers, U
 // K-blocks at once, with no barrier; the accumulators meet in LDS, each wave
 // adds and requantises its share of the quads and the codes are packed there.
-template <int B, int PB, int NW, int MODE, bool DUMP>
+template <int B, int PB, int NW, int MODE, bool DUMP, Ep EP>
 __device__ __forceinline__ void conv_fp_split(const FpArgs &a) {
+  static_assert(EP != kFp4 && (!DUMP || EP == kWide), "fp32 or any parameters; the dump with the latter");
   using T = FpT<B>;
   constexpr int U = B == 8 ? 2 : 4, Q = PB * 4;
   using V4 = typename std::conditional<B == 8, v4i, v4f>::type;
   static_assert(Q % NW == 0 || NW % Q == 0, "whole quads per wave");
   __shared__ V4 red[NW * Q * 64];
   __shared__ uint32_t cw[32 * PB * 9];  // packed quads of a pixel's 32 channels (9: no bank conflicts)
-  if (a.gated && a.bad[0] != 0) return;
+  if (gated_off(a)) return;
   TileId id;
   if (!tile_of(a, id)) return;
   const int tid = (int)threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
@@ -1060,22 +1088,31 @@ __device__ __forceinline__ void conv_fp_split(const FpArgs &a) {
       }
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        int32_t u = v[e] + ci[e];
+        int32_t t = v[e] + ci[e];
         if constexpr (DUMP)
           if (m < a.M && k32 + c0 + e < a.cout)
             a.dump[((int64_t)m * a.G + gd) * a.cout + k32 + c0 + e] = v[e] + a.wsum[g * a.cout + k32 + c0 + e];
-        if constexpr (MODE == 1) u += ci[64 + e] * (int32_t)((rc >> (8 * e)) & 255u);
-        w |= min(requant_f64(u, sc[e]), q8) << (8 * e);
+        const int32_t code = (int32_t)((rc >> (8 * e)) & 255u);
+        asm volatile("" : "+v"(t));  // after set_round_down
+        double u;
+        if constexpr (MODE == 1 && EP == kWide) u = __builtin_fma((double)ci[64 + e], (double)code, (double)t);
+        else u = (double)(MODE == 1 ? t + ci[64 + e] * code : t);
+        w |= requant_f64(u, sc[e], q8) << (8 * e);
       }
       cw[pixel * 9 + 2 * qi + half] = w;
       continue;
     } else {
     const float *cst = blk + (k32 & 32) + c0;
-    const v4f sc = *(const v4f *)cst, b = *(const v4f *)(cst + 64);
-    float rcode[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    v4f rm = {0.0f, 0.0f, 0.0f, 0.0f};
+    const double *csd = (const double *)blk + (k32 & 32) + c0;  // kWide
+    const int32_t *csi = (const int32_t *)blk + 128 + (k32 & 32) + c0;
+    v4f sc, b, rm = {0.0f, 0.0f, 0.0f, 0.0f};
+    if constexpr (EP != kWide) {
+      sc = *(const v4f *)cst;
+      b = *(const v4f *)(cst + 64);
+      if constexpr (MODE == 1) rm = *(const v4f *)(cst + 128);
+    }
+    typename std::conditional<EP == kWide, int32_t, float>::type rcode[4] = {0, 0, 0, 0};
     if constexpr (MODE == 1) {
-      rm = *(const v4f *)(cst + 128);
       const auto r_res = __builtin_amdgcn_make_buffer_rsrc((void *)a.res, (short)0, (int)a.res_bytes, 0x00020000);
       const uint32_t vo = m < a.M ? (uint32_t)(m * a.res_pix + gd * a.res_gs) : kOob;
       uint32_t rc[4];
@@ -1092,10 +1129,18 @@ __device__ __forceinline__ void conv_fp_split(const FpArgs &a) {
     uint32_t w = 0, h = 0;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      float u = v[e] + b[e];
-      if constexpr (MODE == 1) u = __builtin_fmaf(rm[e], rcode[e], u);
-      asm volatile("" : "+v"(u));  // after set_round_down
-      const uint32_t q = requant_rd(u, sc[e], (1u << B) - 1u);
+      uint32_t q;
+      if constexpr (EP == kWide) {
+        int32_t t = (int32_t)(v[e] * (float)(1 << T::L)) + csi[e];
+        if constexpr (MODE == 1) t += __mul24(csi[64 + e], rcode[e]);
+        asm volatile("" : "+v"(t));  // after set_round_down
+        q = requant_f64((double)t, csd[e], (1u << B) - 1u);
+      } else {
+        float u = v[e] + b[e];
+        if constexpr (MODE == 1) u = __builtin_fmaf(rm[e], rcode[e], u);
+        asm volatile("" : "+v"(u));  // after set_round_down
+        q = requant_rd(u, sc[e], (1u << B) - 1u);
+      }
       if constexpr (B == 3) {
         w |= (q & 3u) << (2 * e);
         h |= (q >> 2) << (2 * e);
@@ -1131,14 +1176,14 @@ __device__ __forceinline__ void conv_fp_split(const FpArgs &a) {
 
 // Entry points by matrix-core format.
 #define PALQ_FP_TILE(NAME)                                                                            \
-  template <int B, int PB, int WN, int WM, int MODE, bool DUMP, int KPS, int S, bool FAST, bool PAIR>    \
-  __global__ __launch_bounds__(WN *WM * 64, B == 2 ? 4 : B == 8 ? 2 : 3) void NAME(FpArgs a) {  \
-    conv_fp_tile<B, PB, WN, WM, MODE, DUMP, KPS, S, FAST, PAIR>(a);                                     \
+  template <int B, int PB, int WN, int WM, int MODE, bool DUMP, int KPS, int S, Ep EP, bool PAIR>     \
+  __global__ __launch_bounds__(WN *WM * 64, B == 2 ? 4 : B == 8 ? 2 : 3) void NAME(FpArgs a) {        \
+    conv_fp_tile<B, PB, WN, WM, MODE, DUMP, KPS, S, EP, PAIR>(a);                                     \
   }
 #define PALQ_FP_SPLIT(NAME)                                                     \
-  template <int B, int PB, int NW, int MODE, bool DUMP>                         \
+  template <int B, int PB, int NW, int MODE, bool DUMP, Ep EP>                  \
   __global__ __launch_bounds__(NW * 64, 4) void NAME(FpArgs a) {                \
-    conv_fp_split<B, PB, NW, MODE, DUMP>(a);                                    \
+    conv_fp_split<B, PB, NW, MODE, DUMP, EP>(a);                                \
   }
 PALQ_FP_TILE(conv_fp4_kernel)
 PALQ_FP_TILE(conv_fp6_kernel)
@@ -1163,13 +1208,12 @@ int fp_kb(const ConvArgs &a) { return fp_km(a) + (a.proj.data ? cpb_of(a.proj.cp
 int fp_coutp(const ConvArgs &a) { return (a.cout + 63) / 64 * 64; }
 int64_t fp_slab(int bits) { return bits == 2 ? 1024 : bits >= 6 ? 2048 : 1536; }
 
-FpArgs fp_args(const ConvArgs &a, const uint8_t *wp, const int32_t *thr, bool checked) {
+FpArgs fp_args(const ConvArgs &a, const uint8_t *wp, const int32_t *thr) {
   FpArgs f{};
   f.in = a.in.data; f.wp = wp; f.res = a.res.data; f.proj = a.proj.data; f.out = a.out.data;
   f.cst = (const float *)thr;
   f.bad = conv_fp_flag(a, thr);
-  f.gated = checked ? 0 : 1;
-  f.fast = checked && a.fp_fast;
+  f.fast = a.fp_fast;
   f.dump = a.acc_dump;
   f.cout = a.cout;
   f.coutp = fp_coutp(a);
@@ -1240,48 +1284,49 @@ int cu_count() {
   return cus;
 }
 
-template <int B, int PB, int WN, int WM, int MODE, bool DUMP, int KPS, int S, bool PAIR>
-hipError_t launch_tile_mode(const FpArgs &f, unsigned grid, hipStream_t s) {
-  const dim3 block(WN * WM * 64);
+template <int B, int PB, int WN, int WM, int MODE, bool DUMP, int KPS, int S, bool PAIR, Ep EP>
+hipError_t launch_tile_ep(const FpArgs &f, unsigned g, hipStream_t s) {
+  const dim3 block(WN * WM * 64), grid(g);
   if constexpr (B == 8)
-    hipLaunchKernelGGL((conv_i8_kernel<B, PB, WN, WM, MODE, DUMP, KPS, S, false, PAIR>), dim3(grid), block, 0, s, f);
+    hipLaunchKernelGGL((conv_i8_kernel<B, PB, WN, WM, MODE, DUMP, KPS, S, EP, PAIR>), grid, block, 0, s, f);
   else if constexpr (B != 2)
-    hipLaunchKernelGGL((conv_fp6_kernel<B, PB, WN, WM, MODE, DUMP, KPS, S, false, PAIR>), dim3(grid), block, 0, s, f);
-  else if (f.fast)
-    hipLaunchKernelGGL((conv_fp4_kernel<B, PB, WN, WM, MODE, DUMP, KPS, S, true, PAIR>), dim3(grid), block, 0, s, f);
+    hipLaunchKernelGGL((conv_fp6_kernel<B, PB, WN, WM, MODE, DUMP, KPS, S, EP, PAIR>), grid, block, 0, s, f);
   else
-    hipLaunchKernelGGL((conv_fp4_kernel<B, PB, WN, WM, MODE, DUMP, KPS, S, false, PAIR>), dim3(grid), block, 0, s, f);
+    hipLaunchKernelGGL((conv_fp4_kernel<B, PB, WN, WM, MODE, DUMP, KPS, S, EP, PAIR>), grid, block, 0, s, f);
   return hipGetLastError();
 }
-template <int B, int PB, int WN, int WM, bool DUMP, int KPS, int S, bool PAIR>
+template <int B, int PB, int WN, int WM, int MODE, bool DUMP, int KPS, int S, bool PAIR, bool WIDE>
+hipError_t launch_tile_mode(const FpArgs &f, unsigned grid, hipStream_t s) {
+  if constexpr (WIDE) return launch_tile_ep<B, PB, WN, WM, MODE, DUMP, KPS, S, PAIR, kWide>(f, grid, s);
+  else if constexpr (B == 2)
+    if (f.fast) return launch_tile_ep<B, PB, WN, WM, MODE, DUMP, KPS, S, PAIR, kFp4>(f, grid, s);
+  if constexpr (!WIDE) return launch_tile_ep<B, PB, WN, WM, MODE, DUMP, KPS, S, PAIR, kBase>(f, grid, s);
+}
+template <int B, int PB, int WN, int WM, int KPS, int S, bool PAIR, bool WIDE = false, bool DUMP = false>
 hipError_t launch_tile(FpArgs f, int64_t in_bytes, hipStream_t s) {
   const unsigned grid = fp_tiles(f, 64 * WN, 32 * PB * WM, in_bytes);
-  if (f.res) return launch_tile_mode<B, PB, WN, WM, 1, DUMP, KPS, S, PAIR>(f, grid, s);
-  if (f.proj) return launch_tile_mode<B, PB, WN, WM, 2, DUMP, KPS, S, PAIR>(f, grid, s);
-  return launch_tile_mode<B, PB, WN, WM, 0, DUMP, KPS, S, PAIR>(f, grid, s);
+  if (f.res) return launch_tile_mode<B, PB, WN, WM, 1, DUMP, KPS, S, PAIR, WIDE>(f, grid, s);
+  if (f.proj) return launch_tile_mode<B, PB, WN, WM, 2, DUMP, KPS, S, PAIR, WIDE>(f, grid, s);
+  return launch_tile_mode<B, PB, WN, WM, 0, DUMP, KPS, S, PAIR, WIDE>(f, grid, s);
 }
 
-template <int B, int PB, int NW, int MODE>
-hipError_t launch_split_mode(const FpArgs &f, unsigned grid, hipStream_t s) {
-  const dim3 block(NW * 64);
-  if constexpr (B == 2) {
-    if (f.dump) hipLaunchKernelGGL((conv_fp4_split_kernel<B, PB, NW, MODE, true>), dim3(grid), block, 0, s, f);
-    else hipLaunchKernelGGL((conv_fp4_split_kernel<B, PB, NW, MODE, false>), dim3(grid), block, 0, s, f);
-  } else if constexpr (B == 8) {
-    if (f.dump) hipLaunchKernelGGL((conv_i8_split_kernel<B, PB, NW, MODE, true>), dim3(grid), block, 0, s, f);
-    else hipLaunchKernelGGL((conv_i8_split_kernel<B, PB, NW, MODE, false>), dim3(grid), block, 0, s, f);
-  } else {
-    if (f.dump) hipLaunchKernelGGL((conv_fp6_split_kernel<B, PB, NW, MODE, true>), dim3(grid), block, 0, s, f);
-    else hipLaunchKernelGGL((conv_fp6_split_kernel<B, PB, NW, MODE, false>), dim3(grid), block, 0, s, f);
-  }
+template <int B, int PB, int NW, int MODE, bool DUMP, Ep EP>
+hipError_t launch_split_ep(const FpArgs &f, unsigned g, hipStream_t s) {
+  const dim3 block(NW * 64), grid(g);
+  if constexpr (B == 8)
+    hipLaunchKernelGGL((conv_i8_split_kernel<B, PB, NW, MODE, DUMP, EP>), grid, block, 0, s, f);
+  else if constexpr (B != 2)
+    hipLaunchKernelGGL((conv_fp6_split_kernel<B, PB, NW, MODE, DUMP, EP>), grid, block, 0, s, f);
+  else
+    hipLaunchKernelGGL((conv_fp4_split_kernel<B, PB, NW, MODE, DUMP, EP>), grid, block, 0, s, f);
   return hipGetLastError();
 }
-template <int B, int PB, int NW>
+template <int B, int PB, int NW, bool DUMP, Ep EP>
 hipError_t launch_split(FpArgs f, int64_t in_bytes, hipStream_t s) {
   const unsigned grid = fp_tiles(f, 32, 32 * PB, in_bytes);
-  if (f.res) return launch_split_mode<B, PB, NW, 1>(f, grid, s);
-  if (f.proj) return launch_split_mode<B, PB, NW, 2>(f, grid, s);
-  return launch_split_mode<B, PB, NW, 0>(f, grid, s);
+  if (f.res) return launch_split_ep<B, PB, NW, 1, DUMP, EP>(f, grid, s);
+  if (f.proj) return launch_split_ep<B, PB, NW, 2, DUMP, EP>(f, grid, s);
+  return launch_split_ep<B, PB, NW, 0, DUMP, EP>(f, grid, s);
 }
 
 // Which build takes a layer (times for the 14x14, 256-channel layer unless
@@ -1305,33 +1350,47 @@ hipError_t launch_split(FpArgs f, int64_t in_bytes, hipStream_t s) {
 //    two need an even number of K-blocks per tap (pieces by pixel: ResNet-18 G = 2
 //    4-bit batch 32, stage 3, 16.2 -> 13.7 us; 14x14 3-bit batch 128 with shortcut
 //    55.9 -> 51.5).
+// The wide builds come without the stages of four (2-bit) and of two (3- and
+// 4-bit), the accumulator dump in one build for every layer.
 template <int B>
-hipError_t launch_fp(const FpArgs &f, int64_t in_bytes, hipStream_t s) {
+hipError_t launch_fp(const FpArgs &f, bool wide_ep, int64_t in_bytes, hipStream_t s) {
   const int64_t cus = cu_count();
   const int64_t few = (int64_t)((f.M + 63) / 64) * ((f.cout + 31) / 32) * f.G;
-  if (few <= 2 * cus || (few <= 4 * cus && f.kb >= 64)) return launch_split<B, 2, 8>(f, in_bytes, s);
+  if (few <= 2 * cus || (few <= 4 * cus && f.kb >= 64)) {
+    if (f.dump) return launch_split<B, 2, 8, true, kWide>(f, in_bytes, s);
+    if (wide_ep) return launch_split<B, 2, 8, false, kWide>(f, in_bytes, s);
+    return launch_split<B, 2, 8, false, kBase>(f, in_bytes, s);
+  }
   const bool wide = f.coutp % 128 == 0;
+  constexpr int KW = B == 2 ? 2 : 1, SW = B == 2 ? 2 : 3;
+  if (f.dump) return launch_tile<B, 2, 1, 4, KW, SW, B != 2, true, true>(f, in_bytes, s);
+  if (wide_ep) {
+    if constexpr (B == 2)
+      if (f.kb < 12)
+        return wide ? launch_tile<B, 2, 2, 2, 1, 3, false, true>(f, in_bytes, s)
+                    : launch_tile<B, 2, 1, 4, 1, 3, false, true>(f, in_bytes, s);
+    return wide ? launch_tile<B, 2, 2, 2, KW, SW, B != 2, true>(f, in_bytes, s)
+                : launch_tile<B, 2, 1, 4, KW, SW, B != 2, true>(f, in_bytes, s);
+  }
   if constexpr (B == 2) {
-    if (f.dump) return launch_tile<B, 2, 1, 4, true, 2, 2, false>(f, in_bytes, s);
     if (wide && f.cpb % 4 == 0) {
-      if (f.kb == 4) return launch_tile<B, 2, 2, 2, false, 4, 1, true>(f, in_bytes, s);
+      if (f.kb == 4) return launch_tile<B, 2, 2, 2, 4, 1, true>(f, in_bytes, s);
       const int64_t tiles = (int64_t)((f.M + 127) / 128) * (f.coutp / 128) * f.G;
       if (f.kb >= 8 && (tiles <= 3 * cus || tiles >= 6 * cus))
-        return launch_tile<B, 2, 2, 2, false, 4, 2, true>(f, in_bytes, s);
+        return launch_tile<B, 2, 2, 2, 4, 2, true>(f, in_bytes, s);
     }
     if (f.kb < 12)
-      return wide ? launch_tile<B, 2, 2, 2, false, 1, 3, false>(f, in_bytes, s)
-                  : launch_tile<B, 2, 1, 4, false, 1, 3, false>(f, in_bytes, s);
-    return wide ? launch_tile<B, 2, 2, 2, false, 2, 2, false>(f, in_bytes, s)
-                : launch_tile<B, 2, 1, 4, false, 2, 2, false>(f, in_bytes, s);
+      return wide ? launch_tile<B, 2, 2, 2, 1, 3, false>(f, in_bytes, s)
+                  : launch_tile<B, 2, 1, 4, 1, 3, false>(f, in_bytes, s);
+    return wide ? launch_tile<B, 2, 2, 2, 2, 2, false>(f, in_bytes, s)
+                : launch_tile<B, 2, 1, 4, 2, 2, false>(f, in_bytes, s);
   } else {
-    if (f.dump) return launch_tile<B, 2, 1, 4, true, 1, 3, true>(f, in_bytes, s);
     if constexpr (B != 8)
       if (f.kb >= 12 && f.cpb % 2 == 0)
-        return wide ? launch_tile<B, 2, 2, 2, false, 2, 2, true>(f, in_bytes, s)
-                    : launch_tile<B, 2, 1, 4, false, 2, 2, true>(f, in_bytes, s);
-    return wide ? launch_tile<B, 2, 2, 2, false, 1, 3, true>(f, in_bytes, s)
-                : launch_tile<B, 2, 1, 4, false, 1, 3, true>(f, in_bytes, s);
+        return wide ? launch_tile<B, 2, 2, 2, 2, 2, true>(f, in_bytes, s)
+                    : launch_tile<B, 2, 1, 4, 2, 2, true>(f, in_bytes, s);
+    return wide ? launch_tile<B, 2, 2, 2, 1, 3, true>(f, in_bytes, s)
+                : launch_tile<B, 2, 1, 4, 1, 3, true>(f, in_bytes, s);
   }
 }
 
@@ -1367,17 +1426,16 @@ bool conv_fp_applies(const ConvArgs &a) {
   return ((int64_t)a.out.n * a.ho * a.wo + 63) / 64 * ((a.cout + 31) / 32) * a.in.groups < lim;
 }
 
-ConvPlan conv_fp_plan(const ConvArgs &a) {
-  const int64_t ch = (int64_t)a.in.groups * fp_coutp(a);
-  return {fp_slab_bytes(a) + (fp_is_i8(a) ? (size_t)a.in.groups * a.cout * 4 : 0), (size_t)(ch * 16 + 16)};
-}
+// Words of one set of constants (base or wide; B = 8 has one).
+static int64_t fp_cst_words(const ConvArgs &a) { return (int64_t)a.in.groups * fp_coutp(a) * 4; }
 
-const int32_t *conv_fp_wsum(const ConvArgs &a, const uint8_t *wp) {
-  return fp_is_i8(a) ? (const int32_t *)(wp + fp_slab_bytes(a)) : nullptr;
+ConvPlan conv_fp_plan(const ConvArgs &a) {
+  return {fp_slab_bytes(a) + (fp_is_i8(a) ? (size_t)a.in.groups * a.cout * 4 : 0),
+          (size_t)(fp_cst_words(a) * (fp_is_i8(a) ? 4 : 8) + 16)};
 }
 
 const int32_t *conv_fp_flag(const ConvArgs &a, const int32_t *thr) {
-  return thr + (int64_t)a.in.groups * fp_coutp(a) * 4;
+  return thr + fp_cst_words(a) * (fp_is_i8(a) ? 1 : 2);
 }
 
 bool conv_fp_fast(const ConvArgs &a, const int32_t *thr) {
@@ -1401,6 +1459,7 @@ hipError_t launch_conv_fp_prepare(const ConvArgs &a, uint8_t *wp, int32_t *thr, 
   p.acc_bound = fp_acc_bound(a);
   p.wp = wp;
   p.cst = (float *)thr;
+  p.wide = (uint8_t *)(thr + (fp_is_i8(a) ? 0 : fp_cst_words(a)));
   p.bad = (int32_t *)conv_fp_flag(a, thr);
   p.w_bits = a.w_bits;
   if (fp_is_i8(a)) {
@@ -1416,16 +1475,31 @@ hipError_t launch_conv_fp_prepare(const ConvArgs &a, uint8_t *wp, int32_t *thr, 
   return hipGetLastError();
 }
 
-hipError_t launch_conv_fp(const ConvArgs &a, const uint8_t *wp, const int32_t *thr, bool checked, hipStream_t s) {
+const char *conv_fp_label(const ConvArgs &a, int epi) {
+  if (a.in.bits == 2) return epi == 1 ? "conv_fp4_kernel[wide]" : "conv_fp4_kernel";
+  if (a.in.bits >= 6) return epi == 1 ? "conv_i8_kernel[wide]" : "conv_i8_kernel";
+  return epi == 1 ? "conv_fp6_kernel[wide]" : "conv_fp6_kernel";
+}
+
+// gate: FpArgs::gate.
+static hipError_t launch_fp_ep(const ConvArgs &a, FpArgs f, const int32_t *thr, bool wide, int gate, hipStream_t s) {
+  f.gate = gate;
+  if (wide && !fp_is_i8(a)) f.cst = (const float *)(thr + fp_cst_words(a));
+  if (fp_is_i8(a)) return launch_fp<8>(f, wide, a.in.bytes, s);
+  if (a.in.bits == 2) return launch_fp<2>(f, wide, a.in.bytes, s);
+  if (a.in.bits == 3) return launch_fp<3>(f, wide, a.in.bytes, s);
+  return launch_fp<4>(f, wide, a.in.bytes, s);
+}
+
+hipError_t launch_conv_fp(const ConvArgs &a, const uint8_t *wp, const int32_t *thr, int epi, hipStream_t s) {
   if ((int64_t)a.out.n * a.ho * a.wo == 0) return hipSuccess;
-  FpArgs f = fp_args(a, wp, thr, checked);
-  if (fp_is_i8(a)) {
-    f.wsum = conv_fp_wsum(a, wp);
-    return launch_fp<8>(f, a.in.bytes, s);
-  }
-  if (a.in.bits == 2) return launch_fp<2>(f, a.in.bytes, s);
-  if (a.in.bits == 3) return launch_fp<3>(f, a.in.bytes, s);
-  return launch_fp<4>(f, a.in.bytes, s);
+  FpArgs f = fp_args(a, wp, thr);
+  if (fp_is_i8(a)) f.wsum = (const int32_t *)(wp + fp_slab_bytes(a));
+  if (a.acc_dump) return launch_fp_ep(a, f, thr, true, 0, s);
+  if (epi >= 0) return launch_fp_ep(a, f, thr, epi == 1, 0, s);
+  f.fast = 0;
+  const hipError_t e = launch_fp_ep(a, f, thr, false, 1, s);
+  return e == hipSuccess ? launch_fp_ep(a, f, thr, true, 2, s) : e;
 }
 
 }  // namespace palq

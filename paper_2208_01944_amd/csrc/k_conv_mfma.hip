@@ -238,8 +238,7 @@ struct Geo {
   int64_t pw_ch;      // bytes of one projection filter channel
   int32_t scale;      // operand scale of the accumulator (16 for 2-bit codes)
   const uint8_t *wp;  // weights in MFMA operand order (see prepack_kernel)
-  const RqConst *rq;  // per-channel requant constants, then the int64-path flag (null: int64 path)
-  const int32_t *gate;  // a.gated launches: the general build runs only if *gate (null: always)
+  const RqConst *rq;  // per-channel requant constants, then the int64-path flag
   const int32_t *acc0;  // B = 8: per-channel accumulator start 128 sum(w) (act_operand)
   float inv_hw, inv_wo;  // 1 / (ho wo) and 1 / wo, rounded to fp32 (fdiv's estimates)
 };
@@ -368,22 +367,9 @@ __device__ inline int fdiv(int m, int d, float inv_d) {
 
 // Workgroup prologue shared by both kernels: copy the channel block's
 // prepacked weights (all K-blocks) and its requant constants into LDS.
-// geo.wp null (the general partner of an FP4 / FP6 layer, whose int8 slabs do
-// not exist; it runs only where a channel leaves the fp32 bounds): expand the
-// packed filter here.
-template <int B, bool STEM, int CB>
+template <int CB>
 __device__ inline void stage_block(const ConvArgs &a, const Geo &geo, int g, uint8_t *lds) {
   const int KB = geo.kb_total;
-  if (geo.wp == nullptr) {
-    for (int c = threadIdx.x; c < KB * CB * 128; c += kNW * 64) {
-      const int kb = c / (CB * 128), within = c & 127;
-      const int k = blockIdx.y * CB * 32 + ((c >> 7) % CB) * 32 + (within & 31);
-      *(v4i *)(lds + c * 16) = weight_unit<B, STEM>(a, geo, g, (g + a.shuffle) % a.in.groups, k, kb,
-                                                    2 * ((within >> 5) & 1) + (within >> 6));
-    }
-    __syncthreads();
-    return;
-  }
   const uint8_t *wsrc = geo.wp + (int64_t)(g * (a.cout / 32) + blockIdx.y * CB) * KB * kSlab;
   const int chunks = KB * CB * 128;
   for (int c = threadIdx.x; c < chunks; c += kNW * 64) {
@@ -411,7 +397,7 @@ __device__ __forceinline__ void epilogue(const ConvArgs &a, const Geo &geo, v16i
   const int qmax = (1 << a.out.bits) - 1;
   const int64_t outC = (int64_t)a.in.groups * a.cout;
   const int lsc = geo.scale == 16 ? 4 : 0;
-  const bool exact64 = geo.rq == nullptr || ((const int32_t *)(geo.rq + (int64_t)a.in.groups * a.cout))[0] != 0;
+  const bool exact64 = ((const int32_t *)(geo.rq + (int64_t)a.in.groups * a.cout))[0] != 0;
 #pragma unroll
   for (int cb = 0; cb < CB; ++cb) {
     const int kc = ch0 + cb * 32;
@@ -428,7 +414,7 @@ __device__ __forceinline__ void epilogue(const ConvArgs &a, const Geo &geo, v16i
       if constexpr (RB != 0) rmu = *(const v4i *)(a.res_mult + csb + cq);
       RqConst k[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) k[e] = rq[cb * 32 + cq + e];  // (not staged, and not used, when geo.rq is null)
+      for (int e = 0; e < 4; ++e) k[e] = rq[cb * 32 + cq + e];
 #pragma unroll
       for (int pb = 0; pb < PB; ++pb) {
         const int64_t mp = mbase + pb * 32 + l32;
@@ -693,10 +679,10 @@ __device__ inline bool needs_general(const ConvArgs &a, const Geo &geo, int rb) 
 
 // Whether this build of a persistent kernel leaves at once.  a.gated: the
 // launch is the general partner of a tiled launch, so only the general build
-// runs, and only when the partner's device flag is set; otherwise the fast and
-// the general build split by needs_general.
+// runs, and only when the int64 flag is set; otherwise the fast and the general
+// build split by needs_general.
 __device__ inline bool skip_build(const ConvArgs &a, const Geo &geo, int rb, bool gen) {
-  if (a.gated) return !gen || (geo.gate && *geo.gate == 0);
+  if (a.gated) return !gen || !int64_flag(a, geo);
   return needs_general(a, geo, rb) != gen;
 }
 
@@ -761,7 +747,7 @@ __global__ __launch_bounds__(kNW * 64) void conv_grouped_kernel(ConvArgs a, Geo 
   // the launcher may start both builds when it cannot tell which applies:
   // the other one leaves at once (before any barrier)
   if (skip_build(a, geo, RB, GEN)) return;
-  stage_block<B, false, CB>(a, geo, g, lds);
+  stage_block<CB>(a, geo, g, lds);
   const int first = blockIdx.x * kNW + wave;
   const int tstride = gridDim.x * kNW;
   if (first >= tiles) return;  // no barrier follows
@@ -914,7 +900,7 @@ __global__ __launch_bounds__(kNW * 64) void conv_stem_kernel(ConvArgs a, Geo geo
   // the launcher may start both builds when it cannot tell which applies:
   // the other one leaves at once (before any barrier)
   if (skip_build(a, geo, RB, GEN)) return;
-  stage_block<8, true, CB>(a, geo, g, lds);
+  stage_block<CB>(a, geo, g, lds);
   const int first = blockIdx.x * kNW + wave;
   const int tstride = gridDim.x * kNW;
   if (first >= tiles) return;
@@ -2364,7 +2350,9 @@ static bool int8_shape(const ConvArgs &a) {
   return true;
 }
 
-bool conv_mfma_general_fits(const ConvArgs &a) { return int8_shape(a) && pick_cb(a, make_geo(a)) > 0; }
+bool conv_mfma_general_fits(const ConvArgs &a) {
+  return conv_fp_applies(a) || (int8_shape(a) && pick_cb(a, make_geo(a)) > 0);
+}
 
 // The general build needs the filter in LDS; layers longer than that still
 // run on the tiled kernel (its fast epilogue).
@@ -2566,11 +2554,11 @@ size_t stem_rows_offset(const ConvArgs &a) { return (size_t)a.in.groups * a.cout
 
 // Tiled-kernel builds: the 8-bit stem; 2-bit layers on int8 with 64- or
 // 128-channel blocks (256-pixel tiles); wide layers as the Eq. 4 decomposition
-// with 64- or 128-channel tiles; 2-, 3- and 4-bit layers on FP4 / FP6
-// (k_conv_fp.hip, which picks its own tile).
-enum TileBuild { kTileNone = 0, kTileFp, kTileStem, kTileI8C64, kTileI8C128, kTileBdC64, kTileBdC128 };
+// with 64- or 128-channel tiles.
+enum TileBuild { kTileNone = 0, kTileStem, kTileI8C64, kTileI8C128, kTileBdC64, kTileBdC128 };
 
-// The one selection rule of the conv launches: which tiled build (if any)
+// The one selection rule of the conv launches past the layers of k_conv_fp.hip
+// (which picks its own builds): which tiled build (if any)
 // takes the layer given the epilogue build epi (0 fast, 1 general, -1 not
 // known: a tiled build is then launched with its general partner, which
 // runs only if the layer's flag is set).
@@ -2582,10 +2570,6 @@ struct ConvChoice {
 ConvChoice conv_choice(const ConvArgs &a, const Geo &geo, int epi) {
   ConvChoice c{kTileNone, int8_shape(a) ? pick_cb(a, geo) : 0};
   if (epi == 1) return c;
-  if (conv_fp_applies(a)) {
-    c.tile = kTileFp;
-    return c;
-  }
   if (bd_applies(a)) {
     c.tile = a.cout % 128 ? kTileBdC64 : kTileBdC128;
     return c;
@@ -2732,11 +2716,10 @@ hipError_t launch_stem_pool(const ConvArgs &a, const uint8_t *wp, const int32_t 
 }
 
 const char *conv_kernel_label(const ConvArgs &a, int epi) {
+  if (conv_fp_applies(a)) return conv_fp_label(a, epi);
   const Geo geo = make_geo(a);
   switch (conv_choice(a, geo, epi).tile) {
     case kTileStem: return "conv_tile_kernel[stem]";
-    case kTileFp:
-      return a.in.bits == 2 ? "conv_fp4_kernel" : a.in.bits >= 6 ? "conv_i8_kernel" : "conv_fp6_kernel";
     case kTileBdC64: case kTileBdC128: return "conv_bitdecomp_kernel";
     case kTileI8C64: case kTileI8C128: return "conv_tile_kernel[int8]";
     default: return is_stem(a) ? "conv_stem_kernel" : "conv_grouped_kernel";
@@ -2744,6 +2727,7 @@ const char *conv_kernel_label(const ConvArgs &a, int epi) {
 }
 
 hipError_t launch_conv_mfma(const ConvArgs &a_in, const uint8_t *wp, const int32_t *thr, int epi, hipStream_t s) {
+  if (conv_fp_applies(a_in)) return launch_conv_fp(a_in, wp, thr, epi, s);
   ConvArgs a = a_in;
   a.gated = 0;
   Geo geo = make_geo(a);
@@ -2752,46 +2736,30 @@ hipError_t launch_conv_mfma(const ConvArgs &a_in, const uint8_t *wp, const int32
   geo.rq = (const RqConst *)thr;
   const ConvChoice c = conv_choice(a, geo, epi);
   if (c.cb == 0 && c.tile == kTileNone) return hipErrorNotSupported;  // no build for this layer
+  if (a.acc_dump && c.tile == kTileNone) epi = 1;  // only the general persistent build dumps
   hipError_t e = hipSuccess;
   const int nch = a.in.groups * a.cout;
-  if (conv_fp_applies(a)) {
-    // the general partner takes the packed filter and the int64 requant
-    geo.wp = nullptr;
-    geo.rq = nullptr;
-    geo.acc0 = conv_fp_wsum(a, wp);
+  switch (c.tile) {
+    case kTileStem: e = launch_tile<2, 2, 2, 2, true, PALQ_STEM_STAGES>(a, geo, s); break;
+    case kTileBdC64: case kTileBdC128: {
+      Geo gb = geo;
+      gb.wp = wp + bd_offset(a);
+      gb.rq = geo.rq + nch + 1;
+      e = a.in.bits == 4 ? launch_bd_m<4>(a, gb, c.tile, s)
+                         : a.in.bits == 6 ? launch_bd_m<6>(a, gb, c.tile, s) : launch_bd_m<8>(a, gb, c.tile, s);
+      break;
+    }
+    case kTileI8C64: e = launch_tile<2, 2, 1, 4>(a, geo, s); break;
+    case kTileI8C128: e = launch_tile<2, 2, 2, 4>(a, geo, s); break;
+    default: break;
+  }
+  if (e != hipSuccess) return e;
+  if (c.tile != kTileNone) {
+    if (epi == 0) return hipSuccess;
+    // epi unknown: the general partner, which runs only if the flag is set
     a.gated = 1;
-    if (c.tile == kTileFp) {
-      geo.gate = conv_fp_flag(a, thr);
-      e = launch_conv_fp(a, wp, thr, epi == 0, s);
-      if (e != hipSuccess || epi == 0) return e;
-      if (c.cb == 0) return launch_conv_direct(a, s, geo.gate);
-    }
+    if (c.cb == 0) return launch_conv_direct(a, s, (const int32_t *)(geo.rq + nch));
     epi = 1;
-  } else {
-    if (a.acc_dump && c.tile == kTileNone) epi = 1;  // only the general persistent build dumps
-    geo.gate = (const int32_t *)(geo.rq + nch);
-    switch (c.tile) {
-      case kTileStem: e = launch_tile<2, 2, 2, 2, true, PALQ_STEM_STAGES>(a, geo, s); break;
-      case kTileBdC64: case kTileBdC128: {
-        Geo gb = geo;
-        gb.wp = wp + bd_offset(a);
-        gb.rq = geo.rq + nch + 1;
-        e = a.in.bits == 4 ? launch_bd_m<4>(a, gb, c.tile, s)
-                           : a.in.bits == 6 ? launch_bd_m<6>(a, gb, c.tile, s) : launch_bd_m<8>(a, gb, c.tile, s);
-        break;
-      }
-      case kTileI8C64: e = launch_tile<2, 2, 1, 4>(a, geo, s); break;
-      case kTileI8C128: e = launch_tile<2, 2, 2, 4>(a, geo, s); break;
-      default: break;
-    }
-    if (e != hipSuccess) return e;
-    if (c.tile != kTileNone) {
-      if (epi == 0) return hipSuccess;
-      // epi unknown: the general partner, which runs only if the flag is set
-      a.gated = 1;
-      if (c.cb == 0) return launch_conv_direct(a, s, geo.gate);
-      epi = 1;
-    }
   }
   const int cb = c.cb, pb = 1;
   if (is_stem(a)) return cb == 2 ? launch_stem<2, 1>(a, geo, epi, s) : launch_stem<1, 1>(a, geo, epi, s);
@@ -2800,7 +2768,7 @@ hipError_t launch_conv_mfma(const ConvArgs &a_in, const uint8_t *wp, const int32
     case 3: return dispatch_bits<3>(a, geo, cb, pb, epi, s);
     case 4: return dispatch_bits<4>(a, geo, cb, pb, epi, s);
     case 6: case 8:
-      if (!geo.acc0) geo.acc0 = (const int32_t *)(wp + (size_t)nch * geo.kb_total * 64);
+      geo.acc0 = (const int32_t *)(wp + (size_t)nch * geo.kb_total * 64);
       return dispatch_bits<8>(a, geo, cb, pb, epi, s);
   }
   return hipErrorNotSupported;

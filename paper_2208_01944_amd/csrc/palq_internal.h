@@ -144,18 +144,18 @@ int conv_mfma_epilogue(const ConvArgs &a, const int32_t *thr);
 // at once); no host synchronisation either way.
 hipError_t launch_conv_mfma(const ConvArgs &a, const uint8_t *wp, const int32_t *thr, int epi, hipStream_t s);
 // The FP4 / FP6 / int8 kernels (k_conv_fp.hip): layers they take, the scratch they
-// need, their preparation (one launch), the device flag it leaves (non-zero:
-// some channel is outside the requant's bounds and the general partner must run) and
-// the launch (checked: the flag is known to be clear, else the kernel reads it).
+// need, their preparation (one launch), the device flag it leaves (non-zero: some
+// channel needs the wide builds) and the launch (epi 0: the base builds, 1: the
+// wide ones, -1: both, each reading the flag).
 bool conv_fp_applies(const ConvArgs &a);
 ConvPlan conv_fp_plan(const ConvArgs &a);
 const int32_t *conv_fp_flag(const ConvArgs &a, const int32_t *thr);
-const int32_t *conv_fp_wsum(const ConvArgs &a, const uint8_t *wp);  // 6- and 8-bit layers: 128 sum(w), else null
 // Whether the prepared layer's shifts allow the FP4 kernel's shorter requant
 // (reads a flag back, blocking); callers keep the answer in ConvArgs::fp_fast.
 bool conv_fp_fast(const ConvArgs &a, const int32_t *thr);
 hipError_t launch_conv_fp_prepare(const ConvArgs &a, uint8_t *wp, int32_t *thr, hipStream_t s);
-hipError_t launch_conv_fp(const ConvArgs &a, const uint8_t *wp, const int32_t *thr, bool checked, hipStream_t s);
+hipError_t launch_conv_fp(const ConvArgs &a, const uint8_t *wp, const int32_t *thr, int epi, hipStream_t s);
+const char *conv_fp_label(const ConvArgs &a, int epi);
 // The scratch size that palq_group_conv_noalloc's limit is documented for.
 size_t conv_noalloc_bytes(const ConvArgs &a);
 // The static per-GPU buffer of palq_group_conv_noalloc (PALQ_NOALLOC_SCRATCH_BYTES):

@@ -399,10 +399,9 @@ def test_conv_c2_full_batch_every_image(ctx, torch, layer):
 @pytest.mark.parametrize("bits", [2, 3, 4])
 def test_conv_c4_sweep_every_image(ctx, torch, groups, bits):
     """The G x B sweep on the 14x14 / 256-channel layer at batch 128: every
-    image, on the FP4 (2-bit) and FP6 (3- and 4-bit) matrix cores and, 2 and
-    3 bits, on int8."""
+    image, on the FP4 (2-bit) and FP6 (3- and 4-bit) matrix cores and on int8."""
     say(f"conv C4 G={groups} b={bits} batch 128 (every image)")
-    check_full(ctx, torch, I.config_c4(groups, bits), (True, False) if bits in (2, 3) else (True,))
+    check_full(ctx, torch, I.config_c4(groups, bits))
 
 
 @pytest.mark.parametrize("pb4", [False, True])
@@ -582,22 +581,161 @@ def test_conv_fp4_short_k(ctx, torch, name):
     check_full(ctx, torch, case)
 
 
-@pytest.mark.parametrize("kind", ["shift23", "big_bias"])
-def test_conv_fp4_requant_outside_fp32_bounds(ctx, torch, kind):
-    """FP4 layers whose requant leaves the fp32 epilogue's bounds (a shift
-    of 23; biases of magnitude 2^24 on some channels, with an identity
-    shortcut) run the fp64 epilogue of the same kernel in a plan: every
-    image's codes and accumulators, stated and centred, equal the oracle's."""
-    if kind == "shift23":
-        case = I.single_layer(2800, n=2, h=14, w=14, groups=4, cin=64, cout=64, shuffle=1, shift=23)
-    else:
-        case = I.single_layer(2801, n=2, h=14, w=14, groups=2, cin=128, cout=128, shuffle=1, residual="identity")
-        b = np.array(case["layer"]["bias"], np.int64)
-        b[::7] = 1 << 24
-        b[3::7] = -(1 << 24)
-        case["layer"]["bias"] = b.astype(np.int32)
-    say(f"conv FP4 requant outside the fp32 bounds: {kind}")
+# layers of one split-kernel shape and of both tile widths, whole and ragged
+REQUANT_SHAPES = {
+    "split": dict(n=2, h=14, w=14, groups=2, cin=128, cout=128),
+    "split_ragged": dict(n=1, h=9, w=11, groups=3, cin=24, cout=40),
+    "c64": dict(n=24, h=23, w=21, groups=3, cin=64, cout=64),
+    "c64_ragged": dict(n=5, h=43, w=41, groups=3, cin=72, cout=40),
+    "c128": dict(n=13, h=28, w=27, groups=2, cin=64, cout=128),
+}
+
+
+def plan_name(ctx, case, bias):
+    from paper_2208_01944_amd import palq
+    L = case["layer"]
+    t = _layer_tensors(ctx, case, bias)
+    return palq.ConvPlan(ctx, t["x"], t["w"], L["stride"], L["pad"], t["mult"], t["shift"], t["bias"], t["out"],
+                         shuffle=L["shuffle"], **t["kw"]).kernels
+
+
+@pytest.mark.parametrize("bits", [2, 3, 4, 6, 8])
+@pytest.mark.parametrize("residual", [None, "identity", "projection"])
+@pytest.mark.parametrize("shape", sorted(REQUANT_SHAPES))
+def test_conv_wide_multipliers(ctx, torch, shape, residual, bits):
+    """31-bit multipliers (the 15-bit ones with 16 random bits below them): the
+    wide builds of the FP4 / FP6 kernels, whose name the plan says; 6- and
+    8-bit layers stay on their one fp64 requant.  Codes of a one-off call, of a
+    plan and of the dump build, and accumulators, equal the oracle's."""
+    case = I.single_layer(2800 + bits, bits=bits, shuffle=1, residual=residual, **REQUANT_SHAPES[shape])
+    L = case["layer"]
+    low = I.rng(bits).integers(0, 1 << 16, L["mult"].shape)
+    L["mult"] = ((L["mult"].astype(np.int64) << 16) + low).astype(np.int32)
+    L["shift"] = L["shift"] + 16
+    say(f"conv wide multipliers {shape} {residual} b={bits}")
+    want = {2: "conv_fp4_kernel[wide]", 3: "conv_fp6_kernel[wide]", 4: "conv_fp6_kernel[wide]"}.get(bits, "conv_i8_kernel")
+    assert plan_name(ctx, case, L["bias"]) == want
     check_full(ctx, torch, case, fp4_modes=(True,), all_codes=False)
+
+
+@pytest.mark.parametrize("bits", [2, 3, 4])
+@pytest.mark.parametrize("residual", [None, "identity", "projection"])
+@pytest.mark.parametrize("shape", sorted(REQUANT_SHAPES))
+def test_conv_fp32_requant_at_its_bound(ctx, torch, shape, residual, bits):
+    """Biases that bring |t| + |bias| + qmax |res_mult| to 2^24 - 1, the last
+    value the fp32 accumulator and requant take (every channel's threshold
+    between the codes 0 and 1 lies at the middle of its sums, so that an error of one
+    unit shows), and one more on one channel, the first of the wide builds."""
+    case = I.single_layer(2900 + bits, bits=bits, shuffle=1, residual=residual, **REQUANT_SHAPES[shape])
+    L = case["layer"]
+    G, co, kh, kw, ci = L["w"].shape
+    qmax = (1 << bits) - 1
+    bound = kh * kw * ci * qmax << (bits - 1)
+    if residual == "projection":
+        bound += L["proj_w"].shape[-1] * qmax << (bits - 1)
+    nch = G * co
+    if residual == "identity":
+        L["res_mult"] = I.rng(5).integers(1, 64, nch).astype(np.int32)
+        room = (1 << 24) - 1 - bound - qmax * L["res_mult"].astype(np.int64)
+    else:
+        room = np.full(nch, (1 << 24) - 1 - bound, np.int64)
+    bias = room.copy()
+    bias[3::8] *= -1
+    res = case["extra"].get(1) if L["res"] >= 0 else None
+    px = case["extra"].get(1) if L["proj_src"] >= 0 else None
+    acc = O.group_conv(case["x"], L["w"], L["stride"], L["pad"])
+    sc = dict(res=res, res_mult=L["res_mult"] if res is not None else None, proj_x=px, proj_w=L["proj_w"],
+              proj_stride=L["proj_stride"])
+    _, acc_d = O.layer_epilogue(acc, G, L["mult"], L["shift"], None, L["out_bits"], L["shuffle"], **sc)
+    t = acc_d.reshape(-1, nch)
+    if res is not None:
+        t = t + O.cyclic_permute(L["res_mult"].astype(np.int64), G, L["shuffle"]) * np.asarray(res).reshape(-1, nch)
+    mid = np.median(O.cyclic_permute(t, G, -L["shuffle"]), axis=0).astype(np.int64) + room
+    assert (mid >= 1 << 22).all()  # a multiplier below 2^24 puts the threshold there
+    L["shift"] = np.full(nch, 46, np.int32)
+    L["mult"] = np.minimum((1 << 45) // mid, (1 << 24) - 1).astype(np.int32)
+    say(f"conv fp32 requant at its bound {shape} {residual} b={bits}")
+    name = {2: "conv_fp4_kernel", 3: "conv_fp6_kernel", 4: "conv_fp6_kernel"}[bits]
+    for extra, want in ((0, name), (1, name + "[wide]")):
+        b = bias.copy()
+        b[nch // 2] += extra if b[nch // 2] > 0 else -extra
+        assert plan_name(ctx, case, b) == want
+        q, _ = O.layer_epilogue(acc, G, L["mult"], L["shift"], b, L["out_bits"], L["shuffle"], **sc)
+        hist = np.bincount(q.reshape(-1), minlength=2)
+        assert hist[1] > q.size // 5, hist  # both sides of the thresholds
+        for got in run_conv_full(ctx, torch, case, b)[:3]:
+            np.testing.assert_array_equal(got, q)
+
+
+@pytest.mark.parametrize("shift", [21, 22, 26])
+@pytest.mark.parametrize("residual", [None, "identity", "projection"])
+@pytest.mark.parametrize("shape", ["c64", "c128"])
+def test_conv_fp4_shift_bound(ctx, torch, shape, residual, shift):
+    """2-bit tile kernels at the largest shift of the requant by FP4
+    conversions (21) and past it (the fp32 form), with multipliers to match."""
+    case = I.single_layer(3000 + shift, shuffle=1, residual=residual, **REQUANT_SHAPES[shape])
+    L = case["layer"]
+    up = shift - int(L["shift"][0])
+    L["mult"] = L["mult"] << up if up >= 0 else L["mult"] >> -up
+    L["shift"] = L["shift"] + up
+    say(f"conv FP4 shift {shift} {shape} {residual}")
+    assert (L["mult"] < 1 << 24).all() and plan_name(ctx, case, L["bias"]) == "conv_fp4_kernel"
+    check_full(ctx, torch, case, fp4_modes=(True,))
+
+
+@pytest.mark.parametrize("bits", [2, 3, 4, 6, 8])
+@pytest.mark.parametrize("shape", sorted(REQUANT_SHAPES))
+def test_conv_requant_rounds_down(ctx, torch, shape, bits):
+    """u M + 2^60 just below 2^61 (sh = 61, remainders of 2^60 by M under 128):
+    x = u M 2^-61 + 1/2 lies within 2^-54 of 1 from below, so that fp64 to
+    nearest gives 1 and the definition 0; u is the bias, on inputs of code 0."""
+    m = I.rng(12).integers((1 << 30) + 1, 1 << 31, 1 << 25)
+    r = (1 << 60) % m
+    m = m[(r > 0) & (r < 128)]
+    assert len(m) >= 2
+    case = I.single_layer(3100 + bits, bits=bits, shuffle=1, **REQUANT_SHAPES[shape])
+    L = case["layer"]
+    nch = L["w"].shape[0] * L["w"].shape[1]
+    m = np.resize(m, nch)
+    up = np.arange(nch) % 2  # every other channel one unit on: code 1
+    L["mult"], L["shift"] = m.astype(np.int32), np.full(nch, 61, np.int32)
+    L["bias"] = ((1 << 60) // m + up).astype(np.int32)
+    case["x"] = np.zeros_like(case["x"])
+    say(f"conv requant rounds down {shape} b={bits}: {len(np.unique(m))} multipliers")
+    for q in run_conv_full(ctx, torch, case, L["bias"])[:3]:
+        ref = O.cyclic_permute(up.astype(np.int64), L["w"].shape[0], L["shuffle"])
+        np.testing.assert_array_equal(q, np.broadcast_to(ref, q.shape))
+
+
+def test_conv_i8_sums_past_int32(ctx, torch):
+    """An 8-bit layer at every limit of its parameters: t + bias + 255 res_mult
+    passes -2^31, which the wide build forms in fp64."""
+    case = I.single_layer(3200, n=1, h=5, w=5, groups=1, cin=32800, cout=96, k=1, pad=0, bits=8, shuffle=0,
+                          residual="identity")
+    L = case["layer"]
+    case["x"][0, 0], L["w"][:, ::3] = 255, -128
+    case["extra"][1][0, 0] = 255
+    L["bias"][:] = -(1 << 30) + 1
+    L["res_mult"][:] = -32767
+    L["mult"][:] = (1 << 31) - 1
+    say("conv i8 sums past int32")
+    assert plan_name(ctx, case, L["bias"]) == "conv_i8_kernel[wide]"
+    acc_d, q, _, _ = oracle_full(case)
+    assert (acc_d.min() - (1 << 30) + 1 - 32767 * 255) < -(1 << 31) and not q.any()
+    for got in run_conv_full(ctx, torch, case, L["bias"])[:3]:
+        np.testing.assert_array_equal(got, q)
+
+
+@pytest.mark.parametrize("bits", [2, 3, 4, 6, 8])
+@pytest.mark.parametrize("residual", [None, "identity", "projection"])
+@pytest.mark.parametrize("shape", ["c64_ragged", "c128"])
+def test_conv_fp_tiles_group_layout(ctx, torch, shape, residual, bits):
+    """The tile builds of every width with their tensors in the group layout
+    and with the shortcut's and the output's layouts mixed."""
+    case = I.single_layer(3300 + bits, bits=bits, shuffle=1, residual=residual, **REQUANT_SHAPES[shape])
+    for layout in ((1, 1, 1), (0, 1, 0), (1, 0, 1)):
+        say(f"conv FP tiles {shape} {residual} b={bits} layouts={layout}")
+        check_conv(ctx, torch, case, centred=True, layout=layout)
 
 
 def test_conv_deterministic(ctx, torch):
@@ -788,9 +926,9 @@ def test_channel_shuffle_full_size(ctx):
 
 @pytest.mark.parametrize("big_bias", [False, True])
 def test_conv_filter_longer_than_lds(ctx, torch, big_bias):
-    """A 2-bit layer whose filter (K = 9 x 1024) is too long for the general
-    build's filter-in-LDS: the tiled kernel takes it; the accumulator dump and
-    (big_bias: the int64 requant fallback) go to the direct kernel."""
+    """A 2-bit layer whose filter (K = 9 x 1024) is too long for a kernel that
+    holds it in LDS, also with the accumulator dump and (big_bias) parameters
+    past the fp32 requant."""
     say(f"conv K=9x1024 G=1 big_bias={big_bias}")
     case = I.single_layer(77, n=1, h=7, w=7, groups=1, cin=1024, cout=128, shuffle=0)
     if big_bias:

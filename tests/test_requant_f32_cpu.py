@@ -80,6 +80,22 @@ def test_round_down_requant_equals_definition_for_every_shift():
                 assert min(((num >> drop) << drop) >> sh, 15) == min(num >> sh, 15), (sh, m, u)
 
 
+def test_fp64_round_down_requant_equals_definition():
+    """The wide builds: the same fma in fp64, over the whole parameter range
+    (u = t + bias + shortcut below 2^32, M below 2^31, every shift)."""
+    rng = np.random.default_rng(12)
+    for sh in range(1, 63):
+        for m in [1, (1 << 31) - 1, (1 << 30) + 1] + [int(v) for v in rng.integers(1, 1 << 31, 5)]:
+            us = [0, 1, (1 << 32) - 1] + [int(v) for v in rng.integers(1, 1 << 32, 20)]
+            for k in (1, 2, 3, 8, 15, 200, 255):
+                th = -(-((2 * k - 1) << (sh - 1)) // m)
+                us += [v for v in (th - 1, th, th + 1) if 0 <= v < 1 << 32]
+            for u in us:
+                num = u * m + (1 << (sh - 1))
+                drop = max(0, num.bit_length() - 53)
+                assert min(((num >> drop) << drop) >> sh, 255) == min(num >> sh, 255), (sh, m, u)
+
+
 def test_fp4_conversion_requant_equals_definition():
     """The 2-bit form by the FP4 conversion, shifts up to 21: z = clamp(RN32(v / 4
     + 2^-24)) to [0, 1], v = u M 2^-sh, and the nibble RNE(4 z) with 4 taken to
