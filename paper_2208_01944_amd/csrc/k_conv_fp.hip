@@ -297,7 +297,7 @@ struct FpArgs {
   const float *cst;
   const int32_t *bad;  // the prepare kernel's flags
   int32_t fast;        // bad[1] is known to be clear
-  int32_t gate;        // 0: run; 1: run unless bad[0]; 2: run if bad[0] (the two launches of a one-off call)
+  int32_t gated;       // one of the two launches of a one-off call: base builds leave if bad[0], wide ones unless
   int32_t *dump;
   uint32_t in_bytes, w_bytes, res_bytes, proj_bytes, cst_bytes;
   int32_t in_pix, in_gs, res_pix, res_gs, proj_pix, proj_gs, out_pix, out_gs;  // bytes, < 2^30
@@ -333,10 +333,6 @@ __device__ __forceinline__ bool tile_of(const FpArgs &a, TileId &id) {
   id.g = (int)a.d_ncb.div(combo);
   id.cbk = (int)combo - id.g * a.ncb;
   return true;
-}
-
-__device__ __forceinline__ bool gated_off(const FpArgs &a) {
-  return a.gate != 0 && (a.bad[0] != 0) != (a.gate == 2);
 }
 
 // Geometry of output pixel m: byte offset of tap (0, 0) (may be negative), the
@@ -513,7 +509,7 @@ __device__ __forceinline__ void conv_fp_tile(const FpArgs &a) {
   constexpr int RSB = MODE == 1 && !LATE ? C::RP * 16 : 0;
   __shared__ __attribute__((aligned(1024))) uint8_t lds[RING + CST + RSB];
 
-  if (gated_off(a)) return;
+  if (a.gated && (a.bad[0] != 0) != (EP == kWide)) return;
   TileId id;
   if (!tile_of(a, id)) return;
   const int tid = (int)threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
@@ -973,7 +969,7 @@ __device__ __forceinline__ void conv_fp_split(const FpArgs &a) {
   static_assert(Q % NW == 0 || NW % Q == 0, "whole quads per wave");
   __shared__ V4 red[NW * Q * 64];
   __shared__ uint32_t cw[32 * PB * 9];  // packed quads of a pixel's 32 channels (9: no bank conflicts)
-  if (gated_off(a)) return;
+  if (a.gated && (a.bad[0] != 0) != (EP == kWide)) return;
   TileId id;
   if (!tile_of(a, id)) return;
   const int tid = (int)threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
@@ -1331,16 +1327,27 @@ hipError_t launch_split(FpArgs f, int64_t in_bytes, hipStream_t s) {
 
 // Which build takes a layer (times for the 14x14, 256-channel layer unless
 // stated; K-blocks of 64 codes):
-//  * few 32 x 64 tiles: the split kernel up to two per CU, or four with a long
-//    K loop (7x7, 512 channels, 2-bit: batch 1, 64 tiles, 6.8 us against 14.3 on
-//    128 x 128 tiles; batch 8, 448 tiles, 11.4 against 14.7; at 800 tiles 17.4
-//    against 20.8 with 72 K-blocks, but 10.0 against 9.2 with 36);
+//  * few 32 x 64 tiles: the split kernel up to two per CU (14x14, 512 channels
+//    3x3, 2-bit, 304 and 496 tiles: 12.4 and 12.7 us against 14.0 and 14.2 on
+//    128 x 128 tiles, at 688 and 992 tiles 17.6 and 22.3 against 14.4 and 14.5;
+//    8-bit 20.9, 21.6, 30.0 and 42.9 against 26.2, 26.7, 26.9 and 27.3; 1024
+//    channels, 992 tiles: 38.6 against 24.7), 3- and 4-bit layers of 64 K-blocks
+//    and more three (4-bit 688 tiles 18.8 against 20.3, 848 23.4 against 20.3; 704
+//    tiles of 1024 channels 33.7 against 36.3).  64 x 256 tiles leave more of the
+//    chip idle: there it pays up to four per CU with 24 K-blocks and more, 8-bit
+//    excepted (320 channels 3x3, 860 tiles: 2-bit 10.3 against 11.6, 4-bit 12.7
+//    against 17.5; 20 K-blocks, 860 tiles: 8.4 against 7.6 and 11.0 against 9.0).
+//    With one or two K-blocks (2-bit: four) most of its waves have none: one per
+//    CU (128 -> 512 channels 1x1 with a shortcut, 448 tiles, 2-bit 5.4 against 4.2,
+//    4-bit 6.1 against 4.6, but at 64 and 128 tiles 4.3-4.8 against 4.1-4.5);
 //  * 128 x 128 tiles, else (channel blocks that are no multiple of 128) 64 x 256;
 //  * 2-bit, four or more K-blocks per tap in fours: stages of four K-blocks,
-//    whose pieces fill whole lines.  Two stages take a third of a CU's LDS, so
-//    between three and six tiles per CU a second, nearly empty round costs more
-//    (ResNet-50 batch 128, 3x3: 392 tiles 29.2 -> 20.7 us, 1568 with a projection
-//    32.6 -> 28.6, but 784 19.2 -> 22.0); four K-blocks in all are one stage (14x14
+//    whose pieces fill whole lines.  Two stages take a third of a CU's LDS and
+//    the smaller stages a quarter, so with more than three and up to four tiles
+//    per CU the fours need a second, nearly empty round and the others none
+//    (14x14, 256 channels 3x3, G = 4: 704 tiles 17.9 -> 16.5 us, 776 20.5 -> 21.5,
+//    1208 31.8 -> 27.2, 1536 35.4 -> 30.9; 1x1 with 8 K-blocks: 704 8.4 -> 7.5, 848
+//    9.4 -> 10.0, 1400 13.6 -> 11.8); four K-blocks in all are one stage (14x14
 //    256 -> 1024 with shortcut, 3136 tiles, 19.6 -> 18.9; for 64-channel tiles and
 //    two K-blocks in all one stage measured the same as three of one);
 //  * else from 12 K-blocks on, two stages of two K-blocks: half the barriers (batch 64,
@@ -1356,12 +1363,15 @@ template <int B>
 hipError_t launch_fp(const FpArgs &f, bool wide_ep, int64_t in_bytes, hipStream_t s) {
   const int64_t cus = cu_count();
   const int64_t few = (int64_t)((f.M + 63) / 64) * ((f.cout + 31) / 32) * f.G;
-  if (few <= 2 * cus || (few <= 4 * cus && f.kb >= 64)) {
+  const bool wide = f.coutp % 128 == 0;
+  int per_cu = f.kb <= (B == 2 ? 4 : 2) ? 1 : 2;
+  if (B != 8 && !wide && f.kb >= 24) per_cu = 4;
+  else if ((B == 3 || B == 4) && f.kb >= 64) per_cu = 3;
+  if (few <= per_cu * cus) {
     if (f.dump) return launch_split<B, 2, 8, true, kWide>(f, in_bytes, s);
     if (wide_ep) return launch_split<B, 2, 8, false, kWide>(f, in_bytes, s);
     return launch_split<B, 2, 8, false, kBase>(f, in_bytes, s);
   }
-  const bool wide = f.coutp % 128 == 0;
   constexpr int KW = B == 2 ? 2 : 1, SW = B == 2 ? 2 : 3;
   if (f.dump) return launch_tile<B, 2, 1, 4, KW, SW, B != 2, true, true>(f, in_bytes, s);
   if (wide_ep) {
@@ -1376,7 +1386,7 @@ hipError_t launch_fp(const FpArgs &f, bool wide_ep, int64_t in_bytes, hipStream_
     if (wide && f.cpb % 4 == 0) {
       if (f.kb == 4) return launch_tile<B, 2, 2, 2, 4, 1, true>(f, in_bytes, s);
       const int64_t tiles = (int64_t)((f.M + 127) / 128) * (f.coutp / 128) * f.G;
-      if (f.kb >= 8 && (tiles <= 3 * cus || tiles >= 6 * cus))
+      if (f.kb >= 8 && (tiles <= 3 * cus || tiles > 4 * cus))
         return launch_tile<B, 2, 2, 2, 4, 2, true>(f, in_bytes, s);
     }
     if (f.kb < 12)
@@ -1481,9 +1491,7 @@ const char *conv_fp_label(const ConvArgs &a, int epi) {
   return epi == 1 ? "conv_fp6_kernel[wide]" : "conv_fp6_kernel";
 }
 
-// gate: FpArgs::gate.
-static hipError_t launch_fp_ep(const ConvArgs &a, FpArgs f, const int32_t *thr, bool wide, int gate, hipStream_t s) {
-  f.gate = gate;
+static hipError_t launch_fp_ep(const ConvArgs &a, FpArgs f, const int32_t *thr, bool wide, hipStream_t s) {
   if (wide && !fp_is_i8(a)) f.cst = (const float *)(thr + fp_cst_words(a));
   if (fp_is_i8(a)) return launch_fp<8>(f, wide, a.in.bytes, s);
   if (a.in.bits == 2) return launch_fp<2>(f, wide, a.in.bytes, s);
@@ -1495,11 +1503,12 @@ hipError_t launch_conv_fp(const ConvArgs &a, const uint8_t *wp, const int32_t *t
   if ((int64_t)a.out.n * a.ho * a.wo == 0) return hipSuccess;
   FpArgs f = fp_args(a, wp, thr);
   if (fp_is_i8(a)) f.wsum = (const int32_t *)(wp + fp_slab_bytes(a));
-  if (a.acc_dump) return launch_fp_ep(a, f, thr, true, 0, s);
-  if (epi >= 0) return launch_fp_ep(a, f, thr, epi == 1, 0, s);
+  if (a.acc_dump) return launch_fp_ep(a, f, thr, true, s);
+  if (epi >= 0) return launch_fp_ep(a, f, thr, epi == 1, s);
   f.fast = 0;
-  const hipError_t e = launch_fp_ep(a, f, thr, false, 1, s);
-  return e == hipSuccess ? launch_fp_ep(a, f, thr, true, 2, s) : e;
+  f.gated = 1;
+  const hipError_t e = launch_fp_ep(a, f, thr, false, s);
+  return e == hipSuccess ? launch_fp_ep(a, f, thr, true, s) : e;
 }
 
 }  // namespace palq

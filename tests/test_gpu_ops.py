@@ -477,6 +477,11 @@ FP_EDGE_CASES = {
     "c128_stages_of_four_projection": dict(n=11, h=28, w=27, groups=2, cin=200, cout=256, stride=2,
                                            residual="projection"),
     "c128_5x5_odd": dict(n=15, h=14, w=14, groups=3, cin=64, cout=512, k=5, pad=2),
+    # tiles from one 32 x 64 block per CU on (two K-blocks), the split kernel up to
+    # four per CU (64-channel blocks, 27 K-blocks) and to three (3 and 4 bits, 64)
+    "c128_short_few": dict(n=5, h=14, w=13, groups=2, cin=128, cout=500, k=1, pad=0, residual="identity"),
+    "split_c64_long": dict(n=10, h=28, w=27, groups=3, cin=192, cout=40),
+    "split_c128_long": dict(n=7, h=14, w=14, groups=2, cin=4096, cout=512, k=1, pad=0),
 }
 
 
