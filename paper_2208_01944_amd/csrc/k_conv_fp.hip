@@ -1420,7 +1420,7 @@ static size_t fp_slab_bytes(const ConvArgs &a) {
 bool conv_fp_applies(const ConvArgs &a) {
   const int b = a.in.bits;
   const bool i8 = b == 6 || b == 8;
-  if (a.in.is_signed || (!i8 && (!a.fp4 || (b != 2 && b != 3 && b != 4))) || a.w_bits != b || a.out.bits != b)
+  if (a.int8_only || a.in.is_signed || (!i8 && (!a.fp4 || (b != 2 && b != 3 && b != 4))) || a.w_bits != b || a.out.bits != b)
     return false;
   if (a.bitdecomp && b >= 4) return false;
   if (a.res.data && (a.res.bits != b || a.res.is_signed)) return false;

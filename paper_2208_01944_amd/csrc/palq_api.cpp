@@ -387,19 +387,22 @@ palq_status group_conv_impl(palq_ctx *ctx, const palq_act *in, const palq_filter
   // a layer that only the padded kernels take: without room for its slabs it
   // runs on the direct kernel, which needs none
   const bool direct_ok = mfma && conv_direct_partner(a);
-  if (noalloc && direct_ok) {
-    const ConvPlan p = conv_mfma_plan(a);
-    if (((p.w_bytes + 255) & ~(size_t)255) + p.thr_bytes > (size_t)PALQ_NOALLOC_SCRATCH_BYTES) mfma = false;
-  }
   if (noalloc && mfma && !direct_ok && conv_noalloc_bytes(a) > (size_t)PALQ_NOALLOC_SCRATCH_BYTES)
     return fail(ctx, PALQ_ERR_UNSUPPORTED,
                 "no-alloc call: the prepacked filter and requant constants need " + std::to_string(conv_noalloc_bytes(a)) +
                     " bytes; the library's static buffer holds " + std::to_string((long long)PALQ_NOALLOC_SCRATCH_BYTES));
-  const ConvPlan plan = mfma ? conv_mfma_plan(a) : ConvPlan{0, 0};
-  const size_t wbytes = (plan.w_bytes + 255) & ~(size_t)255;
+  auto slabs = [](const ConvPlan &p) { return (p.w_bytes + 255) & ~(size_t)255; };
+  ConvPlan plan = mfma ? conv_mfma_plan(a) : ConvPlan{0, 0};
+  if (noalloc && slabs(plan) + plan.thr_bytes > (size_t)PALQ_NOALLOC_SCRATCH_BYTES) {
+    // slabs padded to 64 channels pass the buffer: the int8 kernels' need no
+    // more than the documented size (8-bit, G = 32, 512 -> 96 channels, batch 8:
+    // 0.76 ms, 95 ms on the direct kernel)
+    if (direct_ok) mfma = false;
+    else a.int8_only = 1;
+    plan = mfma ? conv_mfma_plan(a) : ConvPlan{0, 0};
+  }
+  const size_t wbytes = slabs(plan);
   const size_t need = wbytes + plan.thr_bytes;
-  // (slabs padded to 64 channels may pass the buffer where the documented size does not)
-  if (noalloc && need > (size_t)PALQ_NOALLOC_SCRATCH_BYTES) mfma = false;
   if (ctx->device < 0 || out->n == 0) return PALQ_OK;
   hipSetDevice(ctx->device);
   hipError_t e;

@@ -117,6 +117,37 @@ def test_noalloc_rejects_layers_beyond_its_buffer():
     assert bool((out.buf == 0x5A).all())
 
 
+@pytest.mark.parametrize("bits", [4, 6, 8])
+def test_noalloc_slabs_padded_past_the_buffer(bits):
+    """A layer whose slabs fit the static buffer unpadded (G = 32 groups of 512
+    -> 96 channels) but not padded to 64-channel blocks stays on matrix cores:
+    equal to the oracle's, and within a factor of palq_group_conv's time that
+    the scalar kernel (over 500 times slower) is far from."""
+    import torch
+    from paper_2208_01944_amd import palq
+    ctx = palq.Context(0)
+    say(f"no-alloc padded slabs b={bits}")
+    case = I.single_layer(3110, n=2, h=14, w=14, groups=32, cin=512, cout=96, bits=bits, shuffle=1)
+    bias, q_ref, acc_ref = centred(case)
+    lay = Layer(ctx, torch, case, bias)
+    out, dump = lay.outputs(torch)
+    lay.run(out, dump, noalloc=True)
+    q, acc = lay.read(out, dump)
+    np.testing.assert_array_equal(q, q_ref)
+    np.testing.assert_array_equal(acc, acc_ref)
+    t = {}
+    for noalloc in (False, True):
+        ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        lay.run(out, None, noalloc)
+        ev[0].record()
+        lay.run(out, None, noalloc)
+        ev[1].record()
+        ctx.sync()
+        t[noalloc] = ev[0].elapsed_time(ev[1])
+    np.testing.assert_array_equal(ctx.unpack(out), q_ref)
+    assert t[True] < 50 * t[False], t
+
+
 def test_noalloc_in_captured_graph_replays():
     """The no-alloc call captured into a HIP graph (capture fails on any
     allocation or synchronisation) and replayed several times with other
