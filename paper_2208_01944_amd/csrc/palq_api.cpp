@@ -415,23 +415,24 @@ palq_status group_conv_impl(palq_ctx *ctx, const palq_act *in, const palq_filter
     if (e == hipSuccess) e = launch_conv_mfma(a, wp, thr, -1, ctx->stream);
     return e == hipSuccess ? PALQ_OK : device_fail(ctx, e, "group conv");
   }
-  if (mfma && need > ctx->conv_scratch_bytes) {
-    // a capture allows no allocation
+  if (mfma && direct_ok) {
+    // a capture allows no allocation, and a graph that held the context's
+    // scratch would outlive it (a later call may grow it)
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (direct_ok && hipStreamIsCapturing(ctx->stream, &cap) == hipSuccess && cap != hipStreamCaptureStatusNone) {
-      mfma = false;
+    if (hipStreamIsCapturing(ctx->stream, &cap) != hipSuccess) (void)hipGetLastError();
+    else if (cap != hipStreamCaptureStatusNone) mfma = false;
+  }
+  if (mfma && need > ctx->conv_scratch_bytes) {
+    if (ctx->conv_scratch) hipFree(ctx->conv_scratch);  // waits for work still reading it
+    ctx->conv_scratch = nullptr;
+    ctx->conv_scratch_bytes = 0;
+    if (hipMalloc(&ctx->conv_scratch, need) == hipSuccess) {
+      ctx->conv_scratch_bytes = need;
     } else {
-      if (ctx->conv_scratch) hipFree(ctx->conv_scratch);  // waits for work still reading it
       ctx->conv_scratch = nullptr;
-      ctx->conv_scratch_bytes = 0;
-      if (hipMalloc(&ctx->conv_scratch, need) == hipSuccess) {
-        ctx->conv_scratch_bytes = need;
-      } else {
-        ctx->conv_scratch = nullptr;
-        if (!direct_ok) return fail(ctx, PALQ_ERR_NOMEM, "conv scratch");
-        (void)hipGetLastError();
-        mfma = false;
-      }
+      if (!direct_ok) return fail(ctx, PALQ_ERR_NOMEM, "conv scratch");
+      (void)hipGetLastError();
+      mfma = false;
     }
   }
   if (mfma) {

@@ -1057,24 +1057,41 @@ def test_conv_plan_runs(ctx, torch, kind):
         ctx.sync()
 
 
-def test_group_conv_captured_without_scratch(ctx, torch):
-    """palq_group_conv on a context without scratch inside a capture, which
-    allows no allocation: a channel count that only the padded kernels take
-    runs on the direct kernel."""
+@pytest.mark.parametrize("warm", [False, True])
+def test_group_conv_captured(ctx, torch, warm):
+    """palq_group_conv of a channel count that only the padded kernels take,
+    inside a capture: it runs on the direct kernel, which needs no scratch,
+    on a context without (a capture allows no allocation) and with it (warm:
+    an eager call before, and one after the capture that needs more and frees
+    it, before the replays)."""
     from paper_2208_01944_amd import palq
-    say("group_conv captured on a fresh context")
+    say(f"group_conv captured warm={warm}")
     c = I.single_layer(4300, n=2, h=9, w=9, groups=3, cin=48, cout=80, shuffle=1)
     L = c["layer"]
     ref = O.conv_layer(c["x"], L["w"], 1, 1, L["mult"], L["shift"], L["bias"], 2, 1)[0]
     t = _layer_tensors(ctx, c, L["bias"])
     ctx.sync()
     fresh = palq.Context(0)
+    if warm:
+        fresh.group_conv(t["x"], t["w"], 1, 1, t["mult"], t["shift"], t["bias"], t["out"], shuffle=1)
+        fresh.sync()
+        np.testing.assert_array_equal(fresh.unpack(t["out"]), ref)
+        more = I.single_layer(4301, n=1, h=7, w=7, groups=2, cin=256, cout=256, shuffle=1)
+        tm = _layer_tensors(ctx, more, more["layer"]["bias"])
+        ctx.sync()
     side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
     with torch.cuda.stream(side):
         fresh.set_stream(side)
         graph.capture_begin()
         fresh.group_conv(t["x"], t["w"], 1, 1, t["mult"], t["shift"], t["bias"], t["out"], shuffle=1)
         graph.capture_end()
+    if warm:
+        m = more["layer"]
+        fresh.set_stream(torch.cuda.current_stream())
+        fresh.group_conv(tm["x"], tm["w"], 1, 1, tm["mult"], tm["shift"], tm["bias"], tm["out"], shuffle=1)
+        fresh.sync()
+        np.testing.assert_array_equal(fresh.unpack(tm["out"]), O.conv_layer(
+            more["x"], m["w"], 1, 1, m["mult"], m["shift"], m["bias"], 2, 1)[0])
     for r in range(3):
         t["out"].buf.fill_(0)
         torch.cuda.synchronize()
