@@ -365,11 +365,12 @@ __device__ __forceinline__ PixelGeo pixel_geo(const FpArgs &a, int m) {
 // 16 bytes per lane from the buffer into LDS at `dst` (uniform) + 16 lane.  In
 // asm, so that the compiler does not order its LDS reads after these loads:
 // the ring's own waits and barriers do (the loads have no register results).
-// m0 is set in the same statement; nothing else in these kernels reads it.
+// m0 is set in the same statement and named as overwritten.
 __device__ __forceinline__ void dma16(v4i rsrc, uint32_t dst, uint32_t voff, uint32_t soff) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
                :
-               : "s"(dst), "v"(voff), "s"(rsrc), "s"(soff));
+               : "s"(dst), "v"(voff), "s"(rsrc), "s"(soff)
+               : "m0");
 }
 __device__ __forceinline__ v4i rsrc4(const void *base, uint32_t bytes) {
   const uint64_t p = (uint64_t)base;
