@@ -1507,6 +1507,11 @@ hipError_t launch_conv_fp(const ConvArgs &a, const uint8_t *wp, const int32_t *t
   if (a.acc_dump) return launch_fp_ep(a, f, thr, true, s);
   if (epi >= 0) return launch_fp_ep(a, f, thr, epi == 1, s);
   f.fast = 0;
+  // B = 8: within the interface's |bias| < 2^30 and |res_mult| < 2^15 only sums
+  // next to their own bound can need the wide build
+  const int64_t res = a.res.data ? code_max(a.res.bits, 0) << 15 : 0;
+  if (fp_is_i8(a) && fp_acc_bound(a) + ((int64_t)1 << 30) + res <= (int64_t)1 << 31)
+    return launch_fp_ep(a, f, thr, false, s);
   f.gated = 1;
   const hipError_t e = launch_fp_ep(a, f, thr, false, s);
   return e == hipSuccess ? launch_fp_ep(a, f, thr, true, s) : e;
