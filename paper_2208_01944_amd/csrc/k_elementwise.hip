@@ -638,12 +638,13 @@ __device__ inline void avgsum_wg(const ActView &in, int32_t *out, int8_t *planes
                                  int32_t *logits, int cout) {
   using T = SumT<B>;
   __shared__ uint32_t part[T::NA][256];
-  const int units = in.cpg / T::CODES;
+  const int u0 = (int)blockIdx.y * 256, units = min(256, in.cpg / T::CODES - u0);
   const int R = 256 / units;
   const int n = (int)(blockIdx.x / in.groups), g = (int)(blockIdx.x % in.groups);
   const int wi = threadIdx.x % units, r = threadIdx.x / units;
   const int hw = in.h * in.w;
-  const uint8_t *base = in.data + (int64_t)n * hw * in.pixel + (int64_t)g * in.gstride + 4 * T::W * wi;
+  const uint8_t *base = in.data + (int64_t)n * hw * in.pixel + (int64_t)g * in.gstride +
+                        (int64_t)u0 * (4 * T::W) + 4 * T::W * wi;
   uint32_t acc[T::NA] = {};
   if (r < R)
     for (int p0 = r; p0 < hw; p0 += 8 * R) {
@@ -661,6 +662,7 @@ __device__ inline void avgsum_wg(const ActView &in, int32_t *out, int8_t *planes
   for (int k = 0; k < T::NA; ++k) part[k][threadIdx.x] = acc[k];
   __syncthreads();
   constexpr int SA = B == 3 ? 8 : T::NA;  // accumulators that yield codes
+  const int64_t cg = ((int64_t)n * in.groups + g) * in.cpg + (int64_t)u0 * T::CODES;
   for (int idx = threadIdx.x; idx < SA * units; idx += 256) {
     const int w2 = idx / SA, k = idx % SA;
     uint32_t sum = 0, hi = 0;
@@ -668,8 +670,7 @@ __device__ inline void avgsum_wg(const ActView &in, int32_t *out, int8_t *planes
       sum += part[k][rr * units + w2];
       if constexpr (B == 3) hi += part[8 + k][rr * units + w2];
     }
-    const int64_t c0 = (int64_t)n * in.groups * in.cpg + (int64_t)g * in.cpg + T::CODES * w2 +
-                       (B == 3 ? 16 * (k >> 2) + (k & 3) : k);
+    const int64_t c0 = cg + T::CODES * w2 + (B == 3 ? 16 * (k >> 2) + (k & 3) : k);
 #pragma unroll
     for (int f = 0; f < 32 / T::FB; ++f) {
       int32_t v = (int32_t)((sum >> (T::FB * f)) & ((1u << T::FB) - 1u));
@@ -688,7 +689,7 @@ __device__ inline void avgsum_wg(const ActView &in, int32_t *out, int8_t *planes
       }
     }
   }
-  if (logits && g == 0)
+  if (logits && g == 0 && u0 == 0)
     for (int i = threadIdx.x; i < cout; i += 256) logits[(int64_t)n * cout + i] = 0;
 }
 __global__ __launch_bounds__(256) void avgsum2_wg_kernel(ActView in, int32_t *out, int8_t *planes, int P,
@@ -1091,14 +1092,14 @@ hipError_t launch_pad_pixels(const ActView &in, int pad, const ActView &out, hip
   return hipGetLastError();
 }
 
-// One workgroup per image and group (avgsum_wg): whole units in a row,
-// no more of them than threads, and no more pixels than a field can sum.
+// One workgroup per image, group and 256 units (avgsum_wg): whole units in a
+// row and no more pixels than a field can sum.
 bool avgsum_makes_fc_planes(const ActView &in) {
   const int b = in.bits;
   if (b != 2 && b != 3 && b != 4 && b != 8) return false;
   const int codes = b == 3 ? 32 : 32 / b;
   const int64_t max_hw = b == 4 ? SumT<4>::MAXHW : b == 8 ? SumT<8>::MAXHW : SumT<2>::MAXHW;
-  return in.cpg % codes == 0 && in.cpg / codes <= 256 && (int64_t)in.h * in.w <= max_hw &&
+  return in.cpg % codes == 0 && in.cpg / codes <= 256 * 65535 && (int64_t)in.h * in.w <= max_hw &&
          (int64_t)in.n * in.groups < ((int64_t)1 << 31);
 }
 
@@ -1118,7 +1119,9 @@ hipError_t launch_avgsum(const ActView &in, int32_t *out, hipStream_t s, int8_t 
              : in.bits == 3 ? avgsum_wg_kernel<3>
              : in.bits == 4 ? avgsum_wg_kernel<4>
                             : avgsum_wg_kernel<8>;
-    hipLaunchKernelGGL(k, dim3((unsigned)(in.n * in.groups)), dim3(256), 0, s, in, out, planes, P, items, logits, cout);
+    const int units = in.cpg / (in.bits == 3 ? 32 : 32 / in.bits);
+    const dim3 grid((unsigned)(in.n * in.groups), (unsigned)((units + 255) / 256));
+    hipLaunchKernelGGL(k, grid, dim3(256), 0, s, in, out, planes, P, items, logits, cout);
     return hipGetLastError();
   }
   if (planes) return hipErrorInvalidValue;

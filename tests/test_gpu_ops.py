@@ -792,9 +792,10 @@ def test_maxpool_avgsum_fc(ctx, torch, bits, cpg, layout):
 
 
 # field sums at their largest: the pixel limit of each width and one past it
-# (the per-channel kernel), unit counts that do not divide 256
+# (the per-channel kernel), unit counts that do not divide 256, more than 256
 @pytest.mark.parametrize("bits,cpg,h,w", [(2, 80, 5, 17), (3, 96, 5, 17), (3, 64, 2, 43), (4, 64, 17, 257), (4, 40, 15, 292),
-                                          (8, 20, 1, 257), (8, 12, 6, 43), (3, 1024, 3, 3)])
+                                          (8, 20, 1, 257), (8, 12, 6, 43), (3, 1024, 3, 3),
+                                          (2, 4112, 5, 17), (3, 8224, 2, 3), (4, 2056, 7, 5), (8, 2052, 3, 3)])
 def test_avgsum_field_limits(ctx, torch, bits, cpg, h, w):
     say(f"avgsum limits bits={bits} cpg={cpg} {h}x{w}")
     x = I.codes(np.random.default_rng(bits + cpg), (2, h, w, 2 * cpg), bits, False).astype(np.int64)
