@@ -2381,11 +2381,16 @@ ConvPlan conv_mfma_plan(const ConvArgs &a) {
 
 // Layers on the FP4 / FP6 kernels need less scratch than they used to and
 // others fit that never went through the buffer; the call's limit stays the
-// documented one, the int8 slabs with their constants and a second, narrower
-// copy for the FP4 / FP6 formats.
+// documented one, the int8 slabs with their constants and a second copy: a
+// narrower one for the FP4 / FP6 formats, by filter row for stems.
 size_t conv_noalloc_bytes(const ConvArgs &a) {
   const ConvPlan p = conv_mfma_plan(a);
-  const size_t actual = ((p.w_bytes + 255) & ~(size_t)255) + p.thr_bytes;
+  size_t actual = ((p.w_bytes + 255) & ~(size_t)255) + p.thr_bytes;
+  if (is_stem(a) && a.out.bits == 2 && a.cout % 128 == 0) {
+    ConvArgs b = a;
+    b.pool_rows = 1;
+    if (stem_rows(b)) actual += (size_t)a.cout * sp::KH * 32;  // a copy by filter row
+  }
   if (!conv_fp_applies(a) || !int8_shape(a)) return actual;
   const size_t nch = (size_t)a.in.groups * a.cout, kb = make_geo(a).kb_total;
   const bool shortcut = a.res.data || a.proj.data;
@@ -2541,11 +2546,11 @@ bool stem_tile_applies(const ConvArgs &a) {
 
 // Stems whose weights are also prepacked by filter row, for the fused max pool
 // (prepack_stem_rows_kernel, after the K-block slabs, then the fp32 requant
-// constants and their flag): one input group, an explicit border, 7 filter rows
+// constants and their flag), where a network asks for it: one input group, an explicit border, 7 filter rows
 // of at most 8 taps, stride 2, whole 64-channel halves of the kernel's
 // 128-channel blocks and 2-, 3- or 4-bit outputs.
 bool stem_rows(const ConvArgs &a) {
-  return is_stem(a) && a.pad == 0 && a.in.groups == 1 && a.cout % 64 == 0 && !a.res.data && !a.acc_dump &&
+  return a.pool_rows && is_stem(a) && a.pad == 0 && a.in.groups == 1 && a.cout % 64 == 0 && !a.res.data && !a.acc_dump &&
          (a.out.bits == 2 || a.out.bits == 3 || a.out.bits == 4) && a.kh == sp::KH && a.stride == 2 &&
          (int64_t)a.cout * make_geo(a).kb_total * 64 < ((int64_t)1 << 30);
 }

@@ -107,6 +107,7 @@ struct ConvArgs {
   int32_t bitdecomp;     // 1: M-bit layers run as the Eq. 4 bit decomposition on FP4
   int32_t gated;         // set by the launcher: general partner of a tiled launch
   int32_t fp_fast;       // conv_fp_fast, where the caller asked
+  int32_t pool_rows;     // 1: a network's stem whose output only a max pool reads (stem_rows)
   int32_t int8_only;     // 1: not on k_conv_fp.hip, whose slabs have no room
 };
 

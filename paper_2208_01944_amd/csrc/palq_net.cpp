@@ -480,6 +480,8 @@ palq_status palq_net_create(palq_ctx *ctx, const palq_act *input, const palq_lay
         regroup(net->tensors[L.proj_src].d, L.proj_w.groups, L.proj_w.cin_pg, &pv);
         a.proj = view_of(&pv);
       }
+      a.pool_rows = !(flags & PALQ_NET_KEEP_ALL) && i + 1 < n_layers && layers[i + 1].op == PALQ_OP_MAXPOOL &&
+                    layers[i + 1].src == L.dst && net->tensors[L.dst].last_use == i + 1;
       NL.use_mfma = conv_mfma_supported(a);
       if (NL.use_mfma && conv_mfma_pads_input(a)) {
         palq_act pv = iv;
@@ -557,20 +559,17 @@ palq_status palq_net_create(palq_ctx *ctx, const palq_act *input, const palq_lay
       NL.conv.fp_fast = NL.epi == 0 && conv_fp_fast(NL.conv, NL.thr);
     }
   // fuse the stem with a max pool that is its output's only reader
-  if (!(flags & PALQ_NET_KEEP_ALL))
-    for (int i = 0; i + 1 < n_layers; ++i) {
-      Layer &NL = net->layers[i];
-      const palq_layer &P = layers[i + 1];
-      if (layers[i].op != PALQ_OP_CONV || !NL.use_mfma || P.op != PALQ_OP_MAXPOOL || P.src != layers[i].dst ||
-          net->tensors[layers[i].dst].last_use != i + 1)
-        continue;
-      const ActView po = view_of(&net->tensors[P.dst].d);
-      if (!stem_pool_applies(NL.conv, po, P.pool_k, P.pool_stride, P.pool_pad)) continue;
-      NL.pool_fused = stem_pool_requant(NL.conv, NL.wp, NL.thr);
-      if (!NL.pool_fused) continue;
-      NL.pool_out = po;
-      net->layers[i + 1].skip = true;
-    }
+  for (int i = 0; i + 1 < n_layers; ++i) {
+    Layer &NL = net->layers[i];
+    const palq_layer &P = layers[i + 1];
+    if (layers[i].op != PALQ_OP_CONV || !NL.use_mfma || !NL.conv.pool_rows) continue;
+    const ActView po = view_of(&net->tensors[P.dst].d);
+    if (!stem_pool_applies(NL.conv, po, P.pool_k, P.pool_stride, P.pool_pad)) continue;
+    NL.pool_fused = stem_pool_requant(NL.conv, NL.wp, NL.thr);
+    if (!NL.pool_fused) continue;
+    NL.pool_out = po;
+    net->layers[i + 1].skip = true;
+  }
   // palq_forward_image: quantise straight into the zero-border copies when
   // they are the only readers of tensor 0, else into a buffer of its own
   if (net->img_input) {

@@ -359,6 +359,12 @@ def test_validate_only_group_conv_noalloc(P, vctx):
     # filter too long for the int8 builds and a channel count of none of them
     long8 = P.Filter(1, 2048, 1024, 3, 3, 8, _fake(10))
     assert call(_act(P, g=1, c=1024, bits=8), long8, _act(P, g=1, c=2048, bits=8, slot=20)) == P.OK
+    # a stem with an explicit border: one copy of its filter (no network's max pool)
+    x = P.make_act(1, 14, 14, 1, 3, 8, True, _fake(1))
+    stem, out = P.Filter(1, 40000, 3, 7, 7, 8, _fake(10)), P.make_act(1, 4, 4, 1, 40000, 3, False, _fake(20))
+    rq = P.Requant(_fake(30), _fake(31), None, 3)
+    assert P._group_conv_noalloc(vctx.h, ctypes.byref(x), ctypes.byref(stem), 2, 0, ctypes.byref(rq), None, 0,
+                                 ctypes.byref(out), None) == P.OK
     odd = P.Filter(8, 520, 520, 3, 3, 2, _fake(10))
     assert call(_act(P, g=8, c=520), odd, _act(P, g=8, c=520, slot=20)) == P.OK
 
