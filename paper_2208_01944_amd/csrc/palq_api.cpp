@@ -539,7 +539,7 @@ palq_status palq_conv_plan_create(palq_ctx *ctx, const palq_act *in, const palq_
   const int64_t o_s = off; off += up(cb);
   const int64_t o_b = off; off += up(cb);
   const int64_t o_r = off; off += up(cb);
-  a.in.data = (uint8_t *)plan_fake(1);  // for the kernel choice only: no device access
+  a.in.data = (uint8_t *)plan_fake(1);  // for the kernel choice only (palq_conv_plan_kernels too): no device access
   a.out.data = (uint8_t *)plan_fake(1000);
   if (a.res.cpg) a.res.data = (uint8_t *)plan_fake(2000);
   if (a.proj.cpg) a.proj.data = (uint8_t *)plan_fake(3000);
@@ -577,7 +577,8 @@ palq_status palq_conv_plan_create(palq_ctx *ctx, const palq_act *in, const palq_
     if (p->epi == 1 && !conv_mfma_general_fits(a)) p->mfma = false;
     a.fp_fast = p->epi == 0 && conv_fp_fast(a, p->thr);
   }
-  a.in.data = a.out.data = a.res.data = a.proj.data = nullptr;
+  // (the tensors keep their stand-in addresses, by which the kernel choice sees
+  // a shortcut; a run sets every one)
   *plan = p;
   return PALQ_OK;
 }

@@ -1058,6 +1058,23 @@ def test_conv_plan_runs(ctx, torch, kind):
         ctx.sync()
 
 
+@pytest.mark.parametrize("shortcut_bits", [2, 4])
+def test_conv_plan_names_its_kernel(ctx, torch, shortcut_bits):
+    """A 2-bit layer with an identity shortcut of its own width and of a wider
+    one, which the FP4 kernel does not take: the plan names the kernel it runs."""
+    from paper_2208_01944_amd import palq
+    say(f"conv plan name, shortcut of {shortcut_bits} bits")
+    case = I.single_layer(4400, n=2, h=9, w=8, groups=2, cin=64, cout=64, shuffle=1, residual="identity")
+    L = case["layer"]
+    t = _layer_tensors(ctx, case, L["bias"])
+    t["kw"]["identity"] = t["res_in"] = ctx.pack(case["extra"][1], 2, shortcut_bits)
+    plan = palq.ConvPlan(ctx, t["x"], t["w"], 1, 1, t["mult"], t["shift"], t["bias"], t["out"], shuffle=1, **t["kw"])
+    assert plan.kernels == {2: "conv_fp4_kernel", 4: "conv_grouped_kernel"}[shortcut_bits]
+    plan.run(t["x"], t["out"], t["res_in"])
+    ctx.sync()
+    np.testing.assert_array_equal(ctx.unpack(t["out"]), oracle_full(case)[1])
+
+
 @pytest.mark.parametrize("warm", [False, True])
 def test_group_conv_captured(ctx, torch, warm):
     """palq_group_conv of a channel count that only the padded kernels take,
