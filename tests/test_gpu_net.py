@@ -334,6 +334,27 @@ def test_stem_pool_widths(ctx, torch, groups, bits, hw, big_mult):
     np.testing.assert_array_equal(logits, O.run_net(spec, spec["x"]))
 
 
+@pytest.mark.parametrize("bits", [2, 4])
+def test_resnet18_wide_multipliers(ctx, torch, bits):
+    """30-bit multipliers (shifts to match) on every layer: the grouped layers
+    run the wide builds, the stem its fp64 requant."""
+    say(f"resnet18 hw=64 n=2 G=2 b={bits} centred, 30-bit multipliers")
+    spec = I.resnet18(n=2, groups=2, bits=bits, hw=64, classes=10, seed=19)
+    spec = O.calibrate_centring(spec, spec["x"])
+    for L in spec["layers"]:
+        if L["op"] == "conv":
+            L["mult"], L["shift"] = (L["mult"] << 15) + 12345, L["shift"] + 15
+    net, logits = gpu_forward(ctx, torch, spec, keep=True)
+    kernels = net.layer_kernels()
+    want = {2: "conv_fp4_kernel[wide]", 4: "conv_fp6_kernel[wide]"}[bits]
+    assert kernels.count(want) == 16, kernels
+    ref, tensors, _ = O.run_net(spec, spec["x"], keep=True)
+    compare_tensors(ctx, net, spec, tensors, slice(None))
+    np.testing.assert_array_equal(logits, ref)
+    _, logits = gpu_forward(ctx, torch, spec)
+    np.testing.assert_array_equal(logits, ref)
+
+
 def codes_input_net(ctx, spec, groups, bits):
     """A network over `spec` whose input tensor is unsigned codes of several
     groups (the binding describes every input as a signed 8-bit image)."""

@@ -86,7 +86,7 @@ def test_quantize_matches_oracle(ctx, torch, bits, signed, layout):
 # alignment (the word-per-thread kernel)
 @pytest.mark.parametrize("bits", [2, 3, 4, 6, 8])
 @pytest.mark.parametrize("n,hw,groups,cpg,layout,shift", [(1, 1, 1, 4, 0, 0), (2, 5, 3, 20, 1, 0), (3, 7, 2, 44, 0, 0),
-                                                          (1, 9, 1, 96, 0, 1), (9, 56, 4, 84, 1, 0)])
+                                                          (1, 9, 1, 96, 0, 1), (9, 56, 4, 84, 1, 0), (9, 56, 4, 84, 0, 1)])
 def test_quantize_quads(ctx, torch, bits, n, hw, groups, cpg, layout, shift):
     say(f"quantize quads bits={bits} n={n} hw={hw} groups={groups} cpg={cpg} layout={layout} shift={shift}")
     g = np.random.default_rng(cpg + bits)
