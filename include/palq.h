@@ -68,7 +68,7 @@ typedef struct palq_ctx palq_ctx;
 typedef struct palq_net palq_net;
 
 /* An activation tensor: n x h x w pixels of `groups` rows of ch_per_group
- * codes, `bits` in {2, 3, 4, 8}.  data: device, palq_act_bytes() bytes.
+ * codes, `bits` in {2, 3, 4, 6, 8}.  data: device, palq_act_bytes() bytes.
  * layout: PALQ_LAYOUT_PIXEL (0, what a zeroed descriptor holds) or
  * PALQ_LAYOUT_GROUP (see the packed code layout above); every call takes
  * either, and the tensors of one call may mix them. */
@@ -84,7 +84,7 @@ typedef struct {
 } palq_act;
 
 /* A grouped filter: groups x cout_pg output channels, each a kh x kw x
- * cin_pg block of signed `bits`-bit codes (bits in {2, 3, 4, 8}).
+ * cin_pg block of signed `bits`-bit codes (bits in {2, 3, 4, 6, 8}).
  * data: device, packed as described above. */
 typedef struct {
   int32_t groups, cout_pg, cin_pg, kh, kw, bits;
@@ -99,7 +99,7 @@ typedef struct {
  * The result is exact for mult in [0, 2^31), shift in [1, 62], |bias| < 2^30
  * and |res_mult| < 2^15 (outside that range the output is unspecified but
  * no memory outside the output tensor is touched).  bias may be NULL (0).
- * out_bits in {2, 3, 4, 8}; output codes are unsigned.  The arrays (and
+ * out_bits in {2, 3, 4, 6, 8}; output codes are unsigned.  The arrays (and
  * res_mult below) must be 16-byte aligned. */
 typedef struct {
   const int32_t *mult;
@@ -136,13 +136,13 @@ void palq_destroy(palq_ctx *ctx);
  * work already queued on the old one (which may still read context memory
  * that later calls reuse). */
 palq_status palq_set_stream(palq_ctx *ctx, void *hip_stream);
-/* Matrix-core format of 2- and 3-bit grouped convolutions (Section 4.1):
+/* Matrix-core format of 2-, 3- and 4-bit grouped convolutions (Section 4.1):
  * with enable = 1 (the default; environment PALQ_CONV_FP4=0 starts a context
- * at 0) a layer whose accumulator bound sum |w| |x| stays below 2^23 runs on
- * the FP4 (E2M1) matrix cores if it is a 2-bit layer, on the FP6 (E2M3)
- * matrix cores if it is a 3-bit layer with 3-bit outputs, 64-channel blocks
- * and no shortcut, where its fp32 accumulator is exact; with 0 every layer
- * runs on int8.  Results are identical either way.  Applies to
+ * at 0) a layer whose filter, outputs and shortcut have its inputs' width and
+ * whose accumulator bound sum |w| |x| stays below 2^23 runs on the FP4 (E2M1)
+ * matrix cores if it is a 2-bit layer, on the FP6 (E2M3) ones if it is a 3- or
+ * 4-bit layer, any channel count, where its fp32 accumulator is exact; with 0
+ * every layer runs on int8.  Results are identical either way.  Applies to
  * palq_group_conv calls and networks created after the call.
  * PALQ_ERR_ARG: enable not 0 or 1. */
 palq_status palq_set_conv_fp4(palq_ctx *ctx, int32_t enable);
@@ -264,8 +264,9 @@ palq_status palq_conv_run(palq_ctx *ctx, const palq_conv_plan *plan, const void 
 /* Frees a plan (waits for device work that still reads it). */
 void palq_conv_plan_destroy(palq_conv_plan *plan);
 /* The kernel family a plan runs without an accumulator dump (static host
- * string, e.g. "conv_fp4_kernel"; "" for a validate-only plan; NULL
- * for a null plan). */
+ * string, e.g. "conv_fp4_kernel"; with "[wide]" where the requant
+ * parameters need that build; "" for a validate-only plan; NULL for a null
+ * plan). */
 const char *palq_conv_plan_kernels(const palq_conv_plan *plan);
 
 /* The cyclic permutation of Section 4.2 (Eq. 6-8) on its own:

@@ -452,9 +452,11 @@ __device__ __forceinline__ void quad_codes(const uint32_t *c, int qi, int half, 
 // and LDS reads 23k, but the vector memory data unit busy for 58k of 64k with
 // one 16-byte piece of a 64-byte pixel row per lane, as each piece takes a
 // line of its own; 40k of 55k with a pixel's four pieces in neighbouring lanes
-// (PAIR: 43k vector L1 accesses -> 24k; the layer 31.2 -> 30.5 us, 7x7 512
-// channels of ResNet-50 at batch 128 29 -> 21).  Deeper rings (three and four
-// stages of two K-blocks) measured equal or slower.  The prologue has no loops
+// (PAIR: 43k vector L1 accesses -> 24k).  With the stages of four that it allows
+// ResNet-18 G = 4 2-bit at batch 64 went 417 -> 386 us, ResNet-50 at batch 128
+// 1123 -> 1086, the 3-bit layer with a shortcut 56.4 -> 52.8; the 2-bit layer
+// above stayed (31.5, 31.7), latency-bound.  Deeper rings (three and four stages
+// of two K-blocks) measured equal or slower.  The prologue has no loops
 // and no dependent loads before the first fetch (constants arrive by the same LDS
 // loads), a K-block's position is decoded with two multiplies instead of carried
 // state, the in-image test is three VALU instructions, and a stage's LDS reads are
@@ -491,8 +493,10 @@ struct FpCfg {
 
 // PAIR (K-blocks per tap a multiple of KPS): a stage's pieces are ordered by
 // pixel, so that neighbouring lanes fetch a pixel's adjacent pieces from one
-// line; a pixel's NP pieces are swizzled so that 16 consecutive pixels' reads of
-// one piece meet all banks.
+// line; a pixel's NP pieces are swizzled so that 16 consecutive pixels' 16-byte
+// reads of one piece meet all banks.  2-bit lanes read eight bytes of a piece, so
+// half of the banks idle: two conflict cycles per MFMA on the layers without a
+// shortcut (SQ_LDS_BANK_CONFLICT / SQ_INSTS_MFMA), swizzled or not.
 template <int NP>
 __device__ __forceinline__ int piece_swizzle(int pixel) { return (pixel / (16 / NP)) & (NP - 1); }
 template <int B, int PB, int WN, int WM, int MODE, bool DUMP, int KPS, int S, Ep EP, bool PAIR>

@@ -1569,8 +1569,8 @@ __global__ void stem_prep_f32_kernel(const int32_t *mult, const int32_t *shift, 
 // Runs hold at most ho2 units (the launcher's grid), so a run meets at most
 // two channel blocks, cbb0 and cbb0 + 1 (mod ncb): their requant constants
 // sit in LDS.  BO: output bits.  F32: the requant of SpConst instead of the
-// fp64 one, whose three quarter-rate instructions a value were a quarter of the
-// kernel's issue time (ResNet-18 G = 4, batch 64: SPBEFORE -> SPAFTER us).
+// fp64 one, which takes three quarter-rate instructions a value (ResNet-18 G =
+// 4, batch 64: 71.1 -> 69.2 us, the two builds in turn in one trace).
 template <int BO, bool F32>
 __global__ __launch_bounds__(sp::NT, 2) void stem_pool_kernel(ConvArgs a, Geo geo, ActView po, const uint8_t *wrow,
                                                               const SpConst *spc, int units) {
@@ -2379,9 +2379,8 @@ ConvPlan conv_mfma_plan(const ConvArgs &a) {
   return p;
 }
 
-// Layers on the FP4 / FP6 kernels need less scratch than they used to and
-// others fit that never went through the buffer; the call's limit stays the
-// documented one, the int8 slabs with their constants and a second copy: a
+// Layers of k_conv_fp.hip need other amounts than the int8 kernels; the call's
+// limit stays the documented one, the int8 slabs with their constants and a second copy: a
 // narrower one for the FP4 / FP6 formats, by filter row for stems.
 size_t conv_noalloc_bytes(const ConvArgs &a) {
   const ConvPlan p = conv_mfma_plan(a);
@@ -2546,12 +2545,12 @@ bool stem_tile_applies(const ConvArgs &a) {
 
 // Stems whose weights are also prepacked by filter row, for the fused max pool
 // (prepack_stem_rows_kernel, after the K-block slabs, then the fp32 requant
-// constants and their flag), where a network asks for it: one input group, an explicit border, 7 filter rows
-// of at most 8 taps, stride 2, whole 64-channel halves of the kernel's
-// 128-channel blocks and 2-, 3- or 4-bit outputs.
+// constants and their flag), where a network asks for it: one input group, an
+// explicit border, 7 filter rows of at most 8 taps, stride 2, whole 64-channel
+// halves of the kernel's 128-channel blocks and 2-, 3- or 4-bit outputs.
 bool stem_rows(const ConvArgs &a) {
-  return a.pool_rows && is_stem(a) && a.pad == 0 && a.in.groups == 1 && a.cout % 64 == 0 && !a.res.data && !a.acc_dump &&
-         (a.out.bits == 2 || a.out.bits == 3 || a.out.bits == 4) && a.kh == sp::KH && a.stride == 2 &&
+  return a.pool_rows && is_stem(a) && a.pad == 0 && a.in.groups == 1 && a.cout % 64 == 0 && !a.res.data &&
+         !a.acc_dump && (a.out.bits == 2 || a.out.bits == 3 || a.out.bits == 4) && a.kh == sp::KH && a.stride == 2 &&
          (int64_t)a.cout * make_geo(a).kb_total * 64 < ((int64_t)1 << 30);
 }
 size_t stem_rows_bytes(const ConvArgs &a) { return (size_t)((a.cout + 127) / 128 * 128) * sp::KH * 32; }
@@ -2661,9 +2660,8 @@ hipError_t launch_tile(const ConvArgs &a, const Geo &geo, hipStream_t s) {
 // stem_pool_kernel: the stem's tiled-kernel conditions with a 7-row filter
 // at stride 2 and its weights also prepacked by filter row (stem_rows), an
 // input row of at most 1024 bytes (so at most 125 output columns), and a
-// pooled view of the stem's output shape.  The caller must know the fast
-// epilogue applies (conv_mfma_epilogue == 0): the kernel has no general
-// build.
+// pooled view of the stem's output shape.  stem_pool_requant says, once the
+// layer is prepared, whether the kernel has a requant for it.
 bool stem_pool_applies(const ConvArgs &a, const ActView &po, int k, int stride, int pad) {
   if (!stem_rows(a) || a.wo < 1 || a.ho < 1) return false;
   if (k != 3 || stride != 2 || pad != 1) return false;

@@ -118,7 +118,7 @@ hipError_t launch_conv_direct(const ConvArgs &a, hipStream_t s, const int32_t *o
 // Whether the MFMA kernels take this layer.
 bool conv_mfma_supported(const ConvArgs &a);
 // Whether, of those, only the padded kernels of k_conv_fp.hip do: where their
-// slabs have no room the layer runs on the direct kernel.
+// slabs have no room, and in a capture, the layer runs on the direct kernel.
 bool conv_direct_partner(const ConvArgs &a);
 // Whether the general (persistent, filter-in-LDS) build fits this layer;
 // when it does not, a supported layer runs only on the tiled kernel's fast

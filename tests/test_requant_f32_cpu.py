@@ -1,12 +1,12 @@
-"""The FP4 kernel's fp32 requant, checked on the CPU.  With u = t + bias
-(+ the identity shortcut) the kernel's accumulator holds u / 4 and one fp32
-fma computes y = RN(u/4 * M 2^(2 - sh) + 1/2), a single rounding of
-x = (u M + 2^(sh-1)) 2^-sh; it stores min(trunc(y), 3).  For the bounds the
-device checks before taking this path (1 <= sh <= 22, |M| < 2^24,
-|u| < 2^24) that equals the requant's definition clamp(floor(x), 0, 3)
-(the reading of the fixed-point requant with 2-bit outputs).  x is exact in
-float64 here (|u M| < 2^48) and numpy's float64 -> float32 conversion
-rounds it once to nearest even, as the fma does."""
+"""The requants of the tile kernels, checked on the CPU against the definition
+clamp(floor(x), 0, qmax), x = (u M + 2^(sh-1)) 2^-sh with u = t + bias (+ the
+identity shortcut): one fma rounding towards minus infinity, in fp32 (|u|, M <
+2^24) and in fp64 (every parameter), and the 2-bit form by FP4 conversions
+(shifts up to 21).  The first two tests hold the fma's rounding to nearest
+against them: y = RN(x) gives min(trunc(y), 3) up to a shift of 22 and fails past
+it, which is why the kernels set the rounding mode.  x is exact in float64 there
+(|u M| < 2^48) and numpy's float64 -> float32 conversion rounds it once to
+nearest even, as an fma does."""
 import numpy as np
 
 
@@ -51,9 +51,8 @@ def test_fp32_requant_equals_definition_within_bounds():
 
 
 def test_fp32_requant_shift_bound_is_needed():
-    """Past the bound a single fp32 rounding can cross a step: for large
-    shifts some u rounds up onto the next code, which is why the device
-    keeps such layers on the fp64 epilogue."""
+    """Past the bound a single fp32 rounding to nearest can cross a step: for
+    large shifts some u rounds up onto the next code."""
     rng = np.random.default_rng(7)
     found = False
     for sh in (26, 27, 28):
