@@ -499,7 +499,7 @@ struct FpCfg {
 // shortcut (SQ_LDS_BANK_CONFLICT / SQ_INSTS_MFMA), swizzled or not.
 template <int NP>
 __device__ __forceinline__ int piece_swizzle(int pixel) { return (pixel / (16 / NP)) & (NP - 1); }
-template <int B, int PB, int WN, int WM, int MODE, bool DUMP, int KPS, int S, Ep EP, bool PAIR>
+template <int B, int PB, int WN, int WM, int MODE, bool DUMP, int KPS, int S, int EP, bool PAIR>
 __device__ __forceinline__ void conv_fp_tile(const FpArgs &a) {
   static_assert(!DUMP || EP == kWide, "one build with the dump, for every layer");
   using C = FpCfg<B, PB, WN, WM, KPS>;
@@ -965,7 +965,7 @@ __device__ __forceinline__ void conv_fp_tile(const FpArgs &a) {
 // of a workgroup.  A wave loads its operands straight into registers, U
 // K-blocks at once, with no barrier; the accumulators meet in LDS, each wave
 // adds and requantises its share of the quads and the codes are packed there.
-template <int B, int PB, int NW, int MODE, bool DUMP, Ep EP>
+template <int B, int PB, int NW, int MODE, bool DUMP, int EP>
 __device__ __forceinline__ void conv_fp_split(const FpArgs &a) {
   static_assert(EP != kFp4 && (!DUMP || EP == kWide), "fp32 or any parameters; the dump with the latter");
   using T = FpT<B>;
@@ -1177,12 +1177,12 @@ __device__ __forceinline__ void conv_fp_split(const FpArgs &a) {
 
 // Entry points by matrix-core format.
 #define PALQ_FP_TILE(NAME)                                                                            \
-  template <int B, int PB, int WN, int WM, int MODE, bool DUMP, int KPS, int S, Ep EP, bool PAIR>     \
+  template <int B, int PB, int WN, int WM, int MODE, bool DUMP, int KPS, int S, int EP, bool PAIR>     \
   __global__ __launch_bounds__(WN *WM * 64, B == 2 ? 4 : B == 8 ? 2 : 3) void NAME(FpArgs a) {        \
     conv_fp_tile<B, PB, WN, WM, MODE, DUMP, KPS, S, EP, PAIR>(a);                                     \
   }
 #define PALQ_FP_SPLIT(NAME)                                                     \
-  template <int B, int PB, int NW, int MODE, bool DUMP, Ep EP>                  \
+  template <int B, int PB, int NW, int MODE, bool DUMP, int EP>                  \
   __global__ __launch_bounds__(NW * 64, 4) void NAME(FpArgs a) {                \
     conv_fp_split<B, PB, NW, MODE, DUMP, EP>(a);                                \
   }
@@ -1285,7 +1285,7 @@ int cu_count() {
   return cus;
 }
 
-template <int B, int PB, int WN, int WM, int MODE, bool DUMP, int KPS, int S, bool PAIR, Ep EP>
+template <int B, int PB, int WN, int WM, int MODE, bool DUMP, int KPS, int S, bool PAIR, int EP>
 hipError_t launch_tile_ep(const FpArgs &f, unsigned g, hipStream_t s) {
   const dim3 block(WN * WM * 64), grid(g);
   if constexpr (B == 8)
@@ -1311,7 +1311,7 @@ hipError_t launch_tile(FpArgs f, int64_t in_bytes, hipStream_t s) {
   return launch_tile_mode<B, PB, WN, WM, 0, DUMP, KPS, S, PAIR, WIDE>(f, grid, s);
 }
 
-template <int B, int PB, int NW, int MODE, bool DUMP, Ep EP>
+template <int B, int PB, int NW, int MODE, bool DUMP, int EP>
 hipError_t launch_split_ep(const FpArgs &f, unsigned g, hipStream_t s) {
   const dim3 block(NW * 64), grid(g);
   if constexpr (B == 8)
@@ -1322,7 +1322,7 @@ hipError_t launch_split_ep(const FpArgs &f, unsigned g, hipStream_t s) {
     hipLaunchKernelGGL((conv_fp4_split_kernel<B, PB, NW, MODE, DUMP, EP>), grid, block, 0, s, f);
   return hipGetLastError();
 }
-template <int B, int PB, int NW, bool DUMP, Ep EP>
+template <int B, int PB, int NW, bool DUMP, int EP>
 hipError_t launch_split(FpArgs f, int64_t in_bytes, hipStream_t s) {
   const unsigned grid = fp_tiles(f, 32, 32 * PB, in_bytes);
   if (f.res) return launch_split_ep<B, PB, NW, 1, DUMP, EP>(f, grid, s);
