@@ -1074,6 +1074,7 @@ __device__ __forceinline__ void conv_fp_split(const FpArgs &a) {
     V4 v = red[j * 64 + lane];
 #pragma unroll
     for (int w = 1; w < NW; ++w) v += red[(w * Q + j) * 64 + lane];
+    if constexpr (B == 8) asm volatile("" : "+v"(v));  // after set_round_down
     const int qi = j & 3, pixel = 32 * (j >> 2) + l32, m = m0 + pixel;
     const int c0 = 8 * qi + 4 * half;
     const float *blk = a.cst + (int64_t)((g * a.coutp + k32) >> 6) * (kCstBlock / 4);
@@ -1089,12 +1090,11 @@ __device__ __forceinline__ void conv_fp_split(const FpArgs &a) {
       }
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        int32_t t = v[e] + ci[e];
+        const int32_t t = v[e] + ci[e];
         if constexpr (DUMP)
           if (m < a.M && k32 + c0 + e < a.cout)
             a.dump[((int64_t)m * a.G + gd) * a.cout + k32 + c0 + e] = v[e] + a.wsum[g * a.cout + k32 + c0 + e];
         const int32_t code = (int32_t)((rc >> (8 * e)) & 255u);
-        asm volatile("" : "+v"(t));  // after set_round_down
         double u;
         if constexpr (MODE == 1 && EP == kWide) u = __builtin_fma((double)ci[64 + e], (double)code, (double)t);
         else u = (double)(MODE == 1 ? t + ci[64 + e] * code : t);
