@@ -706,10 +706,16 @@ def test_conv_requant_rounds_down(ctx, torch, shape, bits):
     L["mult"], L["shift"] = m.astype(np.int32), np.full(nch, 61, np.int32)
     L["bias"] = ((1 << 60) // m + up).astype(np.int32)
     case["x"] = np.zeros_like(case["x"])
-    say(f"conv requant rounds down {shape} b={bits}: {len(np.unique(m))} multipliers")
-    for q in run_conv_full(ctx, torch, case, L["bias"])[:3]:
-        ref = O.cyclic_permute(up.astype(np.int64), L["w"].shape[0], L["shuffle"])
-        np.testing.assert_array_equal(q, np.broadcast_to(ref, q.shape))
+    ref = O.cyclic_permute(up.astype(np.int64), L["w"].shape[0], L["shuffle"])
+    for fp4 in (True, False) if bits <= 4 else (True,):  # False: the int64 requant of the int8 and direct kernels
+        say(f"conv requant rounds down {shape} b={bits} fp4={fp4}: {len(np.unique(m))} multipliers")
+        ctx.set_conv_fp4(fp4)
+        try:
+            got = run_conv_full(ctx, torch, case, L["bias"])[:3]
+        finally:
+            ctx.set_conv_fp4(True)
+        for q in got:
+            np.testing.assert_array_equal(q, np.broadcast_to(ref, q.shape))
 
 
 def test_conv_i8_sums_past_int32(ctx, torch):
