@@ -365,8 +365,8 @@ def table2(args):
     """On-GPU analogue of the paper's Table 2 (Section 5.2) for M = 2G bits at
     B = 2, batch --batch, forward only, ResNet-18: PalQuant (G groups of
     2-bit convs on the FP4 matrix cores) against the M-bit network of the
-    original width (G = 1) run two ways: directly on int8 matrix cores, and
-    as the Eq. 4 bit decomposition the paper's accelerators perform (G^2
+    original width (G = 1) run two ways: directly (4-bit codes on the FP6 matrix
+    cores, 6 and 8 bits on int8; the row names the kernels), and as the Eq. 4 bit decomposition the paper's accelerators perform (G^2
     2-bit chunk products per MAC, shifted and summed exactly, on the same FP4
     matrix cores as PalQuant; palq_set_conv_bitdecomp).  The two runs of the
     M-bit network must give identical logits.  One JSON line per G."""

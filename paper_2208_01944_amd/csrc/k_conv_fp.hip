@@ -30,11 +30,11 @@
 // for every shift (M < 2^24).  Layers with a channel past those bounds (M up to
 // 2^31, bias up to 2^30) take the wide builds: the accumulator starts at 0, u is
 // an int32 (B = 8: formed in fp64) and the same fma in fp64 holds for every u and
-// M the interface admits (both below 2^53).  14x14, 256 channels, 2-bit, G = 4,
-// batch 128: 38.1 us against 34.6 for 15-bit multipliers (119 with the int64
+// M the interface admits (both below 2^53).  14x14, 256 channels, G = 4, batch
+// 128, 2-bit: 38.5 us against 34.7 for 15-bit multipliers (119 with the int64
 // requant of the int8 kernels, which took such layers); 4-bit with a shortcut
-// 59.9 against 52.3 (145); 14x14, 1024 channels, batch 8, 39 us (67 ms on the
-// direct kernel, as its filter does not fit the int8 kernels' LDS).
+// 58.5 against 50.3 (145); 14x14, 1024 channels, batch 8, 2-bit 26.7 against 24.8
+// (67 ms on the direct kernel, as the filter passes the int8 kernels' LDS).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
