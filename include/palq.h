@@ -211,7 +211,9 @@ palq_status palq_quantize(palq_ctx *ctx, const float *x, float l, float u, const
  * must not
  * overlap any input.  Every call prepacks the filter again, into context
  * memory that it grows (allocating) when a call needs more than any before;
- * it never synchronises.  A loop over one layer plans it once instead
+ * it never synchronises.  A graph that captured the call may hold that memory,
+ * which a later, larger call frees: capture palq_group_conv_noalloc or a plan
+ * instead.  A loop over one layer plans it once
  * (palq_conv_plan_create) and runs the plan (palq_conv_run). */
 palq_status palq_group_conv(palq_ctx *ctx, const palq_act *in, const palq_filter *w, int32_t stride,
                             int32_t pad, const palq_requant *rq, const palq_residual *res,
